@@ -168,9 +168,17 @@ __device__ __forceinline__ void gemm_tile(unsigned char* lds0, unsigned char* ld
                         : make_row_rsrc(A + static_cast<int64_t>(m0) * lda + step * kBK, bytes_a - koff);
     __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_ptr_t)dst, 16, b_panel ? vo_b[i] : vo_a[i], 0, 0, 0);
   };
+  // This wave's panel loads have landed, then everyone's.  The wait is written out: a barrier by itself
+  // waits for LDS accesses only, and the wait for loads into LDS that the compiler usually puts in
+  // front of it (for its own fragment reads behind it) it leaves out where it thinks none is pending;
+  // it did in the fp32 forms, whose spill reloads in front of the loop confuse that count.
+  auto landed_barrier = [&]() {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+  };
 #pragma unroll
   for (int q = 0; q < 16; ++q) dma_one(lds0, 0, q);
-  __syncthreads();                       // waits for this wave's loads, then for everyone's
+  landed_barrier();
   bf16x8 f0[16], f1[16];      // [0..7] B blocks, [8..15] A blocks
   // fragment q of the read order: the first A block, the 8 B blocks, then the other A blocks
   constexpr int kOrder[16] = {8, 0, 1, 2, 3, 4, 5, 6, 7, 9, 10, 11, 12, 13, 14, 15};
@@ -192,7 +200,7 @@ __device__ __forceinline__ void gemm_tile(unsigned char* lds0, unsigned char* ld
       if (m < 32 && (m & 1) == 0) { f1[kOrder[m >> 1]] = read_frag(cur, 1, kOrder[m >> 1]); DPPO_PIN; }
     }
     // the next stage is complete (own loads waited for, then everyone's) and this one fully read
-    __syncthreads();
+    landed_barrier();
     DPPO_PIN;
 #pragma unroll
     for (int m = 0; m < 64; ++m) {
@@ -216,9 +224,14 @@ __device__ __forceinline__ void gemm_tile(unsigned char* lds0, unsigned char* ld
   }
   if (kt < nk) step(lds0, lds1, kt, std::false_type{});
   // the matrix-core results must have landed before other instructions read the accumulators
-  // (the products are assembly statements, so the compiler does not keep that distance by itself;
-  // the scheduling barrier keeps the accumulator reads of the store behind the wait)
-  asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+  // (the products are assembly statements, so the compiler does not keep that distance by itself).
+  // The accumulators pass through the wait, so that nothing the compiler makes of them, a spill
+  // included, reads one in front of it.
+#pragma unroll
+  for (int i = 0; i < 8; ++i)
+    asm volatile("s_nop 15\n\ts_nop 15"
+                 : "+a"(acc[i][0]), "+a"(acc[i][1]), "+a"(acc[i][2]), "+a"(acc[i][3]), "+a"(acc[i][4]), "+a"(acc[i][5]), "+a"(acc[i][6]), "+a"(acc[i][7])
+                 :: "memory");
   DPPO_PIN;
 
   // The products were formed with the operands swapped (B fragment first), so a lane's four

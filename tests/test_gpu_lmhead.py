@@ -172,6 +172,24 @@ def test_gemm_tn_exact_inputs_bitwise_and_accumulation(M, N, K, lda, ldb, ldc):
     assert (c[:, N:] == 3.0).all()
 
 
+@pytest.mark.parametrize("by_rows", [False, True])
+def test_gemm_fp32_full_tiles_long_contraction_bitwise(by_rows):
+    """Full tiles on every compute unit and a contraction of 64 steps: every step's panels have to have
+    landed in shared memory before any wave reads them, and every product in the accumulators before the
+    tile is stored.  Exact inputs, so the result is the same in any order."""
+    M, N, K = 4096, 2304, 4096
+    _say(f"[case] gemm fp32 full tiles by_rows={by_rows}")
+    g = torch.Generator(device=DEV); g.manual_seed(17)
+    a = (torch.randint(-8, 9, (K, M) if by_rows else (M, K), generator=g, device=DEV).float() / 64).bfloat16()
+    b = (torch.randint(-8, 9, (K, N) if by_rows else (N, K), generator=g, device=DEV).float() / 8).bfloat16()
+    ref = (a.double().T @ b.double()) if by_rows else (a.double() @ b.double().T)
+    for _ in range(3):
+        c = torch.full((M, N), 3.0, dtype=torch.float32, device=DEV)
+        (B.gemm_tn_f32 if by_rows else B.gemm_nt_f32)(a, b, c)
+        torch.cuda.synchronize()
+        assert torch.equal(c.double(), ref)
+
+
 def test_gemm_tn_poisoned_neighbourhood_and_error_codes():
     """What lies next to the operands (pitch padding, rows past K in a larger buffer) holds NaN and
     infinities and must not reach any result; bad arguments are refused."""
