@@ -263,8 +263,9 @@ typedef struct {
   const void*    weight;        /* bf16 [V, ld_weight]: lm_head weight, 16-byte aligned            */
   int64_t        ld_weight;     /* >= d, multiple of 8                                             */
   int64_t        chunk_rows;    /* tokens per chunk; <= 0: 8192.  The second and third products have  */
-                                /* chunk_rows/256 x d/256 tiles: keep that at or above the number  */
-                                /* of compute units (256)                                          */
+                                /* chunk_rows/256 x d/256 and V/256 x d/256 tiles: keep the former  */
+                                /* at or above the number of compute units (256), or give the call */
+                                /* the workspace of dppo_lmhead_workspace_bytes_best()             */
   void*          grad_hidden;   /* bf16 [T, ld_grad_hidden]; dppo_lmhead_loss_fwd_bwd only         */
   int64_t        ld_grad_hidden;/* >= d                                                            */
   float*         grad_weight;   /* optional fp32 [V, ld_grad_weight], 16-byte aligned:             */
@@ -279,6 +280,13 @@ typedef struct {
 
 /* 64 KiB + min(chunk_rows, T) * V * 2 bytes (chunk_rows <= 0: the default); enough for either call. */
 size_t dppo_lmhead_workspace_bytes(int64_t T, int64_t V, int64_t chunk_rows);
+
+/* The workspace dppo_lmhead_loss_fwd_bwd is fastest with, on the current device: the above and, where
+ * the product for grad_hidden has too few tiles for the compute units (few tokens, or a narrow
+ * model), room for that product's partial sums, so that its contraction over the vocabulary can be
+ * divided among more workgroups.  A call uses what lies behind the first
+ * dppo_lmhead_workspace_bytes() (rounded up to 256) as far as it reaches. */
+size_t dppo_lmhead_workspace_bytes_best(int64_t T, int64_t V, int64_t d, int64_t chunk_rows);
 
 /* What dppo_lmhead_loss_fwd alone needs: 64 KiB + 8 T + min(chunk_rows, T) * (16 ceil(V / 256) +
  * 4 (K + 1)) bytes (each part rounded up to 256), K as the Top-K variants use it (0 for Binary). */

@@ -107,6 +107,8 @@ def lib() -> C.CDLL:
         for f in (l.dppo_lmhead_loss_fwd, l.dppo_lmhead_loss_fwd_bwd):
             f.restype = C.c_int
             f.argtypes = [C.POINTER(DppoLmheadArgs), C.c_void_p]
+        l.dppo_lmhead_workspace_bytes_best.restype = C.c_size_t
+        l.dppo_lmhead_workspace_bytes_best.argtypes = [C.c_int64, C.c_int64, C.c_int64, C.c_int64]
         l.dppo_lmhead_fwd_workspace_bytes.restype = C.c_size_t
         l.dppo_lmhead_fwd_workspace_bytes.argtypes = [C.c_int64, C.c_int64, C.c_int32, C.c_int64]
         l.dppo_lmhead_args_size.restype = C.c_size_t
@@ -336,6 +338,10 @@ def lmhead_workspace_bytes(T: int, V: int, chunk_rows: int = 0) -> int:
     return lib().dppo_lmhead_workspace_bytes(T, V, chunk_rows)
 
 
+def lmhead_workspace_bytes_best(T: int, V: int, d: int, chunk_rows: int = 0) -> int:
+    return lib().dppo_lmhead_workspace_bytes_best(T, V, d, chunk_rows)
+
+
 def lmhead_fwd_workspace_bytes(T: int, V: int, K: int, chunk_rows: int = 0) -> int:
     return lib().dppo_lmhead_fwd_workspace_bytes(T, V, K, chunk_rows)
 
@@ -355,7 +361,8 @@ def run_lmhead(batch: dict, backward: bool = True, chunk_rows: int = 0, out=None
     if workspace is None:
         fused = not backward and not (flags & FLAG_FORCE_STREAMING)
         K = batch["mu_topk_ids"].shape[1] if batch["mu_topk_ids"] is not None else 0
-        workspace = torch.empty(lmhead_fwd_workspace_bytes(T, V, K, chunk_rows) if fused else lmhead_workspace_bytes(T, V, chunk_rows),
+        workspace = torch.empty(lmhead_fwd_workspace_bytes(T, V, K, chunk_rows) if fused else
+                                lmhead_workspace_bytes_best(T, V, d, chunk_rows) if backward else lmhead_workspace_bytes(T, V, chunk_rows),
                                 dtype=torch.uint8, device=dev)
     a = DppoLmheadArgs()
     a.loss = make_args(torch.empty((0, V), dtype=torch.bfloat16, device=dev), batch["sampled_ids"], batch["mu_logp"],

@@ -403,6 +403,22 @@ size_t lmhead_workspace(int64_t T, int64_t V, int64_t chunk_rows) {
   return b > f ? b : f;
 }
 
+// Scratch behind the workspace that every forward + backward call accepts, which makes it faster: the
+// fp32 partial results of the product for the gradient of the hidden states, where that product has
+// too few tiles for the compute units.  The last chunk of a call can be shorter than the others and
+// want more ranges; what both want bounds it.
+size_t lmhead_split_bytes(int64_t T, int64_t V, int64_t d, int64_t chunk, int cus) {
+  size_t most = 0;
+  const int64_t rows[2] = {T < chunk ? T : chunk, T % chunk};
+  for (const int64_t r : rows) {
+    if (r <= 0) continue;
+    const int n = dppo::gemm_nn_splits(r, d, V, cus, SIZE_MAX);
+    const size_t b = n > 1 ? static_cast<size_t>(n) * static_cast<size_t>(r) * static_cast<size_t>(d) * sizeof(float) : 0;
+    if (b > most) most = b;
+  }
+  return most;
+}
+
 dppo_status_t run_lmhead(const dppo_lmhead_args_t* a, void* stream, bool grad) {
   if (!a) return DPPO_ERR_NULL;
   const int64_t T = a->loss.T, V = a->loss.V, d = a->d;
@@ -488,6 +504,11 @@ dppo_status_t run_lmhead(const dppo_lmhead_args_t* a, void* stream, bool grad) {
   const int parts_per_chunk = nchunks > 0 ? static_cast<int>(max_parts / nchunks) : max_parts;
   if (nchunks > 0 && parts_per_chunk < 1) return DPPO_ERR_SHAPE;
   int used = 0;
+  // what the caller's workspace holds beyond the part every call needs
+  const size_t base_bytes = align256(lmhead_workspace(T, V, a->chunk_rows));
+  const size_t extra_bytes = a->workspace_bytes > base_bytes ? a->workspace_bytes - base_bytes : 0;
+  int dev = 0;
+  if (T > 0 && grad && !stream_device(s, &dev)) return DPPO_ERR_LAUNCH;
   for (int64_t r0 = 0; r0 < T; r0 += chunk) {
     const int64_t rows = (T - r0 < chunk) ? (T - r0) : chunk;
     const uint16_t* h = static_cast<const uint16_t*>(a->hidden) + r0 * a->ld_hidden;
@@ -517,8 +538,9 @@ dppo_status_t run_lmhead(const dppo_lmhead_args_t* a, void* stream, bool grad) {
     if (grad) {
       // gradient of the chunk's hidden states: g [rows, V] times W [V, d], the weight as it lies
       uint16_t* gh = static_cast<uint16_t*>(a->grad_hidden) + r0 * a->ld_grad_hidden;
+      const int splits = dppo::gemm_nn_splits(rows, d, V, device_info(dev).cus, extra_bytes);
       if (dppo::launch_gemm_nn(zbuf, V, static_cast<const uint16_t*>(a->weight), a->ld_weight, gh, a->ld_grad_hidden, static_cast<int>(rows),
-                               static_cast<int>(d), static_cast<int>(V), s) != hipSuccess)
+                               static_cast<int>(d), static_cast<int>(V), splits, reinterpret_cast<float*>(ws + base_bytes), s) != hipSuccess)
         return DPPO_ERR_LAUNCH;
     }
     if (want_gw) {
@@ -581,6 +603,15 @@ size_t dppo_lmhead_workspace_bytes(int64_t T, int64_t V, int64_t chunk_rows) {
   return lmhead_workspace(T, V, chunk_rows);
 }
 
+size_t dppo_lmhead_workspace_bytes_best(int64_t T, int64_t V, int64_t d, int64_t chunk_rows) {
+  const size_t base = lmhead_workspace(T, V, chunk_rows);
+  if (T <= 0 || V < 64 || d < 64) return base;
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) dev = 0;
+  const size_t more = lmhead_split_bytes(T, V, d, chunk_rows > 0 ? chunk_rows : kLmheadDefaultChunk, device_info(dev).cus);
+  return more ? align256(base) + more : base;
+}
+
 dppo_status_t dppo_lmhead_loss_fwd(const dppo_lmhead_args_t* args, void* stream) { return run_lmhead(args, stream, false); }
 
 dppo_status_t dppo_lmhead_loss_fwd_bwd(const dppo_lmhead_args_t* args, void* stream) { return run_lmhead(args, stream, true); }
@@ -627,7 +658,7 @@ dppo_status_t dppo_gemm_nn(const void* A, int64_t lda, const void* B, int64_t ld
   if (((reinterpret_cast<uintptr_t>(A) | reinterpret_cast<uintptr_t>(B)) & 15u) || (reinterpret_cast<uintptr_t>(C) & 1u)) return DPPO_ERR_ALIGN;
   const hipError_t e = dppo::launch_gemm_nn(static_cast<const uint16_t*>(A), lda, static_cast<const uint16_t*>(B), ldb,
                                             C, ldc, static_cast<int>(M), static_cast<int>(N), static_cast<int>(K),
-                                            static_cast<hipStream_t>(stream));
+                                            1, nullptr, static_cast<hipStream_t>(stream));
   return e == hipSuccess ? DPPO_OK : DPPO_ERR_LAUNCH;
 }
 

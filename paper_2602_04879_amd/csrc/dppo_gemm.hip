@@ -27,6 +27,7 @@
 // transposed times activations [T, d]), with no transposed copies: the panels of a step are 64
 // rows of 512 bytes, and the LDS transpose read (ds_read_b64_tr_b16) hands every lane the
 // consecutive k of one column.  There K is arbitrary: rows past it read as zeros.
+#include <algorithm>
 #include <type_traits>
 #include "dppo_common.hpp"
 #include "dppo_launch.hpp"
@@ -54,7 +55,9 @@ __device__ __forceinline__ uint32_t lds_off(int row, int kvec) {
 // kOutStats: nothing of C is stored.  The tile's logits, rounded to bf16 as a stored tile would be,
 // leave as softmax statistics per row (GemmStats below): the forward of the hidden-state path then
 // never writes a logit to memory.
-enum : int { kOutBf16 = 0, kOutF32 = 1, kOutF32Add = 2, kOutStats = 3 };
+// kOutSplit: the contraction is cut into `splits` ranges of steps, one workgroup per tile and range, and
+// the tile of a range leaves as fp32 for a second kernel to add up (see gemm_nn_splits).
+enum : int { kOutBf16 = 0, kOutF32 = 1, kOutF32Add = 2, kOutStats = 3, kOutSplit = 4 };
 
 // TA: A is [K, M]; TB: B is [K, N] (the contraction index is the ROW index of that operand; with
 // both, C = A^T B; with TB alone, C = A B).  The panel of such an operand
@@ -417,12 +420,24 @@ template <int OUT, bool TA, bool TB>
 __global__ __launch_bounds__(256) void dppo_gemm_nt_kernel(const uint16_t* __restrict__ A, int64_t lda,
                                                            const uint16_t* __restrict__ B, int64_t ldb,
                                                            void* __restrict__ C, int64_t ldc, int M, int N, int K,
-                                                           int tiles_m, int tiles_n, int blocks_m, int blocks_per_die, const GemmStats gs) {
+                                                           int tiles_m, int tiles_n, int blocks_m, int blocks_per_die, const GemmStats gs,
+                                                           int blocks_per_split, int split_steps) {
   // two stages of (A panel | B panel): 2 x 64 KiB of the compute unit's 160 KiB
   __shared__ __attribute__((aligned(16))) unsigned char lds0[kStageBytes];
   __shared__ __attribute__((aligned(16))) unsigned char lds1[kStageBytes];
   const int die = static_cast<int>(blockIdx.x) & 7, slot = static_cast<int>(blockIdx.x) >> 3;      // slot-th workgroup of its die
-  const int block = die * blocks_per_die + slot / (kGroupM * kGroupN), within = slot % (kGroupM * kGroupN);
+  int block = die * blocks_per_die + slot / (kGroupM * kGroupN);
+  const int within = slot % (kGroupM * kGroupN);
+  if (OUT == kOutSplit) {
+    // the range of the contraction is the outermost index, so the workgroups of a die still share panels
+    const int split = block / blocks_per_split, k0 = split * split_steps * kBK;
+    if (k0 >= K) return;                              // past the last range (the grid is a multiple of the eight dies)
+    block -= split * blocks_per_split;
+    A += k0;
+    B += static_cast<int64_t>(k0) * (TB ? ldb : 1);
+    C = static_cast<float*>(C) + static_cast<int64_t>(split) * M * ldc;
+    K = min(K - k0, split_steps * kBK);
+  }
   const int bn = block / blocks_m, bm = block - bn * blocks_m;
   const int tm = bm * kGroupM + (within % kGroupM), tn = bn * kGroupN + (within / kGroupM);
   if (tm >= tiles_m || tn >= tiles_n) return;
@@ -440,9 +455,9 @@ hipError_t launch_gemm_nt(const uint16_t* A, int64_t lda, const uint16_t* B, int
   const int blocks_m = (tiles_m + kGroupM - 1) / kGroupM, blocks_n = (tiles_n + kGroupN - 1) / kGroupN;
   const int blocks_per_die = (blocks_m * blocks_n + 7) / 8;
   const dim3 grid(8 * blocks_per_die * kGroupM * kGroupN), wg(256);
-  if (out == 0)      hipLaunchKernelGGL((dppo_gemm_nt_kernel<kOutBf16, false, false>), grid, wg, 0, s, A, lda, B, ldb, C, ldc, M, N, K, tiles_m, tiles_n, blocks_m, blocks_per_die, GemmStats{});
-  else if (out == 1) hipLaunchKernelGGL((dppo_gemm_nt_kernel<kOutF32, false, false>), grid, wg, 0, s, A, lda, B, ldb, C, ldc, M, N, K, tiles_m, tiles_n, blocks_m, blocks_per_die, GemmStats{});
-  else               hipLaunchKernelGGL((dppo_gemm_nt_kernel<kOutF32Add, false, false>), grid, wg, 0, s, A, lda, B, ldb, C, ldc, M, N, K, tiles_m, tiles_n, blocks_m, blocks_per_die, GemmStats{});
+  if (out == 0)      hipLaunchKernelGGL((dppo_gemm_nt_kernel<kOutBf16, false, false>), grid, wg, 0, s, A, lda, B, ldb, C, ldc, M, N, K, tiles_m, tiles_n, blocks_m, blocks_per_die, GemmStats{}, 0, 0);
+  else if (out == 1) hipLaunchKernelGGL((dppo_gemm_nt_kernel<kOutF32, false, false>), grid, wg, 0, s, A, lda, B, ldb, C, ldc, M, N, K, tiles_m, tiles_n, blocks_m, blocks_per_die, GemmStats{}, 0, 0);
+  else               hipLaunchKernelGGL((dppo_gemm_nt_kernel<kOutF32Add, false, false>), grid, wg, 0, s, A, lda, B, ldb, C, ldc, M, N, K, tiles_m, tiles_n, blocks_m, blocks_per_die, GemmStats{}, 0, 0);
   return hipGetLastError();
 }
 
@@ -457,7 +472,7 @@ hipError_t launch_gemm_stats(const uint16_t* A, int64_t lda, const uint16_t* B, 
   const int blocks_per_die = (blocks_m * blocks_n + 7) / 8;
   const dim3 grid(8 * blocks_per_die * kGroupM * kGroupN), wg(256);
   hipLaunchKernelGGL((dppo_gemm_nt_kernel<kOutStats, false, false>), grid, wg, 0, s, A, lda, B, ldb, static_cast<void*>(nullptr), int64_t(0), M, N, K,
-                     tiles_m, tiles_n, blocks_m, blocks_per_die, gs);
+                     tiles_m, tiles_n, blocks_m, blocks_per_die, gs, 0, 0);
   return hipGetLastError();
 }
 
@@ -469,20 +484,103 @@ hipError_t launch_gemm_tn(const uint16_t* A, int64_t lda, const uint16_t* B, int
   const int blocks_m = (tiles_m + kGroupM - 1) / kGroupM, blocks_n = (tiles_n + kGroupN - 1) / kGroupN;
   const int blocks_per_die = (blocks_m * blocks_n + 7) / 8;
   const dim3 grid(8 * blocks_per_die * kGroupM * kGroupN), wg(256);
-  if (out == 1) hipLaunchKernelGGL((dppo_gemm_nt_kernel<kOutF32, true, true>), grid, wg, 0, s, A, lda, B, ldb, C, ldc, M, N, K, tiles_m, tiles_n, blocks_m, blocks_per_die, GemmStats{});
-  else          hipLaunchKernelGGL((dppo_gemm_nt_kernel<kOutF32Add, true, true>), grid, wg, 0, s, A, lda, B, ldb, C, ldc, M, N, K, tiles_m, tiles_n, blocks_m, blocks_per_die, GemmStats{});
+  if (out == 1) hipLaunchKernelGGL((dppo_gemm_nt_kernel<kOutF32, true, true>), grid, wg, 0, s, A, lda, B, ldb, C, ldc, M, N, K, tiles_m, tiles_n, blocks_m, blocks_per_die, GemmStats{}, 0, 0);
+  else          hipLaunchKernelGGL((dppo_gemm_nt_kernel<kOutF32Add, true, true>), grid, wg, 0, s, A, lda, B, ldb, C, ldc, M, N, K, tiles_m, tiles_n, blocks_m, blocks_per_die, GemmStats{}, 0, 0);
   return hipGetLastError();
 }
 
+// The gradient of the hidden states contracts over the whole vocabulary (2374 steps of 64 at 151936
+// entries) into few tiles: 1000 tokens of a 2048-wide model are 32 tiles for 256 compute units, 5000 of
+// a 4096-wide one 320, a full round and a quarter.  So the contraction can be cut into ranges: every
+// (tile, range) is a workgroup, fp32 partial tiles go to scratch and dppo_gemm_sum_kernel adds them in
+// a fixed order and rounds once.  The number of ranges is the one with the least estimated time, in
+// steps of a compute unit (1.46 us, measured): rounds of workgroups on the busiest die times (steps of
+// a range + 8 for filling the pipeline and storing a tile), plus the partial sums' way out and back
+// (at 4 TB/s, 5.8 MB per step) and the second launch.  It has to beat the undivided product by 3 %.
+// Contractions of fewer than 128 steps (vocabularies below 8192: at most 0.2 ms undivided) stay whole,
+// and a range has 16 steps or more, twice what filling the pipeline and storing the tile cost.
+// Measured at V = 151936, logits + loss + hidden gradient, undivided against divided: 64 tokens x 1024 wide
+// (63 ranges) 3.13 / 0.57 ms, 512 x 2048 (16) 3.66 / 1.02, 1000 x 2048 (8) 3.95 / 1.37, 2048 x 4096 (2) 5.49 / 3.81,
+// 5000 x 4096 (4) 11.97 / 9.84, 8192 x 1024 (2) 6.50 / 4.91; 8192 x 4096 and 8192 x 2048 fill whole rounds and stay undivided.
+int gemm_nn_splits(int64_t M, int64_t N, int64_t K, int cus, size_t scratch_bytes) {
+  const int tiles_m = static_cast<int>((M + kBM - 1) / kBM), tiles_n = static_cast<int>((N + kBN - 1) / kBN);
+  const int blocks_m = (tiles_m + kGroupM - 1) / kGroupM, blocks_n = (tiles_n + kGroupN - 1) / kGroupN, blocks = blocks_m * blocks_n;
+  const int64_t tiles = static_cast<int64_t>(tiles_m) * tiles_n, nk = K / kBK;
+  const int per_die = cus >= 8 ? cus / 8 : 1;
+  int best = 1;
+  double best_cost = 0.0;
+  for (int64_t s = 1; s <= 64; ++s) {
+    if (s > 1 && (nk < 128 || nk / s < 16 || tiles * s > 16 * static_cast<int64_t>(cus))) break;
+    if (s > 1 && static_cast<uint64_t>(s) * static_cast<uint64_t>(M) * static_cast<uint64_t>(N) * 4u > scratch_bytes) break;
+    // the busiest of the eight dies, each of which takes a contiguous eighth of the blocks (of all ranges)
+    const int64_t share = (blocks * s + 7) / 8;
+    int64_t busiest = 0;
+    for (int64_t b0 = 0; b0 < blocks * s; b0 += share) {
+      int64_t n = 0;
+      for (int64_t b = b0; b < b0 + share && b < blocks * s; ++b) {
+        const int bn = static_cast<int>(b % blocks) / blocks_m, bm = static_cast<int>(b % blocks) % blocks_m;
+        n += std::min(kGroupM, tiles_m - bm * kGroupM) * std::min(kGroupN, tiles_n - bn * kGroupN);
+      }
+      busiest = std::max(busiest, n);
+    }
+    double cost = static_cast<double>((busiest + per_die - 1) / per_die) * static_cast<double>((nk + s - 1) / s + 8);
+    if (s > 1) cost = (cost + static_cast<double>(s * M * N) * 8.0 / 5.8e6 + 4.0) / 0.97;
+    if (s == 1 || cost < best_cost) {
+      best = static_cast<int>(s);
+      best_cost = cost;
+    }
+  }
+  return best;
+}
+
+namespace {
+// Adds the fp32 partial results of the ranges of the contraction, [splits][M][N], in their order and
+// rounds the sum to bf16 once.  Four columns per thread (N a multiple of 4); bound by reading the
+// partial sums, which the products have just written.
+__global__ __launch_bounds__(256) void dppo_gemm_sum_kernel(const f32x4* __restrict__ part, int splits, int64_t quads, int quads_row,
+                                                            uint16_t* __restrict__ C, int64_t ldc) {
+  const int64_t q = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+  if (q >= quads) return;
+  f32x4 v = part[q];
+  for (int s = 1; s < splits; ++s) v += part[static_cast<int64_t>(s) * quads + q];
+  const int64_t row = q / quads_row;
+  uint16_t* dst = C + row * ldc + (q - row * quads_row) * 4;
+  const uint32_t lo = pack_bf16x2(v[0], v[1]), hi = pack_bf16x2(v[2], v[3]);
+  typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+  if ((reinterpret_cast<uintptr_t>(dst) & 7u) == 0) {
+    *reinterpret_cast<u32x2*>(dst) = u32x2{lo, hi};
+  } else {
+    dst[0] = static_cast<uint16_t>(lo & 0xffffu);
+    dst[1] = static_cast<uint16_t>(lo >> 16);
+    dst[2] = static_cast<uint16_t>(hi & 0xffffu);
+    dst[3] = static_cast<uint16_t>(hi >> 16);
+  }
+}
+}  // namespace
+
 // C[M, N] bf16 = A B with A [M, K] (contraction index contiguous) and B [K, N] (contraction index the row index); K % 64 == 0
 hipError_t launch_gemm_nn(const uint16_t* A, int64_t lda, const uint16_t* B, int64_t ldb, void* C, int64_t ldc,
-                          int M, int N, int K, hipStream_t s) {
+                          int M, int N, int K, int splits, float* scratch, hipStream_t s) {
   if (M <= 0 || N <= 0) return hipSuccess;
   const int tiles_m = (M + kBM - 1) / kBM, tiles_n = (N + kBN - 1) / kBN;
   const int blocks_m = (tiles_m + kGroupM - 1) / kGroupM, blocks_n = (tiles_n + kGroupN - 1) / kGroupN;
+  if (splits > 1) {
+    if (N % 4 != 0 || !scratch) return hipErrorInvalidValue;
+    const int split_steps = (K / kBK + splits - 1) / splits;
+    const int used = (K / kBK + split_steps - 1) / split_steps;       // ranges that hold a step
+    const int per_die = (used * blocks_m * blocks_n + 7) / 8;
+    hipLaunchKernelGGL((dppo_gemm_nt_kernel<kOutSplit, false, true>), dim3(8 * per_die * kGroupM * kGroupN), dim3(256), 0, s, A, lda, B, ldb,
+                       static_cast<void*>(scratch), static_cast<int64_t>(N), M, N, K, tiles_m, tiles_n, blocks_m, per_die, GemmStats{},
+                       blocks_m * blocks_n, split_steps);
+    if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
+    const int64_t quads = static_cast<int64_t>(M) * N / 4;
+    hipLaunchKernelGGL(dppo_gemm_sum_kernel, dim3(static_cast<unsigned>((quads + 255) / 256)), dim3(256), 0, s,
+                       reinterpret_cast<const f32x4*>(scratch), used, quads, N / 4, static_cast<uint16_t*>(C), ldc);
+    return hipGetLastError();
+  }
   const int blocks_per_die = (blocks_m * blocks_n + 7) / 8;
   const dim3 grid(8 * blocks_per_die * kGroupM * kGroupN), wg(256);
-  hipLaunchKernelGGL((dppo_gemm_nt_kernel<kOutBf16, false, true>), grid, wg, 0, s, A, lda, B, ldb, C, ldc, M, N, K, tiles_m, tiles_n, blocks_m, blocks_per_die, GemmStats{});
+  hipLaunchKernelGGL((dppo_gemm_nt_kernel<kOutBf16, false, true>), grid, wg, 0, s, A, lda, B, ldb, C, ldc, M, N, K, tiles_m, tiles_n, blocks_m, blocks_per_die, GemmStats{}, 0, 0);
   return hipGetLastError();
 }
 

@@ -52,9 +52,13 @@ hipError_t launch_fullvocab_resident(const KParams& p, bool tv, bool grad, int c
 // C[M, N] = A B^T, A [M, K], B [N, K]; K % 64 == 0; out 0: C bf16; 1: C fp32; 2: C fp32, added to what it holds
 hipError_t launch_gemm_nt(const uint16_t* A, int64_t lda, const uint16_t* B, int64_t ldb, void* C, int64_t ldc,
                           int M, int N, int K, int out, hipStream_t s);
-// C[M, N] bf16 = A B, A [M, K], B [K, N]; K % 64 == 0
+// C[M, N] bf16 = A B, A [M, K], B [K, N]; K % 64 == 0.  splits > 1: the contraction in that many ranges, one
+// workgroup per tile and range, through fp32 partial results in `scratch` (splits * M * N * 4 bytes, 16-byte
+// aligned; N a multiple of 4).  gemm_nn_splits() gives the number a shape runs fastest with, as far as the
+// scratch allows (1: undivided).
 hipError_t launch_gemm_nn(const uint16_t* A, int64_t lda, const uint16_t* B, int64_t ldb, void* C, int64_t ldc,
-                          int M, int N, int K, hipStream_t s);
+                          int M, int N, int K, int splits, float* scratch, hipStream_t s);
+int gemm_nn_splits(int64_t M, int64_t N, int64_t K, int cus, size_t scratch_bytes);
 // C[M, N] fp32 (out 1: written, 2: added to) = A^T B, A [K, M], B [K, N]; any K >= 1
 hipError_t launch_gemm_tn(const uint16_t* A, int64_t lda, const uint16_t* B, int64_t ldb, void* C, int64_t ldc,
                           int M, int N, int K, int out, hipStream_t s);

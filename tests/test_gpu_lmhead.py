@@ -373,6 +373,44 @@ def test_hidden_state_path_can_be_captured_in_a_hip_graph_and_replayed():
     _say("       hidden-state path captured and replayed 3 times, bitwise equal to eager")
 
 
+@pytest.mark.parametrize("T,V,d", [
+    (1, 8192, 64),          # one row, one tile, the shortest contraction that is divided
+    (256, 151936, 64),      # one full tile, many ranges, the last one shorter (2374 steps)
+    (257, 20032, 320),      # a second tile of one row, a last column tile of 64, 313 steps
+    (2100, 32768, 512),     # 18 tiles, some blocks of tiles nearly empty
+])
+def test_divided_contraction_of_the_hidden_gradient(T, V, d):
+    """grad_hidden with the contraction over the vocabulary cut into ranges (the workspace the binding
+    allocates), into fewer (half the extra room, pitched and 2-byte aligned output), and undivided (the
+    workspace any call accepts, compared with the oracle elsewhere in this file).  All three add the same
+    products in fp32 in different orders and round once: |difference| <= 2^-7 |value| (a step of
+    bf16) + the fp32 error of the sums: sum |g_j W_j| <= 2 |c_t| max |W| (the row's entries sum to
+    2 |c_t| at most in absolute value), times 64 * 2^-24 for sums of at most 2374 * 64 terms, whose
+    rounding errors are independent: sqrt(151936) / 2 is 195 half-steps of the largest partial sum at
+    worst, in the mean far fewer, since the partial sums stay well below that bound."""
+    w = W.Workload("lm_split", 1, T, V, W.BINARY_TV, 0.5, logit_std=3.0, noise_std=0.3, adv="normal", seed=131)
+    b = W.make_lmhead_batch(w, d, DEV, rows_per_step=256)
+    _say(f"[case] divided contraction T={T} V={V} d={d}")
+    base, best = B.lmhead_workspace_bytes(T, V), B.lmhead_workspace_bytes_best(T, V, d)
+    assert best > base
+    whole = B.run_lmhead(b, workspace=torch.empty(base, dtype=torch.uint8, device=DEV))
+    pad = torch.full((T, d + 3), 7.0, dtype=torch.bfloat16, device=DEV)
+    runs = [(B.run_lmhead(b), None),
+            (B.run_lmhead(b, workspace=torch.empty((base + best) // 2, dtype=torch.uint8, device=DEV), grad_hidden=pad[:, 1:d + 1]), pad)]
+    torch.cuda.synchronize()
+    c = (whole["loss_tok"].double() * b["loss_scale"]).abs()[:, None]
+    ref = whole["grad_hidden"].double()
+    tol = 2.0 ** -7 * ref.abs() + 64 * 2.0 ** -24 * 2 * c * b["weight"].abs().max().item() + 1e-30
+    for res, p in runs:
+        assert torch.equal(res["loss"], whole["loss"]) and torch.equal(res["mask"], whole["mask"])
+        assert bool(((res["grad_hidden"].double() - ref).abs() <= tol).all())
+        if p is not None:
+            assert bool((p[:, 0] == 7.0).all()) and bool((p[:, d + 1:] == 7.0).all())
+    again = B.run_lmhead(b)
+    torch.cuda.synchronize()
+    assert torch.equal(again["grad_hidden"], runs[0][0]["grad_hidden"])
+
+
 def test_error_codes():
     w = W.Workload("lm_err", 1, 16, 256, W.BINARY_TV, 0.2, logit_std=3.0, adv="pm1", seed=89)
     b = W.make_lmhead_batch(w, 64, DEV, exact=True)
