@@ -410,37 +410,71 @@ __device__ __forceinline__ void gemm_tile(unsigned char* lds0, unsigned char* ld
 }
 
 // Workgroup ids go round-robin over the 8 accelerator dies, each with its own L2.  Tiles are
-// grouped in blocks of 8 (M) x 4 (N) = 32, the number of workgroups that run together on a die, and
-// each die gets a contiguous range of blocks: the workgroups sharing an L2 at any time then share
-// 8 A panels and 4 B panels (12 panel streams for 32 tiles).  Positions of a block that fall
-// outside the matrix exit at once.
-constexpr int kGroupM = 8, kGroupN = 4;
+// numbered block by block, a block being group_m x group_n tiles, at most 32, the number of workgroups
+// that run together on a die, and each die gets a contiguous range of numbers: with 8 x 4 the workgroups sharing
+// an L2 at any time share 8 A panels and 4 B panels (12 panel streams for 32 tiles).  Blocks at the
+// edge are cut to the matrix: a number outside it would wait for a compute unit with free shared memory like
+// any other workgroup (with whole blocks of 8 x 4 over one tile of rows seven of eight were: 64 tokens x 1024
+// wide, logits + loss + hidden gradient 0.57 ms, now 0.23).  Only where that is less than 3 % of the numbers
+// are the edge blocks left whole, so that the rounds of 32 workgroups stay in step with the blocks (the weight
+// gradient at V = 151936, 594 tiles high: 7.8 ms, cut 8.4).
+struct TileMap {
+  int tiles_m, tiles_n, group_m, group_n;
+  int rows, cols;          // tiles_m, tiles_n, or up to the next multiple of the block's
+  int tiles, per_die;      // rows * cols; numbers each die takes (of all ranges of the contraction)
+  int split_steps;         // kOutSplit: steps of a range of the contraction
+};
+TileMap tile_map(int64_t M, int64_t N, int64_t ranges) {
+  TileMap t;
+  t.tiles_m = static_cast<int>((M + kBM - 1) / kBM);
+  t.tiles_n = static_cast<int>((N + kBN - 1) / kBN);
+  // blocks of 32 tiles of whole height where 8 or 4 divides the matrix's, else of nearly equal heights
+  const int high = (t.tiles_m + 7) / 8;
+  t.group_m = t.tiles_m % 8 == 0 ? 8 : t.tiles_m % 4 == 0 ? 4 : (t.tiles_m + high - 1) / high;
+  t.group_n = 32 / t.group_m;
+  const int whole_m = (t.tiles_m + t.group_m - 1) / t.group_m * t.group_m, whole_n = (t.tiles_n + t.group_n - 1) / t.group_n * t.group_n;
+  const bool whole = static_cast<int64_t>(whole_m) * whole_n * 100 < static_cast<int64_t>(t.tiles_m) * t.tiles_n * 103;
+  t.rows = whole ? whole_m : t.tiles_m;
+  t.cols = whole ? whole_n : t.tiles_n;
+  t.tiles = t.rows * t.cols;
+  const int64_t share = (t.tiles * ranges + 7) / 8;
+  // from eight rounds of workgroups per die on, dies start with a whole block (the last round is partly empty either way)
+  t.per_die = static_cast<int>(share >= 256 ? (share + 31) / 32 * 32 : share);
+  t.split_steps = 0;
+  return t;
+}
+inline dim3 tile_grid(const TileMap& t) { return dim3(8u * static_cast<unsigned>(t.per_die)); }
 
 template <int OUT, bool TA, bool TB>
 __global__ __launch_bounds__(256) void dppo_gemm_nt_kernel(const uint16_t* __restrict__ A, int64_t lda,
                                                            const uint16_t* __restrict__ B, int64_t ldb,
                                                            void* __restrict__ C, int64_t ldc, int M, int N, int K,
-                                                           int tiles_m, int tiles_n, int blocks_m, int blocks_per_die, const GemmStats gs,
-                                                           int blocks_per_split, int split_steps) {
+                                                           const TileMap map, const GemmStats gs) {
   // two stages of (A panel | B panel): 2 x 64 KiB of the compute unit's 160 KiB
   __shared__ __attribute__((aligned(16))) unsigned char lds0[kStageBytes];
   __shared__ __attribute__((aligned(16))) unsigned char lds1[kStageBytes];
   const int die = static_cast<int>(blockIdx.x) & 7, slot = static_cast<int>(blockIdx.x) >> 3;      // slot-th workgroup of its die
-  int block = die * blocks_per_die + slot / (kGroupM * kGroupN);
-  const int within = slot % (kGroupM * kGroupN);
+  int tile = die * map.per_die + slot;
   if (OUT == kOutSplit) {
     // the range of the contraction is the outermost index, so the workgroups of a die still share panels
-    const int split = block / blocks_per_split, k0 = split * split_steps * kBK;
-    if (k0 >= K) return;                              // past the last range (the grid is a multiple of the eight dies)
-    block -= split * blocks_per_split;
+    const int split = tile / map.tiles, k0 = split * map.split_steps * kBK;
+    if (k0 >= K) return;                              // past the last range (the dies' shares are rounded up)
+    tile -= split * map.tiles;
     A += k0;
     B += static_cast<int64_t>(k0) * (TB ? ldb : 1);
     C = static_cast<float*>(C) + static_cast<int64_t>(split) * M * ldc;
-    K = min(K - k0, split_steps * kBK);
+    K = min(K - k0, map.split_steps * kBK);
   }
-  const int bn = block / blocks_m, bm = block - bn * blocks_m;
-  const int tm = bm * kGroupM + (within % kGroupM), tn = bn * kGroupN + (within / kGroupM);
-  if (tm >= tiles_m || tn >= tiles_n) return;
+  if (tile >= map.tiles) return;
+  // blocks run down the matrix, then on to the next group_n columns of tiles
+  const int bn = tile / (map.group_n * map.rows);
+  int t = tile - bn * (map.group_n * map.rows);
+  const int width = min(map.group_n, map.cols - bn * map.group_n);
+  const int bm = t / (map.group_m * width);
+  t -= bm * (map.group_m * width);
+  const int height = min(map.group_m, map.rows - bm * map.group_m);
+  const int tn = bn * map.group_n + t / height, tm = bm * map.group_m + t % height;
+  if (tm >= map.tiles_m || tn >= map.tiles_n) return;
   const int m0 = tm * kBM, n0 = tn * kBN;
   if (M - m0 >= kBM && N - n0 >= kBN) gemm_tile<true, OUT, TA, TB>(lds0, lds1, A, lda, B, ldb, C, ldc, M, N, K, m0, n0, gs);
   else                                gemm_tile<false, OUT, TA, TB>(lds0, lds1, A, lda, B, ldb, C, ldc, M, N, K, m0, n0, gs);
@@ -451,13 +485,11 @@ __global__ __launch_bounds__(256) void dppo_gemm_nt_kernel(const uint16_t* __res
 hipError_t launch_gemm_nt(const uint16_t* A, int64_t lda, const uint16_t* B, int64_t ldb, void* C, int64_t ldc,
                           int M, int N, int K, int out, hipStream_t s) {
   if (M <= 0 || N <= 0) return hipSuccess;
-  const int tiles_m = (M + kBM - 1) / kBM, tiles_n = (N + kBN - 1) / kBN;
-  const int blocks_m = (tiles_m + kGroupM - 1) / kGroupM, blocks_n = (tiles_n + kGroupN - 1) / kGroupN;
-  const int blocks_per_die = (blocks_m * blocks_n + 7) / 8;
-  const dim3 grid(8 * blocks_per_die * kGroupM * kGroupN), wg(256);
-  if (out == 0)      hipLaunchKernelGGL((dppo_gemm_nt_kernel<kOutBf16, false, false>), grid, wg, 0, s, A, lda, B, ldb, C, ldc, M, N, K, tiles_m, tiles_n, blocks_m, blocks_per_die, GemmStats{}, 0, 0);
-  else if (out == 1) hipLaunchKernelGGL((dppo_gemm_nt_kernel<kOutF32, false, false>), grid, wg, 0, s, A, lda, B, ldb, C, ldc, M, N, K, tiles_m, tiles_n, blocks_m, blocks_per_die, GemmStats{}, 0, 0);
-  else               hipLaunchKernelGGL((dppo_gemm_nt_kernel<kOutF32Add, false, false>), grid, wg, 0, s, A, lda, B, ldb, C, ldc, M, N, K, tiles_m, tiles_n, blocks_m, blocks_per_die, GemmStats{}, 0, 0);
+  const TileMap map = tile_map(M, N, 1);
+  const dim3 grid = tile_grid(map), wg(256);
+  if (out == 0)      hipLaunchKernelGGL((dppo_gemm_nt_kernel<kOutBf16, false, false>), grid, wg, 0, s, A, lda, B, ldb, C, ldc, M, N, K, map, GemmStats{});
+  else if (out == 1) hipLaunchKernelGGL((dppo_gemm_nt_kernel<kOutF32, false, false>), grid, wg, 0, s, A, lda, B, ldb, C, ldc, M, N, K, map, GemmStats{});
+  else               hipLaunchKernelGGL((dppo_gemm_nt_kernel<kOutF32Add, false, false>), grid, wg, 0, s, A, lda, B, ldb, C, ldc, M, N, K, map, GemmStats{});
   return hipGetLastError();
 }
 
@@ -466,13 +498,11 @@ hipError_t launch_gemm_nt(const uint16_t* A, int64_t lda, const uint16_t* B, int
 hipError_t launch_gemm_stats(const uint16_t* A, int64_t lda, const uint16_t* B, int64_t ldb, int M, int N, int K,
                              const GemmStats& gs, hipStream_t s) {
   if (M <= 0 || N <= 0) return hipSuccess;
-  const int tiles_m = (M + kBM - 1) / kBM, tiles_n = (N + kBN - 1) / kBN;
-  if (gs.tiles_n != tiles_n) return hipErrorInvalidValue;
-  const int blocks_m = (tiles_m + kGroupM - 1) / kGroupM, blocks_n = (tiles_n + kGroupN - 1) / kGroupN;
-  const int blocks_per_die = (blocks_m * blocks_n + 7) / 8;
-  const dim3 grid(8 * blocks_per_die * kGroupM * kGroupN), wg(256);
+  const TileMap map = tile_map(M, N, 1);
+  if (gs.tiles_n != map.tiles_n) return hipErrorInvalidValue;
+  const dim3 grid = tile_grid(map), wg(256);
   hipLaunchKernelGGL((dppo_gemm_nt_kernel<kOutStats, false, false>), grid, wg, 0, s, A, lda, B, ldb, static_cast<void*>(nullptr), int64_t(0), M, N, K,
-                     tiles_m, tiles_n, blocks_m, blocks_per_die, gs, 0, 0);
+                     map, gs);
   return hipGetLastError();
 }
 
@@ -480,12 +510,10 @@ hipError_t launch_gemm_stats(const uint16_t* A, int64_t lda, const uint16_t* B, 
 hipError_t launch_gemm_tn(const uint16_t* A, int64_t lda, const uint16_t* B, int64_t ldb, void* C, int64_t ldc,
                           int M, int N, int K, int out, hipStream_t s) {
   if (M <= 0 || N <= 0) return hipSuccess;
-  const int tiles_m = (M + kBM - 1) / kBM, tiles_n = (N + kBN - 1) / kBN;
-  const int blocks_m = (tiles_m + kGroupM - 1) / kGroupM, blocks_n = (tiles_n + kGroupN - 1) / kGroupN;
-  const int blocks_per_die = (blocks_m * blocks_n + 7) / 8;
-  const dim3 grid(8 * blocks_per_die * kGroupM * kGroupN), wg(256);
-  if (out == 1) hipLaunchKernelGGL((dppo_gemm_nt_kernel<kOutF32, true, true>), grid, wg, 0, s, A, lda, B, ldb, C, ldc, M, N, K, tiles_m, tiles_n, blocks_m, blocks_per_die, GemmStats{}, 0, 0);
-  else          hipLaunchKernelGGL((dppo_gemm_nt_kernel<kOutF32Add, true, true>), grid, wg, 0, s, A, lda, B, ldb, C, ldc, M, N, K, tiles_m, tiles_n, blocks_m, blocks_per_die, GemmStats{}, 0, 0);
+  const TileMap map = tile_map(M, N, 1);
+  const dim3 grid = tile_grid(map), wg(256);
+  if (out == 1) hipLaunchKernelGGL((dppo_gemm_nt_kernel<kOutF32, true, true>), grid, wg, 0, s, A, lda, B, ldb, C, ldc, M, N, K, map, GemmStats{});
+  else          hipLaunchKernelGGL((dppo_gemm_nt_kernel<kOutF32Add, true, true>), grid, wg, 0, s, A, lda, B, ldb, C, ldc, M, N, K, map, GemmStats{});
   return hipGetLastError();
 }
 
@@ -503,26 +531,15 @@ hipError_t launch_gemm_tn(const uint16_t* A, int64_t lda, const uint16_t* B, int
 // (63 ranges) 3.13 / 0.57 ms, 512 x 2048 (16) 3.66 / 1.02, 1000 x 2048 (8) 3.95 / 1.37, 2048 x 4096 (2) 5.49 / 3.81,
 // 5000 x 4096 (4) 11.97 / 9.84, 8192 x 1024 (2) 6.50 / 4.91; 8192 x 4096 and 8192 x 2048 fill whole rounds and stay undivided.
 int gemm_nn_splits(int64_t M, int64_t N, int64_t K, int cus, size_t scratch_bytes) {
-  const int tiles_m = static_cast<int>((M + kBM - 1) / kBM), tiles_n = static_cast<int>((N + kBN - 1) / kBN);
-  const int blocks_m = (tiles_m + kGroupM - 1) / kGroupM, blocks_n = (tiles_n + kGroupN - 1) / kGroupN, blocks = blocks_m * blocks_n;
-  const int64_t tiles = static_cast<int64_t>(tiles_m) * tiles_n, nk = K / kBK;
+  const int64_t nk = K / kBK;
   const int per_die = cus >= 8 ? cus / 8 : 1;
   int best = 1;
   double best_cost = 0.0;
   for (int64_t s = 1; s <= 64; ++s) {
-    if (s > 1 && (nk < 128 || nk / s < 16 || tiles * s > 16 * static_cast<int64_t>(cus))) break;
+    const TileMap t = tile_map(M, N, s);
+    if (s > 1 && (nk < 128 || nk / s < 16 || t.tiles * s > 16 * static_cast<int64_t>(cus))) break;
     if (s > 1 && static_cast<uint64_t>(s) * static_cast<uint64_t>(M) * static_cast<uint64_t>(N) * 4u > scratch_bytes) break;
-    // the busiest of the eight dies, each of which takes a contiguous eighth of the blocks (of all ranges)
-    const int64_t share = (blocks * s + 7) / 8;
-    int64_t busiest = 0;
-    for (int64_t b0 = 0; b0 < blocks * s; b0 += share) {
-      int64_t n = 0;
-      for (int64_t b = b0; b < b0 + share && b < blocks * s; ++b) {
-        const int bn = static_cast<int>(b % blocks) / blocks_m, bm = static_cast<int>(b % blocks) % blocks_m;
-        n += std::min(kGroupM, tiles_m - bm * kGroupM) * std::min(kGroupN, tiles_n - bn * kGroupN);
-      }
-      busiest = std::max(busiest, n);
-    }
+    const int64_t busiest = std::min<int64_t>(t.per_die, t.tiles * s);
     double cost = static_cast<double>((busiest + per_die - 1) / per_die) * static_cast<double>((nk + s - 1) / s + 8);
     if (s > 1) cost = (cost + static_cast<double>(s * M * N) * 8.0 / 5.8e6 + 4.0) / 0.97;
     if (s == 1 || cost < best_cost) {
@@ -562,25 +579,23 @@ __global__ __launch_bounds__(256) void dppo_gemm_sum_kernel(const f32x4* __restr
 hipError_t launch_gemm_nn(const uint16_t* A, int64_t lda, const uint16_t* B, int64_t ldb, void* C, int64_t ldc,
                           int M, int N, int K, int splits, float* scratch, hipStream_t s) {
   if (M <= 0 || N <= 0) return hipSuccess;
-  const int tiles_m = (M + kBM - 1) / kBM, tiles_n = (N + kBN - 1) / kBN;
-  const int blocks_m = (tiles_m + kGroupM - 1) / kGroupM, blocks_n = (tiles_n + kGroupN - 1) / kGroupN;
   if (splits > 1) {
     if (N % 4 != 0 || !scratch) return hipErrorInvalidValue;
     const int split_steps = (K / kBK + splits - 1) / splits;
     const int used = (K / kBK + split_steps - 1) / split_steps;       // ranges that hold a step
-    const int per_die = (used * blocks_m * blocks_n + 7) / 8;
-    hipLaunchKernelGGL((dppo_gemm_nt_kernel<kOutSplit, false, true>), dim3(8 * per_die * kGroupM * kGroupN), dim3(256), 0, s, A, lda, B, ldb,
-                       static_cast<void*>(scratch), static_cast<int64_t>(N), M, N, K, tiles_m, tiles_n, blocks_m, per_die, GemmStats{},
-                       blocks_m * blocks_n, split_steps);
+    TileMap map = tile_map(M, N, used);
+    map.split_steps = split_steps;
+    hipLaunchKernelGGL((dppo_gemm_nt_kernel<kOutSplit, false, true>), tile_grid(map), dim3(256), 0, s, A, lda, B, ldb,
+                       static_cast<void*>(scratch), static_cast<int64_t>(N), M, N, K, map, GemmStats{});
     if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
     const int64_t quads = static_cast<int64_t>(M) * N / 4;
     hipLaunchKernelGGL(dppo_gemm_sum_kernel, dim3(static_cast<unsigned>((quads + 255) / 256)), dim3(256), 0, s,
                        reinterpret_cast<const f32x4*>(scratch), used, quads, N / 4, static_cast<uint16_t*>(C), ldc);
     return hipGetLastError();
   }
-  const int blocks_per_die = (blocks_m * blocks_n + 7) / 8;
-  const dim3 grid(8 * blocks_per_die * kGroupM * kGroupN), wg(256);
-  hipLaunchKernelGGL((dppo_gemm_nt_kernel<kOutBf16, false, true>), grid, wg, 0, s, A, lda, B, ldb, C, ldc, M, N, K, tiles_m, tiles_n, blocks_m, blocks_per_die, GemmStats{}, 0, 0);
+  const TileMap map = tile_map(M, N, 1);
+  const dim3 grid = tile_grid(map), wg(256);
+  hipLaunchKernelGGL((dppo_gemm_nt_kernel<kOutBf16, false, true>), grid, wg, 0, s, A, lda, B, ldb, C, ldc, M, N, K, map, GemmStats{});
   return hipGetLastError();
 }
 
