@@ -21,6 +21,14 @@ import torch
 from . import binding as B
 
 
+def _grad_like(logits: torch.Tensor) -> torch.Tensor:
+    """An empty gradient for rows of `logits`, with the same row pitch: the boundary has one pitch for
+    both.  (torch.empty_like drops the pitch of a slice logits[:, :V] and returns packed rows.)"""
+    T, V = logits.shape
+    ld = logits.stride(0) if T > 1 else V
+    return logits.new_empty((T, max(ld, V)))[:, :V]
+
+
 class _DppoLoss(torch.autograd.Function):
     @staticmethod
     def forward(ctx, logits, sampled_ids, mu_logp, advantages, mu_topk_ids, mu_topk_logp, mu_logits, opts):
@@ -33,7 +41,7 @@ class _DppoLoss(torch.autograd.Function):
         need_grad = ctx.needs_input_grad[0]
         grad = None
         if need_grad:
-            grad = logits.detach() if opts.get("in_place", False) else torch.empty_like(logits)
+            grad = logits.detach() if opts.get("in_place", False) else _grad_like(logits)
         args = B.make_args(logits.detach(), sampled_ids, mu_logp, advantages, opts["delta"], opts["variant"], opts["loss_scale"], out,
                            mu_topk_ids, mu_topk_logp, grad_logits=grad, mu_logits=mu_logits,
                            mask_rule=opts.get("mask_rule", B.MASK_DIVERGENCE), eps_low=opts.get("eps_low", 0.2),

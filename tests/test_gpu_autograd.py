@@ -93,3 +93,20 @@ def test_hidden_state_form_backward_matches_the_direct_call():
     assert B.last_path() == "lmhead_fused"
     assert torch.equal(aux0["mask"], ref["mask"])
     assert torch.allclose(aux0["divergence"], ref["divergence"], rtol=1e-4, atol=1e-7)
+
+
+@pytest.mark.parametrize("V,ld", [(4090, 4096), (3001, 3072), (50257, 50304)])
+def test_backward_of_a_slice_of_padded_logits(V, ld):
+    """logits[:, :V] of a padded buffer: the gradient has the buffer's pitch, its values are those of the
+    direct call, and the bytes around it stay as they were."""
+    w = W.Workload("autograd_pitch", 2, 37, V, W.BINARY_TV, 0.2, logit_std=3.0, noise_std=1.0, adv="normal", seed=97)
+    b = W.make_batch(w, DEV, ld=ld, shift_sampled=2.0)
+    print(f"[case] autograd pitch V={V} ld={ld}", flush=True)
+    direct = torch.full_like(b["logits"], 7.0)
+    B.run_batch(b, grad=direct)
+    logits = b["logits"][:, :V].detach().requires_grad_(True)
+    loss, _ = _call(b, logits)
+    g, = torch.autograd.grad(loss, logits)
+    torch.cuda.synchronize()
+    assert g.stride() == logits.stride() and torch.equal(g, direct[:, :V])
+    assert (direct[:, V:] == 7.0).all()

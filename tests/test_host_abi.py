@@ -6,6 +6,7 @@ import os
 import re
 
 import pytest
+import torch
 
 from paper_2602_04879_amd import binding as B
 
@@ -161,3 +162,16 @@ def test_workspace_sizes():
     both = B.lmhead_workspace_bytes(T, V, chunk)
     assert both == 65536 + chunk * V * 2 and fwd < both // 20
     assert B.lmhead_fwd_workspace_bytes(10, 64, 0, 0) <= B.lmhead_workspace_bytes(10, 64, 0)
+
+
+@pytest.mark.parametrize("T,V,ld", [(4, 10, 16), (1, 10, 16), (3, 7, 7), (5, 33, 64), (0, 8, 8)])
+def test_autograd_gradient_buffer_covers_the_rows_at_the_logits_pitch(T, V, ld):
+    """The library writes gradient row t at t * ld of the LOGITS' pitch: the buffer the autograd wrapper
+    allocates for a slice of padded logits has that pitch too."""
+    from paper_2602_04879_amd import autograd as A
+    logits = torch.empty((T, ld), dtype=torch.bfloat16)[:, :V]
+    g = A._grad_like(logits)
+    assert g.shape == logits.shape and g.dtype == logits.dtype and (V <= 1 or g.stride(1) == 1)
+    if T > 1:
+        assert g.stride(0) == logits.stride(0)
+        assert g.untyped_storage().nbytes() >= 2 * ((T - 1) * ld + V)
