@@ -306,6 +306,16 @@ dppo_status_t dppo_lmhead_loss_fwd_bwd(const dppo_lmhead_args_t* args, void* str
 /* sizeof(dppo_lmhead_args_t) as the library was compiled. */
 size_t dppo_lmhead_args_size(void);
 
+/* x[r, 0..cols) *= *factor for `rows` rows of bf16 at a pitch of ld entries, each product formed in fp32
+ * and rounded once: a gradient above times the incoming gradient of the scalar loss, one float in DEVICE
+ * memory that the kernel reads (a factor of exactly one leaves x untouched).  Any 2-byte aligned
+ * rows; nothing outside them is written. */
+dppo_status_t dppo_scale_rows_bf16(void* x, int64_t rows, int64_t cols, int64_t ld, const float* factor, void* stream);
+
+/* dst[i] = bf16(src[i] * *factor), i < n, formed in fp32 and rounded once (the fp32 weight gradient in
+ * the weight's own type); dst and src 16-byte aligned, factor one float in device memory. */
+dppo_status_t dppo_scale_to_bf16(void* dst, const float* src, int64_t n, const float* factor, void* stream);
+
 /* C[M, N] = A[M, K] * B[N, K]^T on the matrix cores: bf16 operands, both row-major with the
  * contraction index contiguous (activations [T, d] times an lm_head weight [V, d] transposed),
  * fp32 accumulation, C bf16 row-major rounded to nearest even.  The building block of the

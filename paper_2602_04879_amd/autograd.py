@@ -49,7 +49,7 @@ class _DppoLoss(torch.autograd.Function):
                            anchor_logp=opts.get("anchor_logp"), relax_alpha=opts.get("relax_alpha", 0.0),
                            relax_sides=opts.get("relax_sides", 0))
         (B.dppo_loss_fwd_bwd if need_grad else B.dppo_loss_fwd)(args)
-        ctx.grad_logits = grad
+        ctx.grad_logits, ctx.own_buffer = grad, not opts.get("in_place", False)
         side = [out[k] for k in ("divergence", "mask", "loss_tok")] + ([out["diagnostics"]] if out["diagnostics"] is not None else [])
         ctx.mark_non_differentiable(*side)
         return (out["loss"].reshape(()), *side)
@@ -61,13 +61,15 @@ class _DppoLoss(torch.autograd.Function):
         if g is None:
             return (None,) * 8
         # d(out)/d(logits) = grad_loss * d(loss)/d(logits); the scale is applied in fp32 and rounded once
+        if ctx.own_buffer and not torch.is_grad_enabled():
+            return (B.scale_rows_(g, grad_loss), None, None, None, None, None, None, None)
+        # a graph through grad_loss (create_graph), or a gradient in the logits' own storage, which stays as it is
         g = (g.float() * grad_loss.float()).to(torch.bfloat16) if not _is_one(grad_loss) else g
         return (g, None, None, None, None, None, None, None)
 
 
 def _is_one(t: torch.Tensor) -> bool:
-    # the usual case, loss.backward(): a scalar one, known on the host only at the cost of a
-    # synchronisation, which one scalar read is
+    # a scalar one, known on the host only at the cost of a synchronisation, which one scalar read is
     return t.numel() == 1 and float(t) == 1.0
 
 
@@ -113,11 +115,16 @@ class _DppoLmheadLoss(torch.autograd.Function):
     def backward(ctx, grad_loss, *unused):
         gh, gw = ctx.grads
         ctx.grads = None
-        one = _is_one(grad_loss)
+        if not torch.is_grad_enabled():
+            if gh is not None:
+                gh = B.scale_rows_(gh, grad_loss)
+            if gw is not None:      # accumulated in fp32; autograd wants the weight's own type
+                gw = B.scale_to_bf16(gw, grad_loss)
+            return (gh, gw, None, None, None, None, None, None)
+        one = _is_one(grad_loss)                      # a graph through grad_loss (create_graph)
         if gh is not None and not one:
             gh = (gh.float() * grad_loss.float()).to(torch.bfloat16)
         if gw is not None:
-            # the library accumulates the weight's gradient in fp32; autograd wants the weight's own type
             gw = (gw if one else gw * grad_loss.float()).to(torch.bfloat16)
         return (gh, gw, None, None, None, None, None, None)
 

@@ -98,6 +98,10 @@ def lib() -> C.CDLL:
             f.restype = C.c_int
             f.argtypes = [C.c_void_p, C.c_int64, C.c_void_p, C.c_int64, C.c_void_p, C.c_int64,
                           C.c_int64, C.c_int64, C.c_int64, C.c_void_p]
+        l.dppo_scale_rows_bf16.restype = C.c_int
+        l.dppo_scale_rows_bf16.argtypes = [C.c_void_p, C.c_int64, C.c_int64, C.c_int64, C.c_void_p, C.c_void_p]
+        l.dppo_scale_to_bf16.restype = C.c_int
+        l.dppo_scale_to_bf16.argtypes = [C.c_void_p, C.c_void_p, C.c_int64, C.c_void_p, C.c_void_p]
         l.dppo_lmhead_workspace_bytes.restype = C.c_size_t
         l.dppo_lmhead_workspace_bytes.argtypes = [C.c_int64, C.c_int64, C.c_int64]
         for f in (l.dppo_gemm_nt_f32, l.dppo_gemm_tn_f32):
@@ -299,6 +303,25 @@ def gemm_tn_f32(a, b, c, accumulate: bool = False, stream=None):
     if st != 0:
         raise DppoError(st)
     return c
+
+
+def scale_rows_(x, factor, stream=None):
+    """dppo_scale_rows_bf16: x *= factor in place, x a bf16 matrix with unit inner stride, factor one fp32
+    value on the device."""
+    ld = x.stride(0) if x.shape[0] > 1 else x.shape[1]
+    st = lib().dppo_scale_rows_bf16(x.data_ptr(), x.shape[0], x.shape[1], ld, factor.data_ptr(), C.c_void_p(_stream_handle(stream)))
+    if st != 0:
+        raise DppoError(st)
+    return x
+
+
+def scale_to_bf16(x, factor, stream=None):
+    """dppo_scale_to_bf16: bf16(x * factor) of a packed fp32 tensor, factor one fp32 value on the device."""
+    out = torch.empty_like(x, dtype=torch.bfloat16)
+    st = lib().dppo_scale_to_bf16(out.data_ptr(), x.data_ptr(), x.numel(), factor.data_ptr(), C.c_void_p(_stream_handle(stream)))
+    if st != 0:
+        raise DppoError(st)
+    return out
 
 
 def last_path() -> str:

@@ -622,6 +622,28 @@ size_t dppo_lmhead_fwd_workspace_bytes(int64_t T, int64_t V, int32_t K, int64_t 
   return lmhead_fwd_workspace(T, V, K < 0 ? 0 : K, chunk_rows);
 }
 
+dppo_status_t dppo_scale_rows_bf16(void* x, int64_t rows, int64_t cols, int64_t ld, const float* factor, void* stream) {
+  if (rows < 0 || cols < 0 || ld < cols || (rows > 0 && cols > 0 && ld > INT64_MAX / 4 / rows)) return DPPO_ERR_SHAPE;
+  if (rows == 0 || cols == 0) return DPPO_OK;
+  if (!x || !factor) return DPPO_ERR_NULL;
+  if ((reinterpret_cast<uintptr_t>(x) & 1u) || (reinterpret_cast<uintptr_t>(factor) & 3u)) return DPPO_ERR_ALIGN;
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  int dev = 0;
+  if (!stream_device(s, &dev)) return DPPO_ERR_LAUNCH;
+  return dppo::launch_scale_rows(static_cast<uint16_t*>(x), rows, cols, ld, factor, device_info(dev).cus, s) == hipSuccess ? DPPO_OK : DPPO_ERR_LAUNCH;
+}
+
+dppo_status_t dppo_scale_to_bf16(void* dst, const float* src, int64_t n, const float* factor, void* stream) {
+  if (n < 0) return DPPO_ERR_SHAPE;
+  if (n == 0) return DPPO_OK;
+  if (!dst || !src || !factor) return DPPO_ERR_NULL;
+  if (((reinterpret_cast<uintptr_t>(dst) | reinterpret_cast<uintptr_t>(src)) & 15u) || (reinterpret_cast<uintptr_t>(factor) & 3u)) return DPPO_ERR_ALIGN;
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  int dev = 0;
+  if (!stream_device(s, &dev)) return DPPO_ERR_LAUNCH;
+  return dppo::launch_scale_to_bf16(static_cast<uint16_t*>(dst), src, n, factor, device_info(dev).cus, s) == hipSuccess ? DPPO_OK : DPPO_ERR_LAUNCH;
+}
+
 dppo_status_t dppo_gemm_nt(const void* A, int64_t lda, const void* B, int64_t ldb, void* C, int64_t ldc,
                            int64_t M, int64_t N, int64_t K, void* stream) {
   if (M < 0 || N < 0 || K < 64 || K % 64 != 0 || M >= (int64_t(1) << 31) || N >= (int64_t(1) << 31) || K >= (int64_t(1) << 31)) return DPPO_ERR_SHAPE;

@@ -110,3 +110,47 @@ def test_backward_of_a_slice_of_padded_logits(V, ld):
     torch.cuda.synchronize()
     assert g.stride() == logits.stride() and torch.equal(g, direct[:, :V])
     assert (direct[:, V:] == 7.0).all()
+
+
+@pytest.mark.parametrize("rows,cols,ld,off", [(1, 1, 1, 0), (1, 7, 7, 3), (3, 8, 8, 0), (5, 8189, 8192, 1), (4, 8193, 8193, 0),
+                                              (2, 65537, 65544, 5), (300, 4099, 4099, 7), (3000, 1024, 1088, 0)])
+def test_scaled_gradient_rows(rows, cols, ld, off):
+    """x *= factor over rows of any pitch and alignment: the fp32 product rounded once, the entries
+    around the rows untouched, and a factor of one leaving every bit alone."""
+    g = torch.Generator(device=DEV); g.manual_seed(rows + cols)
+    buf = torch.randn(off + rows * ld + 9, generator=g, device=DEV).to(torch.bfloat16)
+    buf[off] = float("inf")
+    keep = buf.clone()
+    x = buf[off:off + rows * ld].view(rows, ld)[:, :cols]
+    print(f"[case] scale rows={rows} cols={cols} ld={ld} off={off}", flush=True)
+    B.scale_rows_(x, torch.ones((), device=DEV))
+    torch.cuda.synchronize()
+    assert torch.equal(buf, keep)
+    f = torch.tensor(-0.3125 / 3, device=DEV)
+    B.scale_rows_(x, f)
+    torch.cuda.synchronize()
+    want = keep.clone()
+    v = want[off:off + rows * ld].view(rows, ld)[:, :cols]
+    v.copy_((v.float() * f).to(torch.bfloat16))
+    assert torch.equal(buf, want)
+    src = torch.randn(rows * cols, generator=g, device=DEV)
+    got = B.scale_to_bf16(src, f)
+    torch.cuda.synchronize()
+    assert torch.equal(got, (src * f).to(torch.bfloat16))
+
+
+def test_gradient_with_a_graph_through_the_incoming_gradient():
+    """create_graph keeps the path from the gradient to the weight of the loss."""
+    w = W.Workload("autograd_graph", 2, 16, 4096, W.BINARY_TV, 0.5, logit_std=3.0, noise_std=0.3, adv="normal", seed=99)
+    b = W.make_batch(w, DEV)
+    logits = b["logits"].clone().requires_grad_(True)
+    u = torch.tensor(0.5, device=DEV, requires_grad=True)
+    loss, _ = _call(b, logits)
+    g, = torch.autograd.grad(loss * u, logits, create_graph=True)
+    du, = torch.autograd.grad(g.float().square().sum(), u)
+    plain = b["logits"].clone().requires_grad_(True)
+    loss1, _ = _call(b, plain)
+    loss1.backward()
+    torch.cuda.synchronize()
+    want = plain.grad.double().square().sum().item()          # d/du sum (u g)^2 = 2 u sum g^2, u = 1/2: exact in bf16
+    assert abs(du.item() - want) <= 1e-2 * want
