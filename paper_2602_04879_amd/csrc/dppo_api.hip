@@ -634,14 +634,11 @@ dppo_status_t dppo_scale_rows_bf16(void* x, int64_t rows, int64_t cols, int64_t 
 }
 
 dppo_status_t dppo_scale_to_bf16(void* dst, const float* src, int64_t n, const float* factor, void* stream) {
-  if (n < 0) return DPPO_ERR_SHAPE;
+  if (n < 0 || n >= (int64_t(1) << 42)) return DPPO_ERR_SHAPE;
   if (n == 0) return DPPO_OK;
   if (!dst || !src || !factor) return DPPO_ERR_NULL;
   if (((reinterpret_cast<uintptr_t>(dst) | reinterpret_cast<uintptr_t>(src)) & 15u) || (reinterpret_cast<uintptr_t>(factor) & 3u)) return DPPO_ERR_ALIGN;
-  hipStream_t s = static_cast<hipStream_t>(stream);
-  int dev = 0;
-  if (!stream_device(s, &dev)) return DPPO_ERR_LAUNCH;
-  return dppo::launch_scale_to_bf16(static_cast<uint16_t*>(dst), src, n, factor, device_info(dev).cus, s) == hipSuccess ? DPPO_OK : DPPO_ERR_LAUNCH;
+  return dppo::launch_scale_to_bf16(static_cast<uint16_t*>(dst), src, n, factor, static_cast<hipStream_t>(stream)) == hipSuccess ? DPPO_OK : DPPO_ERR_LAUNCH;
 }
 
 dppo_status_t dppo_gemm_nt(const void* A, int64_t lda, const void* B, int64_t ldb, void* C, int64_t ldc,

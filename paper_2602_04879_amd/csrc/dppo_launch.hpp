@@ -66,7 +66,7 @@ hipError_t launch_gemm_tn(const uint16_t* A, int64_t lda, const uint16_t* B, int
 // x[r, 0..cols) *= *factor (bf16, in place, any pitch and 2-byte alignment; nothing for a factor of one), and
 // dst[i] = bf16(src[i] * *factor) (dst, src 16-byte aligned).  factor: one float on the device.
 hipError_t launch_scale_rows(uint16_t* x, int64_t rows, int64_t cols, int64_t ld, const float* factor, int cus, hipStream_t s);
-hipError_t launch_scale_to_bf16(uint16_t* dst, const float* src, int64_t n, const float* factor, int cus, hipStream_t s);
+hipError_t launch_scale_to_bf16(uint16_t* dst, const float* src, int64_t n, const float* factor, hipStream_t s);
 
 // Clears the eight row counters of the register-resident kernel's run-time row hand-out.
 hipError_t launch_clear_counters(int32_t* counters, hipStream_t s);

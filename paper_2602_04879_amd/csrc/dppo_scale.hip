@@ -52,29 +52,26 @@ __global__ __launch_bounds__(kThreads) void dppo_scale_rows_kernel(uint16_t* x, 
 }
 
 // dst[i] = bf16(src[i] * *factor) for an fp32 source (the weight gradient): the conversion autograd
-// needs anyway, with the factor in it.  src and dst 16-byte aligned.
+// needs anyway, with the factor in it.  src and dst 16-byte aligned; eight 16-byte loads in flight per
+// thread, neighbouring lanes at neighbouring addresses.
+constexpr int kQuads = 8;
 __global__ __launch_bounds__(kThreads) void dppo_scale_to_bf16_kernel(uint16_t* __restrict__ dst, const float* __restrict__ src, int64_t n,
                                                                       const float* factor) {
   typedef float f32x4 __attribute__((ext_vector_type(4)));
+  typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
   const float f = *factor;
-  const int64_t oct = n >> 3;
+  const int64_t quads = n >> 2, i = static_cast<int64_t>(blockIdx.x) * (kQuads * kThreads) + threadIdx.x;
   const f32x4* s = reinterpret_cast<const f32x4*>(src);
-  u32x4* d = reinterpret_cast<u32x4*>(dst);
-  for (int64_t i = static_cast<int64_t>(blockIdx.x) * (2 * kThreads) + threadIdx.x; i < oct; i += static_cast<int64_t>(gridDim.x) * (2 * kThreads)) {
-    f32x4 a[2], b[2];
+  u32x2* d = reinterpret_cast<u32x2*>(dst);
+  f32x4 a[kQuads];
 #pragma unroll
-    for (int u = 0; u < 2; ++u)
-      if (i + u * kThreads < oct) {
-        a[u] = __builtin_nontemporal_load(s + 2 * (i + u * kThreads));
-        b[u] = __builtin_nontemporal_load(s + 2 * (i + u * kThreads) + 1);
-      }
+  for (int u = 0; u < kQuads; ++u)
+    if (i + u * kThreads < quads) a[u] = __builtin_nontemporal_load(s + i + u * kThreads);
 #pragma unroll
-    for (int u = 0; u < 2; ++u)
-      if (i + u * kThreads < oct)
-        d[i + u * kThreads] = u32x4{pack_bf16x2(a[u][0] * f, a[u][1] * f), pack_bf16x2(a[u][2] * f, a[u][3] * f),
-                                    pack_bf16x2(b[u][0] * f, b[u][1] * f), pack_bf16x2(b[u][2] * f, b[u][3] * f)};
-  }
-  if (blockIdx.x == 0 && 8 * oct + threadIdx.x < n) dst[8 * oct + threadIdx.x] = float_to_bf16_bits(src[8 * oct + threadIdx.x] * f);
+  for (int u = 0; u < kQuads; ++u)
+    if (i + u * kThreads < quads)
+      __builtin_nontemporal_store(u32x2{pack_bf16x2(a[u][0] * f, a[u][1] * f), pack_bf16x2(a[u][2] * f, a[u][3] * f)}, d + i + u * kThreads);
+  if (blockIdx.x == 0 && 4 * quads + threadIdx.x < n) dst[4 * quads + threadIdx.x] = float_to_bf16_bits(src[4 * quads + threadIdx.x] * f);
 }
 
 }  // namespace
@@ -88,10 +85,10 @@ hipError_t launch_scale_rows(uint16_t* x, int64_t rows, int64_t cols, int64_t ld
   return hipGetLastError();
 }
 
-hipError_t launch_scale_to_bf16(uint16_t* dst, const float* src, int64_t n, const float* factor, int cus, hipStream_t s) {
+hipError_t launch_scale_to_bf16(uint16_t* dst, const float* src, int64_t n, const float* factor, hipStream_t s) {
   if (n <= 0) return hipSuccess;
-  const int64_t items = (n / 8 + 2 * kThreads - 1) / (2 * kThreads) + 1;
-  const int64_t grid = items < 8 * static_cast<int64_t>(cus) ? items : 8 * static_cast<int64_t>(cus);
+  const int64_t grid = (n / 4 + kQuads * kThreads - 1) / (kQuads * kThreads) + (n < 4 ? 1 : 0);
+  if (grid > 0x7fffffff) return hipErrorInvalidValue;
   hipLaunchKernelGGL(dppo_scale_to_bf16_kernel, dim3(static_cast<unsigned>(grid)), dim3(kThreads), 0, s, dst, src, n, factor);
   return hipGetLastError();
 }
