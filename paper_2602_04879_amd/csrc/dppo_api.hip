@@ -249,7 +249,21 @@ dppo_status_t launch_loss(const dppo_args_t* a, bool grad, const LossScratch& sc
     }
     const bool tv_full = a->variant == DPPO_FULL_TV;
     const int fr_chunks = (full && !(a->flags & DPPO_FLAG_FORCE_STREAMING)) ? dppo::fullvocab_resident_chunks(p, tv_full, grad) : 0;
-    if (fr_chunks) {
+    // Forward only, rows of more than 48 KiB (with the row kept in registers only up to there): streamed.
+    // Measured (us, registers / streamed; plain and with diagnostics): V = 49152, 16384 tokens: 300 / 303 and 335 / 333,
+    // 57344: 338 / 345 and 401 / 388, 65536: 364 / 363 and 413 / 400, 81920, 12000 tokens: 377 / 326 and 419 / 350.  Rows no shape takes that are
+    // shorter (odd lengths around a shape's end) are faster with the many small workgroups of the two-pass
+    // kernel (V = 8181, 16384 tokens: 141 / 207).
+    const bool forward = !full && !grad && !(a->flags & DPPO_FLAG_FORCE_STREAMING) &&
+                         (resident ? !dppo::forward_resident(r_threads, r_chunks) : a->V >= 65536 && a->V < (int64_t(1) << 30));
+    if (forward) {
+      int64_t grid = 2 * static_cast<int64_t>(cus);
+      if (grid > a->T) grid = a->T;
+      if (grid > max_parts) grid = max_parts;
+      nparts = static_cast<int>(grid);
+      if (dppo::launch_forward(p, !on_lines, nparts, s) != hipSuccess) return DPPO_ERR_LAUNCH;
+      g_last_path = resident ? "resident" : "streaming";
+    } else if (fr_chunks) {
       // long aligned rows (backward, or the TV form): the trainer's row stays in registers, one workgroup per compute unit
       int64_t grid = cus;
       if (grid > a->T) grid = a->T;

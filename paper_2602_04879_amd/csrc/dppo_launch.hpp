@@ -20,6 +20,12 @@ bool resident_shape(int64_t V, bool ragged, int* threads, int* chunks);
 hipError_t launch_resident(const KParams& p, bool grad, bool ragged, int threads, int chunks, int grid, hipStream_t s);
 int resident_blocks_per_cu(bool grad, bool dyn, bool ragged, int threads, int chunks);
 
+// Forward only: rows streamed once through the statistics, at most two workgroups per compute unit,
+// any V and pitch with ragged = true (2-byte aligned rows), ragged = false as above.  The register-resident
+// kernel's forward-only form exists for the shapes that forward_resident() names, the shorter rows.
+hipError_t launch_forward(const KParams& p, bool ragged, int grid, hipStream_t s);
+constexpr bool forward_resident(int threads, int chunks) { return threads < 512 || chunks <= 12; }
+
 // Register-resident kernel for rows too long for the register file alone (forward+backward only):
 // part of the row in registers, part in LDS, the rest passed through twice.  resident_long_chunks()
 // gives the number of 512 x 16-byte chunks of a row this form takes, 0 where it does not apply

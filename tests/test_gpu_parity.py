@@ -708,6 +708,60 @@ def test_forward_only_against_oracle(name):
     _run_and_compare(w, backward=False, shift=2.0, flags=B.FLAG_FORCE_STREAMING)
 
 
+@pytest.mark.parametrize("V,ld,path", [
+    (50257, 50257, "resident"),       # 12.3 chunks of 4096 entries: every row's frame starts elsewhere
+    (57352, 57352, "resident"),       # 14 chunks and one block; 16-byte aligned, not on lines
+    (65536, 65536, "resident"),       # 16 chunks exactly: two windows
+    (69632, 69632, "resident"),       # 17 chunks: the last group is mostly past the row
+    (151936, 151936, "resident"),
+    (155586, 155586, "streaming"),    # no register-resident shape takes these
+    (160001, 160064, "streaming"),
+    (262145, 262145, "streaming")])
+def test_forward_only_rows_streamed(V, ld, path):
+    """Forward only, long rows streamed through a window of registers: several rows per workgroup,
+    sampled tokens on the borders of blocks, chunks and windows, ignored rows, blocks of -inf, rows of one sign, K beyond
+    one wave; every row against the oracle, with and without diagnostics the same, and bit for bit what
+    the forward + backward call reports where that runs on 512 threads too."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    T = 2 * cus + 21
+    w = W.Workload("fwd", 1, T, V, W.TOPK_KL, 0.05, K=70, logit_std=3.0, noise_std=1.0, zipf_s=1.1, adv="normal", seed=107)
+    b = W.make_batch(w, DEV, ld=ld, shift_sampled=2.0, rows_per_step=256)
+    b["advantages"] = torch.randn(T, device=DEV)
+    special = [0, 7, 8, 63, 64, 4095, 4096, 32767, 32768, V // 2, V - 4097, V - 9, V - 8, V - 2, V - 1]
+    for t, a in enumerate(special):
+        b["sampled_ids"][2 * t] = a
+        b["sampled_ids"][T - 1 - 2 * t] = a
+    b["sampled_ids"][40::17] = -1
+    rows = torch.arange(T, device=DEV)
+    a = b["sampled_ids"].clamp(min=0).long()
+    keep = b["logits"][rows, a].clone()
+    b["logits"][41, 9000:40000] = float("-inf")
+    b["logits"][42, 10:V - 10] = float("-inf")
+    b["logits"][43, :V] = -50.0
+    b["logits"][44, :V] = 3.0e4
+    b["logits"][rows[41:43], a[41:43]] = keep[41:43]
+    b["sampled_ids"][41:45] = a[41:45].to(torch.int32)
+    _say(f"[case] forward only streamed V={V} ld={ld}")
+    res = B.run_batch(b, backward=False, diagnostics=True)
+    torch.cuda.synchronize()
+    assert B.last_path() == path
+    plain = B.run_batch(b, backward=False)
+    both = B.run_batch(b, diagnostics=True, flags=B.FLAG_STATIC_ROWS)
+    torch.cuda.synchronize()
+    for k in ("loss", "loss_tok", "divergence", "mask"):
+        assert torch.equal(plain[k], res[k]), k
+    if path == "resident":
+        for k in ("loss_tok", "divergence", "mask", "diagnostics"):
+            assert torch.equal(both[k], res[k]), k
+    some = np.arange(0, T, 1 if V < 70000 else 3)
+    some = np.unique(np.concatenate([some, np.arange(0, 48), np.arange(T - 32, T)]))
+    ref = P.oracle_rows(b, some, want_grad=False)
+    st = P.compare_rows(b, res, some, check_grad=False, ref=ref)
+    P.check_loss_scalar(b, res)
+    assert st["masked"] > 20
+    _say(f"       {st}")
+
+
 def test_other_stream_and_loss_tok_optional():
     w = W.Workload("stream", 2, 16, 2048, W.TOPK_TV, 0.1, K=8, logit_std=2.0, noise_std=0.5, adv="pm1", seed=4)
     b = W.make_batch(w, DEV)
