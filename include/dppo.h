@@ -238,8 +238,8 @@ size_t dppo_args_size(void);
  * (rows of 16392 .. 65536 entries with the gradient, many of them per call: groups of two to six
  * rows held in registers), "streaming" (row re-read),
  * "fullvocab" (the two-row kernel of the DPPO_FULL_* variants) or "fullvocab_resident" (their
- * backward, and the forward-only TV form, on long aligned rows: the trainer's row held in
- * registers, the rollout row streamed past it); "lmhead" after a dppo_lmhead_* call that went
+ * backward, and the forward-only TV form on long rows, where rows are aligned and not too few: the
+ * trainer's row held in registers, the rollout row streamed past it); "lmhead" after a dppo_lmhead_* call that went
  * through chunks of logits, "lmhead_fused" after a forward-only one that did not. */
 const char* dppo_last_path(void);
 

@@ -248,7 +248,7 @@ dppo_status_t launch_loss(const dppo_args_t* a, bool grad, const LossScratch& sc
       r_chunks = l_chunks;
     }
     const bool tv_full = a->variant == DPPO_FULL_TV;
-    const int fr_chunks = (full && !(a->flags & DPPO_FLAG_FORCE_STREAMING)) ? dppo::fullvocab_resident_chunks(p, tv_full, grad) : 0;
+    const int fr_chunks = (full && !(a->flags & DPPO_FLAG_FORCE_STREAMING)) ? dppo::fullvocab_resident_chunks(p, tv_full, grad, cus) : 0;
     // Forward only, rows of more than 48 KiB (with the row kept in registers only up to there): streamed.
     // Measured (us, registers / streamed; plain and with diagnostics): V = 49152, 16384 tokens: 300 / 303 and 335 / 333,
     // 57344: 338 / 345 and 401 / 388, 65536: 364 / 363 and 413 / 400, 81920, 12000 tokens: 377 / 326 and 419 / 350.  Rows no shape takes that are
@@ -264,13 +264,14 @@ dppo_status_t launch_loss(const dppo_args_t* a, bool grad, const LossScratch& sc
       if (dppo::launch_forward(p, !on_lines, nparts, s) != hipSuccess) return DPPO_ERR_LAUNCH;
       g_last_path = resident ? "resident" : "streaming";
     } else if (fr_chunks) {
-      // long aligned rows (backward, or the TV form): the trainer's row stays in registers, one workgroup per compute unit
-      int64_t grid = cus;
+      // aligned rows (backward, or the TV form on long ones): the trainer's row stays in registers
+      const int per_cu = dppo::fullvocab_resident_per_cu(fr_chunks);
+      int64_t grid = static_cast<int64_t>(per_cu) * cus;
       if (grid > a->T) grid = a->T;
       if (grid > max_parts) grid = max_parts;
       nparts = static_cast<int>(grid);
       // with the gradient and several rows per workgroup: rows handed out at run time
-      const bool dyn = grad && rows_at_run_time(a, sc, grid);
+      const bool dyn = grad && per_cu == 1 && rows_at_run_time(a, sc, grid);
       if (dyn && arm_rows_at_run_time(p, a, sc, fin, fin_n, s) != DPPO_OK) return DPPO_ERR_LAUNCH;
       if (dppo::launch_fullvocab_resident(p, tv_full, grad, fr_chunks, nparts, s) != hipSuccess) return DPPO_ERR_LAUNCH;
       g_last_path = "fullvocab_resident";

@@ -3,7 +3,8 @@
 // between the rollout policy's and the trainer's next-token distributions, both given as rows of
 // bf16 logits, and the gradient of the masked surrogate over the trainer's row.
 //
-// One persistent workgroup of 512 threads per compute unit owns one row at a time.  The trainer
+// A persistent workgroup of 512 threads, one per compute unit (two for rows of up to 49152 entries), owns
+// one row at a time.  The trainer
 // row z stays packed in its vector registers (as in the register-resident loss kernel: V = 151936
 // is 297 KiB of a compute unit's 512 KiB register file), the rollout row y streams past it a few
 // 16-byte chunks per thread at a time and is never kept in registers:
@@ -28,8 +29,13 @@ namespace dppo {
 namespace {
 
 constexpr int kThreads = 512;
-constexpr int kWindow = 4;        // chunks of y in flight per thread (4, 8 and 12 measure the same)
-constexpr int kKeep = 18;         // TV form: chunks of y kept in LDS between the passes (18 x 8 KiB of the 160 KiB)
+// Shapes (chunks of z per thread).  Up to 12 chunks two workgroups share a compute unit (128 registers,
+// 72 KiB of LDS for y each), from 14 on one owns it.
+constexpr bool two_per_cu(int nchunk) { return nchunk <= 12; }
+constexpr int window_of(int nchunk) { return nchunk <= 8 ? nchunk : 4; }   // chunks of y in flight per thread (32 and 38 chunks: 4, 8 and 12 measure the same)
+// chunks every row of a shape fills (shorter rows take the next smaller one): only later ones can have lanes past the row
+constexpr int full_chunks(int nchunk) { return nchunk <= 16 ? nchunk - 2 : nchunk <= 24 ? nchunk - 4 : nchunk == 32 ? 24 : 32; }
+constexpr int keep_of(int nchunk) { return two_per_cu(nchunk) ? 9 : 18; }   // TV form: chunks of y kept in LDS between the passes (8 KiB each, 144 of the 160 KiB)
 
 // Running sum of 2^(x*log2e + b) over one row with an integer offset b <= -max*log2e that only
 // ever decreases (lowering it rescales the sums by an exact power of two).  T: also sum 2^x * x,
@@ -66,16 +72,17 @@ struct RowStat {
 // / Top-K variants: the dies do not run at one speed, and with rows fixed by the workgroup index the
 // slowest compute unit ends the kernel), the loss terms to one slot per row.
 template <int NCHUNK, bool TV, bool DIAG, bool GRAD, bool DYN>
-__global__ __launch_bounds__(kThreads) void dppo_fullvocab_resident_kernel(const KParams p) {
+__global__ __launch_bounds__(kThreads, two_per_cu(NCHUNK) ? 4 : 2) void dppo_fullvocab_resident_kernel(const KParams p) {
   static_assert(GRAD || TV, "forward only, the KL form reads each row once anyway: the general kernel serves it");
   static_assert(GRAD || !DYN, "rows at run time: the gradient forms only");
-  static_assert(NCHUNK == 32 || NCHUNK == 38, "the forms the host selects: rows of more than 24 and up to 32, more than 32 and up to 38 chunks");
+  static_assert(NCHUNK >= 32 || GRAD, "shorter rows: the gradient forms only");
+  constexpr int kWindow = window_of(NCHUNK);
   constexpr int THREADS = kThreads, NW = THREADS / kWave;
   constexpr uint32_t kStride = THREADS * 16u;      // bytes between a thread's consecutive chunks
   constexpr uint32_t kNegInfPair = 0xFF80FF80u;    // two bf16 -inf
-  constexpr int KEEP = TV ? (kKeep < NCHUNK ? kKeep : NCHUNK) : 0;
+  constexpr int KEEP = TV ? (keep_of(NCHUNK) < NCHUNK ? keep_of(NCHUNK) : NCHUNK) : 0;
   constexpr int REREAD = NCHUNK - KEEP;            // TV form: chunks of y that pass 2 reads from memory again
-  constexpr int FULLCHUNKS = (NCHUNK == 32) ? 24 : 32;   // chunks every row of this form fills (shorter rows take the next smaller form): only later ones can have lanes past the row
+  constexpr int FULLCHUNKS = full_chunks(NCHUNK);  // only later chunks can have lanes past the row
   __shared__ float sh_bz[NW], sh_by[NW];
   __shared__ double sh_sz[NW], sh_tz[NW], sh_sy[NW], sh_uy[NW], sh_acc[NW];
   __shared__ RowCoef sh_rc;
@@ -83,7 +90,7 @@ __global__ __launch_bounds__(kThreads) void dppo_fullvocab_resident_kernel(const
   __shared__ int sh_row[2];
   // chunks wave 0 parks around its float64 arithmetic (the TV form's kept chunks of y leave room for
   // 8), and chunks whose refill waits for the epilogue (forward only)
-  constexpr int kPark = TV ? 8 : 16;
+  constexpr int kPark = NCHUNK < 32 ? 0 : TV ? 8 : 16;
   constexpr int kLate = GRAD ? 0 : 8;
   __shared__ u32x4 sh_park[kPark > 0 ? kPark * kWave : 1];
   // every thread parks its own 16 bytes per kept chunk and takes them back itself: no synchronisation
@@ -120,6 +127,9 @@ __global__ __launch_bounds__(kThreads) void dppo_fullvocab_resident_kernel(const
     __syncthreads();
     if (row >= p.T) return;            // every row already handed out: nothing to do, and no address to form
   }
+  // (in front of the rows: the compiler's one wait at the head of the loop covers both ways into it)
+  int a_next = p.sampled[row];
+  __builtin_amdgcn_sched_barrier(0);
   {
     const row_rsrc_t zr = make_row_rsrc(zbase + row * pitch, row_bytes);
     const row_rsrc_t yr = make_row_rsrc(ybase + row * pitch_y, row_bytes);
@@ -128,7 +138,6 @@ __global__ __launch_bounds__(kThreads) void dppo_fullvocab_resident_kernel(const
 #pragma unroll
     for (int i = 0; i < kWindow; ++i) yb[i] = row_load16<kY1Nt>(yr, voff, i * kStride);
   }
-  int a_next = p.sampled[row];
 
   for (; row < p.T;) {
     const int a = uniform_i(a_next);
@@ -152,11 +161,13 @@ __global__ __launch_bounds__(kThreads) void dppo_fullvocab_resident_kernel(const
     RowCoef rc;
     rc.coef = 0.f; rc.kexp = 0.f; rc.g_a = 0.f;
     if (live) {
-      const float z_a = bf16_bits_to_float(zrow[a]);
+      // Requested now, looked at behind pass 1 (raw bits until then): a use up here would be a wait for
+      // everything requested in front of it, i.e. the whole row.
+      uint32_t za_bits = zrow[a];
+      float packed_scalars = (wid == 0) ? load_row_scalars(p, row, lane) : 0.f;
       // ---- pass 1 ------------------------------------------------------------------------------
       RowStat<DIAG, false> st;       // z, without a_t
       RowStat<false, !TV> cs;        // y, and for the KL form y - z
-      st.cover(fmaxf(kNegBig, z_a));   // the offset must cover z[a_t]
 #pragma unroll
       for (int i = 0; i < NCHUNK; ++i) {
         u32x4 zq = buf[i], yq = yb[i % kWindow];
@@ -188,15 +199,17 @@ __global__ __launch_bounds__(kThreads) void dppo_fullvocab_resident_kernel(const
         for (int i = 0; i < kWindow; ++i)
           if (i < REREAD) yb[i] = row_load16<true>(yr, voff, (KEEP + i) * kStride);
       }
+      asm volatile("" : "+v"(za_bits), "+v"(packed_scalars));
+      const float z_a = __uint_as_float(za_bits << 16);
       // workgroup-wide offsets = the smallest ones; rescaling to them is exact
       const float wbz = -wave_max(-st.b), wby = -wave_max(-cs.b);
       if (lane == 0) { sh_bz[wid] = wbz; sh_by[wid] = wby; }
       if (DYN && tid == 0) sh_row[0] = more ? drawn : kNoRow;
       __syncthreads();
       if (DYN) next2 = uniform_i(sh_row[0]);
-      float bz = sh_bz[0], by = sh_by[0];
+      float bz = -ceilf(fmaxf(z_a, kNegBig) * kLog2e), by = sh_by[0];      // the offset must also cover z[a_t]
 #pragma unroll
-      for (int w = 1; w < NW; ++w) { bz = fminf(bz, sh_bz[w]); by = fminf(by, sh_by[w]); }
+      for (int w = 0; w < NW; ++w) { bz = fminf(bz, sh_bz[w]); by = fminf(by, sh_by[w]); }
       {
         const double dd = static_cast<double>(bz - st.b), sc = static_cast<double>(fast_exp2(bz - st.b));
         const double scy = static_cast<double>(fast_exp2(by - cs.b));
@@ -314,16 +327,16 @@ __global__ __launch_bounds__(kThreads) void dppo_fullvocab_resident_kernel(const
         RowScalars rs;
         rs.a = a;
         rs.za = z_a;
-        rs.lmu = p.mu_logp[row];
-        rs.lanc = anchor_or(p, row, rs.lmu);
-        rs.adv = p.adv[row];
+        unpack_row_scalars(packed_scalars, rs);
         TopkLane tk;
         tk.id = -1; tk.lp = 0.f; tk.z = 0.f;
         // through an empty asm statement, so that the addresses of the per-token outputs are formed
         // here and not held in registers across the passes
         int row_e = row;
         asm volatile("" : "+s"(row_e));
-        const RowResult res = row_epilogue(ep, row_e, rs, tk, zrow, bz, S_rest, T_rest, lane, D);
+        // (two workgroups per compute unit: a call, whose registers stay out of the kernel's budget)
+        const RowResult res = two_per_cu(NCHUNK) ? row_epilogue_call(ep, row_e, rs, tk, zrow, bz, S_rest, T_rest, lane, D)
+                                          : row_epilogue(ep, row_e, rs, tk, zrow, bz, S_rest, T_rest, lane, D);
         rc = res.rc;
         if (DYN) { if (lane == 0) p.row_loss[row] = res.loss_term; }
         else loss_acc += res.loss_term;
@@ -414,15 +427,21 @@ hipError_t launch_chunks(const KParams& p, bool tv, bool grad, int grid, hipStre
   const bool diag = p.diag != nullptr, dyn = p.row_counters != nullptr;
   if (dyn && !grad) return hipErrorInvalidValue;       // rows at run time: the gradient forms only
   const dim3 g(grid), b(kThreads);
+  constexpr bool kDyn = !two_per_cu(NCHUNK);        // rows at run time: one workgroup per compute unit
+  if (dyn && !kDyn) return hipErrorInvalidValue;
 #define DPPO_FORM(TVF, D, G, Y) hipLaunchKernelGGL((dppo_fullvocab_resident_kernel<NCHUNK, TVF, D, G, Y>), g, b, 0, s, p)
   if (!grad) {
-    if (diag) DPPO_FORM(true, true, false, false); else DPPO_FORM(true, false, false, false);
+    if constexpr (NCHUNK >= 32) {
+      if (diag) DPPO_FORM(true, true, false, false); else DPPO_FORM(true, false, false, false);
+    } else {
+      return hipErrorInvalidValue;
+    }
   } else if (tv) {
-    if (diag) { if (dyn) DPPO_FORM(true, true, true, true); else DPPO_FORM(true, true, true, false); }
-    else      { if (dyn) DPPO_FORM(true, false, true, true); else DPPO_FORM(true, false, true, false); }
+    if (diag) { if (dyn) DPPO_FORM(true, true, true, kDyn); else DPPO_FORM(true, true, true, false); }
+    else      { if (dyn) DPPO_FORM(true, false, true, kDyn); else DPPO_FORM(true, false, true, false); }
   } else {
-    if (diag) { if (dyn) DPPO_FORM(false, true, true, true); else DPPO_FORM(false, true, true, false); }
-    else      { if (dyn) DPPO_FORM(false, false, true, true); else DPPO_FORM(false, false, true, false); }
+    if (diag) { if (dyn) DPPO_FORM(false, true, true, kDyn); else DPPO_FORM(false, true, true, false); }
+    else      { if (dyn) DPPO_FORM(false, false, true, kDyn); else DPPO_FORM(false, false, true, false); }
   }
 #undef DPPO_FORM
   return hipGetLastError();
@@ -433,21 +452,35 @@ hipError_t launch_chunks(const KParams& p, bool tv, bool grad, int grid, hipStre
 // Chunks of 512 x 16 bytes that cover a row in this form, 0 where it does not apply.  It applies to
 // the backward of both variants and to the forward-only TV form (which reads both rows twice; the
 // forward-only KL form reads each row once in the general kernel too), on rows of 98312 .. 155648
-// entries (shorter rows stay with the general kernel, several of whose rows fit the caches
-// together), a multiple of 8, every matrix 16-byte aligned with a pitch that is a multiple of 8.
-int fullvocab_resident_chunks(const KParams& p, bool tv, bool grad) {
+// entries, a multiple of 8, every matrix 16-byte aligned with a pitch that is a multiple of 8; to the
+// backward from 8200 entries on if there is a row for every compute unit.  Measured against the general
+// kernel, which reads what it needs again (us, general / this; TV and KL): V = 98304, 8192 tokens 1326 / 1039 and
+// 1201 / 844; 65536: 936 / 676 and 928 / 603; 49152, 16384 tokens 1232 / 977 and 970 / 903; 32000, 8192 tokens 471 / 355
+// and 373 / 317; 16384, 16384 tokens 550 / 434 and 442 / 379; 32000, 520 tokens 48 / 36 and 40 / 33.  The KL form, whose general kernel
+// reads only z again, loses where a quarter of the shape or more lies past the row (V = 16400, six chunks: 451 / 459)
+// and where a second row per workgroup leaves most workgroups idle (V = 40960, 600 tokens: 46 / 51; even at
+// 1100 tokens): it stays with the general kernel there.
+#define DPPO_FULL_SHAPES(X) X(4) X(6) X(8) X(10) X(12) X(14) X(16) X(20) X(24) X(32) X(38)
+int fullvocab_resident_chunks(const KParams& p, bool tv, bool grad, int cus) {
   if (!(grad || tv) || !p.mu_logits || p.V % 8 != 0 || p.ld % 8 != 0 || p.mu_ld % 8 != 0) return 0;
   if ((reinterpret_cast<uintptr_t>(p.logits) | reinterpret_cast<uintptr_t>(p.mu_logits) | (grad ? reinterpret_cast<uintptr_t>(p.grad) : 0)) & 15u) return 0;
   const int64_t nvec = p.V / 8;
-  if (nvec <= kThreads * 24) return 0;
-  if (nvec <= kThreads * 32) return 32;
-  if (nvec <= kThreads * 38) return 38;
+  if (nvec <= kThreads * 24 && (!grad || p.T < cus || nvec <= kThreads * 2)) return 0;
+  auto kl_gains = [&](int c) {
+    return !two_per_cu(c) || (4 * nvec >= 3 * static_cast<int64_t>(kThreads) * c && (p.T <= 2 * cus || p.T >= 4 * cus));
+  };
+#define DPPO_FULL_TRY(C) if (nvec <= kThreads * C) return (tv || kl_gains(C)) ? C : 0;
+  DPPO_FULL_SHAPES(DPPO_FULL_TRY)
+#undef DPPO_FULL_TRY
   return 0;
 }
 
+int fullvocab_resident_per_cu(int chunks) { return two_per_cu(chunks) ? 2 : 1; }
+
 hipError_t launch_fullvocab_resident(const KParams& p, bool tv, bool grad, int chunks, int grid, hipStream_t s) {
-  if (chunks == 32) return launch_chunks<32>(p, tv, grad, grid, s);
-  if (chunks == 38) return launch_chunks<38>(p, tv, grad, grid, s);
+#define DPPO_FULL_LAUNCH(C) if (chunks == C) return launch_chunks<C>(p, tv, grad, grid, s);
+  DPPO_FULL_SHAPES(DPPO_FULL_LAUNCH)
+#undef DPPO_FULL_LAUNCH
   return hipErrorInvalidValue;
 }
 

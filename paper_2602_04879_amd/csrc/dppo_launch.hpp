@@ -49,8 +49,10 @@ hipError_t launch_fullvocab(const KParams& p, bool tv, bool grad, int threads, i
 // Register-resident form of the same variants (backward, and the forward-only TV form): the
 // trainer's row in the registers of one workgroup of 512 threads per compute unit, the rollout row
 // streamed past it.  fullvocab_resident_chunks() says whether a call qualifies (0: no) and with
-// how many 16-byte chunks per thread.
-int fullvocab_resident_chunks(const KParams& p, bool tv, bool grad);
+// how many 16-byte chunks per thread; fullvocab_resident_per_cu() how many workgroups a compute unit
+// takes (with two, rows are fixed by the workgroup index: p.row_counters must be null).
+int fullvocab_resident_chunks(const KParams& p, bool tv, bool grad, int cus);
+int fullvocab_resident_per_cu(int chunks);
 hipError_t launch_fullvocab_resident(const KParams& p, bool tv, bool grad, int chunks, int grid, hipStream_t s);
 
 // bf16 matrix products on the matrix cores (fp32 accumulation).  A, B 16-byte aligned with lda, ldb

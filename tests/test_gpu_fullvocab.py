@@ -315,3 +315,47 @@ def test_mask_anchored_to_a_recomputed_policy(variant, delta, V):
     torch.cuda.synchronize()
     assert (res0["mask"] != res["mask"]).any()
     _say(f"       {st}")
+
+
+@pytest.mark.parametrize("variant,delta", FULL)
+@pytest.mark.parametrize("V,ld", [(8200, 8200), (12296, 12352), (16384, 16384), (20488, 20488), (32000, 32000), (36872, 36872), (49152, 49152),
+                                  (49160, 49160), (65536, 65536), (73736, 73736), (98304, 98304)])
+def test_resident_form_on_shorter_rows(variant, delta, V, ld):
+    """Every shape of the register-resident form below 98312 entries, at its shortest or longest row:
+    several rows per workgroup, ignored, masked and zero-advantage rows, identical policies, sampled tokens at both ends,
+    a poisoned pitch that stays untouched; a sample against the oracle, all rows against the general kernel, in
+    place, and run after run the same bits."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    T = 4 * cus + 37
+    w = W.Workload("fv_mid", 1, T, V, variant, delta, mu_full=True, logit_std=3.0, noise_std=0.7, zipf_s=1.1, adv="normal", seed=137)
+    b = W.make_batch(w, DEV, shift_sampled=1.0, ld=ld, rows_per_step=512)
+    b["advantages"] = torch.randn(T, device=DEV)
+    b["mu_logits"][:3, :V] = b["logits"][:3, :V]
+    b["sampled_ids"][7::17] = -1
+    b["sampled_ids"][8], b["sampled_ids"][9], b["sampled_ids"][T - 1] = V - 1, 0, V - 8
+    b["advantages"][5::19] = 0.0
+    b["logits"][10, 100:4000] = float("-inf"); b["mu_logits"][10, 100:4000] = float("-inf")
+    b["sampled_ids"][10] = 5
+    _say(f"[case] resident full-vocabulary form, shorter rows V={V} ld={ld} variant={variant}")
+    res = B.run_batch(b, diagnostics=True, grad=torch.full_like(b["logits"], 77.0))
+    torch.cuda.synchronize()
+    taken = variant == W.FULL_TV or V != 8200       # the KL form on a shape less than three quarters full
+    assert B.last_path() == ("fullvocab_resident" if taken else "fullvocab")
+    assert (res["grad_logits"][:, V:] == 77.0).all()
+    rows = np.array(sorted(set(list(range(12)) + [T - 1, T - 2, 2 * cus, 2 * cus + 1] + np.random.default_rng(3).integers(0, T, 8).tolist())))
+    st = P.compare_rows(b, res, rows)
+    P.check_loss_scalar(b, res)
+    gen = B.run_batch(b, diagnostics=True, flags=B.FLAG_FORCE_STREAMING)
+    again = B.run_batch(b, diagnostics=True)
+    torch.cuda.synchronize()
+    assert torch.equal(gen["mask"], res["mask"])
+    assert (gen["divergence"] - res["divergence"]).abs().max().item() <= 2e-6
+    for k in ("loss", "loss_tok", "divergence", "mask", "diagnostics"):
+        assert torch.equal(again[k], res[k]), k
+    assert torch.equal(again["grad_logits"][:, :V], res["grad_logits"][:, :V])
+    keep = res["grad_logits"][:, :V].clone()
+    plain = B.run_batch(b, in_place=True)
+    torch.cuda.synchronize()
+    assert torch.equal(plain["grad_logits"][:, :V], keep) and torch.equal(plain["divergence"], res["divergence"])
+    assert 0 < (res["mask"] == 0).sum().item() < T
+    _say(f"       {st}")
