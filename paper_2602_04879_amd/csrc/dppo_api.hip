@@ -503,6 +503,7 @@ dppo_status_t run_lmhead(const dppo_lmhead_args_t* a, void* stream, bool grad) {
       gs.tk_ids = p.tk_ids;
       gs.Ktop = p.K;
       gs.tiles_n = tiles_n;
+      gs.want_t = p.diag != nullptr;
       p.gath = gs.gath;
       const uint16_t* h = static_cast<const uint16_t*>(a->hidden) + r0 * a->ld_hidden;
       if (dppo::launch_gemm_stats(h, a->ld_hidden, static_cast<const uint16_t*>(a->weight), a->ld_weight, static_cast<int>(rows),

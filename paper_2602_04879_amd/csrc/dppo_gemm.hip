@@ -267,7 +267,6 @@ __device__ __forceinline__ void gemm_tile(unsigned char* lds0, unsigned char* ld
       const int row = m0 + wm * 128 + rl;
       const int a_loc = (row < M && samp[i] >= 0) ? samp[i] - col0 : -1;
       float z[8][4];
-      float mx = -INFINITY;
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
         const uint32_t lo = pack_bf16x2(acc[i][j][0], acc[i][j][1]), hi = pack_bf16x2(acc[i][j][2], acc[i][j][3]);
@@ -275,27 +274,41 @@ __device__ __forceinline__ void gemm_tile(unsigned char* lds0, unsigned char* ld
         *reinterpret_cast<u32x2*>(half + rl * 512 + (((wn * 8 + j) ^ frow) << 5) + fk * 8) = u32x2{lo, hi};
         z[j][0] = __uint_as_float(lo << 16); z[j][1] = __uint_as_float(lo & 0xffff0000u);
         z[j][2] = __uint_as_float(hi << 16); z[j][3] = __uint_as_float(hi & 0xffff0000u);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int cl = j * 16 + fk * 4 + e;
-          if ((!FULL && col0 + cl >= N) || cl == a_loc) z[j][e] = -INFINITY;
-          mx = fmaxf(mx, z[j][e]);
-        }
       }
+      // columns that do not exist, and (rarely: one tile in V / 256 holds a row's) the sampled token's
+      if (!FULL || __any(a_loc >= 0 && a_loc < 128)) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const int cl = j * 16 + fk * 4 + e;
+            if ((!FULL && col0 + cl >= N) || cl == a_loc) z[j][e] = -INFINITY;
+          }
+      }
+      float mx = -INFINITY;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) mx = fmaxf(fmaxf(fmaxf(mx, z[j][0]), z[j][1]), fmaxf(z[j][2], z[j][3]));
       mx = fmaxf(mx, __shfl_xor(mx, 16));
       mx = fmaxf(mx, __shfl_xor(mx, 32));
       const float b = -ceilf(fmaxf(mx, kNegBig) * kLog2e);
       float s = 0.f, t = 0.f;
+      if (gs.want_t) {
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        float e4[4];
+        for (int j = 0; j < 8; ++j) {
+          float e4[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float x = fmaf(z[j][e], kLog2e, b);
-          e4[e] = fast_exp2(x);
-          t = fma_ex(e4[e], x, t);
+          for (int e = 0; e < 4; ++e) {
+            const float x = fmaf(z[j][e], kLog2e, b);
+            e4[e] = fast_exp2(x);
+            t = fma_ex(e4[e], x, t);
+          }
+          s += (e4[0] + e4[1]) + (e4[2] + e4[3]);
         }
-        s += (e4[0] + e4[1]) + (e4[2] + e4[3]);
+      } else {
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+          s += (fast_exp2(fmaf(z[j][0], kLog2e, b)) + fast_exp2(fmaf(z[j][1], kLog2e, b))) +
+               (fast_exp2(fmaf(z[j][2], kLog2e, b)) + fast_exp2(fmaf(z[j][3], kLog2e, b)));
       }
       s += __shfl_xor(s, 16); s += __shfl_xor(s, 32);
       t += __shfl_xor(t, 16); t += __shfl_xor(t, 32);

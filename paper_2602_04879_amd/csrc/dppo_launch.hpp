@@ -90,6 +90,7 @@ struct GemmStats {
   const int32_t* sampled = nullptr;  // [M]
   const int32_t* tk_ids = nullptr;   // [M][Ktop] (unused if Ktop = 0)
   int32_t Ktop = 0, tiles_n = 0;
+  bool want_t = false;               // t is wanted (diagnostics); else it is left 0
 };
 constexpr int kGemmTileN = 256;
 hipError_t launch_gemm_stats(const uint16_t* A, int64_t lda, const uint16_t* B, int64_t ldb, int M, int N, int K,
