@@ -230,11 +230,12 @@ __device__ __forceinline__ void gemm_tile(unsigned char* lds0, unsigned char* ld
   // (the products are assembly statements, so the compiler does not keep that distance by itself).
   // The accumulators pass through the wait, so that nothing the compiler makes of them, a spill
   // included, reads one in front of it.
+#define DPPO_THROUGH(CODE, I) asm volatile(CODE : "+a"(acc[I][0]), "+a"(acc[I][1]), "+a"(acc[I][2]), "+a"(acc[I][3]), \
+                                               "+a"(acc[I][4]), "+a"(acc[I][5]), "+a"(acc[I][6]), "+a"(acc[I][7]) :: "memory")
+  DPPO_THROUGH("s_nop 15\n\ts_nop 15", 0);
 #pragma unroll
-  for (int i = 0; i < 8; ++i)
-    asm volatile("s_nop 15\n\ts_nop 15"
-                 : "+a"(acc[i][0]), "+a"(acc[i][1]), "+a"(acc[i][2]), "+a"(acc[i][3]), "+a"(acc[i][4]), "+a"(acc[i][5]), "+a"(acc[i][6]), "+a"(acc[i][7])
-                 :: "memory");
+  for (int i = 1; i < 8; ++i) DPPO_THROUGH("", i);
+#undef DPPO_THROUGH
   DPPO_PIN;
 
   // The products were formed with the operands swapped (B fragment first), so a lane's four
@@ -383,12 +384,22 @@ __device__ __forceinline__ void gemm_tile(unsigned char* lds0, unsigned char* ld
       for (int j = 0; j < 8; j += 2) {
         const uint32_t lo0 = pack_bf16x2(acc[i][j][0], acc[i][j][1]), hi0 = pack_bf16x2(acc[i][j][2], acc[i][j][3]);
         const uint32_t lo1 = pack_bf16x2(acc[i][j + 1][0], acc[i][j + 1][1]), hi1 = pack_bf16x2(acc[i][j + 1][2], acc[i][j + 1][3]);
-        if (FULL && quad_aligned) {
+        if (quad_aligned) {
           const auto l = __builtin_amdgcn_permlane16_swap(lo0, lo1, false, false);
           const auto h = __builtin_amdgcn_permlane16_swap(hi0, hi1, false, false);
           const u32x4 v = {l[0], h[0], l[1], h[1]};
           const int col = n0 + wn * 128 + (j + (fk & 1)) * 16 + (fk >> 1) * 8;
-          *reinterpret_cast<u32x4*>(static_cast<uint16_t*>(Cv) + static_cast<int64_t>(row) * ldc + col) = v;
+          uint16_t* dst = static_cast<uint16_t*>(Cv) + static_cast<int64_t>(row) * ldc + col;
+          // (a tile with rows or columns past the matrix: the same 16-byte stores, but for a vector across the
+          // matrix's edge.  Two bytes at a time for the whole tile, one of four: 1000 x 151936 x 2048 0.75 ms, now 0.53.)
+          if (FULL || (row < M && col + 8 <= N)) {
+            *reinterpret_cast<u32x4*>(dst) = v;
+          } else if (row < M) {
+            const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+              if (col + e < N) dst[e] = static_cast<uint16_t>((e & 1) ? (w[e >> 1] >> 16) : (w[e >> 1] & 0xffffu));
+          }
         } else if (row < M) {
 #pragma unroll
           for (int h = 0; h < 2; ++h) {
