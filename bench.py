@@ -403,7 +403,8 @@ def main() -> int:
                    "kernel_path": path, "buffer_sets": nrot, "rows": "fixed by workgroup index" if args.static_rows else "library default", "mask_rule": args.mask_rule, "mask_anchor": "recomputed policy (synthetic)" if args.anchor else "rollout policy", "ratio_cap": args.ratio_cap, "diagnostics": args.diagnostics, "grad": "none (forward only)" if args.forward_only else "in place over the logits" if in_place else "separate buffer"},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": None if (args.forward_only or in_place or args.diagnostics or args.anchor) else stored_traffic(args.workload, path),
-                     "kernel": DOMINANT_KERNEL.get(path, path), "algorithmic_bytes_per_launch": alg_bytes_launch,
+                     "kernel": "dppo_forward_kernel" if args.forward_only and path in ("resident", "streaming") and V > 49152 else DOMINANT_KERNEL.get(path, path),
+                     "algorithmic_bytes_per_launch": alg_bytes_launch,
                      "step_ms_per_launch": step_ms_per_launch, "device_ceilings": ceilings,
                      "frac_of_copy_ceiling": (achieved / ceilings["copy_GBs"]) if ceilings else None,
                      "frac_of_resident_copy": (achieved / ceilings["copy_resident_GBs"]) if ceilings.get("copy_resident_GBs") else None},

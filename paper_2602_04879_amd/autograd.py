@@ -21,9 +21,20 @@ import torch
 from . import binding as B
 
 
+# Gradients of this many entries and more are scaled by a kernel that reads the incoming gradient of the
+# loss on the device; smaller ones look at it on the host.  Looking is a synchronisation, behind which the
+# device idles while the host prepares the next call (4096 x 256000: 886 us a step, 819 without); but the
+# library call from autograd's own thread costs the host 25 us more than the look (256 x 4096, plain
+# backward: 130 us against 106), which is what counts as long as the device has less than about 50 us of
+# work per step (2^26 entries: a read and a write of 128 MiB).
+SCALE_ON_DEVICE_FROM = 1 << 26
+
+
 def _grad_like(logits: torch.Tensor) -> torch.Tensor:
     """An empty gradient for rows of `logits`, with the same row pitch: the boundary has one pitch for
     both.  (torch.empty_like drops the pitch of a slice logits[:, :V] and returns packed rows.)"""
+    if logits.is_contiguous():
+        return torch.empty_like(logits)
     T, V = logits.shape
     ld = logits.stride(0) if T > 1 else V
     return logits.new_empty((T, max(ld, V)))[:, :V]
@@ -61,9 +72,9 @@ class _DppoLoss(torch.autograd.Function):
         if g is None:
             return (None,) * 8
         # d(out)/d(logits) = grad_loss * d(loss)/d(logits); the scale is applied in fp32 and rounded once
-        if ctx.own_buffer and not torch.is_grad_enabled():
+        if ctx.own_buffer and g.numel() >= SCALE_ON_DEVICE_FROM and not torch.is_grad_enabled():
             return (B.scale_rows_(g, grad_loss), None, None, None, None, None, None, None)
-        # a graph through grad_loss (create_graph), or a gradient in the logits' own storage, which stays as it is
+        # (also: a graph through grad_loss (create_graph), or a gradient in the logits' own storage, which stays as it is)
         g = (g.float() * grad_loss.float()).to(torch.bfloat16) if not _is_one(grad_loss) else g
         return (g, None, None, None, None, None, None, None)
 
@@ -115,13 +126,14 @@ class _DppoLmheadLoss(torch.autograd.Function):
     def backward(ctx, grad_loss, *unused):
         gh, gw = ctx.grads
         ctx.grads = None
-        if not torch.is_grad_enabled():
+        big = max(t.numel() if t is not None else 0 for t in (gh, gw)) >= SCALE_ON_DEVICE_FROM
+        if big and not torch.is_grad_enabled():
             if gh is not None:
                 gh = B.scale_rows_(gh, grad_loss)
             if gw is not None:      # accumulated in fp32; autograd wants the weight's own type
                 gw = B.scale_to_bf16(gw, grad_loss)
             return (gh, gw, None, None, None, None, None, None)
-        one = _is_one(grad_loss)                      # a graph through grad_loss (create_graph)
+        one = _is_one(grad_loss)
         if gh is not None and not one:
             gh = (gh.float() * grad_loss.float()).to(torch.bfloat16)
         if gw is not None:

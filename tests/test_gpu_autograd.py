@@ -154,3 +154,25 @@ def test_gradient_with_a_graph_through_the_incoming_gradient():
     torch.cuda.synchronize()
     want = plain.grad.double().square().sum().item()          # d/du sum (u g)^2 = 2 u sum g^2, u = 1/2: exact in bf16
     assert abs(du.item() - want) <= 1e-2 * want
+
+
+@pytest.mark.parametrize("factor", [1.0, 0.3])
+def test_scaling_on_the_device_and_on_the_host_give_the_same_gradients(monkeypatch, factor):
+    """Large gradients are scaled by a kernel that reads the factor, small ones by tensor operations
+    behind a look at it: the same bits (here on one small call each way)."""
+    w = W.Workload("autograd_scale", 2, 40, 8192, W.BINARY_TV, 0.2, logit_std=3.0, noise_std=1.0, adv="normal", seed=103)
+    b = W.make_batch(w, DEV, shift_sampled=2.0)
+    lb = W.make_lmhead_batch(W.Workload("autograd_scale_lm", 2, 40, 4160, W.BINARY_TV, 0.2, logit_std=3.0, noise_std=1.0, adv="normal", seed=105), 64, DEV)
+    got = []
+    for entries in (0, 1 << 40):
+        monkeypatch.setattr(A, "SCALE_ON_DEVICE_FROM", entries)
+        logits = b["logits"].clone().requires_grad_(True)
+        loss, _ = _call(b, logits)
+        h, wt = lb["hidden"].clone().requires_grad_(True), lb["weight"].clone().requires_grad_(True)
+        lloss, _ = A.dppo_lmhead_loss(h, wt, lb["sampled_ids"], lb["mu_logp"], lb["advantages"], delta=lb["delta"], variant=lb["variant"],
+                                      loss_scale=lb["loss_scale"])
+        (factor * loss + factor * lloss).backward()
+        torch.cuda.synchronize()
+        got.append((logits.grad, h.grad, wt.grad))
+    for x, y in zip(*got):
+        assert torch.equal(x, y)
