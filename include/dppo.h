@@ -280,7 +280,9 @@ typedef struct {
   int32_t        grad_weight_accumulate; /* 0: overwrite grad_weight; 1: add to what it holds (a   */
                                 /* trainer accumulating micro-batches into an fp32 main gradient) */
   void*          workspace;     /* >= dppo_lmhead_workspace_bytes(...) bytes, 256-byte aligned:    */
-                                /* loss partial sums and the chunk of logits                       */
+                                /* loss partial sums, and from DPPO_WORKSPACE_BYTES on the chunk of */
+                                /* logits; after dppo_lmhead_loss_fwd_bwd the last chunk's gradient */
+                                /* with respect to its logits stands there, bf16 [rows, V] packed   */
   size_t         workspace_bytes;
 } dppo_lmhead_args_t;
 
@@ -358,6 +360,13 @@ dppo_status_t dppo_gemm_nn(const void* A, int64_t lda, const void* B, int64_t ld
  * and does nothing.  DPPO_ERR_SHAPE / _NULL / _ALIGN / _LAUNCH as for dppo_gemm_nt. */
 dppo_status_t dppo_gemm_tn_f32(const void* A, int64_t lda, const void* B, int64_t ldb, float* C, int64_t ldc,
                                int64_t M, int64_t N, int64_t K, int accumulate, void* stream);
+
+/* C[M, N] = *factor * A[K, M]^T * B[K, N]: the same product in bf16, scaled and rounded once from its fp32
+ * sums, factor one float in DEVICE memory.  (The weight gradient of one chunk in the weight's own type: A is
+ * the chunk's logit gradients, which dppo_lmhead_loss_fwd_bwd leaves in its workspace.)  C 2-byte
+ * aligned, ldc >= N; otherwise as above. */
+dppo_status_t dppo_gemm_tn_bf16(const void* A, int64_t lda, const void* B, int64_t ldb, void* C, int64_t ldc,
+                                int64_t M, int64_t N, int64_t K, const float* factor, void* stream);
 
 #ifdef __cplusplus
 }

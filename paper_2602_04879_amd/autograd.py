@@ -133,10 +133,18 @@ class _DppoLmheadLoss(torch.autograd.Function):
         batch = {"hidden": hidden.detach(), "weight": weight.detach(), "d": d, "V": V, "sampled_ids": sampled_ids, "mu_logp": mu_logp,
                  "advantages": advantages, "delta": opts["delta"], "variant": opts["variant"], "loss_scale": opts["loss_scale"],
                  "mu_topk_ids": mu_topk_ids, "mu_topk_logp": mu_topk_logp, "anchor_logp": opts.get("anchor_logp")}
-        gw = torch.empty((V, d), dtype=torch.float32, device=hidden.device) if need_w else None
+        chunk = opts.get("chunk_rows", 0)
+        # One chunk: the logits' gradient stays as it is in the workspace, and the weight's gradient is formed from it in
+        # backward, where its factor is known, straight in the weight's type (V = 151936, d = 2048, 1000 tokens: 2158 us a step,
+        # 1775 now; 64 tokens x 768: 416 / 283).  Several chunks are summed in fp32; so is one of more rows than a chunk has
+        # unasked, which would be long to keep.  (Kept until backward: 2 T V bytes in place of 4 V d.)
+        later = need_w and 0 < T <= min(chunk if chunk > 0 else T, B.LMHEAD_CHUNK_ROWS)
+        gw = torch.empty((V, d), dtype=torch.float32, device=hidden.device) if need_w and not later else None
         rule = {k: opts[k] for k in ("mask_rule", "eps_low", "eps_high", "ratio_cap", "relax_alpha", "relax_sides") if k in opts}
-        res = B.run_lmhead(batch, backward=backward, chunk_rows=opts.get("chunk_rows", 0), diagnostics=opts.get("diagnostics", False),
+        res = B.run_lmhead(batch, backward=backward, chunk_rows=chunk, diagnostics=opts.get("diagnostics", False),
                            grad_weight=gw, flags=opts.get("flags", 0), **rule)
+        # (a copy of the hidden states, a few megabytes: the caller may write to its own before backward)
+        ctx.factors = (B.lmhead_logit_gradients(res["workspace_buf"], T, V), hidden.detach().clone(memory_format=torch.contiguous_format)) if later else None
         ctx.grads = (res["grad_hidden"] if need_h else None, gw)
         side = [res[k] for k in ("divergence", "mask", "loss_tok")] + ([res["diagnostics"]] if res["diagnostics"] is not None else [])
         ctx.mark_non_differentiable(*side)
@@ -145,7 +153,17 @@ class _DppoLmheadLoss(torch.autograd.Function):
     @staticmethod
     def backward(ctx, grad_loss, *unused):
         gh, gw = ctx.grads
-        ctx.grads = None
+        factors = ctx.factors
+        ctx.grads = ctx.factors = None
+        if factors is not None:
+            if _value_only(grad_loss):
+                grad_loss = _in_memory(grad_loss)
+                gw = B.gemm_tn_bf16(*factors, grad_loss)
+                if gh is not None:
+                    gh = B.scale_rows_(gh, grad_loss)
+                return (gh, gw, None, None, None, None, None, None)
+            g, h = factors
+            gw = B.gemm_tn_f32(g, h, torch.empty((g.shape[1], h.shape[1]), dtype=torch.float32, device=g.device))
         big = max(t.numel() if t is not None else 0 for t in (gh, gw)) >= SCALE_ON_DEVICE_FROM
         if big and _value_only(grad_loss):
             grad_loss = _in_memory(grad_loss)

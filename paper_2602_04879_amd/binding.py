@@ -21,6 +21,8 @@ FLAG_STATIC_ROWS = 2
 RELAX_HIGH, RELAX_LOW = 1, 2
 WORKSPACE_BYTES = 65536       # the smallest workspace any call accepts; workspace_bytes(T, V, K) is what a call wants
 
+LMHEAD_CHUNK_ROWS = 8192       # tokens per chunk of the hidden-state path where the caller names none
+
 # DPPO_LIB overrides the library path (e.g. a build with other compile-time settings).
 _LIB_PATH = os.environ.get("DPPO_LIB") or os.path.join(os.path.dirname(os.path.abspath(__file__)), "libdppo.so")
 _lib = None
@@ -109,6 +111,9 @@ def lib() -> C.CDLL:
             f.restype = C.c_int
             f.argtypes = [C.c_void_p, C.c_int64, C.c_void_p, C.c_int64, C.c_void_p, C.c_int64,
                           C.c_int64, C.c_int64, C.c_int64, C.c_int, C.c_void_p]
+        l.dppo_gemm_tn_bf16.restype = C.c_int
+        l.dppo_gemm_tn_bf16.argtypes = [C.c_void_p, C.c_int64, C.c_void_p, C.c_int64, C.c_void_p, C.c_int64,
+                                        C.c_int64, C.c_int64, C.c_int64, C.c_void_p, C.c_void_p]
         for f in (l.dppo_lmhead_loss_fwd, l.dppo_lmhead_loss_fwd_bwd):
             f.restype = C.c_int
             f.argtypes = [C.POINTER(DppoLmheadArgs), C.c_void_p]
@@ -313,6 +318,22 @@ def _check_factor(factor, x):
         raise ValueError("factor: one fp32 value in memory on the device of the tensor that it scales")
 
 
+def gemm_tn_bf16(a, b, factor, c=None, stream=None):
+    """dppo_gemm_tn_bf16: c[M, N] = factor * a[K, M]^T @ b[K, N] for bf16 tensors with unit inner stride, factor one
+    fp32 value on the device."""
+    K, M = a.shape
+    N = b.shape[1]
+    assert b.shape[0] == K and a.stride(1) == 1 and b.stride(1) == 1
+    _check_factor(factor, a)
+    if c is None:
+        c = torch.empty((M, N), dtype=torch.bfloat16, device=a.device)
+    st = lib().dppo_gemm_tn_bf16(a.data_ptr(), a.stride(0), b.data_ptr(), b.stride(0), c.data_ptr(), c.stride(0),
+                                 M, N, K, factor.data_ptr(), C.c_void_p(_stream_handle(stream)))
+    if st != 0:
+        raise DppoError(st)
+    return c
+
+
 def scale_rows_(x, factor, stream=None):
     """dppo_scale_rows_bf16: x *= factor in place, x a bf16 matrix with unit inner stride, factor one fp32
     value on the device."""
@@ -373,6 +394,11 @@ def run_batch(batch: dict, backward: bool = True, in_place: bool = False, flags:
     res["grad_logits"] = grad if backward else None
     res["args"] = args
     return res
+
+
+def lmhead_logit_gradients(workspace, T: int, V: int):
+    """The logits' gradient that dppo_lmhead_loss_fwd_bwd left in its workspace, [T, V] bf16 (T: rows of the last chunk)."""
+    return workspace[WORKSPACE_BYTES:WORKSPACE_BYTES + 2 * T * V].view(torch.bfloat16).view(T, V)
 
 
 def lmhead_workspace_bytes(T: int, V: int, chunk_rows: int = 0) -> int:

@@ -737,4 +737,18 @@ dppo_status_t dppo_gemm_tn_f32(const void* A, int64_t lda, const void* B, int64_
   return e == hipSuccess ? DPPO_OK : DPPO_ERR_LAUNCH;
 }
 
+dppo_status_t dppo_gemm_tn_bf16(const void* A, int64_t lda, const void* B, int64_t ldb, void* C, int64_t ldc,
+                                int64_t M, int64_t N, int64_t K, const float* factor, void* stream) {
+  if (M < 0 || N < 0 || K < 1 || M >= (int64_t(1) << 31) || N >= (int64_t(1) << 31) || K >= (int64_t(1) << 31)) return DPPO_ERR_SHAPE;
+  if (lda < M || ldb < N || ldc < N || lda % 8 != 0 || ldb % 8 != 0 || lda >= (int64_t(1) << 22) || ldb >= (int64_t(1) << 22)) return DPPO_ERR_SHAPE;
+  if (M == 0 || N == 0) return DPPO_OK;
+  if (!A || !B || !C || !factor) return DPPO_ERR_NULL;
+  if ((reinterpret_cast<uintptr_t>(A) | reinterpret_cast<uintptr_t>(B)) & 15u) return DPPO_ERR_ALIGN;
+  if ((reinterpret_cast<uintptr_t>(C) & 1u) || (reinterpret_cast<uintptr_t>(factor) & 3u)) return DPPO_ERR_ALIGN;
+  const hipError_t e = dppo::launch_gemm_tn_bf16(static_cast<const uint16_t*>(A), lda, static_cast<const uint16_t*>(B), ldb, C, ldc,
+                                                 static_cast<int>(M), static_cast<int>(N), static_cast<int>(K), factor,
+                                                 static_cast<hipStream_t>(stream));
+  return e == hipSuccess ? DPPO_OK : DPPO_ERR_LAUNCH;
+}
+
 }  // extern "C"

@@ -73,6 +73,9 @@ int gemm_nn_splits(int64_t M, int64_t N, int64_t K, int cus, size_t scratch_byte
 // C[M, N] fp32 (out 1: written, 2: added to) = A^T B, A [K, M], B [K, N]; any K >= 1
 hipError_t launch_gemm_tn(const uint16_t* A, int64_t lda, const uint16_t* B, int64_t ldb, void* C, int64_t ldc,
                           int M, int N, int K, int out, hipStream_t s);
+// C[M, N] bf16 = *factor A^T B (factor: one float on the device), A [K, M], B [K, N]; any K >= 1; C 2-byte aligned
+hipError_t launch_gemm_tn_bf16(const uint16_t* A, int64_t lda, const uint16_t* B, int64_t ldb, void* C, int64_t ldc,
+                               int M, int N, int K, const float* factor, hipStream_t s);
 
 // x[r, 0..cols) *= *factor (bf16, in place, any pitch and 2-byte alignment; nothing for a factor of one), and
 // dst[i] = bf16(src[i] * *factor) (dst, src 16-byte aligned).  factor: one float on the device.
@@ -94,6 +97,7 @@ struct GemmStats {
   const int32_t* tk_ids = nullptr;   // [M][Ktop] (unused if Ktop = 0)
   int32_t Ktop = 0, tiles_n = 0;
   bool want_t = false;               // t is wanted (diagnostics); else it is left 0
+  const float* factor = nullptr;     // A^T B in bf16 only: what its entries are multiplied by
 };
 constexpr int kGemmTileN = 256;
 hipError_t launch_gemm_stats(const uint16_t* A, int64_t lda, const uint16_t* B, int64_t ldb, int M, int N, int K,

@@ -140,6 +140,24 @@ def test_scaled_gradient_rows(rows, cols, ld, off):
     assert torch.equal(got, (src * f).to(torch.bfloat16))
 
 
+@pytest.mark.parametrize("chunk_rows,factor", [(0, 1.0), (0, -0.3), (80, -0.3), (79, -0.3)])
+def test_weight_gradient_formed_in_backward_is_that_of_the_direct_call(chunk_rows, factor):
+    """One chunk: the weight's gradient is formed in backward, from what forward saw (the hidden states are
+    overwritten in between); its bits are those of the fp32 gradient scaled and rounded once."""
+    b = W.make_lmhead_batch(W.Workload("autograd_later", 2, 40, 4160, W.BINARY_TV, 0.2, logit_std=3.0, noise_std=1.0, adv="normal", seed=113), 192, DEV)
+    f = torch.tensor(factor, device=DEV)
+    gw = torch.empty((b["V"], b["d"]), dtype=torch.float32, device=DEV)
+    ref = B.run_lmhead(b, grad_weight=gw, chunk_rows=chunk_rows)
+    h, wt = b["hidden"].clone().requires_grad_(True), b["weight"].clone().requires_grad_(True)
+    loss, _ = A.dppo_lmhead_loss(h, wt, b["sampled_ids"], b["mu_logp"], b["advantages"], delta=b["delta"], variant=b["variant"],
+                                 loss_scale=b["loss_scale"], chunk_rows=chunk_rows)
+    with torch.no_grad():
+        h.fill_(7.0)
+    gh, g = torch.autograd.grad(loss, (h, wt), f)
+    torch.cuda.synchronize()
+    assert torch.equal(g, (gw * f).to(torch.bfloat16)) and torch.equal(gh, (ref["grad_hidden"].float() * f).to(torch.bfloat16))
+
+
 def test_gradient_with_a_graph_through_the_incoming_gradient():
     """create_graph keeps the path from the gradient to the weight of the loss."""
     w = W.Workload("autograd_graph", 2, 16, 4096, W.BINARY_TV, 0.5, logit_std=3.0, noise_std=0.3, adv="normal", seed=99)

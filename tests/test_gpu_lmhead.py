@@ -172,6 +172,29 @@ def test_gemm_tn_exact_inputs_bitwise_and_accumulation(M, N, K, lda, ldb, ldc):
     assert (c[:, N:] == 3.0).all()
 
 
+@pytest.mark.parametrize("M,N,K,lda,ldb,ldc,off", [
+    (256, 256, 64, 256, 256, 256, 0), (8, 8, 1, 8, 8, 8, 0), (300, 520, 100, 304, 520, 520, 0), (1000, 776, 193, 1008, 784, 783, 1),
+    (4160, 128, 321, 4160, 128, 128, 0), (777, 261, 129, 784, 264, 264, 0), (151936, 64, 66, 151936, 64, 64, 0), (512, 512, 1000, 512, 512, 520, 3)])
+def test_gemm_tn_in_bf16_is_the_fp32_product_scaled_and_rounded_once(M, N, K, lda, ldb, ldc, off):
+    """C = bf16(factor * A^T B): bit for bit what scaling and rounding the fp32 product gives, with ragged
+    sizes, pitches and a C on any 2-byte address; nothing around C is written."""
+    _say(f"[case] gemm tn bf16 M={M} N={N} K={K}")
+    g = torch.Generator(device=DEV); g.manual_seed(M + 5 * N + K)
+    a, b = (torch.randn((K, ld), generator=g, device=DEV).bfloat16() for ld in (lda, ldb))
+    f = torch.tensor(-0.3, device=DEV)
+    c32 = torch.empty((M, (N + 3) // 4 * 4), dtype=torch.float32, device=DEV)[:, :N]
+    B.gemm_tn_f32(a[:, :M], b[:, :N], c32)
+    buf = torch.full((off + M * ldc + 8,), 3.0, dtype=torch.bfloat16, device=DEV)
+    want = buf.clone()
+    view = lambda t: t[off:off + M * ldc].view(M, ldc)[:, :N]
+    view(want).copy_((c32 * f).bfloat16())
+    B.gemm_tn_bf16(a[:, :M], b[:, :N], f, view(buf))
+    torch.cuda.synchronize()
+    assert torch.equal(buf, want)
+    with pytest.raises(B.DppoError):
+        B.gemm_tn_bf16(a[:0, :M], b[:0, :N], f, view(buf))                # K = 0
+
+
 @pytest.mark.parametrize("form,M,N,K", [
     ("tn", 115 * 256 - 5, 16 * 256 - 96, 130), ("tn", 594 * 256 - 128, 7 * 256 - 40, 320),     # tall, few steps: whole blocks
     ("tn", 154 * 256, 16 * 256, 1600), ("tn", 143 * 256, 7 * 256 - 8, 1088),                   # tall: whole for equal rounds; cut
