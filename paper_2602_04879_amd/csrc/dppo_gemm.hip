@@ -49,6 +49,47 @@ __device__ __forceinline__ uint32_t lds_off(int row, int kvec) {
   return static_cast<uint32_t>(row) * kRowBytes + static_cast<uint32_t>((kvec ^ ((row >> 1) & 7)) << 4);
 }
 
+// 16 rows x 128 columns of a tile (eight accumulators of four columns each) leave as bf16: row `row` of this lane, from column col0
+// on.  Two neighbouring blocks exchange halves between lane rows (one v_permlane16_swap per register pair), after
+// which a lane owns 8 consecutive columns: one 16-byte store, 64 contiguous bytes per row and instruction.
+template <bool FULL>
+__device__ __forceinline__ void store_row_block_bf16(uint16_t* __restrict__ C, int64_t ldc, int M, int N, int row, int col0, int fk, const f32x4 (&acc)[8]) {
+  const bool quad_aligned = ((reinterpret_cast<uintptr_t>(C) & 15u) == 0) && (ldc % 8 == 0);
+#pragma unroll
+  for (int j = 0; j < 8; j += 2) {
+    const uint32_t lo0 = pack_bf16x2(acc[j][0], acc[j][1]), hi0 = pack_bf16x2(acc[j][2], acc[j][3]);
+    const uint32_t lo1 = pack_bf16x2(acc[j + 1][0], acc[j + 1][1]), hi1 = pack_bf16x2(acc[j + 1][2], acc[j + 1][3]);
+    if (quad_aligned) {
+      const auto l = __builtin_amdgcn_permlane16_swap(lo0, lo1, false, false);
+      const auto h = __builtin_amdgcn_permlane16_swap(hi0, hi1, false, false);
+      const u32x4 v = {l[0], h[0], l[1], h[1]};
+      const int col = col0 + (j + (fk & 1)) * 16 + (fk >> 1) * 8;
+      uint16_t* dst = C + static_cast<int64_t>(row) * ldc + col;
+      // (a tile with rows or columns past the matrix: the same 16-byte stores, but for a vector across the
+      // matrix's edge.  Two bytes at a time for the whole tile, one of four: 1000 x 151936 x 2048 0.75 ms, now 0.53.)
+      if (FULL || (row < M && col + 8 <= N)) {
+        *reinterpret_cast<u32x4*>(dst) = v;
+      } else if (row < M) {
+        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          if (col + e < N) dst[e] = static_cast<uint16_t>((e & 1) ? (w[e >> 1] >> 16) : (w[e >> 1] & 0xffffu));
+      }
+    } else if (row < M) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int col = col0 + (j + h) * 16 + fk * 4;
+        const uint32_t lo = h ? lo1 : lo0, hi = h ? hi1 : hi0;
+        uint16_t* dst = C + static_cast<int64_t>(row) * ldc + col;
+        if (col < N) dst[0] = static_cast<uint16_t>(lo & 0xffffu);
+        if (col + 1 < N) dst[1] = static_cast<uint16_t>(lo >> 16);
+        if (col + 2 < N) dst[2] = static_cast<uint16_t>(hi & 0xffffu);
+        if (col + 3 < N) dst[3] = static_cast<uint16_t>(hi >> 16);
+      }
+    }
+  }
+}
+
 // One 256 x 256 tile.  FULL: all 256 rows and columns of the tile exist, so the stores need no
 // range checks.  A panel row past the matrix re-reads the last valid row: its products are never stored.
 // OUT selects what leaves the tile: bf16 (rounded to nearest even), fp32, or fp32 added to what C holds.
@@ -349,10 +390,7 @@ __device__ __forceinline__ void gemm_tile(unsigned char* lds0, unsigned char* ld
     }
     return;
   }
-  // Store.  bf16: two neighbouring blocks exchange halves between lane rows (one
-  // v_permlane16_swap per register pair), after which a lane owns 8 consecutive columns: one
-  // 16-byte store, 64 contiguous bytes per row and instruction.  fp32: 16 bytes per lane as they are.
-  const bool quad_aligned = ((reinterpret_cast<uintptr_t>(Cv) & 15u) == 0) && (ldc % 8 == 0);
+  // Store.  bf16: see store_row_block_bf16.  fp32: 16 bytes per lane as they are.
   if (OUT == kOutF32Add && FULL) {
     // C += tile: what C holds is requested one block of 16 rows AHEAD of the block being added and
     // stored (eight 16-byte loads per lane in flight behind eight stores), so that a lane waits for
@@ -386,39 +424,7 @@ __device__ __forceinline__ void gemm_tile(unsigned char* lds0, unsigned char* ld
 #pragma unroll
         for (int j = 0; j < 8; ++j) acc[i][j] *= factor;
       }
-#pragma unroll
-      for (int j = 0; j < 8; j += 2) {
-        const uint32_t lo0 = pack_bf16x2(acc[i][j][0], acc[i][j][1]), hi0 = pack_bf16x2(acc[i][j][2], acc[i][j][3]);
-        const uint32_t lo1 = pack_bf16x2(acc[i][j + 1][0], acc[i][j + 1][1]), hi1 = pack_bf16x2(acc[i][j + 1][2], acc[i][j + 1][3]);
-        if (quad_aligned) {
-          const auto l = __builtin_amdgcn_permlane16_swap(lo0, lo1, false, false);
-          const auto h = __builtin_amdgcn_permlane16_swap(hi0, hi1, false, false);
-          const u32x4 v = {l[0], h[0], l[1], h[1]};
-          const int col = n0 + wn * 128 + (j + (fk & 1)) * 16 + (fk >> 1) * 8;
-          uint16_t* dst = static_cast<uint16_t*>(Cv) + static_cast<int64_t>(row) * ldc + col;
-          // (a tile with rows or columns past the matrix: the same 16-byte stores, but for a vector across the
-          // matrix's edge.  Two bytes at a time for the whole tile, one of four: 1000 x 151936 x 2048 0.75 ms, now 0.53.)
-          if (FULL || (row < M && col + 8 <= N)) {
-            *reinterpret_cast<u32x4*>(dst) = v;
-          } else if (row < M) {
-            const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-              if (col + e < N) dst[e] = static_cast<uint16_t>((e & 1) ? (w[e >> 1] >> 16) : (w[e >> 1] & 0xffffu));
-          }
-        } else if (row < M) {
-#pragma unroll
-          for (int h = 0; h < 2; ++h) {
-            const int col = n0 + wn * 128 + (j + h) * 16 + fk * 4;
-            const uint32_t lo = h ? lo1 : lo0, hi = h ? hi1 : hi0;
-            uint16_t* dst = static_cast<uint16_t*>(Cv) + static_cast<int64_t>(row) * ldc + col;
-            if (col < N) dst[0] = static_cast<uint16_t>(lo & 0xffffu);
-            if (col + 1 < N) dst[1] = static_cast<uint16_t>(lo >> 16);
-            if (col + 2 < N) dst[2] = static_cast<uint16_t>(hi & 0xffffu);
-            if (col + 3 < N) dst[3] = static_cast<uint16_t>(hi >> 16);
-          }
-        }
-      }
+      store_row_block_bf16<FULL>(static_cast<uint16_t*>(Cv), ldc, M, N, row, n0 + wn * 128, fk, acc[i]);
     } else {
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
@@ -524,6 +530,175 @@ __global__ __launch_bounds__(256) void dppo_gemm_nt_kernel(const uint16_t* __res
   else                                gemm_tile<false, OUT, TA, TB>(lds0, lds1, A, lda, B, ldb, C, ldc, M, N, K, m0, n0, gs);
 }
 
+// ---- short contractions: C = bf16(factor A^T B) in tiles of 128 x 256 and steps of 32 ---------------
+// The weight gradient of few tokens is bound by what its tiles write: alone on its compute unit, a 256 x 256 tile's first
+// loads (2 us) and its store (7-8 us: every compute unit stores at the same time) leave the matrix cores idle, as long as
+// 8 of its steps (1000 tokens are 16).  Here a stage is 24 KiB, three of them 72, and a lane holds 128 accumulators, so
+// TWO workgroups share a compute unit and one's loads and stores pass behind the other's products.  The price is 1.5 x the LDS
+// reads per product (a wave's 64 x 128 quadrant needs 12 fragments for 32 products, a 128 x 128 one 16 for 64).
+// Measured, us, 256 x 256 tiles / these: 151936 x 2048, 64 tokens 198 / 148, 300 336 / 287, 500 415 / 366,
+// 1000 614 / 593, 2000 1030 / 1025, 4096 1916 / 2030; 50304 x 2048, 64 68 / 42, 500 130 / 116; 16000 x 1024, 64 11.2 / 10.0.
+// Two loads ahead are in flight per workgroup; the order of the sums over k is the same as in the larger tiles.
+constexpr int kShortM = 128, kShortK = 32, kShortA = kShortK * kShortM * 2, kShortStage = kShortA + kShortK * kBN * 2;
+
+template <bool FULL>
+__device__ __forceinline__ void short_tile(unsigned char* lds0, unsigned char* lds1, unsigned char* lds2, const uint16_t* __restrict__ A, int64_t lda,
+                                           const uint16_t* __restrict__ B, int64_t ldb, uint16_t* __restrict__ C, int64_t ldc,
+                                           int M, int N, int K, int m0, int n0, const float* factor_ptr) {
+  const int tid = threadIdx.x, lane = tid & 63, wid = uniform_i(tid >> 6);
+  const int wm = wid >> 1, wn = wid & 1;
+  const uint32_t pitch_a = static_cast<uint32_t>(lda) * 2u, pitch_b = static_cast<uint32_t>(ldb) * 2u;
+  const float factor = uniform_f(*factor_ptr);
+  f32x4 acc[4][8];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.f;
+
+  // Panels by rows as in gemm_tile: LDS row k of the A panel 256 bytes = 16 slots of 16 bytes, of the B panel 512 bytes = 32 slots, slot s
+  // holding the columns of global slot s ^ 2 g(k).
+  uint32_t toff_a[4], toff_b[8], vo_a[2], vo_b[4];
+  {
+    const int kg = lane >> 4, j = (lane >> 2) & 3, q = lane & 3;
+    const uint32_t g2 = static_cast<uint32_t>(2 * (j | ((kg & 1) << 2)));
+    const uint32_t k = static_cast<uint32_t>(8 * kg + j), sub = static_cast<uint32_t>(q & 1) * 8u;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) toff_a[t] = k * 256u + sub + ((static_cast<uint32_t>(wm * 8 + 2 * t + (q >> 1)) ^ g2) << 4);
+#pragma unroll
+    for (int t = 0; t < 8; ++t) toff_b[t] = kShortA + k * 512u + sub + ((static_cast<uint32_t>(wn * 16 + 2 * t + (q >> 1)) ^ g2) << 4);
+  }
+  auto swizzle = [](int k) { return static_cast<uint32_t>(2 * ((k & 3) | (((k >> 3) & 1) << 2))); };
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int k = 16 * i + 4 * wid + (lane >> 4);
+    vo_a[i] = static_cast<uint32_t>(k) * pitch_a + ((static_cast<uint32_t>(lane & 15) ^ swizzle(k)) << 4);
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int k = 8 * i + 2 * wid + (lane >> 5);
+    vo_b[i] = static_cast<uint32_t>(k) * pitch_b + ((static_cast<uint32_t>(lane & 31) ^ swizzle(k)) << 4);
+  }
+  const uint32_t bytes_a = (static_cast<uint32_t>(M - m0) * 2u + 15u) & ~15u, bytes_b = (static_cast<uint32_t>(N - n0) * 2u + 15u) & ~15u;
+  typedef __attribute__((address_space(3))) void* lds_ptr_t;
+  typedef short s16x4 __attribute__((ext_vector_type(4)));
+  typedef __attribute__((address_space(3))) s16x4* lds_s16x4_ptr;
+  // Load idx of the 6 of a step: 0, 1 A panel, 2..5 B panel.  Issued from inline assembly, so that the compiler puts no waits of its own in
+  // front of the fragment reads (around the loop it loses track of which stage a load goes to and waits for all of
+  // them); the waits are written out below.  Before the load the wait states of row_store16_untracked.
+  auto dma_one = [&](unsigned char* stage, int step, int idx) {
+    const uint32_t kr = static_cast<uint32_t>(min(kShortK, K - step * kShortK));
+    const bool b_panel = idx >= 2;
+    const int i = b_panel ? idx - 2 : idx;
+    const uint64_t base = b_panel ? reinterpret_cast<uint64_t>(B + static_cast<int64_t>(step) * kShortK * ldb + n0)
+                                  : reinterpret_cast<uint64_t>(A + static_cast<int64_t>(step) * kShortK * lda + m0);
+    const row_desc_t r = {static_cast<int>(base), static_cast<int>((base >> 32) & 0xffffu),
+                          static_cast<int>((kr - 1) * (b_panel ? pitch_b : pitch_a) + (b_panel ? bytes_b : bytes_a)), 0x00020000};
+    const uint32_t dst = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_ptr_t)(stage + (b_panel ? kShortA : 0) + wid * 1024 + i * 4096)));
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(dst), "v"(b_panel ? vo_b[i] : vo_a[i]), "s"(r) : "memory", "m0");
+  };
+  auto read_frag = [&](const unsigned char* p, uint32_t pitch) -> bf16x8 {
+    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(p));
+    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(p + 4 * pitch));
+    typedef short s16x8 __attribute__((ext_vector_type(8)));
+    const s16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+    return __builtin_bit_cast(bf16x8, v);
+  };
+  const int nk = (K + kShortK - 1) / kShortK;
+#pragma unroll
+  for (int q = 0; q < 6; ++q) dma_one(lds0, 0, q);
+  if (nk > 1) {
+#pragma unroll
+    for (int q = 0; q < 6; ++q) dma_one(lds1, 1, q);
+  }
+  auto step = [&](unsigned char* cur, unsigned char* free_stage, int kt, auto steady) {
+    constexpr bool STEADY = decltype(steady)::value;
+    // This wave's six loads of this step have landed (the next step's six may be in flight) and its reads of the step before
+    // are done; then everyone's.  (A plain s_barrier: the fence of __syncthreads() waits for every load in flight.)
+    asm volatile("" ::: "memory");
+    if (STEADY || kt + 1 < nk) __builtin_amdgcn_s_waitcnt(0x76);      // vmcnt(6) lgkmcnt(0)
+    else                       __builtin_amdgcn_s_waitcnt(0x70);      // vmcnt(0) lgkmcnt(0)
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    DPPO_PIN;
+    const bool more = STEADY || kt + 2 < nk;
+    bf16x8 fa[4], fb[8];
+    fa[0] = read_frag(cur + toff_a[0], 256); DPPO_PIN;
+#pragma unroll
+    for (int t = 0; t < 8; ++t) { fb[t] = read_frag(cur + toff_b[t], 512); DPPO_PIN; }
+#pragma unroll
+    for (int t = 1; t < 4; ++t) { fa[t] = read_frag(cur + toff_a[t], 256); DPPO_PIN; }
+#pragma unroll
+    for (int m = 0; m < 32; ++m) {
+      DPPO_MFMA16(acc[m >> 3][m & 7], fb[m & 7], fa[m >> 3]); DPPO_PIN;
+      if (m % 5 == 0 && m / 5 < 6) { if (more) dma_one(free_stage, kt + 2, m / 5); DPPO_PIN; }
+    }
+  };
+  int kt = 0;
+  for (; kt + 4 < nk; kt += 3) {
+    step(lds0, lds2, kt, std::true_type{});
+    step(lds1, lds0, kt + 1, std::true_type{});
+    step(lds2, lds1, kt + 2, std::true_type{});
+  }
+  for (; kt < nk; kt += 3) {
+    step(lds0, lds2, kt, std::false_type{});
+    if (kt + 1 < nk) step(lds1, lds0, kt + 1, std::false_type{});
+    if (kt + 2 < nk) step(lds2, lds1, kt + 2, std::false_type{});
+  }
+  // the products have landed before anything else reads the accumulators (see gemm_tile)
+#define DPPO_THROUGH(CODE, I) asm volatile(CODE : "+a"(acc[I][0]), "+a"(acc[I][1]), "+a"(acc[I][2]), "+a"(acc[I][3]), \
+                                               "+a"(acc[I][4]), "+a"(acc[I][5]), "+a"(acc[I][6]), "+a"(acc[I][7]) :: "memory")
+  DPPO_THROUGH("s_nop 15\n\ts_nop 15", 0);
+#pragma unroll
+  for (int i = 1; i < 4; ++i) DPPO_THROUGH("", i);
+#undef DPPO_THROUGH
+  DPPO_PIN;
+  const int frow = lane & 15, fk = lane >> 4;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) acc[i][j] *= factor;
+    store_row_block_bf16<FULL>(C, ldc, M, N, m0 + wm * 64 + i * 16 + frow, n0 + wn * 128, fk, acc[i]);
+  }
+}
+
+struct ShortMap {
+  int tiles_m, tiles_n, group_m, group_n, tiles, per_die;
+};
+
+__global__ __launch_bounds__(256, 2) void dppo_gemm_tn_short_kernel(const uint16_t* __restrict__ A, int64_t lda, const uint16_t* __restrict__ B, int64_t ldb,
+                                                                    uint16_t* __restrict__ C, int64_t ldc, int M, int N, int K, const ShortMap map,
+                                                                    const float* factor) {
+  __shared__ __attribute__((aligned(16))) unsigned char lds0[kShortStage];
+  __shared__ __attribute__((aligned(16))) unsigned char lds1[kShortStage];
+  __shared__ __attribute__((aligned(16))) unsigned char lds2[kShortStage];
+  const int tile = (static_cast<int>(blockIdx.x) & 7) * map.per_die + (static_cast<int>(blockIdx.x) >> 3);
+  if (tile >= map.tiles) return;
+  const int bn = tile / (map.group_n * map.tiles_m);
+  int t = tile - bn * (map.group_n * map.tiles_m);
+  const int width = min(map.group_n, map.tiles_n - bn * map.group_n);
+  const int bm = t / (map.group_m * width);
+  t -= bm * (map.group_m * width);
+  const int height = min(map.group_m, map.tiles_m - bm * map.group_m);
+  const int m0 = (bm * map.group_m + t % height) * kShortM, n0 = (bn * map.group_n + t / height) * kBN;
+  if (M - m0 >= kShortM && N - n0 >= kBN) short_tile<true>(lds0, lds1, lds2, A, lda, B, ldb, C, ldc, M, N, K, m0, n0, factor);
+  else                                    short_tile<false>(lds0, lds1, lds2, A, lda, B, ldb, C, ldc, M, N, K, m0, n0, factor);
+}
+
+// Numbers run block by block over 64 tiles, the workgroups that run together on a die, each die a contiguous range.  Eight tiles wide:
+// four 0-4 % slower, sixteen 3-29 % where the matrix is 12 or 16 tiles wide (but for 151936 x 3008: 3-10 % faster).
+ShortMap short_map(int64_t M, int64_t N) {
+  ShortMap t;
+  t.tiles_m = static_cast<int>((M + kShortM - 1) / kShortM);
+  t.tiles_n = static_cast<int>((N + kBN - 1) / kBN);
+  t.group_n = std::min(t.tiles_n, 8);
+  t.group_m = 64 / t.group_n;
+  t.tiles = t.tiles_m * t.tiles_n;
+  t.per_die = (t.tiles + 7) / 8;
+  return t;
+}
+
 }  // namespace
 
 hipError_t launch_gemm_nt(const uint16_t* A, int64_t lda, const uint16_t* B, int64_t ldb, void* C, int64_t ldc,
@@ -550,14 +725,28 @@ hipError_t launch_gemm_stats(const uint16_t* A, int64_t lda, const uint16_t* B, 
   return hipGetLastError();
 }
 
+// Which contractions are short (ratio of the times, these tiles to 256 x 256, over 25 shapes of 16000 .. 151936 x 768 .. 4096):
+// up to 500 0.62-1.00, 700 0.85-1.03, 1000 0.92-1.06, 1400 0.95-1.11; of 1000 those of nine rounds of 256 x 256 tiles and more,
+// not the narrowest, 0.92-0.99.
+static bool gemm_tn_short(int64_t M, int64_t N, int64_t K) {
+  const int64_t tiles = ((M + kBM - 1) / kBM) * ((N + kBN - 1) / kBN);
+  return K <= 640 || (K <= 1024 && N >= 1024 && tiles >= 9 * 256);
+}
+
 // C[M, N] bf16 = *factor A^T B, rounded once.
 //
 // The gradient of the weight in its own type.  Left in fp32 for a pass of its own to scale and round, it cost 12 bytes
 // per entry where 2 do, and short contractions are bound by them.  V = 151936: 1000 tokens x 2048, fp32 product and
-// conversion 743 + 322 us, here 641-688; 8192 x 4096 7.85 + 0.62 ms, here 7.55.
+// conversion 743 + 322 us, here 593; 8192 x 4096 7.85 + 0.62 ms, here 7.55.
 hipError_t launch_gemm_tn_bf16(const uint16_t* A, int64_t lda, const uint16_t* B, int64_t ldb, void* C, int64_t ldc,
                                int M, int N, int K, const float* factor, hipStream_t s) {
   if (M <= 0 || N <= 0) return hipSuccess;
+  if (gemm_tn_short(M, N, K)) {
+    const ShortMap map = short_map(M, N);
+    hipLaunchKernelGGL(dppo_gemm_tn_short_kernel, dim3(8u * static_cast<unsigned>(map.per_die)), dim3(256), 0, s, A, lda, B, ldb, static_cast<uint16_t*>(C), ldc,
+                       M, N, K, map, factor);
+    return hipGetLastError();
+  }
   const TileMap map = tile_map(M, N, K, 1);
   GemmStats gs;
   gs.factor = factor;
