@@ -245,7 +245,8 @@ const char* dppo_last_path(void);
 
 /* Name of the kernel that the same call spent its time in: that of its path ("dppo_resident_kernel" for
  * "resident" and so on; "dppo_gemm_nt_kernel" for the two lmhead paths), or "dppo_forward_kernel" where a forward-only
- * call of path "resident" or "streaming" passed its rows through a window of registers once. */
+ * call of path "resident" or "streaming" passed its rows through a window of registers once, or "dppo_split_stat_kernel"
+ * where a call of few long rows had each divided among several workgroups. */
 const char* dppo_last_kernel(void);
 
 /* ---- the same loss from the hidden states: the [T, V] logits never exist in full -------------

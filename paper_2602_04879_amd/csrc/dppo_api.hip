@@ -157,16 +157,19 @@ dppo::KParams make_kparams(const dppo_args_t* a, bool grad) {
 struct LossScratch {
   double* partial = nullptr;
   int max_parts = 0;
+  size_t split_bytes = 0;     // what a call that divides its rows finds from `partial` on (0: none may)
   int32_t* counters = nullptr;
   double* row_loss = nullptr;
 };
-// The layout of a caller's workspace: [partial sums, 32 KiB | counters | unused up to 64 KiB | row loss terms, 8 T bytes]
+// The layout of a caller's workspace: [partial sums, 32 KiB | counters | unused up to 64 KiB | row loss terms, 8 T bytes], or, where rows
+// are divided among workgroups, [loss terms, segment records and gathered logits, up to 64 KiB]
 constexpr size_t kPartialBytes = 32768;
 LossScratch scratch_of(void* base, size_t bytes, int64_t T) {
   LossScratch sc;
   char* b = static_cast<char*>(base);
   sc.partial = reinterpret_cast<double*>(b);
   sc.max_parts = static_cast<int>(kPartialBytes / sizeof(double));
+  sc.split_bytes = DPPO_WORKSPACE_BYTES;
   if (bytes >= DPPO_WORKSPACE_BYTES + static_cast<size_t>(T) * sizeof(double)) {
     sc.counters = reinterpret_cast<int32_t*>(b + kPartialBytes);
     sc.row_loss = reinterpret_cast<double*>(b + DPPO_WORKSPACE_BYTES);
@@ -227,6 +230,18 @@ bool forward_keeps_row(const dppo_args_t* a, int threads, int chunks, bool ragge
   return a->T >= least && a->T <= most && a->ld % 32768 != 0;
 }
 
+// Few long rows, which would leave most compute units idle: divided among workgroups (dppo_split.hip) where the third launch and the
+// second read cost less than the idle time, the same for calls with and without a gradient, whose per-token outputs then agree bit for bit.
+// Ratio of the times, divided / one workgroup per row, with the gradient and without (whole calls, Top-20 TV, 8 / 64 / 96 / 128 tokens of
+// 256 compute units' share): V = 65536 0.86-1.0 / 0.97-1.08 / 1.01-1.17 / 1.08-1.2 and 0.80-1.0 / 0.82-0.96 / 0.84-0.98 / 0.91-1.03;
+// 81920 0.78 / 0.91 / 1.00 / 1.00; 98304 0.78 / 0.89 / 0.95 / 1.06; 131072 0.69 / 0.81 / 0.89 / 0.95; 151936 0.57 / 0.73 / 0.81 / 0.87 and
+// 0.75 / 0.80 / 0.85 / 0.88; 256000 0.34 / 0.49 / 0.67 (100 tokens) / 0.76.  At 140 tokens and more even or slower below V = 155000.
+bool splits_rows(const dppo_args_t* a, bool ragged_ok, const LossScratch& sc, int cus) {
+  if (a->V < 81920 || a->V > 64 * 8 * static_cast<int64_t>(dppo::kSplitVecs) - 64 || a->T > (a->V >= 131072 ? cus / 2 : cus / 4)) return false;
+  const bool topk = (a->variant == DPPO_TOPK_TV || a->variant == DPPO_TOPK_KL);
+  return ragged_ok && !(a->flags & DPPO_FLAG_FORCE_STREAMING) && dppo::split_scratch_bytes(a->T, a->V, topk ? a->K : 0) <= sc.split_bytes;
+}
+
 // Launch the loss kernel of one (already validated) call.  Afterwards the scalar loss is
 // loss_scale times the sum of fin[0 .. *fin_n) (per-workgroup partial sums, or per-row terms).
 dppo_status_t launch_loss(const dppo_args_t* a, bool grad, const LossScratch& sc, const double** fin, int* fin_n, hipStream_t s) {
@@ -281,7 +296,11 @@ dppo_status_t launch_loss(const dppo_args_t* a, bool grad, const LossScratch& sc
     // kernel (V = 8181, 16384 tokens: 141 / 207).
     const bool forward = !full && !grad && !(a->flags & DPPO_FLAG_FORCE_STREAMING) &&
                          (resident ? !forward_keeps_row(a, r_threads, r_chunks, ragged, on_lines, cus) : a->V >= 65536 && a->V < (int64_t(1) << 30));
-    if (forward) {
+    if (!full && splits_rows(a, ragged_ok, sc, cus)) {
+      if (dppo::launch_split(p, grad, sc.partial, s) != hipSuccess) return DPPO_ERR_LAUNCH;
+      nparts = static_cast<int>(a->T);
+      chose(resident ? "resident" : long_chunks ? "resident_long" : "streaming", "dppo_split_stat_kernel");
+    } else if (forward) {
       int64_t grid = 2 * static_cast<int64_t>(cus);
       if (grid > a->T) grid = a->T;
       if (grid > max_parts) grid = max_parts;
@@ -572,6 +591,7 @@ dppo_status_t run_lmhead(const dppo_lmhead_args_t* a, void* stream, bool grad) {
     LossScratch sc;                   // per-workgroup partial sums only: the chunks of one call share the scratch
     sc.partial = partial + used;
     sc.max_parts = parts_per_chunk;
+    if (nchunks == 1) sc.split_bytes = DPPO_WORKSPACE_BYTES;
     const double* fin = nullptr;
     const dppo_status_t st = launch_loss(&c, grad, sc, &fin, &np, s);   // gradient in place
     if (st != DPPO_OK) return st;

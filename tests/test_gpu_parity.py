@@ -788,6 +788,63 @@ def test_forward_only_rows_kept_or_streamed(V, ld, per_cu, diagnostics, kernel):
     assert 0 < (res["mask"] == 0).sum().item() < T
 
 
+@pytest.mark.parametrize("V,ld,off,per_cu,variant,K,kernel", [
+    (151936, 151936, 0, 2, W.TOPK_TV, 20, "split_stat"), (151643, 151643, 0, 2, W.TOPK_KL, 7, "split_stat"),
+    (131072, 131072, 0, 2, W.BINARY_TV, 0, "split_stat"), (131073, 131136, 5, 2, W.BINARY_KL, 0, "split_stat"), (262145, 262145, 3, 8, W.TOPK_TV, 70, "split_stat"),
+    (81920, 81920, 0, 4, W.TOPK_TV, 100, "split_stat"), (81921, 81984, 1, 4, W.BINARY_TV, 0, "split_stat"), (98303, 98303, 7, 5, W.TOPK_KL, 64, "split_stat"),
+    (81912, 81912, 0, 4, W.BINARY_TV, 0, "resident"), (131071, 131071, 0, 2, W.BINARY_TV, 0, "resident"),
+    (151936, 151936, 0, 2, W.TOPK_TV, 100, "resident"),           # no room for the records in the scratch
+    (1048512, 1048512, 0, 64, W.BINARY_TV, 0, "split_stat"), (1048513, 1048513, 0, 64, W.BINARY_TV, 0, "streaming")])
+def test_few_long_rows_divided_among_workgroups(V, ld, off, per_cu, variant, K, kernel):
+    """Which calls divide their rows, and their results: sampled tokens on the borders of blocks and segments, top-K ids
+    in every segment, ignored rows, blocks of -inf, rows of one sign, any alignment; against the oracle, in place
+    and forward only bit for bit the same, and nothing around the gradient written."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    T = cus // per_cu
+    w = W.Workload("split", 1, T, V, variant, 0.05, K=K, logit_std=3.0, noise_std=1.0, adv="normal", seed=117)
+    b = W.make_batch(w, DEV, ld=ld, shift_sampled=2.0, rows_per_step=32)
+    b["advantages"] = torch.randn(T, device=DEV)
+    flat = torch.full((off + T * ld + 64,), 9.0, dtype=torch.bfloat16, device=DEV)        # finite neighbours, which must not count
+    z = flat[off:off + T * ld].view(T, ld)
+    z[:, :V] = b["logits"][:, :V]
+    b["logits"] = z
+    if K:
+        b["mu_topk_ids"][1, :] = torch.linspace(0, V - 1, K, device=DEV).to(torch.int32)
+    for t, a in zip(range(2, T), (0, 7, 8, 63, 64, 16383, 16384, 16385, V // 2, V - 9, V - 8, V - 2, V - 1, -1, V, V - 1)):
+        b["sampled_ids"][t] = a
+    if T > 24:
+        rows = torch.arange(20, 24, device=DEV)
+        a = b["sampled_ids"][20:24].long()
+        keep = z[rows, a].clone()
+        z[20, 9000:60000] = float("-inf")
+        z[21, 10:V - 10] = float("-inf")
+        z[22, :V] = -50.0
+        z[23, :V] = 3.0e4
+        z[rows[:2], a[:2]] = keep[:2]
+    _say(f"[case] few rows V={V} ld={ld} off={off} T={T} K={K} variant={variant}")
+    some = np.unique(np.concatenate([np.arange(0, T, 1 if V < 200000 else 4), np.arange(0, min(T, 24))]))
+    ref = P.oracle_rows(b, some)
+    gbuf = torch.full_like(flat, 7.0)
+    grad = gbuf[off:off + T * ld].view(T, ld)
+    res = B.run_batch(b, grad=grad, diagnostics=True)
+    torch.cuda.synchronize()
+    assert B.last_kernel() == f"dppo_{kernel}_kernel"
+    st = P.compare_rows(b, res, some, ref=ref)
+    P.check_loss_scalar(b, res)
+    assert (gbuf[:off] == 7.0).all() and (gbuf[off + T * ld:] == 7.0).all() and (grad[:, V:] == 7.0).all()
+    fwd = B.run_batch(b, backward=False, diagnostics=True)
+    plain = B.run_batch(b, backward=False)
+    inp = B.run_batch(b, in_place=True, diagnostics=True)
+    torch.cuda.synchronize()
+    if kernel == "split_stat":
+        for k in ("loss", "loss_tok", "divergence", "mask"):
+            assert torch.equal(res[k], fwd[k]) and torch.equal(res[k], plain[k]) and torch.equal(res[k], inp[k]), k
+        assert torch.equal(res["diagnostics"], fwd["diagnostics"]) and torch.equal(res["diagnostics"], inp["diagnostics"])
+        assert torch.equal(z[:, :V], grad[:, :V])
+    assert (flat[:off] == 9.0).all() and (flat[off + T * ld:] == 9.0).all() and (z[:, V:] == 9.0).all()
+    _say(f"       {st}")
+
+
 def test_other_stream_and_loss_tok_optional():
     w = W.Workload("stream", 2, 16, 2048, W.TOPK_TV, 0.1, K=8, logit_std=2.0, noise_std=0.5, adv="pm1", seed=4)
     b = W.make_batch(w, DEV)
