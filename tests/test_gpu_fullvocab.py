@@ -367,6 +367,46 @@ def test_resident_form_on_shorter_rows(variant, delta, V, ld):
 
 
 @pytest.mark.parametrize("variant,delta", FULL)
+@pytest.mark.parametrize("V", [12296, 16384, 24576, 32000])
+def test_short_rows_whose_largest_entry_is_anywhere(variant, delta, V):
+    """Rows short enough that a thread knows its largest entry before its first exponential: the largest entry of a row in
+    every position of a 16-byte block and far above the rest, rows of one sign, blocks of -inf, and -0.  (Both rows
+    alike in size: the cross term of the KL form, a sum in fp32, loses what the rows differ by.)"""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    T = cus + 40
+    w = W.Workload("fv_max", 1, T, V, variant, delta, mu_full=True, logit_std=3.0, noise_std=0.7, adv="normal", seed=139)
+    b = W.make_batch(w, DEV, shift_sampled=1.0, rows_per_step=512)
+    b["advantages"] = torch.randn(T, device=DEV)
+    z, y = b["logits"], b["mu_logits"]
+    for t in range(16):                               # 8 positions in a block, in the first and the last chunk
+        j = (t if t < 8 else V - 16 + t) if t % 2 else (4096 + t if t < 8 else V - 24 + t)
+        z[t, j], y[t, j] = 20.0 + t, 20.5 + t
+        if t % 3 == 0:
+            b["sampled_ids"][t] = j
+    z[16], y[16] = -1.0 - z[16].abs(), -1.0 - y[16].abs()
+    z[17], y[17] = z[17] - 30.0, y[17] - 30.0
+    z[18, 64:V - 64] = float("-inf"); y[18, 64:V - 64] = float("-inf")
+    z[19], y[19] = -0.0, 0.0
+    z[20], y[20] = -0.0, -1.0
+    z[18, :8], y[18, :8] = -5.0, -6.0
+    b["sampled_ids"][18], b["sampled_ids"][16:18] = 3, 7
+    rows = np.arange(24)
+    _say(f"[case] exact divergence, largest entries anywhere V={V} variant={variant}")
+    res = B.run_batch(b, diagnostics=True)
+    torch.cuda.synchronize()
+    if variant == W.FULL_TV or V != 12296:              # (the KL form: rows that fill their shape)
+        assert B.last_path() == "fullvocab_resident"
+    gen = B.run_batch(b, diagnostics=True, flags=B.FLAG_FORCE_STREAMING)
+    torch.cuda.synchronize()
+    st = P.compare_rows(b, res, rows)
+    ok = torch.isfinite(gen["divergence"])
+    assert torch.equal(ok, torch.isfinite(res["divergence"]))
+    # both sides within the module's bound of the oracle: 1e-4 relative + 3e-7, each
+    assert ((gen["divergence"] - res["divergence"]).abs()[ok] <= 2e-4 * gen["divergence"][ok] + 6e-7).all()
+    _say(f"       {st}")
+
+
+@pytest.mark.parametrize("variant,delta", FULL)
 def test_every_row_whatever_number_is_left_over(variant, delta):
     """Two workgroups per compute unit, rows fixed by the workgroup index: one round exactly and less, one
     row left over, all but one, several rounds.  Every row is written, with the bits that it has in a call of
