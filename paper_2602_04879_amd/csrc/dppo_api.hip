@@ -349,6 +349,8 @@ dppo_status_t launch_loss(const dppo_args_t* a, bool grad, const LossScratch& sc
       chose("resident_multi", "dppo_resident_multi_kernel");
       return DPPO_OK;
     } else if (resident) {
+      if (grad && ragged && r_threads == 512 && r_chunks == 16 && dppo::resident_pairs(a->V, a->T, a->diagnostics != nullptr, cus))
+        r_chunks = dppo::kResidentPairChunks;
       int per_cu = resident_blocks_per_cu_cached(dev, grad, false, ragged, r_threads, r_chunks);
       int64_t grid = static_cast<int64_t>(cus) * per_cu;
       if (grid > a->T) grid = a->T;
@@ -358,7 +360,7 @@ dppo_status_t launch_loss(const dppo_args_t* a, bool grad, const LossScratch& sc
       // forward-only form and the shapes with several workgroups per compute unit measure slower
       // that way: their waves run ahead of wave 0, which would have to wait for the counter.)
       bool dyn = false;
-      if (grad && r_threads == 512 && per_cu == 1) {
+      if (grad && r_threads == 512 && r_chunks != dppo::kResidentPairChunks && per_cu == 1) {
         // the form that draws its rows has its own register count, so its own occupancy
         const int64_t grid_dyn = static_cast<int64_t>(cus) * resident_blocks_per_cu_cached(dev, grad, true, ragged, r_threads, r_chunks);
         if (grid_dyn <= max_parts && rows_at_run_time(a, sc, grid_dyn)) {

@@ -18,6 +18,8 @@ hipError_t launch_streaming(const KParams& p, bool vec, bool grad, int threads, 
 // for a shape (dyn: of the form that hands its rows out at run time).
 bool resident_shape(int64_t V, bool ragged, int* threads, int* chunks);
 hipError_t launch_resident(const KParams& p, bool grad, bool ragged, int threads, int chunks, int grid, hipStream_t s);
+constexpr int kResidentPairChunks = 14;      // a shape of 512 threads for calls that resident_pairs() names, in place of 16 chunks (ragged, with the gradient)
+bool resident_pairs(int64_t V, int64_t T, bool diag, int cus);
 int resident_blocks_per_cu(bool grad, bool dyn, bool ragged, int threads, int chunks);
 
 // Forward only: rows streamed once through the statistics, at most two workgroups per compute unit,

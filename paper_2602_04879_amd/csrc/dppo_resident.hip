@@ -62,7 +62,7 @@ constexpr int kChunkStep = 4;
 // compiled to 130 registers: +3..8 % on rows of 36-48 KiB) and three with 16 chunks (a budget of 168
 // registers; left to itself the compiler lands within a register or two of that limit, on either
 // side; a fourth workgroup there, 128 registers, spills and measured 7-12 % slower).
-constexpr int resident_min_waves(int threads, int nchunk) { return threads == 512 ? (nchunk <= 12 ? 4 : 2) : (nchunk <= 12 ? 4 : nchunk <= 16 ? 3 : 2); }
+constexpr int resident_min_waves(int threads, int nchunk) { return threads == 512 ? (nchunk <= 14 ? 4 : 2) : (nchunk <= 12 ? 4 : nchunk <= 16 ? 3 : 2); }
 
 // RAGGED = true: rows that do not start on a 16-byte boundary or whose length is not a multiple
 // of 8 (a vocabulary of 50257 entries; a pitch that is not a multiple of 8), and rows that start
@@ -471,7 +471,21 @@ bool resident_shape(int64_t V, bool ragged, int* threads, int* chunks) {
   return false;
 }
 
+// Ragged rows of 12 to 13 chunks, with the gradient, without diagnostics and three rows or more per compute unit: 14 chunks and two
+// workgroups per compute unit, 128 registers with a few spilled, in place of 16 chunks and one.  16 / 14 chunks, us (V = 50257): 800 tokens
+// 45.2 / 43.3, 1024 49.8 / 45.3, 2000 85.6 / 81.9, 6000 262 / 246, 10000 420 / 396 (49153 to 52008: 0.90-0.98 of the time).  With fewer
+// rows the last round counts (600: 36.7 / 39.9, 200: 14.6 / 16.3); with diagnostics it spills more (1.07-1.33); 57001 entries
+// fill the fourteenth chunk (2000 tokens 1.09); aligned rows lose 2-6 %.
+bool resident_pairs(int64_t V, int64_t T, bool diag, int cus) {
+  return (V + 70) / 8 <= 512 * 13 && !diag && T >= 3 * static_cast<int64_t>(cus);
+}
+
 hipError_t launch_resident(const KParams& p, bool grad, bool ragged, int threads, int chunks, int grid, hipStream_t s) {
+  if (threads == 512 && chunks == kResidentPairChunks) {
+    if (!grad || !ragged || p.diag || p.row_counters) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((dppo_resident_kernel<512, kResidentPairChunks, true, false, false, true>), dim3(grid), dim3(512), 0, s, p);
+    return hipGetLastError();
+  }
 #define DPPO_LAUNCH(T, C) if (threads == T && chunks == C) return ragged ? launch_shape<T, C, true>(p, grad, grid, s) : launch_shape<T, C, false>(p, grad, grid, s);
   DPPO_SHAPES(DPPO_LAUNCH)
 #undef DPPO_LAUNCH
@@ -479,6 +493,11 @@ hipError_t launch_resident(const KParams& p, bool grad, bool ragged, int threads
 }
 
 int resident_blocks_per_cu(bool grad, bool dyn, bool ragged, int threads, int chunks) {
+  if (threads == 512 && chunks == kResidentPairChunks) {
+    int n = 0;
+    const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, dppo_resident_kernel<512, kResidentPairChunks, true, false, false, true>, 512, 0);
+    return (e == hipSuccess && n > 0) ? n : 1;
+  }
 #define DPPO_OCC(T, C) if (threads == T && chunks == C) return ragged ? occupancy_shape<T, C, true>(grad, dyn) : occupancy_shape<T, C, false>(grad, dyn);
   DPPO_SHAPES(DPPO_OCC)
 #undef DPPO_OCC

@@ -845,6 +845,44 @@ def test_few_long_rows_divided_among_workgroups(V, ld, off, per_cu, variant, K, 
     _say(f"       {st}")
 
 
+@pytest.mark.parametrize("V,ld,off", [(49145, 49145, 3), (50257, 50257, 0), (50264, 50264, 0), (53178, 53184, 1)])
+def test_ragged_rows_of_thirteen_chunks_two_workgroups_per_compute_unit(V, ld, off):
+    """The shape that such rows take without diagnostics, many of them, at its shortest and longest row: the bits of the shape
+    they take with diagnostics, sampled rows against the oracle, in place, and nothing around the gradient written."""
+    T = 3 * torch.cuda.get_device_properties(0).multi_processor_count + 29
+    w = W.Workload("pairs", 1, T, V, W.TOPK_TV, 0.05, K=20, logit_std=3.0, noise_std=1.0, zipf_s=1.1, adv="normal", seed=119)
+    b = W.make_batch(w, DEV, ld=ld, shift_sampled=2.0, rows_per_step=256)
+    b["advantages"] = torch.randn(T, device=DEV)
+    flat = torch.full((off + T * ld + 64,), 9.0, dtype=torch.bfloat16, device=DEV)
+    z = flat[off:off + T * ld].view(T, ld)
+    z[:, :V] = b["logits"][:, :V]
+    b["logits"] = z
+    for t, a in enumerate((0, 7, 8, 63, 64, V // 2, V - 9, V - 8, V - 2, V - 1, -1, V)):
+        b["sampled_ids"][3 * t] = a
+    z[50, 100:40000] = float("-inf")
+    b["sampled_ids"][50] = 5
+    _say(f"[case] rows of thirteen chunks V={V} ld={ld} off={off} T={T}")
+    rows = np.unique(np.concatenate([np.arange(52), np.arange(T - 8, T), np.arange(0, T, 97)]))
+    ref = P.oracle_rows(b, rows)
+    gbuf = torch.full_like(flat, 7.0)
+    grad = gbuf[off:off + T * ld].view(T, ld)
+    res = B.run_batch(b, grad=grad)
+    torch.cuda.synchronize()
+    assert B.last_kernel() == "dppo_resident_kernel"
+    st = P.compare_rows(b, res, rows, ref=ref)
+    P.check_loss_scalar(b, res)
+    assert (gbuf[:off] == 7.0).all() and (gbuf[off + T * ld:] == 7.0).all() and (grad[:, V:] == 7.0).all()
+    other = B.run_batch(b, diagnostics=True, grad=torch.empty_like(flat)[off:off + T * ld].view(T, ld))      # (aligned as the logits are)
+    fwd = B.run_batch(b, backward=False)
+    torch.cuda.synchronize()
+    for k in ("loss_tok", "divergence", "mask"):
+        assert torch.equal(res[k], other[k]) and torch.equal(res[k], fwd[k]), k
+    assert torch.equal(grad[:, :V], other["grad_logits"][:, :V])
+    B.run_batch(b, in_place=True)
+    torch.cuda.synchronize()
+    assert torch.equal(z[:, :V], grad[:, :V]) and (z[:, V:] == 9.0).all() and 0 < st["masked"] < len(rows)
+
+
 def test_other_stream_and_loss_tok_optional():
     w = W.Workload("stream", 2, 16, 2048, W.TOPK_TV, 0.1, K=8, logit_std=2.0, noise_std=0.5, adv="pm1", seed=4)
     b = W.make_batch(w, DEV)
