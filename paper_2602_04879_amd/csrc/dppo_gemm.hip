@@ -801,14 +801,24 @@ int gemm_nn_splits(int64_t M, int64_t N, int64_t K, int cus, size_t scratch_byte
 
 namespace {
 // Adds the fp32 partial results of the ranges of the contraction, [splits][M][N], in their order and
-// rounds the sum to bf16 once.  Four columns per thread (N a multiple of 4); bound by reading the
-// partial sums, which the products have just written.
-__global__ __launch_bounds__(256) void dppo_gemm_sum_kernel(const f32x4* __restrict__ part, int splits, int64_t quads, int quads_row,
-                                                            uint16_t* __restrict__ C, int64_t ldc) {
-  const int64_t q = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+// rounds the sum to bf16 once.  Four columns per thread (N a multiple of 4); bound by the latency of reading the
+// partial sums, which the products have just written: few tokens are few threads and many ranges, so sixteen loads are in flight
+// per thread, and workgroups are one wave (one load at a time, 64 tokens x 768, 63 ranges: 17 us, now 6).
+constexpr int kSumThreads = 64, kSumAhead = 16;
+__global__ __launch_bounds__(kSumThreads) void dppo_gemm_sum_kernel(const f32x4* __restrict__ part, int splits, int64_t quads, int quads_row,
+                                                                    uint16_t* __restrict__ C, int64_t ldc) {
+  const int64_t q = static_cast<int64_t>(blockIdx.x) * kSumThreads + threadIdx.x;
   if (q >= quads) return;
   f32x4 v = part[q];
-  for (int s = 1; s < splits; ++s) v += part[static_cast<int64_t>(s) * quads + q];
+  for (int s = 1; s < splits; s += kSumAhead) {
+    f32x4 x[kSumAhead];
+#pragma unroll
+    for (int u = 0; u < kSumAhead; ++u)
+      if (s + u < splits) x[u] = part[static_cast<int64_t>(s + u) * quads + q];
+#pragma unroll
+    for (int u = 0; u < kSumAhead; ++u)
+      if (s + u < splits) v += x[u];
+  }
   const int64_t row = q / quads_row;
   uint16_t* dst = C + row * ldc + (q - row * quads_row) * 4;
   const uint32_t lo = pack_bf16x2(v[0], v[1]), hi = pack_bf16x2(v[2], v[3]);
@@ -838,7 +848,7 @@ hipError_t launch_gemm_nn(const uint16_t* A, int64_t lda, const uint16_t* B, int
                        static_cast<void*>(scratch), static_cast<int64_t>(N), M, N, K, map, GemmStats{});
     if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
     const int64_t quads = static_cast<int64_t>(M) * N / 4;
-    hipLaunchKernelGGL(dppo_gemm_sum_kernel, dim3(static_cast<unsigned>((quads + 255) / 256)), dim3(256), 0, s,
+    hipLaunchKernelGGL(dppo_gemm_sum_kernel, dim3(static_cast<unsigned>((quads + kSumThreads - 1) / kSumThreads)), dim3(kSumThreads), 0, s,
                        reinterpret_cast<const f32x4*>(scratch), used, quads, N / 4, static_cast<uint16_t*>(C), ldc);
     return hipGetLastError();
   }
