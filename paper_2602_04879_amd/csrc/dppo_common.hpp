@@ -657,10 +657,9 @@ __device__ __forceinline__ RowResult row_epilogue(const EpiParams& p, int row, R
   return res;
 }
 
-// The same epilogue as a real call.  Its float64 arithmetic needs many registers; where
-// several workgroups share a compute unit, keeping those out of the kernel's register budget
-// (the call saves and restores what it needs, in the one wave that makes it) buys occupancy,
-// and the other workgroups hide the call's latency.
+// The same epilogue as a real call.  Its float64 arithmetic needs many registers; a call keeps those out of the
+// kernel's register budget, but saves and restores 32 of them through scratch memory in the wave the row waits for: 5-35 % of a
+// short row's time (see the callers).  For forms that inlined would spill more than that or lose a workgroup per compute unit.
 __device__ __attribute__((noinline)) static RowResult row_epilogue_call(const EpiParams& p, int row, RowScalars rs, TopkLane tk,
                                                                         const uint16_t* zrow, float b, double S_rest, double T_rest,
                                                                         int lane, double D_full = 0.0) {

@@ -216,7 +216,10 @@ __global__ __launch_bounds__(kThreads, 4) void dppo_forward_kernel(const KParams
           S_rest += sh_s[par][w] * sc;
           if (DIAG) T_rest += sc * (sh_t[par][w] + dd * sh_s[par][w]);
         }
-        const RowResult rr = row_epilogue_call(ep, row, rs, tk, zrow, bb, S_rest, T_rest, lane);
+        // (with diagnostics the inlined form spills fifty registers: 2-5 % slower from 1000 tokens on; without, 1000 tokens of
+        // V = 57000, 151936 and 256000: 36.9 / 24.7, 70.5 / 52.4, 106 / 83 us as a call / inlined)
+        const RowResult rr = DIAG ? row_epilogue_call(ep, row, rs, tk, zrow, bb, S_rest, T_rest, lane)
+                                  : row_epilogue(ep, row, rs, tk, zrow, bb, S_rest, T_rest, lane);
         loss_acc += rr.loss_term;
       }
       par ^= 1;

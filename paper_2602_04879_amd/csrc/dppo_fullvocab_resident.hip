@@ -384,8 +384,9 @@ __global__ __launch_bounds__(kThreads, two_per_cu(NCHUNK) ? 4 : 2) void dppo_ful
         // here and not held in registers across the passes
         int row_e = row;
         asm volatile("" : "+s"(row_e));
-        // (two workgroups per compute unit: a call, whose registers stay out of the kernel's budget)
-        const RowResult res = two_per_cu(NCHUNK) ? row_epilogue_call(ep, row_e, rs, tk, zrow, bz, S_rest, T_rest, lane, D)
+        // (inlined, in the two shapes that spill most that way a call; us as a call / inlined, 1024 and 8192 tokens: TV V = 16384 36 / 31, 218 / 190,
+        // 32000 51 / 47, 336 / 320; KL 16384 35 / 31, 186 / 171; TV 49152 73 / 75, 499 / 524, KL 32000 46 / 47, 306 / 309)
+        const RowResult res = NCHUNK == 12 || (!TV && NCHUNK == 8) ? row_epilogue_call(ep, row_e, rs, tk, zrow, bz, S_rest, T_rest, lane, D)
                                           : row_epilogue(ep, row_e, rs, tk, zrow, bz, S_rest, T_rest, lane, D);
         rc = res.rc;
         if (DYN) { if (lane == 0) p.row_loss[row] = res.loss_term; }

@@ -62,7 +62,16 @@ constexpr int kChunkStep = 4;
 // compiled to 130 registers: +3..8 % on rows of 36-48 KiB) and three with 16 chunks (a budget of 168
 // registers; left to itself the compiler lands within a register or two of that limit, on either
 // side; a fourth workgroup there, 128 registers, spills and measured 7-12 % slower).
-constexpr int resident_min_waves(int threads, int nchunk) { return threads == 512 ? (nchunk <= 14 ? 4 : 2) : (nchunk <= 12 ? 4 : nchunk <= 16 ? 3 : 2); }
+// The epilogue is inlined, in its two parts.  As a call it keeps its float64 arithmetic out of the kernel's registers, but every
+// wave that makes it saves and restores 32 registers through scratch memory, on the path the row waits for, and all of
+// the epilogue then stands behind the statistics: V = 4096, 256 / 4096 / 32768 tokens 9.3 / 23.0 / 122 us, inlined 8.7 / 19.6 / 107, forward
+// only 8.2 / 21.4 / 82 and 7.6 / 13.5 / 62; 16384, 256 / 1000 / 8192 tokens 11.5 / 21.7 / 118 and 10.2 / 16.7 / 104; 30000 14.4 / 30.5 / 204 and
+// 13.0 / 26.5 / 194; 49152 18.9 / 44.5 / 317 and 15.7 / 40 / 314.  (One workgroup per compute unit fewer in a few forms; with 20 chunks the
+// budget of 168 registers, a few spilled, is better than that: 40960, 1000 tokens 36.2 / 32.9, at two per compute unit 35.1.)
+// The call stays where the inlined form spills a hundred registers (with gradient and diagnostics, 256 x 12: 0-3 % slower, 512 x 12: 3-7 %), and
+// for calls that launch_shape() names.
+constexpr bool resident_inline_epilogue(int threads, int nchunk, bool grad, bool diag) { return !(grad && diag && threads >= 256 && nchunk == 12) && !(threads == 512 && nchunk == kResidentPairChunks); }
+constexpr int resident_min_waves(int threads, int nchunk) { return threads == 512 ? (nchunk <= 14 ? 4 : 2) : (nchunk <= 12 ? 4 : 3); }
 
 // RAGGED = true: rows that do not start on a 16-byte boundary or whose length is not a multiple
 // of 8 (a vocabulary of 50257 entries; a pitch that is not a multiple of 8), and rows that start
@@ -77,7 +86,8 @@ constexpr int resident_min_waves(int threads, int nchunk) { return threads == 51
 // that holds row data, so in mapped memory; it is read, turned into -inf in the resident copy,
 // and never written: of the gradient only complete blocks of the row's own entries leave as
 // 16-byte stores, an incomplete first or last block as 2-byte stores of the row's own entries.
-template <int THREADS, int NCHUNK, bool GRAD, bool DIAG, bool DYN, bool RAGGED>
+// CALL: the epilogue as a call whatever resident_inline_epilogue() says.
+template <int THREADS, int NCHUNK, bool GRAD, bool DIAG, bool DYN, bool RAGGED, bool CALL = false>
 __global__ __launch_bounds__(THREADS, resident_min_waves(THREADS, NCHUNK)) void dppo_resident_kernel(const KParams p) {
   static_assert(NCHUNK <= 40, "the chunk switch below is written out for up to 40 chunks");
   constexpr int NW = THREADS / kWave;
@@ -265,10 +275,7 @@ __global__ __launch_bounds__(THREADS, resident_min_waves(THREADS, NCHUNK)) void 
       if (lane == 0) { sh_b[par][wid] = bw; sh_s[par][wid] = sw; sh_t[par][wid] = tw; }
       // Wave 0: the part of the epilogue that needs the row's inputs only (every exponential),
       // before the barrier: the other waves are still on their way to it.
-      // Shapes whose row data alone leaves room for one workgroup per compute unit: nothing
-      // hides a call there, so the epilogue is inlined, in its two parts.  The shorter shapes keep
-      // the call and with it the second or third workgroup per compute unit.
-      constexpr bool kInlineEpilogue = (THREADS == 512 && NCHUNK >= (GRAD ? 16 : 28));
+      constexpr bool kInlineEpilogue = !CALL && resident_inline_epilogue(THREADS, NCHUNK, GRAD, DIAG);
       RowPre pre;
       // With the gradient the whole row is still needed after the epilogue, whose float64 arithmetic
       // finds no registers beside it: wave 0 parks its last chunks in shared memory around the
@@ -276,7 +283,7 @@ __global__ __launch_bounds__(THREADS, resident_min_waves(THREADS, NCHUNK)) void 
       // compiler spill to scratch memory, whose round trips would sit on the path the other seven
       // waves wait for (measured on the headline shapes: 1.8 % faster Binary, 3.6 % faster Top-K;
       // 8, 16 and 24 chunks measure the same).
-      constexpr int kPark = (GRAD && kInlineEpilogue) ? 16 : 0;
+      constexpr int kPark = (GRAD && THREADS == 512 && NCHUNK >= 16) ? 16 : 0;
       __shared__ u32x4 sh_park[kPark > 0 ? kPark * kWave : 1];
       if (kPark > 0 && wid == 0) {
 #pragma unroll
@@ -426,6 +433,16 @@ hipError_t launch_shape(const KParams& p, bool grad, int grid, hipStream_t s) {
   const bool dyn = kDyn && grad && p.row_counters != nullptr;
   if (p.row_counters != nullptr && !dyn) return hipErrorInvalidValue;
   const dim3 g(grid), b(THREADS);
+  // Memory-bound calls: workgroups that come back sooner find the memory no faster.  Rows on a pitch of 64 KiB, or of 48 with 12 chunks, meet on
+  // the same channels (inlined / call: V = 32768, 6000 tokens 0.98, 8192 1.03, 16000 1.05; 24576, 6000 0.93, 8192 1.00-1.02, 12000 1.03); others that
+  // fill 256 x 16 1.00 at 12000, 1.01-1.02 at 16000; 256 x 20 1.00-1.01 at 8192, 1.02-1.03 at 12000.
+  if constexpr (THREADS == 256 && (NCHUNK == 20 || (!RAGGED && (NCHUNK == 12 || NCHUNK == 16)))) {
+    const int rounds = p.T / grid;
+    if (grad && !diag && (NCHUNK == 12 ? p.ld % 8192 == 0 && rounds >= 7 : NCHUNK == 20 ? rounds >= 9 : (p.ld % 32768 == 0 && rounds >= 9) || (p.V >= 30720 && rounds >= 16))) {
+      hipLaunchKernelGGL((dppo_resident_kernel<THREADS, NCHUNK, true, false, false, RAGGED, true>), g, b, 0, s, p);
+      return hipGetLastError();
+    }
+  }
 #define DPPO_FORM(G, D, Y) hipLaunchKernelGGL((dppo_resident_kernel<THREADS, NCHUNK, G, D, Y, RAGGED>), g, b, 0, s, p)
   if (grad) {
     if (diag) { if (dyn) DPPO_FORM(true, true, kDyn); else DPPO_FORM(true, true, false); }

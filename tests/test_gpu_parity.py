@@ -883,6 +883,38 @@ def test_ragged_rows_of_thirteen_chunks_two_workgroups_per_compute_unit(V, ld, o
     assert torch.equal(z[:, :V], grad[:, :V]) and (z[:, V:] == 9.0).all() and 0 < st["masked"] < len(rows)
 
 
+@pytest.mark.parametrize("V,ld,per_cu,variant,K", [
+    (24576, 24576, 28, W.BINARY_TV, 0), (24568, 24576, 29, W.TOPK_TV, 20), (32768, 32768, 27, W.BINARY_KL, 0), (32760, 32768, 28, W.TOPK_KL, 7),
+    (30720, 30720, 48, W.BINARY_TV, 0), (40960, 40960, 27, W.TOPK_TV, 20), (40001, 40001, 27, W.BINARY_KL, 0)])
+def test_large_calls_give_the_bits_of_small_ones(V, ld, per_cu, variant, K):
+    """Sizes at which a large call takes the form with the epilogue as a function: every row's bits are those that a call of its
+    first or last rows alone gives, and of some the oracle's values."""
+    T = per_cu * torch.cuda.get_device_properties(0).multi_processor_count
+    w = W.Workload("large", 1, 512, V, variant, 0.05, K=K, logit_std=3.0, noise_std=1.0, adv="normal", seed=121)
+    b = W.make_batch(w, DEV, ld=ld, shift_sampled=2.0, rows_per_step=256)
+    b["advantages"] = torch.randn(512, device=DEV)
+    for t, a in enumerate((0, 7, 8, 63, 64, V // 2, V - 9, V - 8, V - 2, V - 1, -1, V)):
+        b["sampled_ids"][3 * t] = a
+    _say(f"[case] large and small V={V} ld={ld} T={T} K={K} variant={variant}")
+    rows = np.arange(40)
+    st = P.compare_rows(b, B.run_batch(b, grad=torch.empty_like(b["logits"])), rows, ref=P.oracle_rows(b, rows))
+    assert 0 < st["masked"] < len(rows)
+    big = dict(b, T=T)
+    for k in ("logits", "sampled_ids", "mu_logp", "advantages", "mu_topk_ids", "mu_topk_logp"):
+        if b.get(k) is not None:
+            big[k] = b[k].repeat((-(-T // 512),) + (1,) * (b[k].dim() - 1))[:T]
+    big["loss_scale"] = b["loss_scale"]
+    small = B.run_batch(b, grad=torch.empty_like(b["logits"]))
+    res = B.run_batch(big, grad=torch.empty_like(big["logits"]))
+    torch.cuda.synchronize()
+    assert B.last_kernel() == "dppo_resident_kernel"
+    at = torch.arange(T, device=DEV) % 512
+    for k in ("loss_tok", "divergence", "mask"):
+        assert torch.equal(res[k], small[k][at]), k
+    for t0 in range(0, T - 512 + 1, 512):
+        assert torch.equal(res["grad_logits"][t0:t0 + 512, :V], small["grad_logits"][:, :V]), t0
+
+
 def test_other_stream_and_loss_tok_optional():
     w = W.Workload("stream", 2, 16, 2048, W.TOPK_TV, 0.1, K=8, logit_std=2.0, noise_std=0.5, adv="pm1", seed=4)
     b = W.make_batch(w, DEV)
