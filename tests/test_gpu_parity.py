@@ -915,6 +915,13 @@ def test_large_calls_give_the_bits_of_small_ones(V, ld, per_cu, variant, K):
         assert torch.equal(res["grad_logits"][t0:t0 + 512, :V], small["grad_logits"][:, :V]), t0
 
 
+def test_default_stream_is_the_current_one():
+    s = torch.cuda.Stream()
+    assert B._stream_handle(None) == torch.cuda.current_stream().cuda_stream and B._stream_handle(s) == s.cuda_stream
+    with torch.cuda.stream(s):
+        assert B._stream_handle(None) == s.cuda_stream
+
+
 def test_other_stream_and_loss_tok_optional():
     w = W.Workload("stream", 2, 16, 2048, W.TOPK_TV, 0.1, K=8, logit_std=2.0, noise_std=0.5, adv="pm1", seed=4)
     b = W.make_batch(w, DEV)
