@@ -10,8 +10,8 @@
 //                           rows than 128 are 39 MB at V = 151936, and workgroup ids, so dies, are those of the first kernel.
 //   dppo_split_rows_kernel  forward only: one wave per row
 // Bound by launches and latencies (three kernels, 2 us each when empty) up to some 30 rows, then by the memory traffic of the two passes.
-// V = 151936, Top-20 TV, whole calls, one workgroup per row / divided: 8 tokens 23.7 / 13.5 us, 64 24.6 / 17.5, 100 25.1 / 20.1, 128 25.7 / 21.9;
-// forward only 17.1 / 12.9, 18.3 / 14.4, 18.7 / 15.8, 19.3 / 16.8; V = 256000: 64 42.4 / 20.7, 128 46.1 / 35.
+// V = 151936, calls in a graph, us, one workgroup per row / divided: 8 tokens 23.1 / 10.7, 64 23.4 / 14.8, 100 24.2 / 17.6, 128 25.4 / 20.0;
+// forward only 14.7 / 8.6, 15.6 / 10.5, 15.0 / 12.2, 16.3 / 14.4; V = 256000: 64 41.7 / 17.7, 128 45.8 / 31.3.
 // Segments of 16 or 64 KiB, and 128 or 512 threads: the same to 30 % slower.  Code that few workgroups need (edges of a row, the
 // sampled token) stands behind branches of the whole workgroup: a kernel this short runs each instruction once and waits
 // for its fetch (100 tokens: 21.6 -> 20.1 us).
