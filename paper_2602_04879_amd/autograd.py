@@ -139,7 +139,8 @@ class _DppoLmheadLoss(torch.autograd.Function):
         # 1775 now; 64 tokens x 768: 416 / 283).  Several chunks are summed in fp32; so is one of more rows than a chunk has
         # unasked, which would be long to keep.  (Kept until backward: 2 T V bytes in place of 4 V d.)
         later = need_w and 0 < T <= min(chunk if chunk > 0 else T, B.LMHEAD_CHUNK_ROWS)
-        gw = torch.empty((V, d), dtype=torch.float32, device=hidden.device) if need_w and not later else None
+        # (no tokens: the library runs no product and leaves the buffer as it is)
+        gw = (torch.empty if T > 0 else torch.zeros)((V, d), dtype=torch.float32, device=hidden.device) if need_w and not later else None
         rule = {k: opts[k] for k in ("mask_rule", "eps_low", "eps_high", "ratio_cap", "relax_alpha", "relax_sides") if k in opts}
         res = B.run_lmhead(batch, backward=backward, chunk_rows=chunk, diagnostics=opts.get("diagnostics", False),
                            grad_weight=gw, flags=opts.get("flags", 0), **rule)

@@ -158,6 +158,26 @@ def test_weight_gradient_formed_in_backward_is_that_of_the_direct_call(chunk_row
     assert torch.equal(g, (gw * f).to(torch.bfloat16)) and torch.equal(gh, (ref["grad_hidden"].float() * f).to(torch.bfloat16))
 
 
+@pytest.mark.parametrize("entries", [0, 1 << 40])
+@pytest.mark.parametrize("chunk_rows", [0, 64])
+def test_no_tokens_give_zero_gradients(monkeypatch, chunk_rows, entries):
+    """T = 0: no product runs, and the weight's gradient is zero whatever its memory held before (blocks of its size, in
+    both types, are freed full of NaN first)."""
+    monkeypatch.setattr(A, "SCALE_ON_DEVICE_FROM", entries)
+    b = W.make_lmhead_batch(W.Workload("autograd_empty", 1, 4, 4160, W.BINARY_TV, 0.2, logit_std=3.0, noise_std=1.0, adv="normal", seed=115), 192, DEV)
+    wt = b["weight"].clone().requires_grad_(True)
+    for factor in (1.0, 0.3):
+        h = b["hidden"][:0].clone().requires_grad_(True)
+        blocks = [torch.full((b["V"], b["d"]), float("nan"), dtype=dt, device=DEV) for dt in (torch.float32, torch.bfloat16) for _ in range(3)]
+        del blocks
+        loss, _ = A.dppo_lmhead_loss(h, wt, b["sampled_ids"][:0], b["mu_logp"][:0], b["advantages"][:0], delta=b["delta"], variant=b["variant"],
+                                     loss_scale=b["loss_scale"], chunk_rows=chunk_rows)
+        gh, gw = torch.autograd.grad(loss * factor, (h, wt))
+        torch.cuda.synchronize()
+        assert loss.item() == 0.0 and gh.shape == h.shape and gw.shape == wt.shape and gw.dtype == wt.dtype
+        assert (gw == 0).all()
+
+
 def test_gradient_with_a_graph_through_the_incoming_gradient():
     """create_graph keeps the path from the gradient to the weight of the loss."""
     w = W.Workload("autograd_graph", 2, 16, 4096, W.BINARY_TV, 0.5, logit_std=3.0, noise_std=0.3, adv="normal", seed=99)
