@@ -315,6 +315,13 @@ dppo_status_t dppo_lmhead_loss_fwd(const dppo_lmhead_args_t* args, void* stream)
 /* Forward and backward: also grad_hidden = d loss / d hidden and, if asked for, grad_weight. */
 dppo_status_t dppo_lmhead_loss_fwd_bwd(const dppo_lmhead_args_t* args, void* stream);
 
+/* The same with the room for the divided contraction apart from the workspace: a caller that keeps the
+ * logits' gradient (see workspace) then keeps nothing else.  scratch: 256-byte aligned, used as far as
+ * scratch_bytes reach, in place of what lies behind the first dppo_lmhead_workspace_bytes(), and best with
+ * as many bytes as dppo_lmhead_workspace_bytes_best() names beyond them; free once the call's work has
+ * finished.  NULL: as dppo_lmhead_loss_fwd_bwd. */
+dppo_status_t dppo_lmhead_loss_fwd_bwd_apart(const dppo_lmhead_args_t* args, void* scratch, size_t scratch_bytes, void* stream);
+
 /* sizeof(dppo_lmhead_args_t) as the library was compiled. */
 size_t dppo_lmhead_args_size(void);
 

@@ -142,8 +142,10 @@ class _DppoLmheadLoss(torch.autograd.Function):
         # (no tokens: the library runs no product and leaves the buffer as it is)
         gw = (torch.empty if T > 0 else torch.zeros)((V, d), dtype=torch.float32, device=hidden.device) if need_w and not later else None
         rule = {k: opts[k] for k in ("mask_rule", "eps_low", "eps_high", "ratio_cap", "relax_alpha", "relax_sides") if k in opts}
+        # what is kept lies in a workspace of its own, without the room for the divided contraction (up to 1 GiB) behind it
+        workspace, scratch = B.alloc_lmhead_apart(T, V, d, chunk, hidden.device) if later else (None, None)
         res = B.run_lmhead(batch, backward=backward, chunk_rows=chunk, diagnostics=opts.get("diagnostics", False),
-                           grad_weight=gw, flags=opts.get("flags", 0), **rule)
+                           grad_weight=gw, flags=opts.get("flags", 0), workspace=workspace, scratch=scratch, **rule)
         # (a copy of the hidden states, a few megabytes: the caller may write to its own before backward)
         ctx.factors = (B.lmhead_logit_gradients(res["workspace_buf"], T, V), hidden.detach().clone(memory_format=torch.contiguous_format)) if later else None
         ctx.grads = (res["grad_hidden"] if need_h else None, gw)

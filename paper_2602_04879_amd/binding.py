@@ -117,6 +117,8 @@ def lib() -> C.CDLL:
         for f in (l.dppo_lmhead_loss_fwd, l.dppo_lmhead_loss_fwd_bwd):
             f.restype = C.c_int
             f.argtypes = [C.POINTER(DppoLmheadArgs), C.c_void_p]
+        l.dppo_lmhead_loss_fwd_bwd_apart.restype = C.c_int
+        l.dppo_lmhead_loss_fwd_bwd_apart.argtypes = [C.POINTER(DppoLmheadArgs), C.c_void_p, C.c_size_t, C.c_void_p]
         l.dppo_lmhead_workspace_bytes_best.restype = C.c_size_t
         l.dppo_lmhead_workspace_bytes_best.argtypes = [C.c_int64, C.c_int64, C.c_int64, C.c_int64]
         l.dppo_lmhead_fwd_workspace_bytes.restype = C.c_size_t
@@ -413,11 +415,24 @@ def lmhead_fwd_workspace_bytes(T: int, V: int, K: int, chunk_rows: int = 0) -> i
     return lib().dppo_lmhead_fwd_workspace_bytes(T, V, K, chunk_rows)
 
 
+def alloc_lmhead_apart(T: int, V: int, d: int, chunk_rows: int, device):
+    """The workspace of a forward + backward call that keeps the logits' gradient, and the room for the divided contraction
+    apart from it (None where the call wants none, or there is no memory: slower without it, but it runs)."""
+    need, best = lmhead_workspace_bytes(T, V, chunk_rows), lmhead_workspace_bytes_best(T, V, d, chunk_rows)
+    workspace, scratch = torch.empty(need, dtype=torch.uint8, device=device), None
+    if best > need:
+        try:
+            scratch = torch.empty(best - (need + 255) // 256 * 256, dtype=torch.uint8, device=device)
+        except torch.OutOfMemoryError:
+            pass
+    return workspace, scratch
+
+
 def run_lmhead(batch: dict, backward: bool = True, chunk_rows: int = 0, out=None, grad_hidden=None,
                workspace=None, stream=None, diagnostics: bool = False, grad_weight=None, accumulate: bool = False,
-               flags: int = 0, **rule) -> dict:
-    """Run one hidden-state batch (workloads.make_lmhead_batch) through dppo_lmhead_loss_fwd[_bwd].
-    Returns the output tensors (device), grad_hidden among them."""
+               flags: int = 0, scratch=None, **rule) -> dict:
+    """Run one hidden-state batch (workloads.make_lmhead_batch) through dppo_lmhead_loss_fwd[_bwd], forward + backward with
+    the room for the divided contraction in `scratch` if given.  Returns the output tensors (device), grad_hidden among them."""
     h, w = batch["hidden"], batch["weight"]
     T, d, V = h.shape[0], batch["d"], batch["V"]
     dev = h.device
@@ -448,8 +463,11 @@ def run_lmhead(batch: dict, backward: bool = True, chunk_rows: int = 0, out=None
     a.grad_weight, a.ld_grad_weight = _ptr(grad_weight), (0 if grad_weight is None else grad_weight.stride(0))
     a.grad_weight_accumulate = int(accumulate)
     a.workspace, a.workspace_bytes = workspace.data_ptr(), workspace.numel()
-    fn = lib().dppo_lmhead_loss_fwd_bwd if backward else lib().dppo_lmhead_loss_fwd
-    st = fn(C.byref(a), C.c_void_p(_stream_handle(stream)))
+    if backward and scratch is not None:
+        st = lib().dppo_lmhead_loss_fwd_bwd_apart(C.byref(a), scratch.data_ptr(), scratch.numel(), C.c_void_p(_stream_handle(stream)))
+    else:
+        fn = lib().dppo_lmhead_loss_fwd_bwd if backward else lib().dppo_lmhead_loss_fwd
+        st = fn(C.byref(a), C.c_void_p(_stream_handle(stream)))
     if st != 0:
         raise DppoError(st)
     res = dict(out)

@@ -480,7 +480,8 @@ size_t lmhead_split_bytes(int64_t T, int64_t V, int64_t d, int64_t chunk, int cu
   return most;
 }
 
-dppo_status_t run_lmhead(const dppo_lmhead_args_t* a, void* stream, bool grad) {
+// scratch (optional): the room for the divided contraction apart from the workspace, in place of what lies behind it
+dppo_status_t run_lmhead(const dppo_lmhead_args_t* a, void* stream, bool grad, void* scratch = nullptr, size_t scratch_bytes = 0) {
   if (!a) return DPPO_ERR_NULL;
   const int64_t T = a->loss.T, V = a->loss.V, d = a->d;
   if (T < 0 || V < 64 || V % 64 != 0 || d < 64 || d % 64 != 0 || a->ld_hidden < d || a->ld_weight < d ||
@@ -500,7 +501,7 @@ dppo_status_t run_lmhead(const dppo_lmhead_args_t* a, void* stream, bool grad) {
   const int32_t Ktop = topk_variant ? a->loss.K : 0;
   if (!a->workspace || a->workspace_bytes < (fused_fwd ? lmhead_fwd_workspace(T, V, Ktop, a->chunk_rows) : lmhead_workspace(T, V, a->chunk_rows)))
     return DPPO_ERR_WORKSPACE;
-  if (reinterpret_cast<uintptr_t>(a->workspace) & 255u) return DPPO_ERR_ALIGN;
+  if ((reinterpret_cast<uintptr_t>(a->workspace) | reinterpret_cast<uintptr_t>(scratch)) & 255u) return DPPO_ERR_ALIGN;
   if (T > 0) {
     if (!a->hidden || !a->weight || (grad && !a->grad_hidden)) return DPPO_ERR_NULL;
     if ((reinterpret_cast<uintptr_t>(a->hidden) | reinterpret_cast<uintptr_t>(a->weight)) & 15u)
@@ -566,9 +567,10 @@ dppo_status_t run_lmhead(const dppo_lmhead_args_t* a, void* stream, bool grad) {
   const int parts_per_chunk = nchunks > 0 ? static_cast<int>(max_parts / nchunks) : max_parts;
   if (nchunks > 0 && parts_per_chunk < 1) return DPPO_ERR_SHAPE;
   int used = 0;
-  // what the caller's workspace holds beyond the part every call needs
+  // what the caller's workspace holds beyond the part every call needs, or the room given apart from it
   const size_t base_bytes = align256(lmhead_workspace(T, V, a->chunk_rows));
-  const size_t extra_bytes = a->workspace_bytes > base_bytes ? a->workspace_bytes - base_bytes : 0;
+  const size_t extra_bytes = scratch ? scratch_bytes : a->workspace_bytes > base_bytes ? a->workspace_bytes - base_bytes : 0;
+  float* extra = reinterpret_cast<float*>(scratch ? static_cast<char*>(scratch) : ws + base_bytes);
   int dev = 0;
   if (T > 0 && grad && !stream_device(s, &dev)) return DPPO_ERR_LAUNCH;
   for (int64_t r0 = 0; r0 < T; r0 += chunk) {
@@ -603,7 +605,7 @@ dppo_status_t run_lmhead(const dppo_lmhead_args_t* a, void* stream, bool grad) {
       uint16_t* gh = static_cast<uint16_t*>(a->grad_hidden) + r0 * a->ld_grad_hidden;
       const int splits = dppo::gemm_nn_splits(rows, d, V, device_info(dev).cus, extra_bytes);
       if (dppo::launch_gemm_nn(zbuf, V, static_cast<const uint16_t*>(a->weight), a->ld_weight, gh, a->ld_grad_hidden, static_cast<int>(rows),
-                               static_cast<int>(d), static_cast<int>(V), splits, reinterpret_cast<float*>(ws + base_bytes), s) != hipSuccess)
+                               static_cast<int>(d), static_cast<int>(V), splits, extra, s) != hipSuccess)
         return DPPO_ERR_LAUNCH;
     }
     if (want_gw) {
@@ -680,6 +682,10 @@ size_t dppo_lmhead_workspace_bytes_best(int64_t T, int64_t V, int64_t d, int64_t
 dppo_status_t dppo_lmhead_loss_fwd(const dppo_lmhead_args_t* args, void* stream) { return run_lmhead(args, stream, false); }
 
 dppo_status_t dppo_lmhead_loss_fwd_bwd(const dppo_lmhead_args_t* args, void* stream) { return run_lmhead(args, stream, true); }
+
+dppo_status_t dppo_lmhead_loss_fwd_bwd_apart(const dppo_lmhead_args_t* args, void* scratch, size_t scratch_bytes, void* stream) {
+  return run_lmhead(args, stream, true, scratch, scratch_bytes);
+}
 
 size_t dppo_lmhead_args_size(void) { return sizeof(dppo_lmhead_args_t); }
 

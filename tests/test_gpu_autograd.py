@@ -290,3 +290,27 @@ def test_weighted_gradient_stays_in_its_buffer(monkeypatch, V, ld, entries):
     g, = torch.autograd.grad(loss, logits, f)
     torch.cuda.synchronize()
     assert torch.cuda.max_memory_allocated() - before < 74 * V and torch.equal(g, want)
+
+
+@pytest.mark.parametrize("T,V,d", [(256, 16384, 768), (1536, 16384, 768), (300, 8192, 1024)])
+def test_memory_held_until_backward(T, V, d):
+    """Between forward and backward the hidden-state loss holds the logits' gradient, and none of the scratch that forward alone needed."""
+    b = W.make_lmhead_batch(W.Workload("autograd_held", 1, T, V, W.BINARY_TV, 0.2, logit_std=3.0, noise_std=1.0, adv="normal", seed=119), d, DEV)
+    h, wt = b["hidden"].requires_grad_(True), b["weight"].requires_grad_(True)
+
+    def forward():
+        return A.dppo_lmhead_loss(h, wt, b["sampled_ids"], b["mu_logp"], b["advantages"], delta=b["delta"], variant=b["variant"],
+                                  loss_scale=b["loss_scale"])[0]
+    torch.autograd.grad(forward(), (h, wt))
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    before = torch.cuda.memory_allocated()
+    loss = forward()
+    torch.cuda.synchronize()
+    held = torch.cuda.memory_allocated() - before
+    # beside it: the hidden states' gradient and copy, the per-token outputs, and what the allocator adds to a
+    # block (up to 1 MiB to each of three large ones)
+    slack = 4 * T * d + 64 * T + (3 << 20)
+    assert B.lmhead_workspace_bytes_best(T, V, d) > B.lmhead_workspace_bytes(T, V) + slack
+    assert held <= B.lmhead_workspace_bytes(T, V) + slack
+    torch.autograd.grad(loss, (h, wt))

@@ -490,6 +490,35 @@ def test_no_room_for_the_divided_contraction(monkeypatch):
     assert torch.equal(res["grad_hidden"], want["grad_hidden"]) and torch.equal(res["loss"], want["loss"])
 
 
+def test_room_for_the_divided_contraction_apart_from_the_workspace(monkeypatch):
+    """The room given on its own: the bits of the same room behind the workspace, nothing written past it, and a pointer that is not
+    aligned refused; where there is no memory for it the binding goes without."""
+    T, V, d = 257, 20032, 320
+    w = W.Workload("lm_apart", 1, T, V, W.BINARY_TV, 0.5, logit_std=3.0, noise_std=0.3, adv="normal", seed=135)
+    b = W.make_lmhead_batch(w, d, DEV, rows_per_step=256)
+    _say(f"[case] divided contraction, room apart T={T} V={V} d={d}")
+    want = B.run_lmhead(b)
+    ws, scratch = B.alloc_lmhead_apart(T, V, d, 0, DEV)
+    assert ws.numel() == B.lmhead_workspace_bytes(T, V) and scratch.numel() >= 2 * 4 * T * d
+    guard = torch.full((scratch.numel() + 4096,), 0xAB, dtype=torch.uint8, device=DEV)
+    res = B.run_lmhead(b, workspace=ws, scratch=guard[:scratch.numel()])
+    torch.cuda.synchronize()
+    assert (guard[:scratch.numel()] != 0xAB).any() and (guard[scratch.numel():] == 0xAB).all()
+    for k in ("loss", "loss_tok", "mask", "grad_hidden"):
+        assert torch.equal(res[k], want[k]), k
+    with pytest.raises(B.DppoError):
+        B.run_lmhead(b, workspace=ws, scratch=guard[16:])
+    empty = torch.empty
+
+    def no_room(*size, **kw):
+        if size == (scratch.numel(),):
+            raise torch.OutOfMemoryError("no room")
+        return empty(*size, **kw)
+
+    monkeypatch.setattr(torch, "empty", no_room)
+    assert B.alloc_lmhead_apart(T, V, d, 0, DEV)[1] is None
+
+
 def test_error_codes():
     w = W.Workload("lm_err", 1, 16, 256, W.BINARY_TV, 0.2, logit_std=3.0, adv="pm1", seed=89)
     b = W.make_lmhead_batch(w, 64, DEV, exact=True)
