@@ -137,8 +137,12 @@ class _DppoLmheadLoss(torch.autograd.Function):
         # One chunk: the logits' gradient stays as it is in the workspace, and the weight's gradient is formed from it in
         # backward, where its factor is known, straight in the weight's type (V = 151936, d = 2048, 1000 tokens: 2158 us a step,
         # 1775 now; 64 tokens x 768: 416 / 283).  Several chunks are summed in fp32; so is one of more rows than a chunk has
-        # unasked, which would be long to keep.  (Kept until backward: 2 T V bytes in place of 4 V d.)
-        later = need_w and 0 < T <= min(chunk if chunk > 0 else T, B.LMHEAD_CHUNK_ROWS)
+        # unasked.  And so are tokens whose logits' gradient would be more to hold than the weight's in fp32 (the two are as large at
+        # T = 2 d; an eighth more is let pass, the copy of the hidden states among it): a step that sums the losses of
+        # several micro-batches before one backward holds all of them.  That costs 3-4 % of a step at 8192 tokens x 768 .. 3584,
+        # 5-9 % at 4096 and 2048 x 768, and up to 17 % where the vocabulary is small (3000 x 1024, V = 32768: 597 / 700 us).
+        held = B.lmhead_workspace_bytes(T, V, chunk) + 2 * T * d
+        later = need_w and 0 < T <= min(chunk if chunk > 0 else T, B.LMHEAD_CHUNK_ROWS) and held <= 4 * V * d * 9 // 8
         # (no tokens: the library runs no product and leaves the buffer as it is)
         gw = (torch.empty if T > 0 else torch.zeros)((V, d), dtype=torch.float32, device=hidden.device) if need_w and not later else None
         rule = {k: opts[k] for k in ("mask_rule", "eps_low", "eps_high", "ratio_cap", "relax_alpha", "relax_sides") if k in opts}
@@ -146,7 +150,7 @@ class _DppoLmheadLoss(torch.autograd.Function):
         workspace, scratch = B.alloc_lmhead_apart(T, V, d, chunk, hidden.device) if later else (None, None)
         res = B.run_lmhead(batch, backward=backward, chunk_rows=chunk, diagnostics=opts.get("diagnostics", False),
                            grad_weight=gw, flags=opts.get("flags", 0), workspace=workspace, scratch=scratch, **rule)
-        # (a copy of the hidden states, a few megabytes: the caller may write to its own before backward)
+        # (a copy of the hidden states: the caller may write to its own before backward)
         ctx.factors = (B.lmhead_logit_gradients(res["workspace_buf"], T, V), hidden.detach().clone(memory_format=torch.contiguous_format)) if later else None
         ctx.grads = (res["grad_hidden"] if need_h else None, gw)
         side = [res[k] for k in ("divergence", "mask", "loss_tok")] + ([res["diagnostics"]] if res["diagnostics"] is not None else [])
