@@ -320,15 +320,24 @@ def _check_factor(factor, x):
         raise ValueError("factor: one fp32 value in memory on the device of the tensor that it scales")
 
 
+def _check_bf16_matrix(name, x, rows, cols, device):
+    if (x.dtype != torch.bfloat16 or not x.is_cuda or x.device != device or tuple(x.shape) != (rows, cols)
+            or (cols > 1 and x.stride(1) != 1) or (rows > 1 and x.stride(0) < cols)):
+        raise ValueError(f"{name}: a bf16 [{rows}, {cols}] matrix with contiguous rows on one GPU with the others")
+
+
 def gemm_tn_bf16(a, b, factor, c=None, stream=None):
     """dppo_gemm_tn_bf16: c[M, N] = factor * a[K, M]^T @ b[K, N] for bf16 tensors with unit inner stride, factor one
     fp32 value on the device."""
-    K, M = a.shape
-    N = b.shape[1]
-    assert b.shape[0] == K and a.stride(1) == 1 and b.stride(1) == 1
+    if a.dim() != 2 or b.dim() != 2:
+        raise ValueError("a [K, M] and b [K, N]: matrices")
+    (K, M), N = a.shape, b.shape[1]
+    _check_bf16_matrix("a", a, K, M, a.device)
+    _check_bf16_matrix("b", b, K, N, a.device)
     _check_factor(factor, a)
     if c is None:
         c = torch.empty((M, N), dtype=torch.bfloat16, device=a.device)
+    _check_bf16_matrix("c", c, M, N, a.device)
     st = lib().dppo_gemm_tn_bf16(a.data_ptr(), a.stride(0), b.data_ptr(), b.stride(0), c.data_ptr(), c.stride(0),
                                  M, N, K, factor.data_ptr(), C.c_void_p(_stream_handle(stream)))
     if st != 0:

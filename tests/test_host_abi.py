@@ -190,3 +190,31 @@ def test_scaling_refuses_what_a_kernel_cannot_read():
     for bad in (good.double(), good.half(), torch.ones(2), torch.empty((), device="meta"), negated, torch._efficientzerotensor(())):
         with pytest.raises(ValueError):
             B._check_factor(bad, good)
+
+
+def test_weight_gradient_product_refuses_operands_of_other_shapes_and_types(monkeypatch):
+    """dppo_gemm_tn_bf16 is handed addresses: operands and results that do not fit the product are refused before the library is
+    called, also where assertions are off.  (Host tensors that pass for device memory; the library's call is replaced.)"""
+    from types import SimpleNamespace
+    calls = []
+    monkeypatch.setattr(B, "lib", lambda: SimpleNamespace(dppo_gemm_tn_bf16=lambda *a: calls.append(a) or 0))
+    monkeypatch.setattr(B, "_stream_handle", lambda stream: 0)
+    monkeypatch.setattr(torch.Tensor, "is_cuda", property(lambda t: True))
+    bf = dict(dtype=torch.bfloat16)
+    a, b, f = torch.zeros((5, 24), **bf)[:, :16], torch.zeros((5, 8), **bf), torch.ones(())
+    assert B.gemm_tn_bf16(a, b, f).shape == (16, 8)
+    B.gemm_tn_bf16(a, b, f, torch.zeros((16, 12), **bf)[:, 1:9])                     # any pitch, any start
+    assert len(calls) == 2
+    negated = torch.zeros((5, 8), dtype=torch.complex64).conj().imag
+    bad = [dict(a=a.float()), dict(a=a[:4]), dict(a=torch.zeros((16, 5), **bf).t()), dict(a=a[0]), dict(b=b.half()), dict(b=b[:, ::2]), dict(b=b.to("meta")),
+           dict(b=negated),
+           dict(c=torch.zeros((16, 8))), dict(c=torch.zeros((15, 8), **bf)), dict(c=torch.zeros((16, 7), **bf)), dict(c=torch.zeros((8, 16), **bf)),
+           dict(c=torch.zeros((8, 16), **bf).t()), dict(c=torch.zeros((1, 8), **bf).expand(16, 8)), dict(c=torch.zeros((128,), **bf)),
+           dict(c=torch.empty((16, 8), device="meta", **bf))]
+    for kw in bad:
+        with pytest.raises(ValueError):
+            B.gemm_tn_bf16(**{"a": a, "b": b, "factor": f, **kw})
+    monkeypatch.undo()
+    with pytest.raises(ValueError):
+        B.gemm_tn_bf16(a, b, f)                                                       # not on a GPU
+    assert len(calls) == 2
