@@ -218,3 +218,19 @@ def test_weight_gradient_product_refuses_operands_of_other_shapes_and_types(monk
     with pytest.raises(ValueError):
         B.gemm_tn_bf16(a, b, f)                                                       # not on a GPU
     assert len(calls) == 2
+
+
+def test_stream_handle_without_the_raw_accessor(monkeypatch):
+    """The handle of the current stream comes from a private function of torch where it has one, else from the stream object."""
+    import importlib.util
+    from types import SimpleNamespace
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 0)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: SimpleNamespace(cuda_stream=4711))
+    spec = importlib.util.spec_from_file_location("paper_2602_04879_amd.binding_without_raw_stream", B.__file__)
+    m = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(m)                       # a second copy, so that the binding in use stays as it is
+    assert m._stream_handle(None) == 4711 and m._stream_handle(SimpleNamespace(cuda_stream=5)) == 5
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 100 + device, raising=False)
+    spec.loader.exec_module(m)
+    assert m._stream_handle(None) == 100
