@@ -195,30 +195,35 @@ def test_gradient_with_a_graph_through_the_incoming_gradient():
     assert abs(du.item() - want) <= 1e-2 * want
 
 
+@pytest.mark.parametrize("chunk_rows", [0, 32])
 @pytest.mark.parametrize("factor", [1.0, 0.3])
-def test_scaling_on_the_device_and_on_the_host_give_the_same_gradients(monkeypatch, factor):
+def test_scaling_on_the_device_and_on_the_host_give_the_same_gradients(monkeypatch, factor, chunk_rows):
     """Large gradients are scaled by a kernel that reads the factor, small ones by tensor operations
-    behind a look at it: the same bits (here on one small call each way)."""
+    behind a look at it: the same bits (here on one small call each way).  Of the hidden states, the weight's gradient is left to
+    scale where several chunks were summed in fp32; one chunk's is formed with the factor, whatever its size."""
     w = W.Workload("autograd_scale", 2, 40, 8192, W.BINARY_TV, 0.2, logit_std=3.0, noise_std=1.0, adv="normal", seed=103)
     b = W.make_batch(w, DEV, shift_sampled=2.0)
     lb = W.make_lmhead_batch(W.Workload("autograd_scale_lm", 2, 40, 4160, W.BINARY_TV, 0.2, logit_std=3.0, noise_std=1.0, adv="normal", seed=105), 64, DEV)
-    got = []
+    got, conversions, convert = [], [], B.scale_to_bf16
+    monkeypatch.setattr(B, "scale_to_bf16", lambda *a: conversions.append(1) or convert(*a))
     for entries in (0, 1 << 40):
         monkeypatch.setattr(A, "SCALE_ON_DEVICE_FROM", entries)
         logits = b["logits"].clone().requires_grad_(True)
         loss, _ = _call(b, logits)
         h, wt = lb["hidden"].clone().requires_grad_(True), lb["weight"].clone().requires_grad_(True)
         lloss, _ = A.dppo_lmhead_loss(h, wt, lb["sampled_ids"], lb["mu_logp"], lb["advantages"], delta=lb["delta"], variant=lb["variant"],
-                                      loss_scale=lb["loss_scale"])
+                                      loss_scale=lb["loss_scale"], chunk_rows=chunk_rows)
         (factor * loss + factor * lloss).backward()
         torch.cuda.synchronize()
         got.append((logits.grad, h.grad, wt.grad))
+        assert len(conversions) == (1 if chunk_rows else 0)         # by the kernel the first time, never the second
     for x, y in zip(*got):
         assert torch.equal(x, y)
 
 
-def _both_losses():
-    """(inputs, losses of fresh graphs) of one small call of each wrapper, and the plain gradients."""
+def _both_losses(chunk_rows):
+    """(inputs, losses of fresh graphs) of one small call of each wrapper, and the plain gradients.  The hidden states in one chunk (0:
+    the weight's gradient is formed in backward) or several (summed in fp32)."""
     w = W.Workload("autograd_in", 2, 40, 8192, W.BINARY_TV, 0.2, logit_std=3.0, noise_std=1.0, adv="normal", seed=107)
     b = W.make_batch(w, DEV, shift_sampled=2.0)
     lb = W.make_lmhead_batch(W.Workload("autograd_in_lm", 2, 40, 4160, W.BINARY_TV, 0.2, logit_std=3.0, noise_std=1.0, adv="normal", seed=109), 64, DEV)
@@ -227,18 +232,19 @@ def _both_losses():
     def losses():
         yield leaves[0], _call(b, leaves[0][0])[0]
         yield leaves[1], A.dppo_lmhead_loss(*leaves[1], lb["sampled_ids"], lb["mu_logp"], lb["advantages"], delta=lb["delta"], variant=lb["variant"],
-                                            loss_scale=lb["loss_scale"])[0]
+                                            loss_scale=lb["loss_scale"], chunk_rows=chunk_rows)[0]
     return losses, [torch.autograd.grad(loss, x) for x, loss in losses()]
 
 
+@pytest.mark.parametrize("chunk_rows", [0, 32])
 @pytest.mark.parametrize("entries", [0, 1 << 40])
 @pytest.mark.parametrize("how", ["argument", "hook"])
 @pytest.mark.parametrize("kind", ["negated", "zero", "plain"])
-def test_incoming_gradient_whose_memory_does_not_hold_its_value(monkeypatch, entries, how, kind):
+def test_incoming_gradient_whose_memory_does_not_hold_its_value(monkeypatch, entries, how, kind, chunk_rows):
     """A lazily negated incoming gradient (memory of the opposite sign) and a lazy zero (no memory at all):
     the gradient is that of the value, whichever way it is scaled."""
     monkeypatch.setattr(A, "SCALE_ON_DEVICE_FROM", entries)
-    losses, plain = _both_losses()
+    losses, plain = _both_losses(chunk_rows)
     c = {"negated": torch.tensor(0.5 + 0.75j, device=DEV).conj().imag, "zero": torch._efficientzerotensor((), device=DEV),
          "plain": torch.tensor(-0.75, device=DEV)}[kind]
     assert c.is_neg() == (kind == "negated") and (c.data_ptr() == 0) == (kind == "zero")
@@ -257,11 +263,12 @@ def test_incoming_gradient_whose_memory_does_not_hold_its_value(monkeypatch, ent
                 assert ((g.float() - value * g1.float()).abs() <= 2.0 ** -7 * g1.float().abs()).all()
 
 
+@pytest.mark.parametrize("chunk_rows", [0, 32])
 @pytest.mark.parametrize("entries", [0, 1 << 40])
-def test_tangent_of_the_incoming_gradient(monkeypatch, entries):
+def test_tangent_of_the_incoming_gradient(monkeypatch, entries, chunk_rows):
     """Forward mode over the backward: the gradient is linear in the incoming gradient, tangent and all."""
     monkeypatch.setattr(A, "SCALE_ON_DEVICE_FROM", entries)
-    losses, plain = _both_losses()
+    losses, plain = _both_losses(chunk_rows)
     for (x, loss), want in zip(losses(), plain):
         with fwAD.dual_level():
             u = fwAD.make_dual(torch.tensor(0.5, device=DEV), torch.tensor(2.0, device=DEV))
