@@ -212,7 +212,8 @@ dppo_status_t dppo_loss_fwd_bwd(const dppo_args_t* args, void* stream);
  * to the CURRENT device, else DPPO_ERR_LAUNCH; DPPO_ERR_WORKSPACE if the runtime yields no
  * address for the array.  All calls on one GPU share that GPU's array: calls that overlap in
  * time on one GPU (different streams, or a replaying graph beside eager calls) race on it and
- * return wrong losses; serialise them or use dppo_loss_fwd_bwd with distinct workspaces.  The
+ * return wrong losses, and where few long rows are divided among workgroups, whose statistics then stand there too, wrong
+ * gradients, masks and divergences; serialise them or use dppo_loss_fwd_bwd with distinct workspaces.  The
  * array's address is looked up on the first call on a device, or by dppo_static_init() -- call
  * that once per device, with the device current and outside any stream capture, if the first
  * call would otherwise fall inside a capture. */

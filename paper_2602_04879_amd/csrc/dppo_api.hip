@@ -201,26 +201,27 @@ dppo_status_t arm_rows_at_run_time(dppo::KParams& p, const dppo_args_t* a, const
 
 // Rows of middle length in groups of rows per workgroup: the number of groups per compute unit from
 // which that form is taken.  A group is 23 us of a compute unit's time: with few of them a call ends
-// sooner on the one-row shapes, whose unit of work is a row.  Measured, per shape: groups of 4
-// rows (V up to 32768) gain 1 % at 16 groups per compute unit, 5 % at 32, 7.5 % at 64, and lose
-// below; groups of 6 (up to 24576) are even at 16, gain 4 % at 24, 6 % at 32; groups of 2 (up to
-// 65536) gain 1.5-7 % from 32 on; groups of 3 (up to 40960 / 49152) are even at 8-12 groups per
-// compute unit and gain 0-3 % at 16, 3.5-9 % at 32.
+// sooner on the one-row shapes, whose unit of work is a row.  Time of the groups over that of one row per
+// workgroup, at 16 / 24 / 32 groups per compute unit: groups of 6 rows (V up to 24576) 20480 1.07 / 1.02 / 0.99, 24576
+// 1.00 / 0.97; of 4 (up to 32768) 30000 1.03 / 0.99 / 0.97, 32768 0.96 / 0.94 / 0.92, off lines 32008 1.00 / 0.98 / 0.96; of 3 (up to
+// 49152) 40960 0.96 / 0.92 / 0.91, 49152 0.96 / 0.93, ragged 39001 1.03 / 1.00 / 0.98, 49001 1.02 / 1.00; of 2 (up to 65536)
+// 57344 0.98 / 0.98 / 0.97, 65536 1.02 / 1.02 / 1.02.  (The lines were drawn before the one-row shapes' epilogue was inlined and
+// have not moved with it.)
 int64_t multi_min_groups(int rows) { return rows == 3 ? 16 : rows == 2 ? 32 : 24; }
 
 // Forward only, a row of a register-resident shape: whether the row is kept in registers, all of its loads in
-// flight at once, or streamed through a window, two workgroups per compute unit.  Streamed is better
-// from 49160 entries on (us, registers / streamed, 8192 tokens: V = 81920 262 / 234, 151936 446 / 407), except
+// flight at once, or streamed through a window, two workgroups per compute unit.  Streamed from 49160 entries on, except
 //  * rows of 28 and 32 chunks while a workgroup has a few rows at most, so that the window limits what is in flight: from
-//    half a row per compute unit to 12 (28 chunks) or 8 (with diagnostics, more arithmetic per entry: 2).  Streamed is 1.10-1.13 x the
-//    time at 256 tokens, 1.06-1.12 at 512, 1.04-1.08 at 1024, 1.00-1.05 at 2048, 1.00-1.04 (28) and 0.99-1.01 at 3072,
-//    0.93-1.00 at 8192, 1.00-1.04 (28) and 0.94-0.99 at 128; with
-//    diagnostics 1.01-1.10 at 256, 0.98-1.06 at 512, 0.94-1.00 at 1024.  Ragged 1.03-1.07 at 256, 1.02-1.08 from 512 to 1024, with
-//    diagnostics 0.96-1.03 (streamed).  Not on a pitch of a multiple of 64 KiB, where whole rows meet on the same memory
-//    channels (V = 131072, 512 tokens: 41.5 / 38.0; at a pitch of 131136 entries 34.5 / 37.2);
-//  * aligned rows of 16 chunks without diagnostics: one row per compute unit at most (1.00-1.04 at 256 tokens; 0.95 at 128), or many
-//    (1.01-1.02 from 8192 tokens on; 0.95-0.99 between), and with many also those with diagnostics that do not start on
-//    lines (V = 65528, 8192 tokens: 226 / 233, 16384: 1.06).
+//    half a row per compute unit to 12 (28 chunks) or 8 (with diagnostics, more arithmetic per entry: 2).  Not on a pitch of a multiple of
+//    64 KiB, where whole rows meet on the same memory channels;
+//  * aligned rows of 16 chunks without diagnostics: one row per compute unit at most, or many, and with many also those with
+//    diagnostics that do not start on lines.
+// The lines were drawn when the streamed kernel made its epilogue as a call; since that is inlined (without diagnostics), time streamed over time
+// kept, 128 / 256 / 512 / 1024 / 2048 / 8192 tokens:
+//   28 chunks   V = 106496 0.89 / 0.86 / 0.86 / 0.82 / 0.81 / 0.82, with diagnostics 1.04 / 1.18 / 1.14 / 1.02 / 0.94 / 0.87; ragged 100001 0.84 / 0.82 / 0.81 / 0.79 / 0.79 / 0.79
+//   32          V = 128000 0.86 / 0.86 / 0.82 / 0.80 / 0.82 / 0.84, with diagnostics 1.01 / 1.12 / 1.06 / 0.99 / 0.93 / 0.84; ragged 120001 0.82 / 0.81 / 0.80 / 0.78 / 0.78 / 0.79
+//   16          V = 57344 0.99 / 0.96 / 0.90 / 0.86 / 0.85 / 0.83, 65528 1.02 / 1.00 / 0.99 / 0.92 / 0.91 / 0.90; with diagnostics 1.16 / 1.28 / 1.27 / 1.18 / 1.07 / 0.99
+// so without diagnostics every exception costs time now, and with them rows of 16 chunks are streamed where keeping them would be faster: lines to move.
 bool forward_keeps_row(const dppo_args_t* a, int threads, int chunks, bool ragged, bool on_lines, int cus) {
   if (threads < 512 || chunks <= 12) return true;
   const bool diag = a->diagnostics != nullptr;
@@ -231,11 +232,13 @@ bool forward_keeps_row(const dppo_args_t* a, int threads, int chunks, bool ragge
 }
 
 // Few long rows, which would leave most compute units idle: divided among workgroups (dppo_split.hip) where the third launch and the
-// second read cost less than the idle time, the same for calls with and without a gradient, whose per-token outputs then agree bit for bit.
+// second read cost less than the idle time, by the same sizes for calls with and without a gradient: where both are divided their per-token
+// outputs agree bit for bit.  Not divided: a gradient that does not share the logits' address modulo 16 (the forward-only call on the same
+// logits still is), DPPO_FLAG_FORCE_STREAMING, the hidden states in several chunks, records and gathered logits beyond 64 KiB.
 // Ratio of the times, divided / one workgroup per row, with the gradient and without (whole calls, Top-20 TV, 8 / 64 / 96 / 128 tokens of
-// 256 compute units' share): V = 65536 0.86-1.0 / 0.97-1.08 / 1.01-1.17 / 1.08-1.2 and 0.80-1.0 / 0.82-0.96 / 0.84-0.98 / 0.91-1.03;
-// 81920 0.78 / 0.91 / 1.00 / 1.00; 98304 0.78 / 0.89 / 0.95 / 1.06; 131072 0.69 / 0.81 / 0.89 / 0.95; 151936 0.57 / 0.73 / 0.81 / 0.87 and
-// 0.75 / 0.80 / 0.85 / 0.88; 256000 0.34 / 0.49 / 0.67 (100 tokens) / 0.76.  At 140 tokens and more even or slower below V = 155000.
+// 256 compute units' share): V = 65536 0.94 / 1.02 / 1.02 / 1.09 and 0.95 / 0.98 / 1.04 / 1.04; 81920 0.83 / 0.92 / 0.98 / 0.99 and 0.89 / 0.97 / 1.03 / 1.01; 98304
+// 0.74 / 0.82 / 0.89 / 0.96 and 0.85 / 0.91 / 0.94 / 0.99; 131072 0.60 / 0.73 / 0.81 / 0.88 and 0.73 / 0.85 / 0.89 / 0.94; 151936 0.54 / 0.65 / 0.73 / 0.78
+// and 0.71 / 0.78 / 0.82 / 0.88; 256000 0.31 / 0.44 / 0.58 / 0.69 and 0.54 / 0.68 / 0.77 / 0.86.  160 tokens: 98304 1.06 and 1.05, 131072 1.03 and 1.04, 151936 0.94 and 1.01.
 bool splits_rows(const dppo_args_t* a, bool ragged_ok, const LossScratch& sc, int cus) {
   if (a->V < 81920 || a->V > 64 * 8 * static_cast<int64_t>(dppo::kSplitVecs) - 64 || a->T > (a->V >= 131072 ? cus / 2 : cus / 4)) return false;
   const bool topk = (a->variant == DPPO_TOPK_TV || a->variant == DPPO_TOPK_KL);
@@ -292,8 +295,8 @@ dppo_status_t launch_loss(const dppo_args_t* a, bool grad, const LossScratch& sc
     const bool tv_full = a->variant == DPPO_FULL_TV;
     const int fr_chunks = (full && !(a->flags & DPPO_FLAG_FORCE_STREAMING)) ? dppo::fullvocab_resident_chunks(p, tv_full, grad, cus) : 0;
     // Forward only, longer rows: streamed, but where keeping the row is faster.  Rows no shape takes that are
-    // shorter (odd lengths around a shape's end) are faster with the many small workgroups of the two-pass
-    // kernel (V = 8181, 16384 tokens: 141 / 207).
+    // shorter (odd lengths around a shape's end) go to the many small workgroups of the two-pass
+    // kernel (V = 8181, 16384 tokens: 97 / 154 us; 49110: 310 / 273).
     const bool forward = !full && !grad && !(a->flags & DPPO_FLAG_FORCE_STREAMING) &&
                          (resident ? !forward_keeps_row(a, r_threads, r_chunks, ragged, on_lines, cus) : a->V >= 65536 && a->V < (int64_t(1) << 30));
     if (!full && splits_rows(a, ragged_ok, sc, cus)) {

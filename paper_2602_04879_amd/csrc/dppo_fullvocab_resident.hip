@@ -368,9 +368,9 @@ __global__ __launch_bounds__(kThreads, two_per_cu(NCHUNK) ? 4 : 2) void dppo_ful
         D = Uy / Sy + kLn2 * (lse2_z - lse2_y);
         D = (D > 0.0 || D != D) ? D : 0.0;       // rounding can leave -1e-8 for identical rows
       }
-      // ---- epilogue on wave 0 (inlined: one workgroup per compute unit, nothing would hide a call)
+      // ---- epilogue on wave 0 (inlined but in two shapes, see below) ------------------------------
       // With the gradient the resident row is still needed afterwards, and the epilogue's float64
-      // arithmetic finds no registers beside it: wave 0 parks its last chunks in shared memory around
+      // arithmetic finds no registers beside a long one: from 32 chunks on wave 0 parks its last chunks in shared memory around
       // it (its own 16 bytes per lane and chunk, no synchronisation) instead of spilling to scratch
       // memory, whose round trips would sit on the path the other seven waves wait for.
       if (wid == 0) {
@@ -509,18 +509,19 @@ hipError_t launch_chunks(const KParams& p, bool tv, bool grad, int grid, hipStre
 // forward-only KL form reads each row once in the general kernel too), on rows of 98312 .. 155648
 // entries, a multiple of 8, every matrix 16-byte aligned with a pitch that is a multiple of 8; to the
 // backward from 8200 entries on if there is a row for every compute unit.  Measured against the general
-// kernel, which reads what it needs again (us, general / this; TV and KL): V = 98304, 8192 tokens 1326 / 1039 and
-// 1201 / 844; 65536: 936 / 676 and 928 / 603; 49152, 8192 tokens 639 / 502 (TV); 32000, 8192 tokens 469 / 355
-// and 348 / 315; 16384, 8192 tokens 284 / 226 and 216 / 197; 32000, 520 tokens 51 / 39 and 41 / 35.
+// kernel, which reads what it needs again (us, general / this; TV and KL): V = 98304, 8192 tokens 1285 / 963 and
+// 1207 / 842; 65536: 919 / 666 and 930 / 601; 49152, 8192 tokens 595 / 500 (TV); 32000, 8192 tokens 424 / 322
+// and 348 / 309; 16384, 8192 tokens 254 / 191 and 202 / 176; 32000, 520 tokens 39 / 32 and 36 / 33.
 //
 // The KL form's general kernel reads only z again, so idle lanes and waves count: this form needs a row that fills its
 // shape, and below 65536 entries (from there on the general kernel runs one workgroup per compute unit, a third
-// slower) one that leaves room for a second workgroup.  General = 1, at 256 to 8192 tokens: 16400 entries
-// of six chunks (67 %) 0.93-1.06, 18432 (75 %) 0.94-1.04, 18944 (77 %) 0.91-0.99, 20480 0.88-0.98; eight chunks, 24584 (75 %)
-// 0.93-1.03, 25600 (78 %) 0.90-1.00, 32000 0.81-0.92; ten, 34816 (85 %) 0.93-1.03, 35840 (87 %) 0.89-1.00, 40960 0.87-0.98; twelve, 49152
-// (100 %) 0.95-1.03: never (kl_shape).  With one workgroup per compute unit (14 and 16 chunks) it gains up to four rows per compute
-// unit and where many are handed out at run time, and loses between: 57344 entries 0.82-0.98 up to 1024 tokens, 1.03-1.05 at
-// 1040 to 1600, 0.97-1.00 from 4096 on; 51200 (89 %) up to 1.11.
+// slower) one that leaves room for a second workgroup.  The lines were drawn when the general kernel made its epilogue as
+// a call; inlined, it takes back what few rows gained, and they have not moved.  General = 1, at 256 to 1024 and at 2048 to 8192 tokens: four chunks,
+// 10240 entries 0.99-1.02 and 0.98-1.00, 12288 (75 %) 0.95-0.96 and 0.90-0.94, 16384 0.84-0.99 and 0.87-0.94; six, 18432 (75 %) 1.00-1.05 and 0.95-0.99, 20480
+// 0.95-0.97 and 0.88-0.94; eight, 24584 (75 %) 1.07-1.16 and 0.98-1.02, 25600 (78 %) 1.08-1.13 and 0.95-1.04, 28672 1.04-1.08 and 0.92-0.97, 32000 0.96-1.01
+// and 0.87-0.90; ten, 34816 (85 %) 1.06-1.13 and 0.99-1.02, 35840 (87 %) 1.02-1.08 and 0.96-0.99, 40960 0.98-1.03 and 0.95-0.98; twelve: never (kl_shape).
+// With one workgroup per compute unit (14 and 16 chunks) it gains up to four rows per compute
+// unit and where many are handed out at run time: 57344 entries 0.83-1.00 and 0.96-1.01, 65528 0.82-0.98 and 0.91-0.96; 51200 (89 %) 0.88-1.09 and 1.01-1.07.
 #define DPPO_FULL_SHAPES(X) X(4) X(6) X(8) X(10) X(12) X(14) X(16) X(20) X(24) X(32) X(38)
 int fullvocab_resident_chunks(const KParams& p, bool tv, bool grad, int cus) {
   if (!(grad || tv) || !p.mu_logits || p.V % 8 != 0 || p.ld % 8 != 0 || p.mu_ld % 8 != 0) return 0;

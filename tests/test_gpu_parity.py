@@ -845,6 +845,32 @@ def test_few_long_rows_divided_among_workgroups(V, ld, off, per_cu, variant, K, 
     _say(f"       {st}")
 
 
+@pytest.mark.parametrize("V,ld,variant,K", [(151936, 151936, W.TOPK_TV, 20), (131073, 131136, W.BINARY_KL, 0)])
+def test_few_long_rows_whose_gradient_lies_otherwise_modulo_16(V, ld, variant, K):
+    """A gradient that does not share the logits' misalignment is none of the divided rows': the two-pass kernel takes the call, the
+    forward-only call on the same logits is still divided, and both agree with the oracle."""
+    T = torch.cuda.get_device_properties(0).multi_processor_count // 4
+    w = W.Workload("split_apart", 1, T, V, variant, 0.05, K=K, logit_std=3.0, noise_std=1.0, adv="normal", seed=121)
+    b = W.make_batch(w, DEV, ld=ld, shift_sampled=2.0, rows_per_step=32)
+    b["advantages"] = torch.randn(T, device=DEV)
+    _say(f"[case] few rows, gradient 6 bytes further V={V} ld={ld} T={T} variant={variant}")
+    rows = np.arange(T)
+    ref = P.oracle_rows(b, rows)
+    gbuf = torch.full((T * ld + 16,), 7.0, dtype=torch.bfloat16, device=DEV)
+    grad = gbuf[3:3 + T * ld].view(T, ld)
+    assert b["logits"].data_ptr() % 16 == 0 and grad.data_ptr() % 16 == 6
+    res = B.run_batch(b, grad=grad, diagnostics=True)
+    torch.cuda.synchronize()
+    assert B.last_kernel() == "dppo_streaming_kernel"
+    P.compare_rows(b, res, rows, ref=ref)
+    P.check_loss_scalar(b, res)
+    assert (gbuf[:3] == 7.0).all() and (gbuf[3 + T * ld:] == 7.0).all() and (grad[:, V:] == 7.0).all()
+    fwd = B.run_batch(b, backward=False, diagnostics=True)
+    torch.cuda.synchronize()
+    assert B.last_kernel() == "dppo_split_stat_kernel"
+    P.compare_rows(b, fwd, rows, check_grad=False, ref=ref)
+
+
 @pytest.mark.parametrize("V,ld,off", [(49145, 49145, 3), (50257, 50257, 0), (50264, 50264, 0), (53178, 53184, 1)])
 def test_ragged_rows_of_thirteen_chunks_two_workgroups_per_compute_unit(V, ld, off):
     """The shape that such rows take without diagnostics, many of them, at its shortest and longest row: the bits of the shape
