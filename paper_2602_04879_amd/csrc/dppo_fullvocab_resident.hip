@@ -24,6 +24,7 @@
 // 16-byte aligned with pitches that are multiples of 8 entries.
 #include "dppo_common.hpp"
 #include "dppo_launch.hpp"
+#include "dppo_resident_parts.hpp"
 
 namespace dppo {
 namespace {
@@ -75,20 +76,18 @@ struct RowStat {
 
 // The largest entry of a row's chunks, on the packed bf16 patterns as signed 16-bit integers: non-negative patterns order like the
 // floats and every negative one stays below them; where every entry of a lane is negative the float maximum is the integer minimum.
-typedef short s16x2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ s16x2 as_pair(uint32_t w) { return __builtin_bit_cast(s16x2, w); }      // (by value: the cast of a vector's element itself yields its first)
 template <int N>
 __device__ __forceinline__ float packed_max(const u32x4 (&v)[N]) {
-  s16x2 m = as_pair(0x80008000u);
+  s16x2 m = as_s16x2(0x80008000u);
 #pragma unroll
   for (int i = 0; i < N; ++i)
-    m = __builtin_elementwise_max(m, __builtin_elementwise_max(__builtin_elementwise_max(as_pair(v[i].x), as_pair(v[i].y)), __builtin_elementwise_max(as_pair(v[i].z), as_pair(v[i].w))));
+    m = __builtin_elementwise_max(m, __builtin_elementwise_max(__builtin_elementwise_max(as_s16x2(v[i].x), as_s16x2(v[i].y)), __builtin_elementwise_max(as_s16x2(v[i].z), as_s16x2(v[i].w))));
   int top = max(static_cast<int>(m.x), static_cast<int>(m.y));
   if (__any(top < 0)) {
-    s16x2 n = as_pair(0x7FFF7FFFu);
+    s16x2 n = as_s16x2(0x7FFF7FFFu);
 #pragma unroll
     for (int i = 0; i < N; ++i)
-      n = __builtin_elementwise_min(n, __builtin_elementwise_min(__builtin_elementwise_min(as_pair(v[i].x), as_pair(v[i].y)), __builtin_elementwise_min(as_pair(v[i].z), as_pair(v[i].w))));
+      n = __builtin_elementwise_min(n, __builtin_elementwise_min(__builtin_elementwise_min(as_s16x2(v[i].x), as_s16x2(v[i].y)), __builtin_elementwise_min(as_s16x2(v[i].z), as_s16x2(v[i].w))));
     top = top < 0 ? min(static_cast<int>(n.x), static_cast<int>(n.y)) : top;
   }
   return __uint_as_float(static_cast<uint32_t>(top) << 16);
@@ -105,7 +104,6 @@ __global__ __launch_bounds__(kThreads, two_per_cu(NCHUNK) ? 4 : 2) void dppo_ful
   constexpr int kWindow = window_of(NCHUNK);
   constexpr int THREADS = kThreads, NW = THREADS / kWave;
   constexpr uint32_t kStride = THREADS * 16u;      // bytes between a thread's consecutive chunks
-  constexpr uint32_t kNegInfPair = 0xFF80FF80u;    // two bf16 -inf
   constexpr int KEEP = TV ? (keep_of(NCHUNK) < NCHUNK ? keep_of(NCHUNK) : NCHUNK) : 0;
   constexpr int REREAD = NCHUNK - KEEP;            // TV form: chunks of y that pass 2 reads from memory again
   constexpr int FULLCHUNKS = full_chunks(NCHUNK);  // only later chunks can have lanes past the row

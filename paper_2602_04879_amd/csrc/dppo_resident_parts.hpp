@@ -10,6 +10,7 @@ typedef short s16x2 __attribute__((ext_vector_type(2)));
 
 constexpr uint32_t kNegInfPair = 0xFF80FF80u;   // two bf16 -inf
 
+// (by value: the cast of a vector's element itself yields its first)
 __device__ __forceinline__ s16x2 as_s16x2(uint32_t w) { return __builtin_bit_cast(s16x2, w); }
 
 // Replace 16-bit entry `sub` (0..7) of a packed vector by `bits`.
