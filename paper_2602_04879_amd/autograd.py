@@ -141,13 +141,15 @@ class _DppoLmheadLoss(torch.autograd.Function):
         # T = 2 d; an eighth more is let pass, the copy of the hidden states among it): a step that sums the losses of
         # several micro-batches before one backward holds all of them.  That costs 3-4 % of a step at 8192 tokens x 768 .. 3584,
         # 5-9 % at 4096 and 2048 x 768, and up to 17 % where the vocabulary is small (3000 x 1024, V = 32768: 597 / 700 us).
-        held = B.lmhead_workspace_bytes(T, V, chunk) + 2 * T * d
-        later = need_w and 0 < T <= min(chunk if chunk > 0 else T, B.LMHEAD_CHUNK_ROWS) and held <= 4 * V * d * 9 // 8
+        later = need_w and 0 < T <= min(chunk if chunk > 0 else T, B.LMHEAD_CHUNK_ROWS)
+        if later:
+            room = B.lmhead_workspace_bytes(T, V, chunk)
+            later = room + 2 * T * d <= 4 * V * d * 9 // 8
         # (no tokens: the library runs no product and leaves the buffer as it is)
         gw = (torch.empty if T > 0 else torch.zeros)((V, d), dtype=torch.float32, device=hidden.device) if need_w and not later else None
         rule = {k: opts[k] for k in ("mask_rule", "eps_low", "eps_high", "ratio_cap", "relax_alpha", "relax_sides") if k in opts}
         # what is kept lies in a workspace of its own, without the room for the divided contraction (up to 1 GiB) behind it
-        workspace, scratch = B.alloc_lmhead_apart(T, V, d, chunk, hidden.device) if later else (None, None)
+        workspace, scratch = B.alloc_lmhead_apart(T, V, d, chunk, hidden.device, room) if later else (None, None)
         res = B.run_lmhead(batch, backward=backward, chunk_rows=chunk, diagnostics=opts.get("diagnostics", False),
                            grad_weight=gw, flags=opts.get("flags", 0), workspace=workspace, scratch=scratch, **rule)
         # (a copy of the hidden states: the caller may write to its own before backward)

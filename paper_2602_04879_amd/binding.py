@@ -329,9 +329,11 @@ def _check_factor(factor, x):
 
 
 def _check_bf16_matrix(name, x, rows, cols, device):
-    if (x.dtype != torch.bfloat16 or not x.is_cuda or x.device != device or tuple(x.shape) != (rows, cols)
-            or (cols > 1 and x.stride(1) != 1) or (rows > 1 and x.stride(0) < cols)):
-        raise ValueError(f"{name}: a bf16 [{rows}, {cols}] matrix with contiguous rows on one GPU with the others")
+    if x.dtype is torch.bfloat16 and x.device == device and x.is_cuda and x.shape == (rows, cols):
+        pitch, step = x.stride()
+        if (step == 1 or cols <= 1) and (pitch >= cols or rows <= 1):
+            return
+    raise ValueError(f"{name}: a bf16 [{rows}, {cols}] matrix with contiguous rows on one GPU with the others")
 
 
 def gemm_tn_bf16(a, b, factor, c=None, stream=None):
@@ -339,13 +341,14 @@ def gemm_tn_bf16(a, b, factor, c=None, stream=None):
     fp32 value on the device."""
     if a.dim() != 2 or b.dim() != 2:
         raise ValueError("a [K, M] and b [K, N]: matrices")
-    (K, M), N = a.shape, b.shape[1]
-    _check_bf16_matrix("a", a, K, M, a.device)
-    _check_bf16_matrix("b", b, K, N, a.device)
+    (K, M), N, dev = a.shape, b.shape[1], a.device
+    _check_bf16_matrix("a", a, K, M, dev)
+    _check_bf16_matrix("b", b, K, N, dev)
     _check_factor(factor, a)
     if c is None:
-        c = torch.empty((M, N), dtype=torch.bfloat16, device=a.device)
-    _check_bf16_matrix("c", c, M, N, a.device)
+        c = torch.empty((M, N), dtype=torch.bfloat16, device=dev)
+    else:
+        _check_bf16_matrix("c", c, M, N, dev)
     st = lib().dppo_gemm_tn_bf16(a.data_ptr(), a.stride(0), b.data_ptr(), b.stride(0), c.data_ptr(), c.stride(0),
                                  M, N, K, factor.data_ptr(), C.c_void_p(_stream_handle(stream)))
     if st != 0:
@@ -432,10 +435,10 @@ def lmhead_fwd_workspace_bytes(T: int, V: int, K: int, chunk_rows: int = 0) -> i
     return lib().dppo_lmhead_fwd_workspace_bytes(T, V, K, chunk_rows)
 
 
-def alloc_lmhead_apart(T: int, V: int, d: int, chunk_rows: int, device):
-    """The workspace of a forward + backward call that keeps the logits' gradient, and the room for the divided contraction
-    apart from it (None where the call wants none, or there is no memory: slower without it, but it runs)."""
-    need, best = lmhead_workspace_bytes(T, V, chunk_rows), lmhead_workspace_bytes_best(T, V, d, chunk_rows)
+def alloc_lmhead_apart(T: int, V: int, d: int, chunk_rows: int, device, need: int):
+    """The workspace of a forward + backward call that keeps the logits' gradient (need: lmhead_workspace_bytes), and the room for
+    the divided contraction apart from it (None where the call wants none, or there is no memory: slower without it, but it runs)."""
+    best = lmhead_workspace_bytes_best(T, V, d, chunk_rows)
     workspace, scratch = torch.empty(need, dtype=torch.uint8, device=device), None
     if best > need:
         try:
@@ -469,10 +472,10 @@ def run_lmhead(batch: dict, backward: bool = True, chunk_rows: int = 0, out=None
                 raise
             workspace = torch.empty(need, dtype=torch.uint8, device=dev)
     a = DppoLmheadArgs()
-    a.loss = make_args(torch.empty((0, V), dtype=torch.bfloat16, device=dev), batch["sampled_ids"], batch["mu_logp"],
+    a.loss = make_args(h, batch["sampled_ids"], batch["mu_logp"],            # (no logits to name: what it takes from them is set below)
                        batch["advantages"], batch["delta"], batch["variant"], batch["loss_scale"], out,
                        batch["mu_topk_ids"], batch["mu_topk_logp"], V=V, flags=flags, anchor_logp=batch.get("anchor_logp"), **rule)
-    a.loss.T, a.loss.logits = T, None
+    a.loss.T, a.loss.logits, a.loss.ld = T, None, V
     a.hidden, a.ld_hidden, a.d = h.data_ptr(), h.stride(0), d
     a.weight, a.ld_weight = w.data_ptr(), w.stride(0)
     a.chunk_rows = chunk_rows

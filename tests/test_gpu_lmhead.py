@@ -498,7 +498,7 @@ def test_room_for_the_divided_contraction_apart_from_the_workspace(monkeypatch):
     b = W.make_lmhead_batch(w, d, DEV, rows_per_step=256)
     _say(f"[case] divided contraction, room apart T={T} V={V} d={d}")
     want = B.run_lmhead(b)
-    ws, scratch = B.alloc_lmhead_apart(T, V, d, 0, DEV)
+    ws, scratch = B.alloc_lmhead_apart(T, V, d, 0, DEV, B.lmhead_workspace_bytes(T, V))
     assert ws.numel() == B.lmhead_workspace_bytes(T, V) and scratch.numel() >= 2 * 4 * T * d
     guard = torch.full((scratch.numel() + 4096,), 0xAB, dtype=torch.uint8, device=DEV)
     res = B.run_lmhead(b, workspace=ws, scratch=guard[:scratch.numel()])
@@ -516,7 +516,7 @@ def test_room_for_the_divided_contraction_apart_from_the_workspace(monkeypatch):
         return empty(*size, **kw)
 
     monkeypatch.setattr(torch, "empty", no_room)
-    assert B.alloc_lmhead_apart(T, V, d, 0, DEV)[1] is None
+    assert B.alloc_lmhead_apart(T, V, d, 0, DEV, ws.numel())[1] is None
 
 
 def test_error_codes():
