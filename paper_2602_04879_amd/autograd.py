@@ -31,6 +31,13 @@ from . import binding as B
 # entries 173-189 / 141.  (The hidden-state loss goes by its larger gradient: its products alone take longer than either.)
 SCALE_ON_DEVICE_FROM = 5 << 24
 
+# What a pending hidden-state loss may hold beyond the 4 V d bytes of the weight's gradient in fp32 to have that gradient formed in
+# backward: an eighth of them (the logits' gradient is as large as they are at T = 2 d), or this, a thousandth of the card's memory.  A step
+# that sums the losses of several micro-batches before one backward holds every one of them: 8192 tokens x 768 at V = 151936 would
+# be 2.5 GB each in place of 0.47.  Formed in fp32 in forward, such a step takes 1.03-1.04 of the time at 8192 x 768 .. 3584, 1.05-1.06 at 4096 x
+# 768 and 1024; what this lets pass would take 1.09 at 2048 x 768 and, V = 32768, 1.17 at 3000 x 1024 (597 / 700 us), V = 16000, 1.07 at 8192 x 2048.
+HELD_MORE = 256 << 20
+
 
 def _grad_like(logits: torch.Tensor) -> torch.Tensor:
     """An empty gradient for rows of `logits`, with the same row pitch: the boundary has one pitch for
@@ -137,14 +144,11 @@ class _DppoLmheadLoss(torch.autograd.Function):
         # One chunk: the logits' gradient stays as it is in the workspace, and the weight's gradient is formed from it in
         # backward, where its factor is known, straight in the weight's type (V = 151936, d = 2048, 1000 tokens: 2158 us a step,
         # 1775 now; 64 tokens x 768: 416 / 283).  Several chunks are summed in fp32; so is one of more rows than a chunk has
-        # unasked.  And so are tokens whose logits' gradient would be more to hold than the weight's in fp32 (the two are as large at
-        # T = 2 d; an eighth more is let pass, the copy of the hidden states among it): a step that sums the losses of
-        # several micro-batches before one backward holds all of them.  That costs 3-4 % of a step at 8192 tokens x 768 .. 3584,
-        # 5-9 % at 4096 and 2048 x 768, and up to 17 % where the vocabulary is small (3000 x 1024, V = 32768: 597 / 700 us).
+        # unasked.  And so are tokens whose logits' gradient would be far more to hold than the weight's in fp32: see HELD_MORE.
         later = need_w and 0 < T <= min(chunk if chunk > 0 else T, B.LMHEAD_CHUNK_ROWS)
         if later:
             room = B.lmhead_workspace_bytes(T, V, chunk)
-            later = room + 2 * T * d <= 4 * V * d * 9 // 8
+            later = room + 2 * T * d <= 4 * V * d + max(V * d // 2, HELD_MORE)
         # (no tokens: the library runs no product and leaves the buffer as it is)
         gw = (torch.empty if T > 0 else torch.zeros)((V, d), dtype=torch.float32, device=hidden.device) if need_w and not later else None
         rule = {k: opts[k] for k in ("mask_rule", "eps_low", "eps_high", "ratio_cap", "relax_alpha", "relax_sides") if k in opts}
