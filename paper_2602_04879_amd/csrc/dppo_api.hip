@@ -526,6 +526,9 @@ dppo_status_t run_lmhead(const dppo_lmhead_args_t* a, void* stream, bool grad, v
   const dppo_status_t st0 = check_args(&c, grad);
   if (st0 != DPPO_OK) return st0;
 
+  int dev = 0;
+  if (T > 0 && !stream_device(s, &dev)) return DPPO_ERR_LAUNCH;
+  const int cus = device_info(dev).cus;
   if (fused_fwd) {
     const int tiles_n = static_cast<int>((V + dppo::kGemmTileN - 1) / dppo::kGemmTileN);
     double* row_loss = reinterpret_cast<double*>(ws + DPPO_WORKSPACE_BYTES);
@@ -557,7 +560,7 @@ dppo_status_t run_lmhead(const dppo_lmhead_args_t* a, void* stream, bool grad, v
       p.gath = gs.gath;
       const uint16_t* h = static_cast<const uint16_t*>(a->hidden) + r0 * a->ld_hidden;
       if (dppo::launch_gemm_stats(h, a->ld_hidden, static_cast<const uint16_t*>(a->weight), a->ld_weight, static_cast<int>(rows),
-                                  static_cast<int>(V), static_cast<int>(d), gs, s) != hipSuccess)
+                                  static_cast<int>(V), static_cast<int>(d), gs, cus, s) != hipSuccess)
         return DPPO_ERR_LAUNCH;
       if (dppo::launch_lmhead_rows(p, gs, row_loss + r0, s) != hipSuccess) return DPPO_ERR_LAUNCH;
     }
@@ -574,14 +577,12 @@ dppo_status_t run_lmhead(const dppo_lmhead_args_t* a, void* stream, bool grad, v
   const size_t base_bytes = align256(lmhead_workspace(T, V, a->chunk_rows));
   const size_t extra_bytes = scratch ? scratch_bytes : a->workspace_bytes > base_bytes ? a->workspace_bytes - base_bytes : 0;
   float* extra = reinterpret_cast<float*>(scratch ? static_cast<char*>(scratch) : ws + base_bytes);
-  int dev = 0;
-  if (T > 0 && grad && !stream_device(s, &dev)) return DPPO_ERR_LAUNCH;
   for (int64_t r0 = 0; r0 < T; r0 += chunk) {
     const int64_t rows = (T - r0 < chunk) ? (T - r0) : chunk;
     const uint16_t* h = static_cast<const uint16_t*>(a->hidden) + r0 * a->ld_hidden;
     // logits of the chunk (bf16, as a trainer's lm_head produces them)
     if (dppo::launch_gemm_nt(h, a->ld_hidden, static_cast<const uint16_t*>(a->weight), a->ld_weight, zbuf, V,
-                             static_cast<int>(rows), static_cast<int>(V), static_cast<int>(d), 0, s) != hipSuccess)
+                             static_cast<int>(rows), static_cast<int>(V), static_cast<int>(d), 0, cus, s) != hipSuccess)
       return DPPO_ERR_LAUNCH;
     c.T = rows;
     c.sampled_ids = a->loss.sampled_ids + r0;
@@ -606,9 +607,9 @@ dppo_status_t run_lmhead(const dppo_lmhead_args_t* a, void* stream, bool grad, v
     if (grad) {
       // gradient of the chunk's hidden states: g [rows, V] times W [V, d], the weight as it lies
       uint16_t* gh = static_cast<uint16_t*>(a->grad_hidden) + r0 * a->ld_grad_hidden;
-      const int splits = dppo::gemm_nn_splits(rows, d, V, device_info(dev).cus, extra_bytes);
+      const int splits = dppo::gemm_nn_splits(rows, d, V, cus, extra_bytes);
       if (dppo::launch_gemm_nn(zbuf, V, static_cast<const uint16_t*>(a->weight), a->ld_weight, gh, a->ld_grad_hidden, static_cast<int>(rows),
-                               static_cast<int>(d), static_cast<int>(V), splits, extra, s) != hipSuccess)
+                               static_cast<int>(d), static_cast<int>(V), splits, extra, cus, s) != hipSuccess)
         return DPPO_ERR_LAUNCH;
     }
     if (want_gw) {
@@ -617,7 +618,7 @@ dppo_status_t run_lmhead(const dppo_lmhead_args_t* a, void* stream, bool grad, v
       // caller's buffer if asked to accumulate)
       const int out = (r0 == 0 && !a->grad_weight_accumulate) ? 1 : 2;
       if (dppo::launch_gemm_tn(zbuf, V, h, a->ld_hidden, a->grad_weight, a->ld_grad_weight, static_cast<int>(V), static_cast<int>(d),
-                               static_cast<int>(rows), out, s) != hipSuccess)
+                               static_cast<int>(rows), out, cus, s) != hipSuccess)
         return DPPO_ERR_LAUNCH;
     }
   }
@@ -723,9 +724,11 @@ dppo_status_t dppo_gemm_nt(const void* A, int64_t lda, const void* B, int64_t ld
   if (!A || !B || !C) return DPPO_ERR_NULL;
   if ((reinterpret_cast<uintptr_t>(A) | reinterpret_cast<uintptr_t>(B)) & 15u) return DPPO_ERR_ALIGN;
   if (reinterpret_cast<uintptr_t>(C) & 1u) return DPPO_ERR_ALIGN;
+  int dev = 0;
+  if (!stream_device(static_cast<hipStream_t>(stream), &dev)) return DPPO_ERR_LAUNCH;
   const hipError_t e = dppo::launch_gemm_nt(static_cast<const uint16_t*>(A), lda, static_cast<const uint16_t*>(B), ldb,
                                             C, ldc, static_cast<int>(M), static_cast<int>(N),
-                                            static_cast<int>(K), 0, static_cast<hipStream_t>(stream));
+                                            static_cast<int>(K), 0, device_info(dev).cus, static_cast<hipStream_t>(stream));
   return e == hipSuccess ? DPPO_OK : DPPO_ERR_LAUNCH;
 }
 
@@ -736,9 +739,11 @@ dppo_status_t dppo_gemm_nt_f32(const void* A, int64_t lda, const void* B, int64_
   if (M == 0 || N == 0) return DPPO_OK;
   if (!A || !B || !C) return DPPO_ERR_NULL;
   if ((reinterpret_cast<uintptr_t>(A) | reinterpret_cast<uintptr_t>(B) | reinterpret_cast<uintptr_t>(C)) & 15u) return DPPO_ERR_ALIGN;
+  int dev = 0;
+  if (!stream_device(static_cast<hipStream_t>(stream), &dev)) return DPPO_ERR_LAUNCH;
   const hipError_t e = dppo::launch_gemm_nt(static_cast<const uint16_t*>(A), lda, static_cast<const uint16_t*>(B), ldb,
                                             C, ldc, static_cast<int>(M), static_cast<int>(N), static_cast<int>(K),
-                                            accumulate ? 2 : 1, static_cast<hipStream_t>(stream));
+                                            accumulate ? 2 : 1, device_info(dev).cus, static_cast<hipStream_t>(stream));
   return e == hipSuccess ? DPPO_OK : DPPO_ERR_LAUNCH;
 }
 
@@ -749,9 +754,11 @@ dppo_status_t dppo_gemm_nn(const void* A, int64_t lda, const void* B, int64_t ld
   if (M == 0 || N == 0) return DPPO_OK;
   if (!A || !B || !C) return DPPO_ERR_NULL;
   if (((reinterpret_cast<uintptr_t>(A) | reinterpret_cast<uintptr_t>(B)) & 15u) || (reinterpret_cast<uintptr_t>(C) & 1u)) return DPPO_ERR_ALIGN;
+  int dev = 0;
+  if (!stream_device(static_cast<hipStream_t>(stream), &dev)) return DPPO_ERR_LAUNCH;
   const hipError_t e = dppo::launch_gemm_nn(static_cast<const uint16_t*>(A), lda, static_cast<const uint16_t*>(B), ldb,
                                             C, ldc, static_cast<int>(M), static_cast<int>(N), static_cast<int>(K),
-                                            1, nullptr, static_cast<hipStream_t>(stream));
+                                            1, nullptr, device_info(dev).cus, static_cast<hipStream_t>(stream));
   return e == hipSuccess ? DPPO_OK : DPPO_ERR_LAUNCH;
 }
 
@@ -762,9 +769,11 @@ dppo_status_t dppo_gemm_tn_f32(const void* A, int64_t lda, const void* B, int64_
   if (M == 0 || N == 0) return DPPO_OK;
   if (!A || !B || !C) return DPPO_ERR_NULL;
   if ((reinterpret_cast<uintptr_t>(A) | reinterpret_cast<uintptr_t>(B) | reinterpret_cast<uintptr_t>(C)) & 15u) return DPPO_ERR_ALIGN;
+  int dev = 0;
+  if (!stream_device(static_cast<hipStream_t>(stream), &dev)) return DPPO_ERR_LAUNCH;
   const hipError_t e = dppo::launch_gemm_tn(static_cast<const uint16_t*>(A), lda, static_cast<const uint16_t*>(B), ldb,
                                             C, ldc, static_cast<int>(M), static_cast<int>(N), static_cast<int>(K),
-                                            accumulate ? 2 : 1, static_cast<hipStream_t>(stream));
+                                            accumulate ? 2 : 1, device_info(dev).cus, static_cast<hipStream_t>(stream));
   return e == hipSuccess ? DPPO_OK : DPPO_ERR_LAUNCH;
 }
 
@@ -776,9 +785,11 @@ dppo_status_t dppo_gemm_tn_bf16(const void* A, int64_t lda, const void* B, int64
   if (!A || !B || !C || !factor) return DPPO_ERR_NULL;
   if ((reinterpret_cast<uintptr_t>(A) | reinterpret_cast<uintptr_t>(B)) & 15u) return DPPO_ERR_ALIGN;
   if ((reinterpret_cast<uintptr_t>(C) & 1u) || (reinterpret_cast<uintptr_t>(factor) & 3u)) return DPPO_ERR_ALIGN;
+  int dev = 0;
+  if (!stream_device(static_cast<hipStream_t>(stream), &dev)) return DPPO_ERR_LAUNCH;
   const hipError_t e = dppo::launch_gemm_tn_bf16(static_cast<const uint16_t*>(A), lda, static_cast<const uint16_t*>(B), ldb, C, ldc,
                                                  static_cast<int>(M), static_cast<int>(N), static_cast<int>(K), factor,
-                                                 static_cast<hipStream_t>(stream));
+                                                 device_info(dev).cus, static_cast<hipStream_t>(stream));
   return e == hipSuccess ? DPPO_OK : DPPO_ERR_LAUNCH;
 }
 

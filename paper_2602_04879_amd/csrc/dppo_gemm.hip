@@ -3,22 +3,32 @@
 // activations [T, d] times weight [V, d] transposed), C row-major: bf16 rounded to nearest even,
 // or fp32, optionally added to what C holds.
 //
-// One workgroup of 256 threads (4 waves, one per SIMD) per 256 x 256 tile of C, each wave a
+// Workgroups of 256 threads (4 waves, one per SIMD), one per compute unit, form 256 x 256 tiles of C, each wave a
 // 128 x 128 quadrant as 8 x 8 products of v_mfma_f32_16x16x32_bf16 (256 fp32 accumulators per
 // lane, the whole accumulation register file).  That shape is chosen for power: with every
 // compute unit busy the clock is set by the power limit, and a loop of nothing but 16x16x32
 // products sustains about 13 % more than one of 32x32x16 products (measured, 2.2-2.3 against
 // 1.9-2.0 PFLOP/s).  The contraction runs in steps of 64: the A and B panels of a step (256 x 64
-// each, 32 KiB) are loaded from global memory straight into one of two LDS stages, 16 bytes per
+// each, 32 KiB) are loaded from global memory straight into LDS, 16 bytes per
 // lane, in a layout swizzled so that the fragment reads (one 16-byte read per lane: 8 consecutive
 // k of one row) spread over all banks.
+// What bounds it besides the power limit is the latency of those loads: a step is 2048 cycles of products, loads from beyond the L2 take as long, and a panel's
+// place is free only from the middle of its own step on.  So all 160 KiB of LDS are panels, five of them: two of the near operand (activations,
+// which the Infinity Cache holds), loaded a step and a half ahead, three of the far one (the weight; the logits' gradient for the weight's), loaded
+// two and a half ahead.  And a workgroup forms several tiles one behind the other: the next tile's first panels are loaded during the last steps of a
+// tile, whose stores travel behind the next one's products.  Measured, us, V = 151936, one tile per workgroup and two panels each / as it is:
+// A B^T 300 x 2048 263 / 231, 1000 x 2048 514 / 484, 2048 x 1024 578 / 535, 2048 x 2048 1010 / 928, 8192 x 1024 2170 / 1985, 8192 x 4096 6880 / 6735;
+// bf16 A^T B 500 x 2048 369 / 355, 1000 x 2048 598 / 549, 2048 x 2048 1039 / 934, 4096 x 4096 3720 / 3375, 8192 x 4096 7410 / 7150.
+// (With operands of zeros, which draw no power, 2048 x 2048 931 / 760, of 520 for the products alone: 130 of the rest are the stores, whose 32 MiB leave at
+// once and fill the dies' way to memory for five microseconds; held back in registers and spread over the next tile's first six steps they cost the
+// same but for 1 %, written in whole lines through shared memory too.)
 // A 16x16x32 product occupies the matrix pipe for 16 cycles and a wave issues at most one
 // instruction every 4, so whatever else the wave issues has to sit in the shadow of a product:
 // the matrix-core instructions are written as assembly statements in a fixed order (that also
 // keeps each accumulator in place in its own registers, which the register allocator does not
 // manage by itself at this pressure), with one fragment read or one panel load pinned behind
 // every second to fourth of them.
-// Panel rows past M or N re-read the last valid row (their products are never stored); all
+// Panel rows past M or N are zeros (their products are never stored): all
 // loads go through range-checked buffer resources over exactly the rows a tile owns.  K must be
 // a multiple of 64, rows 16-byte aligned (checked by the host).
 //
@@ -29,6 +39,7 @@
 // consecutive k of one column.  There K is arbitrary: rows past it read as zeros.
 #include <algorithm>
 #include <type_traits>
+#include <utility>
 #include "dppo_common.hpp"
 #include "dppo_launch.hpp"
 
@@ -38,10 +49,52 @@ namespace {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
+// f(std::integral_constant<int, 0>{}), ..., f(N - 1): a loop whose index is a constant
+template <typename F, int... I>
+__device__ __forceinline__ void unrolled(std::integer_sequence<int, I...>, F&& f) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void unrolled(F&& f) {
+  unrolled(std::make_integer_sequence<int, N>{}, f);
+}
+
+// The accumulators of a 256 x 256 tile are the whole accumulation register file, named in the statements that use it: block (i, j) of 16 x 16 is
+// a[4 (8 i + j)] .. + 3.  As values of the compiler's they were moved, some between a tile's products and some in front of its stores, wherever
+// a workgroup forms one tile behind another, and it does not keep the distances that such moves need from products in assembly statements.
+// The compiler itself uses this file for nothing unless it runs out of the other 256 registers.
+template <int M, bool FIRST>
+__device__ __forceinline__ void product(bf16x8 x, bf16x8 y) {      // block M += x y, or = x y
+  if constexpr (FIRST) asm volatile("v_mfma_f32_16x16x32_bf16 a[%2:%3], %0, %1, 0" ::"v"(x), "v"(y), "n"(4 * M), "n"(4 * M + 3));
+  else                 asm volatile("v_mfma_f32_16x16x32_bf16 a[%2:%3], %0, %1, a[%2:%3]" ::"v"(x), "v"(y), "n"(4 * M), "n"(4 * M + 3));
+}
+template <int R>
+__device__ __forceinline__ float accumulator() {
+  float v;
+  asm volatile("v_accvgpr_read_b32 %0, a[%1]" : "=v"(v) : "n"(R));
+  return v;
+}
+// row block I: eight blocks of four columns each per lane
+template <int I>
+__device__ __forceinline__ void accumulators(f32x4 (&row)[8]) {
+  unrolled<8>([&](auto j) __attribute__((always_inline)) {
+    constexpr int R = 4 * (8 * I + decltype(j)::value);
+    row[decltype(j)::value] = f32x4{accumulator<R>(), accumulator<R + 1>(), accumulator<R + 2>(), accumulator<R + 3>()};
+  });
+}
+// the whole file is in use (what the register count of a kernel is taken from)
+#define DPPO_ALL_ACCUMULATORS() asm volatile("" ::: "a0","a1","a2","a3","a4","a5","a6","a7","a8","a9","a10","a11","a12","a13","a14","a15","a16","a17","a18","a19","a20","a21","a22","a23","a24","a25","a26","a27","a28","a29","a30","a31", \
+  "a32","a33","a34","a35","a36","a37","a38","a39","a40","a41","a42","a43","a44","a45","a46","a47","a48","a49","a50","a51","a52","a53","a54","a55","a56","a57","a58","a59","a60","a61","a62","a63", \
+  "a64","a65","a66","a67","a68","a69","a70","a71","a72","a73","a74","a75","a76","a77","a78","a79","a80","a81","a82","a83","a84","a85","a86","a87","a88","a89","a90","a91","a92","a93","a94","a95", \
+  "a96","a97","a98","a99","a100","a101","a102","a103","a104","a105","a106","a107","a108","a109","a110","a111","a112","a113","a114","a115","a116","a117","a118","a119","a120","a121","a122","a123","a124","a125","a126","a127", \
+  "a128","a129","a130","a131","a132","a133","a134","a135","a136","a137","a138","a139","a140","a141","a142","a143","a144","a145","a146","a147","a148","a149","a150","a151","a152","a153","a154","a155","a156","a157","a158","a159", \
+  "a160","a161","a162","a163","a164","a165","a166","a167","a168","a169","a170","a171","a172","a173","a174","a175","a176","a177","a178","a179","a180","a181","a182","a183","a184","a185","a186","a187","a188","a189","a190","a191", \
+  "a192","a193","a194","a195","a196","a197","a198","a199","a200","a201","a202","a203","a204","a205","a206","a207","a208","a209","a210","a211","a212","a213","a214","a215","a216","a217","a218","a219","a220","a221","a222","a223", \
+  "a224","a225","a226","a227","a228","a229","a230","a231","a232","a233","a234","a235","a236","a237","a238","a239","a240","a241","a242","a243","a244","a245","a246","a247","a248","a249","a250","a251","a252","a253","a254","a255")
+
 constexpr int kBM = 256, kBN = 256, kBK = 64;
 constexpr int kRowBytes = kBK * 2;                    // one panel row in LDS: 128 bytes = 8 vectors
 constexpr int kPanelBytes = kBM * kRowBytes;          // 32 KiB (kBM == kBN)
-constexpr int kStageBytes = 2 * kPanelBytes;          // A panel then B panel
 
 // LDS byte offset of the 16-byte vector `kvec` (0..7) of panel row `row`: the vector index is
 // XOR-ed with bits 1..3 of the row, so 16 consecutive rows at one kvec cover all 64 banks once.
@@ -90,356 +143,128 @@ __device__ __forceinline__ void store_row_block_bf16(uint16_t* __restrict__ C, i
   }
 }
 
-// One 256 x 256 tile.  FULL: all 256 rows and columns of the tile exist, so the stores need no
-// range checks.  A panel row past the matrix re-reads the last valid row: its products are never stored.
-// OUT selects what leaves the tile: bf16 (rounded to nearest even), fp32, or fp32 added to what C holds.
+// OUT selects what leaves a tile: bf16 (rounded to nearest even), fp32, or fp32 added to what C holds.
 // kOutStats: nothing of C is stored.  The tile's logits, rounded to bf16 as a stored tile would be,
 // leave as softmax statistics per row (GemmStats below): the forward of the hidden-state path then
 // never writes a logit to memory.
-// kOutSplit: the contraction is cut into `splits` ranges of steps, one workgroup per tile and range, and
-// the tile of a range leaves as fp32 for a second kernel to add up (see gemm_nn_splits).
+// kOutSplit: the contraction is cut into ranges of steps, and the tile of a range leaves as fp32 for a second
+// kernel to add up (see gemm_nn_splits).
 enum : int { kOutBf16 = 0, kOutF32 = 1, kOutF32Add = 2, kOutStats = 3, kOutSplit = 4 };
 
-// TA: A is [K, M]; TB: B is [K, N] (the contraction index is the ROW index of that operand; with
-// both, C = A^T B; with TB alone, C = A B).  The panel of such an operand
-// is then 64 rows of 512 bytes per step, and its fragment reads use the LDS transpose read
-// (ds_read_b64_tr_b16: out of a 16-lane group's sixteen 8-byte blocks, lane i gets element i%4 of
-// the blocks i/4, i/4 + 4, i/4 + 8, i/4 + 12), which turns four k rows of four neighbouring m
-// into the four consecutive k of one m that a matrix-core operand wants.
-template <bool FULL, int OUT, bool TA, bool TB>
-__device__ __forceinline__ void gemm_tile(unsigned char* lds0, unsigned char* lds1, const uint16_t* __restrict__ A, int64_t lda,
-                                          const uint16_t* __restrict__ B, int64_t ldb, void* __restrict__ Cv, int64_t ldc,
-                                          int M, int N, int K, int m0, int n0, const GemmStats& gs) {
-  const int tid = threadIdx.x, lane = tid & 63, wid = uniform_i(tid >> 6);
-  const int wm = wid >> 1, wn = wid & 1;
-  const int rows_a = min(kBM, M - m0), rows_b = min(kBN, N - n0);     // (TA / TB: columns of A / of B)
-  // requested here: the store at the end waits for no memory of its own
-  const float factor = (OUT == kOutBf16 && TA && TB) ? uniform_f(*gs.factor) : 1.f;
-  const uint32_t pitch_a = static_cast<uint32_t>(lda) * 2u, pitch_b = static_cast<uint32_t>(ldb) * 2u;
-
-  // Loader role: thread t moves LDS vector slot (t % 8) of rows t/8 + 32 i, i = 0..7, of each panel;
-  // the slot holds global k-vector slot ^ ((row >> 1) & 7), the same for all eight rows.
-  const int lrow = tid >> 3, lslot = tid & 7;
-  const uint32_t lkv = static_cast<uint32_t>((lslot ^ ((lrow >> 1) & 7)) << 4);
-
-  f32x4 acc[8][8];
+// What leaves a tile of kOutStats.  Per row of the tile, over its 256 columns (those below N), of the logits ROUNDED to bf16:
+// the integer offset b = -ceil(max * log2e), s = sum 2^(z*log2e + b) and t = sum 2^x * x (for
+// the entropy), the row's sampled token left out as in the loss kernels.  A lane holds 32
+// columns of each of its 8 rows; the four lanes of a row (lane, lane+16, +32, +48) combine by
+// register swaps, the two waves of a row through shared memory.  The logit of the row's sampled token leaves from the registers (one tile in V / 256 holds it).
+// With top-K ids the rounded tile itself goes to shared memory, into the panels of the products (64 rows of 512 bytes each, 32-byte blocks
+// XOR-ed with the row so that a 16-lane write spreads over the banks), from where the logits at the ids that fall into this tile are picked: then
+// no next tile's panels may be on their way, and a workgroup forms one tile.
+// A value of each of the four rows of 16 lanes, combined over the rows in every lane (register swaps between lane rows: a shuffle through shared memory is 120 cycles
+// that a wave alone on its SIMD waits for).
+template <typename F>
+__device__ __forceinline__ float across_rows(float v, F&& f) {
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = f(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return f(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+struct StatRoom {
+  float part[2][kBM][3];
+};
+// FULL: every column of the tile exists (rows that do not are zeros and leave nothing).  quarter: room for 64 rows of the tile each.
+template <bool FULL>
+__device__ __forceinline__ void tile_statistics(const int (&samp)[8], int M, int N, int m0, int n0, const GemmStats& gs, StatRoom& sh,
+                                                unsigned char* const (&quarter)[4], int wid, int lane) {
+  const int tid = wid * 64 + lane, wm = wid >> 1, wn = wid & 1, frow = lane & 15, fk = lane >> 4;
+  const int K1 = gs.Ktop + 1;
+  const int col0 = n0 + wn * 128;        // first column of this wave's quadrant
+  unrolled<8>([&](auto ic) __attribute__((always_inline)) {
+    constexpr int i = decltype(ic)::value;
+    f32x4 acc[8];
+    accumulators<i>(acc);
+    const int rl = wm * 128 + i * 16 + frow;            // row inside the tile
+    const int row = m0 + rl;
+    const int a_loc = (row < M && samp[i] >= 0 && samp[i] < N) ? samp[i] - col0 : -1;
+    float z[8][4];
 #pragma unroll
-  for (int i = 0; i < 8; ++i)
-#pragma unroll
-    for (int j = 0; j < 8; ++j)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.f;
-
-  // Fragment role: lane holds 8 consecutive k (k quarter `fk` of a 32-wide sub-step) of row `frow`
-  // of a 16-row block.  The swizzle depends on the row only through frow, so one offset per
-  // k-vector serves every block of both panels.
-  const int frow = lane & 15, fk = lane >> 4;
-  uint32_t foff[2];
-#pragma unroll
-  for (int ks = 0; ks < 2; ++ks) foff[ks] = lds_off(frow, ks * 4 + fk);
-  const uint32_t fbase_a = static_cast<uint32_t>(wm * 128) * kRowBytes;
-  const uint32_t fbase_b = kPanelBytes + static_cast<uint32_t>(wn * 128) * kRowBytes;
-  // TN panels: LDS row k (512 bytes = 32 slots of 16 bytes) holds in slot s the 8 columns of
-  // global slot s ^ (2 g(k)), g(k) = (k & 3) | ((k >> 3) & 1) << 2: the sixteen k rows one transpose
-  // read touches (k = 8 kg + j, kg = lane / 16, j = (lane % 16) / 4) then spread their 32-byte pieces
-  // over all banks.  Lane (kg, j, q = lane % 4) reads the 8 bytes of columns 4 q .. 4 q + 3 of block t
-  // in row 8 kg + j (+ 4 for the second half of the fragment, + 32 for the second sub-step).
-  uint32_t toff_a[8], toff_b[8];
-  if (TA || TB) {
-    const int kg = lane >> 4, j = (lane >> 2) & 3, q = lane & 3;
-    const uint32_t g2 = static_cast<uint32_t>(2 * (j | ((kg & 1) << 2)));
-    const uint32_t rowoff = static_cast<uint32_t>(8 * kg + j) * 512u + static_cast<uint32_t>(q & 1) * 8u;
-#pragma unroll
-    for (int t = 0; t < 8; ++t) {
-      toff_a[t] = rowoff + ((static_cast<uint32_t>(wm * 16 + 2 * t + (q >> 1)) ^ g2) << 4);
-      toff_b[t] = kPanelBytes + rowoff + ((static_cast<uint32_t>(wn * 16 + 2 * t + (q >> 1)) ^ g2) << 4);
+    for (int j = 0; j < 8; ++j) {
+      const uint32_t lo = pack_bf16x2(acc[j][0], acc[j][1]), hi = pack_bf16x2(acc[j][2], acc[j][3]);
+      z[j][0] = __uint_as_float(lo << 16); z[j][1] = __uint_as_float(lo & 0xffff0000u);
+      z[j][2] = __uint_as_float(hi << 16); z[j][3] = __uint_as_float(hi & 0xffff0000u);
     }
-  }
-  typedef short s16x4 __attribute__((ext_vector_type(4)));
-  typedef __attribute__((address_space(3))) s16x4* lds_s16x4_ptr;
-  // fragment t of a sub-step: 0..7 the B blocks, 8..15 the A blocks
-  auto read_frag = [&](const unsigned char* stage, int ks, int t) -> bf16x8 {
-    if (t < 8 ? TB : TA) {
-      const unsigned char* p = stage + (t < 8 ? toff_b[t & 7] : toff_a[t & 7]) + ks * (32 * 512);
-      const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(p));
-      const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(p + 4 * 512));
-      typedef short s16x8 __attribute__((ext_vector_type(8)));
-      const s16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-      return __builtin_bit_cast(bf16x8, v);
-    }
-    return *reinterpret_cast<const bf16x8*>(stage + (t < 8 ? fbase_b : fbase_a) + (t & 7) * 16 * kRowBytes + foff[ks]);
-  };
-#define DPPO_MFMA16(ACC, X, Y) asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(ACC) : "v"(X), "v"(Y))
-
-  // Pipeline over the contraction: step kt is multiplied out of LDS stage kt % 2; once every wave
-  // has read its last fragments of that stage (the barrier in the middle of the step) the panels
-  // of step kt+2 are loaded into it.  The fragments of each 32-wide sub-step are read from LDS one
-  // sub-step ahead of the matrix-core instructions that consume them.  One barrier per step.
-  const int nk = (TA && TB) ? (K + kBK - 1) / kBK : K / kBK;     // both by rows: rows past K read as zeros (range check)
-  // Global memory -> LDS directly (buffer_load ... lds): lane l of a wave-level load deposits its
-  // 16 bytes at (LDS base of the instruction) + 16 l, which is exactly the loader layout above for
-  // the base stage + panel + i * 4096 + wave * 1024.  No staging registers, no LDS store
-  // instructions; completion is counted with the other vector-memory loads.
-  typedef __attribute__((address_space(3))) void* lds_ptr_t;
-  // Load i of a panel moves rows lrow + 32 i (clamped to the last row the tile owns), through a
-  // range-checked view of exactly the rows this tile owns.  The k offset of a step goes into the
-  // base of that view (scalar arithmetic), so the per-lane offsets never change.
-  uint32_t vo_a[8], vo_b[8];
-  uint32_t bytes_a, bytes_b;
-  // by rows: load i of a panel (one KiB: two LDS rows) moves k rows 8 i + 2 wave + lane / 32, LDS slot lane % 32
-#pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const int k = 8 * i + 2 * wid + (lane >> 5);
-    const uint32_t gs = static_cast<uint32_t>(lane & 31) ^ static_cast<uint32_t>(2 * ((k & 3) | (((k >> 3) & 1) << 2)));
-    vo_a[i] = TA ? static_cast<uint32_t>(k) * pitch_a + (gs << 4) : static_cast<uint32_t>(min(lrow + 32 * i, rows_a - 1)) * pitch_a + lkv;
-    vo_b[i] = TB ? static_cast<uint32_t>(k) * pitch_b + (gs << 4) : static_cast<uint32_t>(min(lrow + 32 * i, rows_b - 1)) * pitch_b + lkv;
-  }
-  // by rows: bytes of a row from the tile's first column on, in whole 16-byte vectors (the range
-  // check works per 4 bytes, and the pitch, a multiple of 8 entries, covers them); else: bytes of the tile's rows
-  bytes_a = TA ? ((static_cast<uint32_t>(M - m0) * 2u + 15u) & ~15u) : static_cast<uint32_t>(rows_a - 1) * pitch_a + static_cast<uint32_t>(K) * 2u;
-  bytes_b = TB ? ((static_cast<uint32_t>(N - n0) * 2u + 15u) & ~15u) : static_cast<uint32_t>(rows_b - 1) * pitch_b + static_cast<uint32_t>(K) * 2u;
-  auto dma_one = [&](unsigned char* stage, int step, int idx) {     // load idx of the 16 of a step: 0..7 A panel, 8..15 B panel
-    const bool b_panel = idx >= 8;
-    const int i = idx & 7;
-    unsigned char* dst = stage + (b_panel ? kPanelBytes : 0) + wid * 1024 + i * 4096;
-    row_rsrc_t r;
-    // By rows: view of the step's k rows (those that exist) from the tile's first column on: what
-    // lies past the last row's end reads as zero, what lies past a row's M (N) columns belongs to
-    // C rows (columns) that are never stored.  Else: the tile's rows, from the step's k on.
-    const int kr = min(kBK, K - step * kBK);
-    const uint32_t koff = static_cast<uint32_t>(step) * (kBK * 2);
-    if (b_panel) r = TB ? make_row_rsrc(B + static_cast<int64_t>(step) * kBK * ldb + n0, static_cast<uint32_t>(kr - 1) * pitch_b + bytes_b)
-                        : make_row_rsrc(B + static_cast<int64_t>(n0) * ldb + step * kBK, bytes_b - koff);
-    else         r = TA ? make_row_rsrc(A + static_cast<int64_t>(step) * kBK * lda + m0, static_cast<uint32_t>(kr - 1) * pitch_a + bytes_a)
-                        : make_row_rsrc(A + static_cast<int64_t>(m0) * lda + step * kBK, bytes_a - koff);
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_ptr_t)dst, 16, b_panel ? vo_b[i] : vo_a[i], 0, 0, 0);
-  };
-  // This wave's panel loads have landed, then everyone's.  The wait is written out: a barrier by itself
-  // waits for LDS accesses only, and the wait for loads into LDS that the compiler usually puts in
-  // front of it (for its own fragment reads behind it) it leaves out where it thinks none is pending;
-  // it did in the fp32 forms, whose spill reloads in front of the loop confuse that count.
-  auto landed_barrier = [&]() {
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-  };
-#pragma unroll
-  for (int q = 0; q < 16; ++q) dma_one(lds0, 0, q);
-  landed_barrier();
-  bf16x8 f0[16], f1[16];      // [0..7] B blocks, [8..15] A blocks
-  // fragment q of the read order: the first A block, the 8 B blocks, then the other A blocks
-  constexpr int kOrder[16] = {8, 0, 1, 2, 3, 4, 5, 6, 7, 9, 10, 11, 12, 13, 14, 15};
-#pragma unroll
-  for (int t = 0; t < 16; ++t) f0[t] = read_frag(lds0, 0, t);
-  // One step of the contraction out of stage `cur`: two 32-wide sub-steps of 64 matrix-core
-  // instructions each (A block i = m / 8 against B block j = m % 8).  Every other instruction sits
-  // directly behind a matrix-core instruction, where it issues while that one executes.
-  // First sub-step: the 16 fragment reads of the second, behind the first 32 instructions, so they
-  // have landed when the barrier is reached.  Second sub-step: the 16 fragment reads of the next
-  // step's first sub-step and the 16 panel loads of the step after next.
-#define DPPO_PIN __builtin_amdgcn_sched_barrier(0)
-  auto step = [&](unsigned char* cur, unsigned char* nxt, int kt, auto steady) {
-    constexpr bool STEADY = decltype(steady)::value;
-    const bool more = STEADY || kt + 1 < nk, more2 = STEADY || kt + 2 < nk;
-#pragma unroll
-    for (int m = 0; m < 64; ++m) {
-      DPPO_MFMA16(acc[m >> 3][m & 7], f0[m & 7], f0[8 + (m >> 3)]); DPPO_PIN;
-      if (m < 32 && (m & 1) == 0) { f1[kOrder[m >> 1]] = read_frag(cur, 1, kOrder[m >> 1]); DPPO_PIN; }
-    }
-    // the next stage is complete (own loads waited for, then everyone's) and this one fully read
-    landed_barrier();
-    DPPO_PIN;
-#pragma unroll
-    for (int m = 0; m < 64; ++m) {
-      DPPO_MFMA16(acc[m >> 3][m & 7], f1[m & 7], f1[8 + (m >> 3)]); DPPO_PIN;
-      if ((m & 3) == 0) { if (more) f0[kOrder[m >> 2]] = read_frag(nxt, 0, kOrder[m >> 2]); DPPO_PIN; }
-      if ((m & 3) == 2) { if (more2) dma_one(cur, kt + 2, m >> 2); DPPO_PIN; }
-    }
-  };
-  if (nk > 1) {
-#pragma unroll
-    for (int q = 0; q < 16; ++q) dma_one(lds1, 1, q);
-  }
-  int kt = 0;
-  for (; kt + 3 < nk; kt += 2) {
-    step(lds0, lds1, kt, std::true_type{});
-    step(lds1, lds0, kt + 1, std::true_type{});
-  }
-  for (; kt + 1 < nk; kt += 2) {
-    step(lds0, lds1, kt, std::false_type{});
-    step(lds1, lds0, kt + 1, std::false_type{});
-  }
-  if (kt < nk) step(lds0, lds1, kt, std::false_type{});
-  // the matrix-core results must have landed before other instructions read the accumulators
-  // (the products are assembly statements, so the compiler does not keep that distance by itself).
-  // The accumulators pass through the wait, so that nothing the compiler makes of them, a spill
-  // included, reads one in front of it.
-#define DPPO_THROUGH(CODE, I) asm volatile(CODE : "+a"(acc[I][0]), "+a"(acc[I][1]), "+a"(acc[I][2]), "+a"(acc[I][3]), \
-                                               "+a"(acc[I][4]), "+a"(acc[I][5]), "+a"(acc[I][6]), "+a"(acc[I][7]) :: "memory")
-  DPPO_THROUGH("s_nop 15\n\ts_nop 15", 0);
-#pragma unroll
-  for (int i = 1; i < 8; ++i) DPPO_THROUGH("", i);
-#undef DPPO_THROUGH
-  DPPO_PIN;
-
-  // The products were formed with the operands swapped (B fragment first), so a lane's four
-  // accumulators of a 16 x 16 block are four consecutive COLUMNS (lane/16)*4 + 0..3 of row lane%16.
-  if (OUT == kOutStats) {
-    // ---- softmax statistics of the tile instead of the tile ------------------------------------
-    // Per row of the tile, over its 256 columns (those below N), of the logits ROUNDED to bf16:
-    // the integer offset b = -ceil(max * log2e), s = sum 2^(z*log2e + b) and t = sum 2^x * x (for
-    // the entropy), the row's sampled token left out as in the loss kernels.  A lane holds 32
-    // columns of each of its 8 rows; the four lanes of a row (lane, lane+16, +32, +48) combine by
-    // shuffles, the two waves of a row through shared memory.  The rounded tile itself goes to
-    // shared memory (the two stages are free now: 128 rows of 512 bytes each, 32-byte blocks
-    // XOR-ed with the row so that a 16-lane write spreads over the banks), from where the logits at
-    // the sampled and the top-K ids that fall into this tile are picked.
-    __shared__ float sh_part[2][kBM][3];
-    // the sampled ids of the lane's eight rows, requested in one go (one memory latency, which
-    // the barrier covers in part, instead of one per row block)
-    int samp[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int row = m0 + wm * 128 + i * 16 + frow;
-      samp[i] = (row < M) ? gs.sampled[row] : -1;
-    }
-    __syncthreads();                       // every wave has read its last fragments: the stages can be overwritten
-    unsigned char* half = wm ? lds1 : lds0;
-    const int col0 = n0 + wn * 128;        // first column of this wave's quadrant
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int rl = i * 16 + frow;                       // row inside the wave's 128
-      const int row = m0 + wm * 128 + rl;
-      const int a_loc = (row < M && samp[i] >= 0) ? samp[i] - col0 : -1;
-      float z[8][4];
+    if (gs.Ktop > 0) {
+      unsigned char* rows = (wm ? quarter[2 + i / 4] : quarter[i / 4]) + ((i & 3) * 16 + frow) * 512;
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
-        const uint32_t lo = pack_bf16x2(acc[i][j][0], acc[i][j][1]), hi = pack_bf16x2(acc[i][j][2], acc[i][j][3]);
         typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-        *reinterpret_cast<u32x2*>(half + rl * 512 + (((wn * 8 + j) ^ frow) << 5) + fk * 8) = u32x2{lo, hi};
-        z[j][0] = __uint_as_float(lo << 16); z[j][1] = __uint_as_float(lo & 0xffff0000u);
-        z[j][2] = __uint_as_float(hi << 16); z[j][3] = __uint_as_float(hi & 0xffff0000u);
+        *reinterpret_cast<u32x2*>(rows + (((wn * 8 + j) ^ frow) << 5) + fk * 8) =
+            u32x2{(__float_as_uint(z[j][0]) >> 16) | __float_as_uint(z[j][1]), (__float_as_uint(z[j][2]) >> 16) | __float_as_uint(z[j][3])};
       }
-      // columns that do not exist, and (rarely: one tile in V / 256 holds a row's) the sampled token's
-      if (!FULL || __any(a_loc >= 0 && a_loc < 128)) {
+    }
+    // columns that do not exist, and (rarely: one tile in V / 256 holds a row's) the sampled token's
+    if (!FULL || __any(a_loc >= 0 && a_loc < 128)) {
 #pragma unroll
-        for (int j = 0; j < 8; ++j)
+      for (int j = 0; j < 8; ++j)
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const int cl = j * 16 + fk * 4 + e;
-            if ((!FULL && col0 + cl >= N) || cl == a_loc) z[j][e] = -INFINITY;
-          }
-      }
-      float mx = -INFINITY;
-#pragma unroll
-      for (int j = 0; j < 8; ++j) mx = fmaxf(fmaxf(fmaxf(mx, z[j][0]), z[j][1]), fmaxf(z[j][2], z[j][3]));
-      mx = fmaxf(mx, __shfl_xor(mx, 16));
-      mx = fmaxf(mx, __shfl_xor(mx, 32));
-      const float b = -ceilf(fmaxf(mx, kNegBig) * kLog2e);
-      float s = 0.f, t = 0.f;
-      if (gs.want_t) {
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          float e4[4];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const float x = fmaf(z[j][e], kLog2e, b);
-            e4[e] = fast_exp2(x);
-            t = fma_ex(e4[e], x, t);
-          }
-          s += (e4[0] + e4[1]) + (e4[2] + e4[3]);
+        for (int e = 0; e < 4; ++e) {
+          const int cl = j * 16 + fk * 4 + e;
+          if (cl == a_loc) gs.gath[static_cast<int64_t>(row) * K1] = z[j][e];
+          if ((!FULL && col0 + cl >= N) || cl == a_loc) z[j][e] = -INFINITY;
         }
-      } else {
-#pragma unroll
-        for (int j = 0; j < 8; ++j)
-          s += (fast_exp2(fmaf(z[j][0], kLog2e, b)) + fast_exp2(fmaf(z[j][1], kLog2e, b))) +
-               (fast_exp2(fmaf(z[j][2], kLog2e, b)) + fast_exp2(fmaf(z[j][3], kLog2e, b)));
-      }
-      s += __shfl_xor(s, 16); s += __shfl_xor(s, 32);
-      t += __shfl_xor(t, 16); t += __shfl_xor(t, 32);
-      if (fk == 0) { sh_part[wn][wm * 128 + rl][0] = b; sh_part[wn][wm * 128 + rl][1] = s; sh_part[wn][wm * 128 + rl][2] = t; }
     }
-    __syncthreads();
-    {
-      const int row = m0 + tid;
-      const float b0 = sh_part[0][tid][0], b1 = sh_part[1][tid][0], b = fminf(b0, b1);
-      const float d0 = b - b0, d1 = b - b1, c0 = fast_exp2(d0), c1 = fast_exp2(d1);       // exact powers of two
-      const float s = sh_part[0][tid][1] * c0 + sh_part[1][tid][1] * c1;
-      const float t = c0 * fmaf(d0, sh_part[0][tid][1], sh_part[0][tid][2]) + c1 * fmaf(d1, sh_part[1][tid][1], sh_part[1][tid][2]);
-      if (row < M) gs.part[static_cast<int64_t>(row) * gs.tiles_n + n0 / kBN] = f32x4{b, s, t, 0.f};
-    }
-    // the rounded logits at the rows' sampled and top-K ids that fall into this tile; ids fetched
-    // four at a time (one memory latency per four entries)
-    const int K1 = gs.Ktop + 1;
-    for (int idx0 = tid; idx0 < kBM * K1; idx0 += 4 * 256) {
-      int id[4];
+    float mx = -INFINITY;
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int idx = idx0 + u * 256, rl = idx / K1, k = idx - rl * K1, row = m0 + rl;
-        id[u] = -1;
-        if (idx < kBM * K1 && row < M) id[u] = (k == 0) ? gs.sampled[row] : gs.tk_ids[static_cast<int64_t>(row) * gs.Ktop + (k - 1)];
-      }
+    for (int j = 0; j < 8; ++j) mx = fmaxf(fmaxf(fmaxf(mx, z[j][0]), z[j][1]), fmaxf(z[j][2], z[j][3]));
+    mx = across_rows(mx, [](float x, float y) { return fmaxf(x, y); });
+    const float b = -ceilf(fmaxf(mx, kNegBig) * kLog2e);
+    float s = 0.f, t = 0.f;
+    if (gs.want_t) {
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int idx = idx0 + u * 256, rl = idx / K1, k = idx - rl * K1, row = m0 + rl;
-        const int c = id[u] - n0;
-        if (id[u] >= 0 && c >= 0 && c < kBN && id[u] < N) {
-          const unsigned char* src = ((rl >> 7) ? lds1 : lds0) + (rl & 127) * 512 + (((c >> 4) ^ (rl & 15)) << 5) + (c & 15) * 2;
-          gs.gath[static_cast<int64_t>(row) * K1 + k] = bf16_bits_to_float(*reinterpret_cast<const uint16_t*>(src));
+      for (int j = 0; j < 8; ++j) {
+        float e4[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float x = fmaf(z[j][e], kLog2e, b);
+          e4[e] = fast_exp2(x);
+          t = fma_ex(e4[e], x, t);
         }
+        s += (e4[0] + e4[1]) + (e4[2] + e4[3]);
       }
-    }
-    return;
-  }
-  // Store.  bf16: see store_row_block_bf16.  fp32: 16 bytes per lane as they are.
-  if (OUT == kOutF32Add && FULL) {
-    // C += tile: what C holds is requested one block of 16 rows AHEAD of the block being added and
-    // stored (eight 16-byte loads per lane in flight behind eight stores), so that a lane waits for
-    // memory eight times per tile and not sixty-four times.  (Written as load - add - store per
-    // vector, the compiler keeps that order, every load behind the store in front of it.)
-    auto cptr = [&](int i, int j) {
-      const int row = m0 + wm * 128 + i * 16 + frow, col = n0 + wn * 128 + j * 16 + fk * 4;
-      return reinterpret_cast<f32x4*>(static_cast<float*>(Cv) + static_cast<int64_t>(row) * ldc + col);
-    };
-    f32x4 cur[8], nxt[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) cur[j] = __builtin_nontemporal_load(cptr(0, j));
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      if (i + 1 < 8) {
-#pragma unroll
-        for (int j = 0; j < 8; ++j) nxt[j] = __builtin_nontemporal_load(cptr(i + 1, j));
-      }
-#pragma unroll
-      for (int j = 0; j < 8; ++j) *cptr(i, j) = acc[i][j] + cur[j];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) cur[j] = nxt[j];
-    }
-    return;
-  }
-#pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const int row = m0 + wm * 128 + i * 16 + frow;
-    if (OUT == kOutBf16) {
-      if (TA && TB) {
-#pragma unroll
-        for (int j = 0; j < 8; ++j) acc[i][j] *= factor;
-      }
-      store_row_block_bf16<FULL>(static_cast<uint16_t*>(Cv), ldc, M, N, row, n0 + wn * 128, fk, acc[i]);
     } else {
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        // fp32 out (the host requires 16-byte aligned rows for these forms)
-        const int col = n0 + wn * 128 + j * 16 + fk * 4;
-        float* dst = static_cast<float*>(Cv) + static_cast<int64_t>(row) * ldc + col;
-        f32x4 v = acc[i][j];
-        if (FULL || (row < M && col + 3 < N)) {
-          if (OUT == kOutF32Add) v += *reinterpret_cast<const f32x4*>(dst);
-          *reinterpret_cast<f32x4*>(dst) = v;
-        } else if (row < M) {
+      for (int j = 0; j < 8; ++j)
+        s += (fast_exp2(fmaf(z[j][0], kLog2e, b)) + fast_exp2(fmaf(z[j][1], kLog2e, b))) +
+             (fast_exp2(fmaf(z[j][2], kLog2e, b)) + fast_exp2(fmaf(z[j][3], kLog2e, b)));
+    }
+    s = across_rows(s, [](float x, float y) { return x + y; });
+    if (gs.want_t) t = across_rows(t, [](float x, float y) { return x + y; });
+    if (fk == 0) { sh.part[wn][rl][0] = b; sh.part[wn][rl][1] = s; sh.part[wn][rl][2] = t; }
+  });
+  __syncthreads();
+  {
+    const int row = m0 + tid;
+    const float b0 = sh.part[0][tid][0], b1 = sh.part[1][tid][0], b = fminf(b0, b1);
+    const float d0 = b - b0, d1 = b - b1, c0 = fast_exp2(d0), c1 = fast_exp2(d1);       // exact powers of two
+    const float s = sh.part[0][tid][1] * c0 + sh.part[1][tid][1] * c1;
+    const float t = c0 * fmaf(d0, sh.part[0][tid][1], sh.part[0][tid][2]) + c1 * fmaf(d1, sh.part[1][tid][1], sh.part[1][tid][2]);
+    if (row < M) gs.part[static_cast<int64_t>(row) * gs.tiles_n + n0 / kBN] = f32x4{b, s, t, 0.f};
+  }
+  // ids fetched sixteen at a time (one memory latency)
+  const int n_ids = min(kBM, M - m0) * gs.Ktop;
+  const int32_t* ids = gs.tk_ids + static_cast<int64_t>(m0) * gs.Ktop;
+  constexpr int kAhead = 16;
+  for (int i0 = tid; i0 < n_ids; i0 += kAhead * kBM) {
+    int id[kAhead];
 #pragma unroll
-          for (int e = 0; e < 4; ++e)
-            if (col + e < N) dst[e] = (OUT == kOutF32Add ? dst[e] : 0.f) + v[e];
-        }
+    for (int u = 0; u < kAhead; ++u) id[u] = (i0 + u * kBM < n_ids) ? ids[i0 + u * kBM] : -1;
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      const int c = id[u] - n0;
+      if (id[u] >= 0 && c >= 0 && c < kBN && id[u] < N) {
+        const int idx = i0 + u * kBM, r = idx / gs.Ktop, k = idx - r * gs.Ktop, q = r >> 6;
+        const unsigned char* rows = q == 0 ? quarter[0] : q == 1 ? quarter[1] : q == 2 ? quarter[2] : quarter[3];
+        gs.gath[static_cast<int64_t>(m0 + r) * K1 + 1 + k] =
+            bf16_bits_to_float(*reinterpret_cast<const uint16_t*>(rows + (r & 63) * 512 + (((c >> 4) ^ (r & 15)) << 5) + (c & 15) * 2));
       }
     }
   }
@@ -464,11 +289,18 @@ __device__ __forceinline__ void gemm_tile(unsigned char* lds0, unsigned char* ld
 //    same rounds on fewer compute units at a higher clock.
 struct TileMap {
   int tiles_m, tiles_n, group_m, group_n;
-  int rows, cols;          // tiles_m, tiles_n, or up to the next multiple of the block's
-  int tiles, per_die;      // rows * cols; numbers each die takes (of all ranges of the contraction)
+  int tiles;               // tiles_m * tiles_n
+  int numbers, per_die;    // the same with whole edge blocks where the shares of the dies count those; a die's share (of all ranges)
   int split_steps;         // kOutSplit: steps of a range of the contraction
+  int slots, run;          // workgroups of a die that run side by side; tiles each forms, one behind the other
+  int start[9];            // die d: the tiles (of all ranges of the contraction) numbered start[d] .. start[d + 1] - 1
 };
-TileMap tile_map(int64_t M, int64_t N, int64_t K, int64_t ranges) {
+// A run is eight tiles at most, so that a workgroup that starts late, another kernel being on its compute unit, holds up no more than that, and 512 steps at
+// most; tiles of 128 steps and more are worth no run: they gain a per cent by it, and workgroups that drift apart lose the panels they
+// share.  Runs of 1 / 2 / 4 / 8 / 32 tiles, us, V = 151936: A B^T 2048 x 2048 975 / 954 / 943 / 938 / 933, 8192 x 4096 6838 / 6770 / 6738 / 6735 / 6712; A^T B
+// 2048 x 2048 983 / 958 / 950 / 945 / 944, 8192 x 4096 (128 steps) 7150 / 7283 / 7377 / 7464 / 7570.
+constexpr int kMaxRun = 8;
+TileMap tile_map(int64_t M, int64_t N, int64_t K, int64_t ranges, int cus, int max_run = kMaxRun) {
   TileMap t;
   t.tiles_m = static_cast<int>((M + kBM - 1) / kBM);
   t.tiles_n = static_cast<int>((N + kBN - 1) / kBN);
@@ -482,52 +314,431 @@ TileMap tile_map(int64_t M, int64_t N, int64_t K, int64_t ranges) {
                                     (steps >= 256 && cut_rounds >= 2 && whole_rounds == cut_rounds));
   t.group_m = even || t.tiles_m % 8 == 0 || (tall && t.tiles_m > 8) ? 8 : t.tiles_m < 8 ? t.tiles_m : 4;
   t.group_n = 32 / t.group_m;
-  const int whole_m = (t.tiles_m + t.group_m - 1) / t.group_m * t.group_m, whole_n = (t.tiles_n + t.group_n - 1) / t.group_n * t.group_n;
-  const bool whole = even || (t.group_m * t.group_n == 32 && static_cast<int64_t>(whole_m) * whole_n * 100 < tiles * 103);
-  t.rows = whole ? whole_m : t.tiles_m;
-  t.cols = whole ? whole_n : t.tiles_n;
-  t.tiles = t.rows * t.cols;
-  const int64_t share = (t.tiles * ranges + 7) / 8;
+  const int64_t whole_m = (t.tiles_m + t.group_m - 1) / t.group_m * t.group_m, whole_n = (t.tiles_n + t.group_n - 1) / t.group_n * t.group_n;
+  const bool whole = even || (t.group_m * t.group_n == 32 && whole_m * whole_n * 100 < tiles * 103);
+  const int64_t rows = whole ? whole_m : t.tiles_m, cols = whole ? whole_n : t.tiles_n;
+  const int64_t share = (rows * cols * ranges + 7) / 8;
   // from eight rounds of workgroups per die on, dies start with a whole block (the last round is partly empty either way)
-  t.per_die = static_cast<int>(even || share >= 256 ? (share + 31) / 32 * 32 : share);
+  const int64_t per_die = even || share >= 256 ? (share + 31) / 32 * 32 : share;
+  t.tiles = static_cast<int>(tiles);
+  t.numbers = static_cast<int>(rows * cols);
+  t.per_die = static_cast<int>(per_die);
   t.split_steps = 0;
+  // tiles in front of number v, edge blocks counted as the dies' shares count them (whole or cut)
+  auto before = [&](int64_t v) -> int64_t {
+    const int64_t range = v / (rows * cols);
+    if (range >= ranges) return ranges * tiles;
+    v -= range * rows * cols;
+    const int64_t bn = v / (t.group_n * rows);
+    v -= bn * t.group_n * rows;
+    const int64_t width = std::min<int64_t>(t.group_n, cols - bn * t.group_n), real_width = std::min<int64_t>(t.group_n, t.tiles_n - bn * t.group_n);
+    const int64_t bm = v / (t.group_m * width);
+    v -= bm * t.group_m * width;
+    const int64_t height = std::min<int64_t>(t.group_m, rows - bm * t.group_m), real_height = std::min<int64_t>(t.group_m, t.tiles_m - bm * t.group_m);
+    const int64_t q = v / height, r = v % height;
+    return range * tiles + bn * t.group_n * t.tiles_m + bm * t.group_m * real_width + std::min(q, real_width) * real_height +
+           (q < real_width ? std::min(r, real_height) : 0);
+  };
+  int64_t most = 0;
+  for (int d = 0; d <= 8; ++d) {
+    t.start[d] = static_cast<int>(d == 8 ? ranges * tiles : before(d * per_die));
+    if (d > 0) most = std::max<int64_t>(most, t.start[d] - t.start[d - 1]);
+  }
+  t.slots = static_cast<int>(std::min<int64_t>(most, std::max(1, cus / 8)));
+  const int64_t rounds = (most + t.slots - 1) / t.slots;
+  t.run = static_cast<int>(std::min<int64_t>(rounds, steps >= 128 ? 1 : std::max<int64_t>(1, std::min<int64_t>(max_run, 512 / steps))));
   return t;
 }
-inline dim3 tile_grid(const TileMap& t) { return dim3(8u * static_cast<unsigned>(t.per_die)); }
+inline dim3 tile_grid(const TileMap& t) {
+  int most = 0;
+  for (int d = 0; d < 8; ++d) most = std::max(most, t.start[d + 1] - t.start[d]);
+  const int per_run = t.slots * t.run;
+  return dim3(8u * static_cast<unsigned>(t.slots) * static_cast<unsigned>((most + per_run - 1) / per_run));
+}
 
+// One tile as the kernel sees it: the operands from the tile's first row (by rows: column) and the range's first k on.
+struct TileAt {
+  const uint16_t *a, *b;
+  void* c;
+  uint32_t bytes_a, bytes_b;      // of the views below
+  int m0, n0, K;
+};
+
+// TA: A is [K, M]; TB: B is [K, N] (the contraction index is the ROW index of that operand; with
+// both, C = A^T B; with TB alone, C = A B).  The panel of such an operand
+// is then 64 rows of 512 bytes per step, and its fragment reads use the LDS transpose read
+// (ds_read_b64_tr_b16: out of a 16-lane group's sixteen 8-byte blocks, lane i gets element i%4 of
+// the blocks i/4, i/4 + 4, i/4 + 8, i/4 + 12), which turns four k rows of four neighbouring m
+// into the four consecutive k of one m that a matrix-core operand wants.
+//
+// A workgroup forms a run of tiles (TileMap::run), one behind the other: while it multiplies the last steps of a
+// tile it already loads the first of the next, and its stores travel behind the next tile's products.
 template <int OUT, bool TA, bool TB>
 __global__ __launch_bounds__(256) void dppo_gemm_nt_kernel(const uint16_t* __restrict__ A, int64_t lda,
                                                            const uint16_t* __restrict__ B, int64_t ldb,
                                                            void* __restrict__ C, int64_t ldc, int M, int N, int K,
                                                            const TileMap map, const GemmStats gs) {
-  // two stages of (A panel | B panel): 2 x 64 KiB of the compute unit's 160 KiB
-  __shared__ __attribute__((aligned(16))) unsigned char lds0[kStageBytes];
-  __shared__ __attribute__((aligned(16))) unsigned char lds1[kStageBytes];
-  const int die = static_cast<int>(blockIdx.x) & 7, slot = static_cast<int>(blockIdx.x) >> 3;      // slot-th workgroup of its die
-  int tile = die * map.per_die + slot;
-  if (OUT == kOutSplit) {
-    // the range of the contraction is the outermost index, so the workgroups of a die still share panels
-    const int split = tile / map.tiles, k0 = split * map.split_steps * kBK;
-    if (k0 >= K) return;                              // past the last range (the dies' shares are rounded up)
-    tile -= split * map.tiles;
-    A += k0;
-    B += static_cast<int64_t>(k0) * (TB ? ldb : 1);
-    C = static_cast<float*>(C) + static_cast<int64_t>(split) * M * ldc;
-    K = min(K - k0, map.split_steps * kBK);
+  // Five panels, all of the compute unit's shared memory: three of the operand that comes from far (`far`: A if FAR_A), two of the other.
+  __shared__ __attribute__((aligned(16))) unsigned char panel0[kPanelBytes];
+  __shared__ __attribute__((aligned(16))) unsigned char panel1[kPanelBytes];
+  __shared__ __attribute__((aligned(16))) unsigned char panel2[kPanelBytes];
+  __shared__ __attribute__((aligned(16))) unsigned char panel3[kPanelBytes];
+  __shared__ __attribute__((aligned(16))) unsigned char panel4[kPanelBytes];
+  auto far_panel = [&](int step) { return step % 3 == 0 ? panel0 : step % 3 == 1 ? panel1 : panel2; };
+  auto near_panel = [&](int step) { return step % 2 == 0 ? panel3 : panel4; };
+  constexpr bool FAR_A = TA;
+  const int tid = threadIdx.x, lane = tid & 63, wid = uniform_i(tid >> 6);
+  const int wm = wid >> 1, wn = wid & 1;
+
+  // This workgroup's run: `map.run` tiles of its die, `map.slots` apart.
+  const int die = static_cast<int>(blockIdx.x) & 7, nth = static_cast<int>(blockIdx.x) >> 3;      // nth workgroup of its die
+  const int group = nth / map.slots;
+  const int first = map.start[die] + group * map.slots * map.run;
+  const int end = min(first + map.slots * map.run, map.start[die + 1]);
+  int number = first + (nth - group * map.slots);
+  if (number >= end) return;
+
+  // requested here: no store waits for it
+  const float factor = (OUT == kOutBf16 && TA && TB) ? uniform_f(*gs.factor) : 1.f;
+  const uint32_t pitch_a = static_cast<uint32_t>(lda) * 2u, pitch_b = static_cast<uint32_t>(ldb) * 2u;
+  auto locate = [&](int v) -> TileAt {
+    TileAt t;
+    t.a = A; t.b = B; t.c = C; t.K = K;
+    if (OUT == kOutSplit) {
+      // the range of the contraction is the outermost index, so the workgroups of a die still share panels
+      const int split = v / map.tiles, k0 = split * map.split_steps * kBK;
+      v -= split * map.tiles;
+      t.a += TA ? static_cast<int64_t>(k0) * lda : static_cast<int64_t>(k0);
+      t.b += TB ? static_cast<int64_t>(k0) * ldb : static_cast<int64_t>(k0);
+      t.c = static_cast<float*>(C) + static_cast<int64_t>(split) * M * ldc;
+      t.K = min(K - k0, map.split_steps * kBK);
+    }
+    // blocks run down the matrix, then on to the next group_n columns of tiles
+    const int bn = v / (map.group_n * map.tiles_m);
+    v -= bn * (map.group_n * map.tiles_m);
+    const int width = min(map.group_n, map.tiles_n - bn * map.group_n);
+    const int bm = v / (map.group_m * width);
+    v -= bm * (map.group_m * width);
+    const int height = min(map.group_m, map.tiles_m - bm * map.group_m);
+    const int q = v / height;
+    t.m0 = (bm * map.group_m + v - q * height) * kBM;
+    t.n0 = (bn * map.group_n + q) * kBN;
+    t.a += TA ? static_cast<int64_t>(t.m0) : static_cast<int64_t>(t.m0) * lda;
+    t.b += TB ? static_cast<int64_t>(t.n0) : static_cast<int64_t>(t.n0) * ldb;
+    // by rows: bytes of a row from the tile's first column on, in whole 16-byte vectors (the range
+    // check works per 4 bytes, and the pitch, a multiple of 8 entries, covers them); else: bytes of the tile's rows
+    t.bytes_a = TA ? ((static_cast<uint32_t>(M - t.m0) * 2u + 15u) & ~15u) : static_cast<uint32_t>(min(kBM, M - t.m0) - 1) * pitch_a + static_cast<uint32_t>(t.K) * 2u;
+    t.bytes_b = TB ? ((static_cast<uint32_t>(N - t.n0) * 2u + 15u) & ~15u) : static_cast<uint32_t>(min(kBN, N - t.n0) - 1) * pitch_b + static_cast<uint32_t>(t.K) * 2u;
+    return t;
+  };
+  // both by rows: rows past K read as zeros (range check)
+  auto steps_of = [&](const TileAt& t) { return uniform_i((TA && TB) ? (t.K + kBK - 1) / kBK : t.K / kBK); };
+  // Range-checked view of what a step of a tile reads of one operand (nothing of it, live = false: every load returns zeros and
+  // touches no memory).  By rows: the step's k rows (those that exist) from the tile's first column on: what lies past the last row's
+  // end reads as zero, what lies past a row's M (N) columns belongs to C rows (columns) that are never stored.  Else: the tile's rows,
+  // from the step's k on; rows past the matrix read as zeros.  The k offset of a step goes into the base (scalar arithmetic), so
+  // the per-lane offsets are the same for every step of every tile.
+  auto view_a = [&](const TileAt& t, int step, bool live) -> row_rsrc_t {
+    if (TA) return make_row_rsrc(t.a + static_cast<int64_t>(step) * kBK * lda, live ? static_cast<uint32_t>(min(kBK, t.K - step * kBK) - 1) * pitch_a + t.bytes_a : 0u);
+    return make_row_rsrc(t.a + step * kBK, live ? t.bytes_a - static_cast<uint32_t>(step) * (kBK * 2) : 0u);
+  };
+  auto view_b = [&](const TileAt& t, int step, bool live) -> row_rsrc_t {
+    if (TB) return make_row_rsrc(t.b + static_cast<int64_t>(step) * kBK * ldb, live ? static_cast<uint32_t>(min(kBK, t.K - step * kBK) - 1) * pitch_b + t.bytes_b : 0u);
+    return make_row_rsrc(t.b + step * kBK, live ? t.bytes_b - static_cast<uint32_t>(step) * (kBK * 2) : 0u);
+  };
+
+  // Loader role: thread t moves LDS vector slot (t % 8) of rows t/8 + 32 i, i = 0..7, of each panel;
+  // the slot holds global k-vector slot ^ ((row >> 1) & 7), the same for all eight rows.
+  // By rows: load i of a panel (one KiB: two LDS rows) moves k rows 8 i + 2 wave + lane / 32, LDS slot lane % 32: the same global slot for every other i.
+  // What differs from load to load is a scalar offset.
+  auto loader = [&](bool by_rows, uint32_t pitch, int i) -> uint32_t {
+    if (!by_rows) return static_cast<uint32_t>(tid >> 3) * pitch + static_cast<uint32_t>(((tid & 7) ^ ((tid >> 4) & 7)) << 4);
+    const int k = 8 * i + 2 * wid + (lane >> 5);
+    return static_cast<uint32_t>(k) * pitch + ((static_cast<uint32_t>(lane & 31) ^ static_cast<uint32_t>(2 * ((k & 3) | (((k >> 3) & 1) << 2)))) << 4);
+  };
+  const uint32_t vo_a[2] = {loader(TA, pitch_a, 0), loader(TA, pitch_a, 1)}, vo_b[2] = {loader(TB, pitch_b, 0), loader(TB, pitch_b, 1)};
+  // Global memory -> LDS directly (buffer_load ... lds): lane l of a wave-level load deposits its
+  // 16 bytes at (LDS base of the instruction) + 16 l, which is exactly the loader layout above for
+  // the base stage + panel + i * 4096 + wave * 1024.  No staging registers, no LDS store
+  // instructions; completion is counted with the other vector-memory loads.
+  typedef __attribute__((address_space(3))) void* lds_ptr_t;
+  auto load_a = [&](unsigned char* panel, row_rsrc_t r, int i) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_ptr_t)(panel + wid * 1024 + i * 4096), 16, vo_a[TA ? i & 1 : 0], (TA ? 16u * (i >> 1) : 32u * i) * pitch_a, 0, 0);
+  };
+  auto load_b = [&](unsigned char* panel, row_rsrc_t r, int i) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_ptr_t)(panel + wid * 1024 + i * 4096), 16, vo_b[TB ? i & 1 : 0], (TB ? 16u * (i >> 1) : 32u * i) * pitch_b, 0, 0);
+  };
+  // load i of the eight of a panel of the far / near operand
+  auto load_far = [&](unsigned char* panel, row_rsrc_t r, int i) { if (FAR_A) load_a(panel, r, i); else load_b(panel, r, i); };
+  auto load_near = [&](unsigned char* panel, row_rsrc_t r, int i) { if (FAR_A) load_b(panel, r, i); else load_a(panel, r, i); };
+  auto view_far = [&](const TileAt& t, int step, bool live) { return FAR_A ? view_a(t, step, live) : view_b(t, step, live); };
+  auto view_near = [&](const TileAt& t, int step, bool live) { return FAR_A ? view_b(t, step, live) : view_a(t, step, live); };
+
+  // Fragment role: lane holds 8 consecutive k (k quarter `fk` of a 32-wide sub-step) of row `frow`
+  // of a 16-row block.  The swizzle depends on the row only through frow, so one offset per
+  // k-vector serves every block of both panels.
+  const int frow = lane & 15, fk = lane >> 4;
+  uint32_t foff[2];
+#pragma unroll
+  for (int ks = 0; ks < 2; ++ks) foff[ks] = lds_off(frow, ks * 4 + fk);
+  const uint32_t fbase_a = static_cast<uint32_t>(wm * 128) * kRowBytes;
+  const uint32_t fbase_b = static_cast<uint32_t>(wn * 128) * kRowBytes;
+  // TN panels: LDS row k (512 bytes = 32 slots of 16 bytes) holds in slot s the 8 columns of
+  // global slot s ^ (2 g(k)), g(k) = (k & 3) | ((k >> 3) & 1) << 2: the sixteen k rows one transpose
+  // read touches (k = 8 kg + j, kg = lane / 16, j = (lane % 16) / 4) then spread their 32-byte pieces
+  // over all banks.  Lane (kg, j, q = lane % 4) reads the 8 bytes of columns 4 q .. 4 q + 3 of block t
+  // in row 8 kg + j (+ 4 for the second half of the fragment, + 32 for the second sub-step).
+  uint32_t toff_a[8], toff_b[8];
+  if (TA || TB) {
+    const int kg = lane >> 4, j = (lane >> 2) & 3, q = lane & 3;
+    const uint32_t g2 = static_cast<uint32_t>(2 * (j | ((kg & 1) << 2)));
+    const uint32_t rowoff = static_cast<uint32_t>(8 * kg + j) * 512u + static_cast<uint32_t>(q & 1) * 8u;
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+      toff_a[t] = rowoff + ((static_cast<uint32_t>(wm * 16 + 2 * t + (q >> 1)) ^ g2) << 4);
+      toff_b[t] = rowoff + ((static_cast<uint32_t>(wn * 16 + 2 * t + (q >> 1)) ^ g2) << 4);
+    }
   }
-  if (tile >= map.tiles) return;
-  // blocks run down the matrix, then on to the next group_n columns of tiles
-  const int bn = tile / (map.group_n * map.rows);
-  int t = tile - bn * (map.group_n * map.rows);
-  const int width = min(map.group_n, map.cols - bn * map.group_n);
-  const int bm = t / (map.group_m * width);
-  t -= bm * (map.group_m * width);
-  const int height = min(map.group_m, map.rows - bm * map.group_m);
-  const int tn = bn * map.group_n + t / height, tm = bm * map.group_m + t % height;
-  if (tm >= map.tiles_m || tn >= map.tiles_n) return;
-  const int m0 = tm * kBM, n0 = tn * kBN;
-  if (M - m0 >= kBM && N - n0 >= kBN) gemm_tile<true, OUT, TA, TB>(lds0, lds1, A, lda, B, ldb, C, ldc, M, N, K, m0, n0, gs);
-  else                                gemm_tile<false, OUT, TA, TB>(lds0, lds1, A, lda, B, ldb, C, ldc, M, N, K, m0, n0, gs);
+  typedef short s16x4 __attribute__((ext_vector_type(4)));
+  typedef __attribute__((address_space(3))) s16x4* lds_s16x4_ptr;
+  // fragment t of a sub-step: 0..7 the B blocks, 8..15 the A blocks
+  auto read_frag = [&](const unsigned char* far, const unsigned char* near, int ks, int t) -> bf16x8 {
+    const unsigned char* stage = (t >= 8) == FAR_A ? far : near;
+    if (t < 8 ? TB : TA) {
+      const unsigned char* p = stage + (t < 8 ? toff_b[t & 7] : toff_a[t & 7]) + ks * (32 * 512);
+      const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(p));
+      const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(p + 4 * 512));
+      typedef short s16x8 __attribute__((ext_vector_type(8)));
+      const s16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+      return __builtin_bit_cast(bf16x8, v);
+    }
+    return *reinterpret_cast<const bf16x8*>(stage + (t < 8 ? fbase_b : fbase_a) + (t & 7) * 16 * kRowBytes + foff[ks]);
+  };
+#define DPPO_MFMA16(ACC, X, Y) asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(ACC) : "v"(X), "v"(Y))
+#define DPPO_PIN __builtin_amdgcn_sched_barrier(0)
+  // Of this wave's memory accesses at most the VM youngest are in flight (they complete in order), and its LDS reads are done; then
+  // everyone's.  The waits are written out: a barrier by itself, or the wait that the compiler puts in front of its own fragment
+  // reads, would wait for more (the stores of the tile before) or, where the compiler thinks none is pending, for nothing.
+  constexpr int kAnyVm = 63;
+  auto meet = [&](auto vm) __attribute__((always_inline)) {
+    constexpr int VM = decltype(vm)::value;
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt((VM & 15) | ((VM >> 4) << 14) | 0x70);      // vmcnt(VM) lgkmcnt(0)
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    DPPO_PIN;
+  };
+
+  // fragment q of the read order: the first A block, the 8 B blocks, then the other A blocks
+  constexpr int kOrder[16] = {8, 0, 1, 2, 3, 4, 5, 6, 7, 9, 10, 11, 12, 13, 14, 15};
+
+  DPPO_ALL_ACCUMULATORS();
+  TileAt tile = locate(number);
+  {
+    const int nk = steps_of(tile);
+    unrolled<3>([&](auto sc) __attribute__((always_inline)) {
+      constexpr int s = decltype(sc)::value;
+      const row_rsrc_t rn = view_near(tile, s < nk ? s : 0, s < nk), rf = view_far(tile, s < nk ? s : 0, s < nk);
+      if (s < 2) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) load_near(near_panel(s), rn, i);
+      }
+#pragma unroll
+      for (int i = 0; i < 8; ++i) load_far(far_panel(s), rf, i);
+    });
+  }
+  meet(std::integral_constant<int, 0>{});
+  for (;;) {
+    // The panels hold the tile's first two (three) steps, for everyone.
+    bf16x8 f0[16], f1[16];      // [0..7] B blocks, [8..15] A blocks
+#pragma unroll
+    for (int t = 0; t < 16; ++t) f0[kOrder[t]] = read_frag(far_panel(0), near_panel(0), 0, kOrder[t]);
+    DPPO_PIN;
+    // Pipeline over the contraction: step kt is multiplied out of far panel kt % 3 and near panel kt % 2; once every wave
+    // has read its last fragments of them (the barrier in the middle of the step) the near panel of step kt + 2 and the far panel of step kt + 3
+    // are loaded there, or, behind the tile's last steps, those of the same place of the next tile.  The fragments of each
+    // 32-wide sub-step are read from LDS one sub-step ahead of the matrix-core instructions that consume them.  One barrier per step.
+    const int nk = steps_of(tile);
+    const bool has_next = number + map.slots < end;
+    TileAt next = tile;
+    int nk_next = 0;
+    // One step of the contraction out of stage `cur`: two 32-wide sub-steps of 64 matrix-core
+    // instructions each (A block i = m / 8 against B block j = m % 8).  Every other instruction sits
+    // directly behind a matrix-core instruction, where it issues while that one executes.
+    // First sub-step: the 16 fragment reads of the second, behind the first 32 instructions, so they
+    // have landed when the barrier is reached.  Second sub-step: the 16 fragment reads of the next
+    // step's first sub-step and the 16 panel loads of the step after next.
+    // P: kt % 6.
+    auto step = [&](int kt, auto phase, auto steady, auto first) __attribute__((always_inline)) {
+      constexpr int P = decltype(phase)::value;
+      constexpr bool STEADY = decltype(steady)::value, FIRST = decltype(first)::value;
+      unrolled<64>([&](auto mc) __attribute__((always_inline)) {
+        constexpr int m = decltype(mc)::value;
+        product<m, FIRST>(f0[m & 7], f0[8 + (m >> 3)]); DPPO_PIN;
+        if constexpr (m < 32 && (m & 1) == 0) { f1[kOrder[m >> 1]] = read_frag(far_panel(P), near_panel(P), 1, kOrder[m >> 1]); DPPO_PIN; }
+      });
+      // The next step's panels are complete (the eight youngest loads are the far panel of the step after it; a tile's second step: complete
+      // since the tile began) and this step's fully read.
+      meet(std::integral_constant<int, (FIRST ? kAnyVm : 8)>{});
+      const bool own_n = STEADY || kt + 2 < nk, own_f = STEADY || kt + 3 < nk;
+      const int sn = own_n ? kt + 2 : P % 2, sf = own_f ? kt + 3 : P % 3;
+      const row_rsrc_t rn = STEADY ? view_near(tile, sn, true) : view_near(own_n ? tile : next, sn, own_n || sn < nk_next);
+      const row_rsrc_t rf = STEADY ? view_far(tile, sf, true) : view_far(own_f ? tile : next, sf, own_f || (sf < nk_next && !(OUT == kOutStats && P % 3 == 2)));
+      unrolled<64>([&](auto mc) __attribute__((always_inline)) {
+        constexpr int m = decltype(mc)::value;
+        product<m, false>(f1[m & 7], f1[8 + (m >> 3)]); DPPO_PIN;
+        if constexpr ((m & 3) == 0) { f0[kOrder[m >> 2]] = read_frag(far_panel(P + 1), near_panel(P + 1), 0, kOrder[m >> 2]); DPPO_PIN; }      // (a tile's last step: not used)
+        if constexpr ((m & 3) == 2 && m < 32)  { load_near(near_panel(P), rn, m >> 2); DPPO_PIN; }
+        if constexpr ((m & 3) == 2 && m >= 32) { load_far(far_panel(P), rf, (m >> 2) - 8); DPPO_PIN; }
+      });
+    };
+    auto look_ahead = [&]() {
+      if (has_next) {
+        next = locate(number + map.slots);
+        nk_next = steps_of(next);
+      }
+    };
+    using Yes = std::true_type;
+    using No = std::false_type;
+#define DPPO_PHASE(P) std::integral_constant<int, P>{}
+    if (nk <= 3) look_ahead();
+    step(0, DPPO_PHASE(0), No{}, Yes{});
+    int kt = 1;
+    for (; kt + 8 < nk; kt += 6) {
+      step(kt, DPPO_PHASE(1), Yes{}, No{});
+      step(kt + 1, DPPO_PHASE(2), Yes{}, No{});
+      step(kt + 2, DPPO_PHASE(3), Yes{}, No{});
+      step(kt + 3, DPPO_PHASE(4), Yes{}, No{});
+      step(kt + 4, DPPO_PHASE(5), Yes{}, No{});
+      step(kt + 5, DPPO_PHASE(0), Yes{}, No{});
+    }
+    if (nk > 3) look_ahead();
+    // (statistics: the sampled ids of the lane's eight rows, in time for the end of the tile)
+    int samp[8];
+    if (OUT == kOutStats) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int row = tile.m0 + wm * 128 + i * 16 + frow;
+        samp[i] = (row < M) ? gs.sampled[row] : -1;
+      }
+    }
+    // At most eight steps more.  (Left by one exit each: with a path around the steps that are not left, the compiler waits for the loads of a step
+    // that it thinks may be read next.)
+    for (;;) {
+      if (kt >= nk) break;
+      step(kt++, DPPO_PHASE(1), No{}, No{});
+      if (kt >= nk) break;
+      step(kt++, DPPO_PHASE(2), No{}, No{});
+      if (kt >= nk) break;
+      step(kt++, DPPO_PHASE(3), No{}, No{});
+      if (kt >= nk) break;
+      step(kt++, DPPO_PHASE(4), No{}, No{});
+      if (kt >= nk) break;
+      step(kt++, DPPO_PHASE(5), No{}, No{});
+      if (kt >= nk) break;
+      step(kt++, DPPO_PHASE(0), No{}, No{});
+    }
+#undef DPPO_PHASE
+    // the matrix-core results must have landed before other instructions read the accumulators
+    // (the products are assembly statements, so the compiler does not keep that distance by itself)
+    asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+    DPPO_PIN;
+    // The products were formed with the operands swapped (B fragment first), so a lane's four
+    // accumulators of a 16 x 16 block are four consecutive COLUMNS (lane/16)*4 + 0..3 of row lane%16.
+    const int m0 = tile.m0, n0 = tile.n0;
+    const bool full = M - m0 >= kBM && N - n0 >= kBN;
+    // Through an empty statement, so that the stores' addresses are formed here: kept from tile to tile they would be spilled, and
+    // their reloads wait for the stores in front of them.
+    int lane_e = lane;
+    asm volatile("" : "+v"(lane_e));
+    const int frow = lane_e & 15, fk = lane_e >> 4;
+    const int row0 = m0 + wm * 128 + frow, col0 = n0 + wn * 128;
+    // This wave's loads of the next tile's first steps have landed: from here on only the tile's own stores are in flight, and
+    // the next wait for memory is in the next tile's second step.
+    auto loads_landed = [&]() {
+      __builtin_amdgcn_s_waitcnt(0x0F70);      // vmcnt(0)
+      DPPO_PIN;
+    };
+    if constexpr (OUT == kOutStats) {
+      // in the far panel of the next tile's third step, which is loaded behind it (and once every wave's last loads, of nothing, into it have ended)
+      meet(std::integral_constant<int, 0>{});
+      static_assert(sizeof(StatRoom) <= kPanelBytes);
+      StatRoom& room = *reinterpret_cast<StatRoom*>(panel2);
+      unsigned char* const quarter[4] = {panel0, panel1, panel3, panel4};
+      if (N - n0 >= kBN) tile_statistics<true>(samp, M, N, m0, n0, gs, room, quarter, wid, lane_e);
+      else               tile_statistics<false>(samp, M, N, m0, n0, gs, room, quarter, wid, lane_e);
+    } else if constexpr (OUT == kOutBf16) {
+      auto store = [&](auto whole) __attribute__((always_inline)) {
+        unrolled<8>([&](auto i) __attribute__((always_inline)) {
+          f32x4 acc[8];
+          accumulators<decltype(i)::value>(acc);
+          if (TA && TB) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) acc[j] *= factor;
+          }
+          store_row_block_bf16<decltype(whole)::value>(static_cast<uint16_t*>(tile.c), ldc, M, N, row0 + i * 16, col0, fk, acc);
+        });
+      };
+      if (full) {
+        store(std::true_type{});
+        __builtin_amdgcn_s_waitcnt(0x8F70);      // vmcnt(32): the youngest 32 of the tile's stores may be in flight, no load in front of them
+      } else {
+        loads_landed();
+        store(std::false_type{});
+      }
+    } else {
+      loads_landed();
+      // fp32: 16 bytes per lane as they are (the host requires 16-byte aligned rows for these forms)
+      auto cptr = [&](int i, int j) { return static_cast<float*>(tile.c) + static_cast<int64_t>(row0 + i * 16) * ldc + (col0 + j * 16 + fk * 4); };
+      auto store = [&](auto whole) __attribute__((always_inline)) {
+        // C += tile: what C holds is requested one block of 16 rows AHEAD of the block being added and
+        // stored (eight 16-byte loads per lane in flight behind eight stores), so that a lane waits for
+        // memory eight times per tile and not sixty-four times.  (Written as load - add - store per
+        // vector, the compiler keeps that order, every load behind the store in front of it.)
+        constexpr bool AHEAD = OUT == kOutF32Add && decltype(whole)::value;
+        f32x4 held[2][8];
+        if (AHEAD) {
+#pragma unroll
+          for (int j = 0; j < 8; ++j) held[0][j] = __builtin_nontemporal_load(reinterpret_cast<f32x4*>(cptr(0, j)));
+        }
+        unrolled<8>([&](auto ic) __attribute__((always_inline)) {
+          constexpr int i = decltype(ic)::value;
+          f32x4 acc[8];
+          accumulators<i>(acc);
+          if (AHEAD && i + 1 < 8) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) held[(i + 1) & 1][j] = __builtin_nontemporal_load(reinterpret_cast<f32x4*>(cptr(i + 1, j)));
+          }
+#pragma unroll
+          for (int j = 0; j < 8; ++j) {
+            float* dst = cptr(i, j);
+            const int row = row0 + i * 16, col = col0 + j * 16 + fk * 4;
+            f32x4 v = acc[j];
+            if (AHEAD) v += held[i & 1][j];
+            if (decltype(whole)::value || (row < M && col + 3 < N)) {
+              if (OUT == kOutF32Add && !AHEAD) v += *reinterpret_cast<const f32x4*>(dst);
+              *reinterpret_cast<f32x4*>(dst) = v;
+            } else if (row < M) {
+#pragma unroll
+              for (int e = 0; e < 4; ++e)
+                if (col + e < N) dst[e] = (OUT == kOutF32Add ? dst[e] : 0.f) + v[e];
+            }
+          }
+        });
+      };
+      if (full) store(std::true_type{});
+      else store(std::false_type{});
+    }
+    if (!has_next) return;
+    meet(std::integral_constant<int, kAnyVm>{});
+    if (OUT == kOutStats) {
+      const row_rsrc_t rf = view_far(next, nk_next > 2 ? 2 : 0, nk_next > 2);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) load_far(panel2, rf, i);
+    }
+    tile = next;
+    number += map.slots;
+  }
 }
 
 // ---- short contractions: C = bf16(factor A^T B) in tiles of 128 x 256 and steps of 32 ---------------
@@ -536,8 +747,7 @@ __global__ __launch_bounds__(256) void dppo_gemm_nt_kernel(const uint16_t* __res
 // 8 of its steps (1000 tokens are 16).  Here a stage is 24 KiB, three of them 72, and a lane holds 128 accumulators, so
 // TWO workgroups share a compute unit and one's loads and stores pass behind the other's products.  The price is 1.5 x the LDS
 // reads per product (a wave's 64 x 128 quadrant needs 12 fragments for 32 products, a 128 x 128 one 16 for 64).
-// Measured, us, 256 x 256 tiles / these: 151936 x 2048, 64 tokens 198 / 148, 300 336 / 287, 500 415 / 366,
-// 1000 614 / 593, 2000 1030 / 1025, 4096 1916 / 2030; 50304 x 2048, 64 68 / 42, 500 130 / 116; 16000 x 1024, 64 11.2 / 10.0.
+// (What both measure: gemm_tn_short.)
 // Two loads ahead are in flight per workgroup; the order of the sums over k is the same as in the larger tiles.
 constexpr int kShortM = 128, kShortK = 32, kShortA = kShortK * kShortM * 2, kShortStage = kShortA + kShortK * kBN * 2;
 
@@ -702,9 +912,9 @@ ShortMap short_map(int64_t M, int64_t N) {
 }  // namespace
 
 hipError_t launch_gemm_nt(const uint16_t* A, int64_t lda, const uint16_t* B, int64_t ldb, void* C, int64_t ldc,
-                          int M, int N, int K, int out, hipStream_t s) {
+                          int M, int N, int K, int out, int cus, hipStream_t s) {
   if (M <= 0 || N <= 0) return hipSuccess;
-  const TileMap map = tile_map(M, N, K, 1);
+  const TileMap map = tile_map(M, N, K, 1, cus);
   const dim3 grid = tile_grid(map), wg(256);
   if (out == 0)      hipLaunchKernelGGL((dppo_gemm_nt_kernel<kOutBf16, false, false>), grid, wg, 0, s, A, lda, B, ldb, C, ldc, M, N, K, map, GemmStats{});
   else if (out == 1) hipLaunchKernelGGL((dppo_gemm_nt_kernel<kOutF32, false, false>), grid, wg, 0, s, A, lda, B, ldb, C, ldc, M, N, K, map, GemmStats{});
@@ -715,9 +925,9 @@ hipError_t launch_gemm_nt(const uint16_t* A, int64_t lda, const uint16_t* B, int
 // The first product of the hidden-state path with nothing of C stored: per row and column tile the
 // softmax statistics of the bf16-rounded logits, and the logits at the sampled and top-K ids.
 hipError_t launch_gemm_stats(const uint16_t* A, int64_t lda, const uint16_t* B, int64_t ldb, int M, int N, int K,
-                             const GemmStats& gs, hipStream_t s) {
+                             const GemmStats& gs, int cus, hipStream_t s) {
   if (M <= 0 || N <= 0) return hipSuccess;
-  const TileMap map = tile_map(M, N, K, 1);
+  const TileMap map = tile_map(M, N, K, 1, cus, gs.Ktop > 0 ? 1 : kMaxRun);
   if (gs.tiles_n != map.tiles_n) return hipErrorInvalidValue;
   const dim3 grid = tile_grid(map), wg(256);
   hipLaunchKernelGGL((dppo_gemm_nt_kernel<kOutStats, false, false>), grid, wg, 0, s, A, lda, B, ldb, static_cast<void*>(nullptr), int64_t(0), M, N, K,
@@ -725,21 +935,21 @@ hipError_t launch_gemm_stats(const uint16_t* A, int64_t lda, const uint16_t* B, 
   return hipGetLastError();
 }
 
-// Which contractions are short (ratio of the times, these tiles to 256 x 256, over 25 shapes of 16000 .. 151936 x 768 .. 4096):
-// up to 500 0.62-1.00, 700 0.85-1.03, 1000 0.92-1.06, 1400 0.95-1.11; of 1000 those of nine rounds of 256 x 256 tiles and more,
-// not the narrowest, 0.92-0.99.
+// Which contractions are short: us, these tiles / 256 x 256, V = 151936: 100 tokens x 2048 188 / 191, 200 237 / 261, 300 284 / 284, 400 324 / 327, 500 369 / 355, 640
+// 430 / 406, 1000 598 / 549; 500 x 4096 716 / 665, 500 x 768 151 / 132; V = 32768: 200 x 2048 42.7 / 44.6, 400 62 / 60, 640 84 / 76; 500 x 768, a round and a half of
+// large tiles, 30 / 33.
 static bool gemm_tn_short(int64_t M, int64_t N, int64_t K) {
   const int64_t tiles = ((M + kBM - 1) / kBM) * ((N + kBN - 1) / kBN);
-  return K <= 640 || (K <= 1024 && N >= 1024 && tiles >= 9 * 256);
+  return K <= 384 || (K <= 512 && tiles < 2 * 256);
 }
 
 // C[M, N] bf16 = *factor A^T B, rounded once.
 //
 // The gradient of the weight in its own type.  Left in fp32 for a pass of its own to scale and round, it cost 12 bytes
 // per entry where 2 do, and short contractions are bound by them.  V = 151936: 1000 tokens x 2048, fp32 product and
-// conversion 743 + 322 us, here 593; 8192 x 4096 7.85 + 0.62 ms, here 7.55.
+// conversion 743 + 322 us, here 549; 8192 x 4096 7.85 + 0.62 ms, here 7.15.
 hipError_t launch_gemm_tn_bf16(const uint16_t* A, int64_t lda, const uint16_t* B, int64_t ldb, void* C, int64_t ldc,
-                               int M, int N, int K, const float* factor, hipStream_t s) {
+                               int M, int N, int K, const float* factor, int cus, hipStream_t s) {
   if (M <= 0 || N <= 0) return hipSuccess;
   if (gemm_tn_short(M, N, K)) {
     const ShortMap map = short_map(M, N);
@@ -747,7 +957,7 @@ hipError_t launch_gemm_tn_bf16(const uint16_t* A, int64_t lda, const uint16_t* B
                        M, N, K, map, factor);
     return hipGetLastError();
   }
-  const TileMap map = tile_map(M, N, K, 1);
+  const TileMap map = tile_map(M, N, K, 1, cus);
   GemmStats gs;
   gs.factor = factor;
   hipLaunchKernelGGL((dppo_gemm_nt_kernel<kOutBf16, true, true>), tile_grid(map), dim3(256), 0, s, A, lda, B, ldb, C, ldc, M, N, K, map, gs);
@@ -756,9 +966,9 @@ hipError_t launch_gemm_tn_bf16(const uint16_t* A, int64_t lda, const uint16_t* B
 
 // C[M, N] (fp32; out 1: written, 2: added to) = A^T B with A [K, M], B [K, N] (row-major, the contraction index the row index)
 hipError_t launch_gemm_tn(const uint16_t* A, int64_t lda, const uint16_t* B, int64_t ldb, void* C, int64_t ldc,
-                          int M, int N, int K, int out, hipStream_t s) {
+                          int M, int N, int K, int out, int cus, hipStream_t s) {
   if (M <= 0 || N <= 0) return hipSuccess;
-  const TileMap map = tile_map(M, N, K, 1);
+  const TileMap map = tile_map(M, N, K, 1, cus);
   const dim3 grid = tile_grid(map), wg(256);
   if (out == 1) hipLaunchKernelGGL((dppo_gemm_nt_kernel<kOutF32, true, true>), grid, wg, 0, s, A, lda, B, ldb, C, ldc, M, N, K, map, GemmStats{});
   else          hipLaunchKernelGGL((dppo_gemm_nt_kernel<kOutF32Add, true, true>), grid, wg, 0, s, A, lda, B, ldb, C, ldc, M, N, K, map, GemmStats{});
@@ -785,10 +995,10 @@ int gemm_nn_splits(int64_t M, int64_t N, int64_t K, int cus, size_t scratch_byte
   int best = 1;
   double best_cost = 0.0;
   for (int64_t s = 1; s <= 64; ++s) {
-    const TileMap t = tile_map(M, N, K, s);
-    if (s > 1 && (nk < 128 || nk / s < 16 || t.tiles * s > 16 * static_cast<int64_t>(cus))) break;
+    const TileMap t = tile_map(M, N, K, s, cus);
+    if (s > 1 && (nk < 128 || nk / s < 16 || t.numbers * s > 16 * static_cast<int64_t>(cus))) break;
     if (s > 1 && static_cast<uint64_t>(s) * static_cast<uint64_t>(M) * static_cast<uint64_t>(N) * 4u > scratch_bytes) break;
-    const int64_t busiest = std::min<int64_t>(t.per_die, t.tiles * s);
+    const int64_t busiest = std::min<int64_t>(t.per_die, t.numbers * s);
     double cost = static_cast<double>((busiest + per_die - 1) / per_die) * static_cast<double>((nk + s - 1) / s + 8);
     if (s > 1) cost = (cost + static_cast<double>(s * M * N) * 8.0 / 5.8e6 + 4.0) / 0.97;
     if (s == 1 || cost < best_cost) {
@@ -836,13 +1046,13 @@ __global__ __launch_bounds__(kSumThreads) void dppo_gemm_sum_kernel(const f32x4*
 
 // C[M, N] bf16 = A B with A [M, K] (contraction index contiguous) and B [K, N] (contraction index the row index); K % 64 == 0
 hipError_t launch_gemm_nn(const uint16_t* A, int64_t lda, const uint16_t* B, int64_t ldb, void* C, int64_t ldc,
-                          int M, int N, int K, int splits, float* scratch, hipStream_t s) {
+                          int M, int N, int K, int splits, float* scratch, int cus, hipStream_t s) {
   if (M <= 0 || N <= 0) return hipSuccess;
   if (splits > 1) {
     if (N % 4 != 0 || !scratch) return hipErrorInvalidValue;
     const int split_steps = (K / kBK + splits - 1) / splits;
     const int used = (K / kBK + split_steps - 1) / split_steps;       // ranges that hold a step
-    TileMap map = tile_map(M, N, K, used);
+    TileMap map = tile_map(M, N, K, used, cus);
     map.split_steps = split_steps;
     hipLaunchKernelGGL((dppo_gemm_nt_kernel<kOutSplit, false, true>), tile_grid(map), dim3(256), 0, s, A, lda, B, ldb,
                        static_cast<void*>(scratch), static_cast<int64_t>(N), M, N, K, map, GemmStats{});
@@ -852,7 +1062,7 @@ hipError_t launch_gemm_nn(const uint16_t* A, int64_t lda, const uint16_t* B, int
                        reinterpret_cast<const f32x4*>(scratch), used, quads, N / 4, static_cast<uint16_t*>(C), ldc);
     return hipGetLastError();
   }
-  const TileMap map = tile_map(M, N, K, 1);
+  const TileMap map = tile_map(M, N, K, 1, cus);
   const dim3 grid = tile_grid(map), wg(256);
   hipLaunchKernelGGL((dppo_gemm_nt_kernel<kOutBf16, false, true>), grid, wg, 0, s, A, lda, B, ldb, C, ldc, M, N, K, map, GemmStats{});
   return hipGetLastError();

@@ -73,23 +73,23 @@ int fullvocab_resident_per_cu(int chunks);
 hipError_t launch_fullvocab_resident(const KParams& p, bool tv, bool grad, int chunks, int grid, hipStream_t s);
 
 // bf16 matrix products on the matrix cores (fp32 accumulation).  A, B 16-byte aligned with lda, ldb
-// multiples of 8 and 256 * ld * 2 < 2^32; the fp32 forms need 16-byte aligned rows of C.
+// multiples of 8 and 256 * ld * 2 < 2^32; the fp32 forms need 16-byte aligned rows of C.  cus: compute units of the device.
 // C[M, N] = A B^T, A [M, K], B [N, K]; K % 64 == 0; out 0: C bf16; 1: C fp32; 2: C fp32, added to what it holds
 hipError_t launch_gemm_nt(const uint16_t* A, int64_t lda, const uint16_t* B, int64_t ldb, void* C, int64_t ldc,
-                          int M, int N, int K, int out, hipStream_t s);
+                          int M, int N, int K, int out, int cus, hipStream_t s);
 // C[M, N] bf16 = A B, A [M, K], B [K, N]; K % 64 == 0.  splits > 1: the contraction in that many ranges, one
 // workgroup per tile and range, through fp32 partial results in `scratch` (splits * M * N * 4 bytes, 16-byte
 // aligned; N a multiple of 4).  gemm_nn_splits() gives the number a shape runs fastest with, as far as the
 // scratch allows (1: undivided).
 hipError_t launch_gemm_nn(const uint16_t* A, int64_t lda, const uint16_t* B, int64_t ldb, void* C, int64_t ldc,
-                          int M, int N, int K, int splits, float* scratch, hipStream_t s);
+                          int M, int N, int K, int splits, float* scratch, int cus, hipStream_t s);
 int gemm_nn_splits(int64_t M, int64_t N, int64_t K, int cus, size_t scratch_bytes);
 // C[M, N] fp32 (out 1: written, 2: added to) = A^T B, A [K, M], B [K, N]; any K >= 1
 hipError_t launch_gemm_tn(const uint16_t* A, int64_t lda, const uint16_t* B, int64_t ldb, void* C, int64_t ldc,
-                          int M, int N, int K, int out, hipStream_t s);
+                          int M, int N, int K, int out, int cus, hipStream_t s);
 // C[M, N] bf16 = *factor A^T B (factor: one float on the device), A [K, M], B [K, N]; any K >= 1; C 2-byte aligned
 hipError_t launch_gemm_tn_bf16(const uint16_t* A, int64_t lda, const uint16_t* B, int64_t ldb, void* C, int64_t ldc,
-                               int M, int N, int K, const float* factor, hipStream_t s);
+                               int M, int N, int K, const float* factor, int cus, hipStream_t s);
 
 // x[r, 0..cols) *= *factor (bf16, in place, any pitch and 2-byte alignment; nothing for a factor of one), and
 // dst[i] = bf16(src[i] * *factor) (dst, src 16-byte aligned).  factor: one float on the device.
@@ -115,7 +115,7 @@ struct GemmStats {
 };
 constexpr int kGemmTileN = 256;
 hipError_t launch_gemm_stats(const uint16_t* A, int64_t lda, const uint16_t* B, int64_t ldb, int M, int N, int K,
-                             const GemmStats& gs, hipStream_t s);
+                             const GemmStats& gs, int cus, hipStream_t s);
 // Per row: combine the tiles' statistics and run the per-row epilogue (one wave per row).  p holds the
 // per-token arrays of the rows (logits unused), row_loss [p.T] receives the loss terms.
 hipError_t launch_lmhead_rows(const KParams& p, const GemmStats& gs, double* row_loss, hipStream_t s);

@@ -288,6 +288,46 @@ def test_gemm_error_codes():
     torch.cuda.synchronize()
 
 
+@pytest.mark.parametrize("steps", [1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 14, 15, 16])
+def test_gemm_tiles_one_behind_the_other(steps):
+    """Workgroups that form several tiles (2115 tiles, more than eight for each of 256 workgroups), by the number of contraction steps
+    of a tile: the panels of the next tile take the places of the last steps' panels, two and three in turn."""
+    M, N, K = 9 * 256 - 3, 235 * 256 - 16, 64 * steps
+    _say(f"[case] gemm runs of tiles, {steps} steps")
+    g = torch.Generator(device=DEV); g.manual_seed(steps)
+    small = lambda *shape: torch.randint(-8, 9, shape, generator=g, device=DEV).float() / 64
+    a, b = small(M, K), small(N, K) * 8
+    ref = a @ b.T                                                              # exact in fp32
+    c = torch.full((M, N), 123.0, dtype=torch.bfloat16, device=DEV)
+    B.gemm_nt(a.bfloat16(), b.bfloat16(), c)
+    assert torch.equal(c, ref.bfloat16())
+    c.fill_(123.0)
+    B.gemm_nn(a.bfloat16(), b.T.contiguous().bfloat16(), c)
+    assert torch.equal(c, ref.bfloat16())
+    k = K - 23                                                                 # by rows any length
+    at = torch.zeros((k, M + 3), dtype=torch.bfloat16, device=DEV)
+    at[:, :M] = a.T[:k]
+    bt = b.T[:k].contiguous().bfloat16()
+    ref -= a[:, k:] @ b[:, k:].T
+    c32 = torch.full((M, N), 123.0, device=DEV)
+    B.gemm_tn_f32(at[:, :M], bt, c32)
+    assert torch.equal(c32, ref)
+    B.gemm_tn_f32(at[:, :M], bt, c32, accumulate=True)
+    assert torch.equal(c32, 2 * ref)
+    c.fill_(123.0)
+    B.gemm_tn_bf16(at[:, :M], bt, torch.tensor(0.5, device=DEV), c)
+    assert torch.equal(c, (0.5 * ref).bfloat16())
+
+
+@pytest.mark.parametrize("d", [64, 128, 192, 256, 384, 576, 704])
+@pytest.mark.parametrize("K", [0, 3])
+def test_forward_tiles_one_behind_the_other(d, K):
+    """The same for the forward-only path, whose statistics use the place of the next tile's third panel (K = 0), and for top-K ids, whose tiles
+    have the shared memory to themselves; rows of every tile height, the last columns half a tile."""
+    w = W.Workload("lm_runs", 7, 100, 64 * 2398, W.TOPK_TV if K else W.BINARY_TV, 0.1, K=K, logit_std=3.0, noise_std=1.0, adv="pm1", seed=d + K)
+    _run_and_compare(w, d, shift=2.0, backward=False, rows=np.array([0, 15, 100, 127, 128, 255, 256, 300, 511, 512, 640, 699]))
+
+
 # --------------------------------------------------------------------------- the whole path, every row
 @pytest.mark.parametrize("variant,K,delta", [(W.BINARY_TV, 0, 0.2), (W.BINARY_KL, 0, 0.05), (W.TOPK_TV, 20, 0.2), (W.TOPK_KL, 64, 0.05)])
 @pytest.mark.parametrize("shift", [0.0, 2.0])
