@@ -246,7 +246,7 @@ bool splits_rows(const dppo_args_t* a, bool ragged_ok, const LossScratch& sc, in
 }
 
 // Launch the loss kernel of one (already validated) call.  Afterwards the scalar loss is
-// loss_scale times the sum of fin[0 .. *fin_n) (per-workgroup partial sums, or per-row terms).
+// loss_scale times the sum of fin[0 .. *fin_n) (per-workgroup partial sums, or per-row terms); *fin null: it has been written.
 dppo_status_t launch_loss(const dppo_args_t* a, bool grad, const LossScratch& sc, const double** fin, int* fin_n, hipStream_t s) {
   double* partial = sc.partial;
   const int max_parts = sc.max_parts;
@@ -300,8 +300,8 @@ dppo_status_t launch_loss(const dppo_args_t* a, bool grad, const LossScratch& sc
     const bool forward = !full && !grad && !(a->flags & DPPO_FLAG_FORCE_STREAMING) &&
                          (resident ? !forward_keeps_row(a, r_threads, r_chunks, ragged, on_lines, cus) : a->V >= 65536 && a->V < (int64_t(1) << 30));
     if (!full && splits_rows(a, ragged_ok, sc, cus)) {
-      if (dppo::launch_split(p, grad, sc.partial, s) != hipSuccess) return DPPO_ERR_LAUNCH;
-      nparts = static_cast<int>(a->T);
+      if (dppo::launch_split(p, grad, sc.partial, a->loss, s) != hipSuccess) return DPPO_ERR_LAUNCH;
+      *fin = nullptr;
       chose(resident ? "resident" : long_chunks ? "resident_long" : "streaming", "dppo_split_stat_kernel");
     } else if (forward) {
       int64_t grid = 2 * static_cast<int64_t>(cus);
@@ -406,7 +406,7 @@ dppo_status_t run(const dppo_args_t* a, void* stream, bool grad) {
   int fin_n = 0;
   st = launch_loss(a, grad, sc, &fin, &fin_n, s);
   if (st != DPPO_OK) return st;
-  if (dppo::launch_finalize(fin, fin_n, a->loss_scale, a->loss, s) != hipSuccess) return DPPO_ERR_LAUNCH;
+  if (fin && dppo::launch_finalize(fin, fin_n, a->loss_scale, a->loss, s) != hipSuccess) return DPPO_ERR_LAUNCH;
   return DPPO_OK;
 }
 
@@ -428,7 +428,7 @@ dppo_status_t run_static(const dppo_args_t* a, void* stream) {
   int fin_n = 0;
   st = launch_loss(a, true, sc, &fin, &fin_n, s);
   if (st != DPPO_OK) return st;
-  if (dppo::launch_finalize(fin, fin_n, a->loss_scale, a->loss, s) != hipSuccess) return DPPO_ERR_LAUNCH;
+  if (fin && dppo::launch_finalize(fin, fin_n, a->loss_scale, a->loss, s) != hipSuccess) return DPPO_ERR_LAUNCH;
   return DPPO_OK;
 }
 
@@ -573,6 +573,7 @@ dppo_status_t run_lmhead(const dppo_lmhead_args_t* a, void* stream, bool grad, v
   const int parts_per_chunk = nchunks > 0 ? static_cast<int>(max_parts / nchunks) : max_parts;
   if (nchunks > 0 && parts_per_chunk < 1) return DPPO_ERR_SHAPE;
   int used = 0;
+  bool summed = false;
   // what the caller's workspace holds beyond the part every call needs, or the room given apart from it
   const size_t base_bytes = align256(lmhead_workspace(T, V, a->chunk_rows));
   const size_t extra_bytes = scratch ? scratch_bytes : a->workspace_bytes > base_bytes ? a->workspace_bytes - base_bytes : 0;
@@ -604,6 +605,7 @@ dppo_status_t run_lmhead(const dppo_lmhead_args_t* a, void* stream, bool grad, v
     const dppo_status_t st = launch_loss(&c, grad, sc, &fin, &np, s);   // gradient in place
     if (st != DPPO_OK) return st;
     used += np;
+    summed = nchunks == 1 && !fin;
     if (grad) {
       // gradient of the chunk's hidden states: g [rows, V] times W [V, d], the weight as it lies
       uint16_t* gh = static_cast<uint16_t*>(a->grad_hidden) + r0 * a->ld_grad_hidden;
@@ -622,7 +624,7 @@ dppo_status_t run_lmhead(const dppo_lmhead_args_t* a, void* stream, bool grad, v
         return DPPO_ERR_LAUNCH;
     }
   }
-  if (dppo::launch_finalize(partial, used, a->loss.loss_scale, a->loss.loss, s) != hipSuccess) return DPPO_ERR_LAUNCH;
+  if (!summed && dppo::launch_finalize(partial, used, a->loss.loss_scale, a->loss.loss, s) != hipSuccess) return DPPO_ERR_LAUNCH;
   if (T > 0) chose("lmhead", "dppo_gemm_nt_kernel");
   return DPPO_OK;
 }

@@ -50,15 +50,16 @@ hipError_t launch_resident_multi(const KParams& p, bool ragged, int rows, int ch
 
 // Few long rows: each divided into segments of kSplitVecs 16-byte blocks, one workgroup each.  Any V with at most 64 segments, any
 // pitch, rows 2-byte aligned, logits and grad sharing their misalignment (address mod 16), in place allowed.  scratch: 8-byte
-// aligned, split_scratch_bytes(); the loss terms of the rows, T float64, are left at its start.
+// aligned, split_scratch_bytes().  Writes the scalar loss too.
 constexpr int kSplitVecs = 2048;
 struct SplitRecord {
   double s, t;      // sum 2^x and sum 2^x x over the segment, x = z log2e + b, the sampled token left out
   float b;          // integer offset
+  uint32_t rows;    // of a call's first record: rows whose loss term has been left so far
 };
 int split_segments(int64_t V);
 size_t split_scratch_bytes(int64_t T, int64_t V, int32_t K);
-hipError_t launch_split(KParams p, bool grad, void* scratch, hipStream_t s);
+hipError_t launch_split(KParams p, bool grad, void* scratch, float* loss, hipStream_t s);
 
 // Two-row kernel of the exact full-vocabulary variants (tv: total variation, else KL).
 hipError_t launch_fullvocab(const KParams& p, bool tv, bool grad, int threads, int grid, hipStream_t s);

@@ -9,14 +9,16 @@
 //                           workgroup writes the per-token outputs.  The second read of a segment comes from the caches: fewer
 //                           rows than 128 are 39 MB at V = 151936, and workgroup ids, so dies, are those of the first kernel.
 //   dppo_split_rows_kernel  forward only: one wave per row
-// Bound by launches and latencies (three kernels, 2 us each when empty) up to some 30 rows, then by the memory traffic of the two passes.
-// V = 151936, calls in a graph, us, one workgroup per row / divided: 8 tokens 23.1 / 10.7, 64 23.4 / 14.8, 100 24.2 / 17.6, 128 25.4 / 20.0;
-// forward only 14.7 / 8.6, 15.6 / 10.5, 15.0 / 12.2, 16.3 / 14.4; V = 256000: 64 41.7 / 17.7, 128 45.8 / 31.3.
+// The row whose loss term is the last to be left adds them all up, beside the other workgroups' gradients; a kernel of its own for the sum was 2.2 us
+// and a launch.  Whole calls with it / without, V = 151936: 8 tokens 12.2 / 10.7, 64 16.8 / 15.5, 100 20.1 / 20.0; forward only 11.3 / 9.0, 13.8 / 11.9, 15.1 / 13.7.
+// Bound by launches and latencies (two kernels, 2 us each when empty) up to some 30 rows, then by the memory traffic of the two passes.
+// V = 151936, calls in a graph, us, one workgroup per row / divided: 8 tokens 23.1 / 12.2, 64 23.4 / 17.1, 128 25.4 / 23.9 (inputs that change from call to call);
+// forward only 14.7 / 10.4, 15.6 / 13.3.
 // Segments of 16 or 64 KiB, and 128 or 512 threads: the same to 30 % slower.  Code that few workgroups need (edges of a row, the
 // sampled token) stands behind branches of the whole workgroup: a kernel this short runs each instruction once and waits
 // for its fetch (100 tokens: 21.6 -> 20.1 us).
 // A kernel boundary instead of a handshake between workgroups: nothing waits for another workgroup, and the scratch needs no
-// particular contents.
+// particular contents (the first kernel clears the count of rows).
 //
 // Any V, pitch and 2-byte alignment (logits and gradient sharing their misalignment): rows are handled in their
 // frame, the aligned 16-byte blocks from the start of the 128-byte line that holds the row's first entry to the block that
@@ -95,7 +97,10 @@ __global__ __launch_bounds__(kThreads) void dppo_split_stat_kernel(const KParams
   const Segment s = segment_of(p, row, seg);
   u32x4 buf[kChunks];
   load_segment(p, row, s, buf);
-  if (!(a >= 0 && a < p.V)) return;                                // an ignored row has no statistics
+  if (!(a >= 0 && a < p.V)) {                                      // an ignored row has no statistics
+    if (blockIdx.x == 0 && threadIdx.x == 0) rec[0].rows = 0;
+    return;
+  }
   if (seg == 0) {
     const uint16_t* zrow = p.logits + static_cast<int64_t>(row) * p.ld;
     for (int k = threadIdx.x; k <= p.K; k += kThreads) {
@@ -124,7 +129,7 @@ __global__ __launch_bounds__(kThreads) void dppo_split_stat_kernel(const KParams
       S += sh_s[w] * sc;
       if (DIAG) T += sc * (sh_t[w] + dd * sh_s[w]);
     }
-    rec[blockIdx.x] = SplitRecord{S, T, b};
+    rec[blockIdx.x] = SplitRecord{S, T, b, 0u};
   }
 }
 
@@ -136,8 +141,11 @@ struct RowInputs {
 };
 __device__ __forceinline__ RowInputs load_row(const KParams& p, int row, const SplitRecord* rec, int segs, int lane) {
   RowInputs in;
-  in.r = SplitRecord{0.0, 0.0, 3.0e38f};
-  if (lane < segs) in.r = rec[static_cast<int64_t>(row) * segs + lane];
+  in.r = SplitRecord{0.0, 0.0, 3.0e38f, 0u};
+  if (lane < segs) {
+    const SplitRecord* r = rec + static_cast<int64_t>(row) * segs + lane;
+    in.r.s = r->s; in.r.t = r->t; in.r.b = r->b;
+  }
   in.scalars = load_row_scalars(p, row, lane);
   const float* gath = p.gath + static_cast<int64_t>(row) * (p.K + 1);
   in.za = gath[0];
@@ -165,34 +173,60 @@ __device__ __forceinline__ RowResult split_row(const KParams& p, const EpiParams
   return row_post(ep, row, q, a, nullptr, b, S, T, lane, 0.0, o);
 }
 
-__device__ __forceinline__ void ignored_row(const KParams& p, int row, double* row_loss) {
+// Leaves a row's loss term, by one lane: written past the die's L2 and waited for before the row is counted, so that whoever finds the count
+// complete finds the terms (read past the L2 again).
+__device__ __forceinline__ void leave_loss_term(double term, int row, double* row_loss) {
+  __hip_atomic_store(row_loss + row, term, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+}
+// Counts rows: true for those that are the last.
+__device__ __forceinline__ bool count_rows(int rows, const KParams& p, SplitRecord* rec) {
+  return __hip_atomic_fetch_add(&rec[0].rows, static_cast<uint32_t>(rows), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + static_cast<uint32_t>(rows) == static_cast<uint32_t>(p.T);
+}
+// The scalar loss from the terms of all rows, by one wave: lane l those numbered l, l + 64, ..., then a tree (the order of the general sum
+// for up to 128 rows).
+__device__ __forceinline__ void sum_loss(const KParams& p, const double* row_loss, float* loss, int lane) {
+  double v = 0.0;
+  for (int r = lane; r < p.T; r += kWave) v += __hip_atomic_load(row_loss + r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+  for (int o = kWave / 2; o > 0; o >>= 1) v += __shfl_xor(v, o);
+  if (lane == 0) *loss = static_cast<float>(static_cast<double>(p.loss_scale) * v);
+}
+
+__device__ __forceinline__ void ignored_row(const KParams& p, int row) {
   p.divergence[row] = 0.f;
   p.mask[row] = 0;
   if (p.loss_tok) p.loss_tok[row] = 0.f;
   if (p.diag) {
     for (int k = 0; k < 8; ++k) p.diag[static_cast<int64_t>(row) * 8 + k] = 0.f;
   }
-  row_loss[row] = 0.0;
 }
 
-__global__ __launch_bounds__(kThreads) void dppo_split_rows_kernel(const KParams p, const SplitRecord* __restrict__ rec, int segs, double* __restrict__ row_loss) {
+__global__ __launch_bounds__(kThreads) void dppo_split_rows_kernel(const KParams p, SplitRecord* rec, int segs, double* row_loss, float* loss) {
   const int lane = threadIdx.x & (kWave - 1), wid = uniform_i(threadIdx.x / kWave);
-  const int row = static_cast<int>(blockIdx.x) * kWaves + wid;
-  if (row >= p.T) return;
-  const RowInputs in = load_row(p, row, rec, segs, lane);
-  const int a = uniform_i(p.sampled[row]);
-  if (!(a >= 0 && a < p.V)) {
-    if (lane == 0) ignored_row(p, row, row_loss);
-    return;
+  const int row0 = static_cast<int>(blockIdx.x) * kWaves, row = row0 + wid;
+  if (row < p.T) {
+    const RowInputs in = load_row(p, row, rec, segs, lane);
+    const int a = uniform_i(p.sampled[row]);
+    double term = 0.0;
+    if (a >= 0 && a < p.V) {
+      const EpiParams ep = epi_params(p);
+      RowOut o;
+      term = split_row(p, ep, row, a, in, segs, lane, o).loss_term;
+      row_store(ep, row, o, lane);
+    } else if (lane == 0) {
+      ignored_row(p, row);
+    }
+    if (lane == 0) leave_loss_term(term, row, row_loss);
   }
-  const EpiParams ep = epi_params(p);
-  RowOut o;
-  const RowResult res = split_row(p, ep, row, a, in, segs, lane, o);
-  row_store(ep, row, o, lane);
-  if (lane == 0) row_loss[row] = res.loss_term;
+  __syncthreads();
+  if (wid != 0) return;
+  bool last = false;
+  if (lane == 0) last = count_rows(min(kWaves, p.T - row0), p, rec);
+  if (__any(last)) sum_loss(p, row_loss, loss, lane);
 }
 
-__global__ __launch_bounds__(kThreads) void dppo_split_grad_kernel(const KParams p, const SplitRecord* __restrict__ rec, int segs, double* __restrict__ row_loss) {
+__global__ __launch_bounds__(kThreads) void dppo_split_grad_kernel(const KParams p, SplitRecord* rec, int segs, double* row_loss, float* loss) {
   __shared__ RowCoef sh_rc;
   // The segments in the opposite order, on the same dies: what the first kernel read last is what their L2 still holds.
   const int idx = static_cast<int>((gridDim.x - 8u - (blockIdx.x & ~7u)) | (blockIdx.x & 7u));
@@ -208,23 +242,29 @@ __global__ __launch_bounds__(kThreads) void dppo_split_grad_kernel(const KParams
   const bool live = (a >= 0 && a < p.V);
   RowCoef rc;
   rc.coef = 0.f; rc.kexp = 0.f; rc.g_a = 0.f;
+  bool last = false;                       // (first lane of the row's first workgroup)
   if (live) {
+    RowOut o;
+    RowResult res;
     if (wid == 0) {
-      const EpiParams ep = epi_params(p);
-      RowOut o;
-      const RowResult res = split_row(p, ep, row, a, in, segs, lane, o);
+      res = split_row(p, epi_params(p), row, a, in, segs, lane, o);
       if (lane == 0) sh_rc = res.rc;
-      if (seg == 0) {
-        row_store(ep, row, o, lane);
-        if (lane == 0) row_loss[row] = res.loss_term;
-      }
     }
     __syncthreads();
+    if (wid == 0 && seg == 0) {
+      row_store(epi_params(p), row, o, lane);
+      if (lane == 0) {
+        leave_loss_term(res.loss_term, row, row_loss);
+        last = count_rows(1, p, rec);
+      }
+    }
     rc.coef = uniform_f(sh_rc.coef);
     rc.kexp = uniform_f(sh_rc.kexp);
     rc.g_a = uniform_f(sh_rc.g_a);
   } else if (seg == 0 && tid == 0) {
-    ignored_row(p, row, row_loss);
+    ignored_row(p, row);
+    leave_loss_term(0.0, row, row_loss);
+    last = count_rows(1, p, rec);
   }
   // Of the frame only complete blocks of the row's own entries leave as 16-byte stores, an incomplete first or last block entry by
   // entry.  A masked, zero-advantage or ignored row's gradient is exactly zero whatever the logits hold.
@@ -244,20 +284,21 @@ __global__ __launch_bounds__(kThreads) void dppo_split_grad_kernel(const KParams
     const row_rsrc_t r = make_row_rsrc(grow - s.h, static_cast<uint32_t>(s.h + p.V) * 2u);
 #pragma unroll
     for (int i = 0; i < kChunks; ++i) __builtin_amdgcn_raw_buffer_store_b128(o[i], r, static_cast<uint32_t>(s.v0) * 16u, i * kThreads * 16u, 2);
-    return;
-  }
+  } else {
 #pragma unroll
-  for (int i = 0; i < kChunks; ++i) {
-    const int v = s.v0 + i * kThreads, e0 = 8 * v - s.h;
-    if (e0 >= 0 && e0 + 8 <= p.V) {
-      __builtin_nontemporal_store(o[i], reinterpret_cast<u32x4*>(grow + e0));
-    } else if (v < s.nvec) {
-      const uint32_t w[4] = {o[i].x, o[i].y, o[i].z, o[i].w};
+    for (int i = 0; i < kChunks; ++i) {
+      const int v = s.v0 + i * kThreads, e0 = 8 * v - s.h;
+      if (e0 >= 0 && e0 + 8 <= p.V) {
+        __builtin_nontemporal_store(o[i], reinterpret_cast<u32x4*>(grow + e0));
+      } else if (v < s.nvec) {
+        const uint32_t w[4] = {o[i].x, o[i].y, o[i].z, o[i].w};
 #pragma unroll
-      for (int e = 0; e < 8; ++e)
-        if (e0 + e >= 0 && e0 + e < p.V) grow[e0 + e] = static_cast<uint16_t>((e & 1) ? (w[e >> 1] >> 16) : (w[e >> 1] & 0xffffu));
+        for (int e = 0; e < 8; ++e)
+          if (e0 + e >= 0 && e0 + e < p.V) grow[e0 + e] = static_cast<uint16_t>((e & 1) ? (w[e >> 1] >> 16) : (w[e >> 1] & 0xffffu));
+      }
     }
   }
+  if (wid == 0 && seg == 0 && __any(last)) sum_loss(p, row_loss, loss, lane);
 }
 
 }  // namespace
@@ -268,7 +309,7 @@ size_t split_scratch_bytes(int64_t T, int64_t V, int32_t K) {
   return static_cast<size_t>(T) * (sizeof(double) + static_cast<size_t>(split_segments(V)) * sizeof(SplitRecord) + static_cast<size_t>(K + 1) * sizeof(float));
 }
 
-hipError_t launch_split(KParams p, bool grad, void* scratch, hipStream_t s) {
+hipError_t launch_split(KParams p, bool grad, void* scratch, float* loss, hipStream_t s) {
   const int segs = split_segments(p.V);
   if (segs > kWave || p.T <= 0) return hipErrorInvalidValue;
   // [loss terms | records | gathered logits]
@@ -280,8 +321,8 @@ hipError_t launch_split(KParams p, bool grad, void* scratch, hipStream_t s) {
   if (p.diag) hipLaunchKernelGGL(dppo_split_stat_kernel<true>, grid, wg, 0, s, p, rec, gath, segs);
   else        hipLaunchKernelGGL(dppo_split_stat_kernel<false>, grid, wg, 0, s, p, rec, gath, segs);
   if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
-  if (grad) hipLaunchKernelGGL(dppo_split_grad_kernel, dim3((grid.x + 7u) & ~7u), wg, 0, s, p, rec, segs, row_loss);
-  else      hipLaunchKernelGGL(dppo_split_rows_kernel, dim3((p.T + kWaves - 1) / kWaves), wg, 0, s, p, rec, segs, row_loss);
+  if (grad) hipLaunchKernelGGL(dppo_split_grad_kernel, dim3((grid.x + 7u) & ~7u), wg, 0, s, p, rec, segs, row_loss, loss);
+  else      hipLaunchKernelGGL(dppo_split_rows_kernel, dim3((p.T + kWaves - 1) / kWaves), wg, 0, s, p, rec, segs, row_loss, loss);
   return hipGetLastError();
 }
 

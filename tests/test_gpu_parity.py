@@ -871,6 +871,39 @@ def test_few_long_rows_whose_gradient_lies_otherwise_modulo_16(V, ld, variant, K
     P.compare_rows(b, fwd, rows, check_grad=False, ref=ref)
 
 
+@pytest.mark.parametrize("backward", [True, False])
+@pytest.mark.parametrize("T,ignored", [(1, []), (1, [0]), (3, [0]), (5, [0, 1, 2, 3, 4]), (6, [5]), (64, [0, 63]), (65, [])])
+def test_divided_rows_add_their_loss_up_themselves(T, ignored, backward):
+    """The scalar loss is written by whichever row is the last to leave its term: with ignored rows first, last and everywhere, over
+    a workspace that holds anything, call after call and in a graph."""
+    w = W.Workload("split_loss", 1, T, 131072, W.BINARY_TV, 0.1, logit_std=3.0, noise_std=1.0, adv="normal", seed=T)
+    b = W.make_batch(w, DEV)
+    b["advantages"] = torch.randn(T, device=DEV)
+    for r in ignored:
+        b["sampled_ids"][r] = -1
+    out = B.alloc_outputs(T, DEV)
+    grad = torch.empty_like(b["logits"]) if backward else None
+    args = B.make_args(b["logits"], b["sampled_ids"], b["mu_logp"], b["advantages"], 0.1, W.BINARY_TV, 0.25, out, grad_logits=grad)
+    call = lambda: (B.dppo_loss_fwd_bwd if backward else B.dppo_loss_fwd)(args)
+    losses = []
+    for fill in (255, 0, 1):
+        out["workspace"].fill_(fill)
+        call()
+        assert B.last_kernel() == "dppo_split_stat_kernel"
+        losses.append(out["loss"].clone())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call()
+    for _ in range(3):
+        out["loss"].fill_(7.0)
+        graph.replay()
+        torch.cuda.synchronize()
+        losses.append(out["loss"].clone())
+    assert all(torch.equal(x, losses[0]) for x in losses)
+    want = 0.25 * out["loss_tok"].double().sum()           # of terms rounded to fp32
+    assert abs(losses[0].double() - want) <= 1e-6 * 0.25 * out["loss_tok"].double().abs().sum() + 1e-12
+
+
 @pytest.mark.parametrize("V,ld,off", [(49145, 49145, 3), (50257, 50257, 0), (50264, 50264, 0), (53178, 53184, 1)])
 def test_ragged_rows_of_thirteen_chunks_two_workgroups_per_compute_unit(V, ld, off):
     """The shape that such rows take without diagnostics, many of them, at its shortest and longest row: the bits of the shape
