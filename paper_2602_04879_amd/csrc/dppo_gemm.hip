@@ -143,6 +143,27 @@ __device__ __forceinline__ void store_row_block_bf16(uint16_t* __restrict__ C, i
   }
 }
 
+// The same 16 rows x 128 columns, all in the matrix and on lines of 128 bytes, in whole lines: through `room` (this wave's own, kLineRoom bytes), where a row is
+// 16 vectors of 16 bytes, vector v in place v ^ row, so that neither side meets its own banks; a store is four rows of 256 bytes then.
+// Past the caches: a result is written once, and what many tiles store at the same time would take the L2 from the operands.  (In 64-byte pieces the
+// same mark costs a third of the rate.)
+constexpr int kLineRoom = 16 * 256;
+__host__ __device__ __forceinline__ bool result_on_lines(const void* C, int64_t ldc) { return (reinterpret_cast<uintptr_t>(C) & 127u) == 0 && ldc % 64 == 0; }
+__device__ __forceinline__ void store_row_block_lines(uint16_t* __restrict__ C, int64_t ldc, int lane, const f32x4 (&acc)[8], unsigned char* room) {
+  const int frow = lane & 15, fk = lane >> 4;
+#pragma unroll
+  for (int j = 0; j < 8; j += 2) {
+    const auto l = __builtin_amdgcn_permlane16_swap(pack_bf16x2(acc[j][0], acc[j][1]), pack_bf16x2(acc[j + 1][0], acc[j + 1][1]), false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap(pack_bf16x2(acc[j][2], acc[j][3]), pack_bf16x2(acc[j + 1][2], acc[j + 1][3]), false, false);
+    *reinterpret_cast<u32x4*>(room + frow * 256 + ((((j + (fk & 1)) * 2 + (fk >> 1)) ^ frow) << 4)) = u32x4{l[0], h[0], l[1], h[1]};
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int r = q * 4 + (lane >> 4), v = lane & 15;
+    __builtin_nontemporal_store(*reinterpret_cast<const u32x4*>(room + r * 256 + ((v ^ r) << 4)), reinterpret_cast<u32x4*>(C + static_cast<int64_t>(r) * ldc + v * 8));
+  }
+}
+
 // OUT selects what leaves a tile: bf16 (rounded to nearest even), fp32, or fp32 added to what C holds.
 // kOutStats: nothing of C is stored.  The tile's logits, rounded to bf16 as a stored tile would be,
 // leave as softmax statistics per row (GemmStats below): the forward of the hidden-state path then
@@ -747,7 +768,8 @@ __global__ __launch_bounds__(256) void dppo_gemm_nt_kernel(const uint16_t* __res
 // 8 of its steps (1000 tokens are 16).  Here a stage is 24 KiB, three of them 72, and a lane holds 128 accumulators, so
 // TWO workgroups share a compute unit and one's loads and stores pass behind the other's products.  The price is 1.5 x the LDS
 // reads per product (a wave's 64 x 128 quadrant needs 12 fragments for 32 products, a 128 x 128 one 16 for 64).
-// (What both measure: gemm_tn_short.)
+// What is left is the rate of the stores: in the order of the accumulators they are pieces of 64 bytes, 4.2 TB/s; in whole lines past the caches (store_row_block_lines),
+// us, 151936 x 2048, 64 tokens 148 / 110, 100 189 / 136, 200 236 / 179, 300 284 / 222.  (What both kinds of tiles measure: gemm_tn_short.)
 // Two loads ahead are in flight per workgroup; the order of the sums over k is the same as in the larger tiles.
 constexpr int kShortM = 128, kShortK = 32, kShortA = kShortK * kShortM * 2, kShortStage = kShortA + kShortK * kBN * 2;
 
@@ -865,6 +887,22 @@ __device__ __forceinline__ void short_tile(unsigned char* lds0, unsigned char* l
 #undef DPPO_THROUGH
   DPPO_PIN;
   const int frow = lane & 15, fk = lane >> 4;
+  if (FULL && result_on_lines(C, ldc)) {
+    int lane_e = lane;
+    asm volatile("" : "+v"(lane_e));         // (addresses formed here, not kept from in front of the loop)
+    // every wave is done with the stages
+    __builtin_amdgcn_s_waitcnt(0xC07F);      // lgkmcnt(0)
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    DPPO_PIN;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) acc[i][j] *= factor;
+      store_row_block_lines(C + static_cast<int64_t>(m0 + wm * 64 + i * 16) * ldc + n0 + wn * 128, ldc, lane_e, acc[i], ((i & 1) ? lds1 : lds0) + wid * kLineRoom);
+    }
+    return;
+  }
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
 #pragma unroll
@@ -935,23 +973,20 @@ hipError_t launch_gemm_stats(const uint16_t* A, int64_t lda, const uint16_t* B, 
   return hipGetLastError();
 }
 
-// Which contractions are short: us, these tiles / 256 x 256, V = 151936: 100 tokens x 2048 188 / 191, 200 237 / 261, 300 284 / 284, 400 324 / 327, 500 369 / 355, 640
-// 430 / 406, 1000 598 / 549; 500 x 4096 716 / 665, 500 x 768 151 / 132; V = 32768: 200 x 2048 42.7 / 44.6, 400 62 / 60, 640 84 / 76; 500 x 768, a round and a half of
-// large tiles, 30 / 33.
-static bool gemm_tn_short(int64_t M, int64_t N, int64_t K) {
-  const int64_t tiles = ((M + kBM - 1) / kBM) * ((N + kBN - 1) / kBN);
-  return K <= 384 || (K <= 512 && tiles < 2 * 256);
-}
+// Which contractions are short: us, these tiles / 256 x 256, results on lines, V = 151936: 64 tokens x 2048 110 / 191, 200 179 / 261, 300 222 / 284, 400 264 / 328, 500
+// 307 / 360, 640 364 / 412, 800 442 / 483, 1000 565 / 546; 500 x 768 119 / 133, 500 x 4096 611 / 673, 1000 x 4096 1145 / 1085.  Others leave both kinds of tiles in pieces
+// of 64 bytes: 200 x 2048 237 / 261, 300 284 / 284, 400 324 / 327, 500 369 / 355.
+static bool gemm_tn_short(const void* C, int64_t ldc, int64_t K) { return K <= (result_on_lines(C, ldc) ? 896 : 384); }
 
 // C[M, N] bf16 = *factor A^T B, rounded once.
 //
 // The gradient of the weight in its own type.  Left in fp32 for a pass of its own to scale and round, it cost 12 bytes
 // per entry where 2 do, and short contractions are bound by them.  V = 151936: 1000 tokens x 2048, fp32 product and
-// conversion 743 + 322 us, here 549; 8192 x 4096 7.85 + 0.62 ms, here 7.15.
+// conversion 743 + 322 us, here 546; 8192 x 4096 7.85 + 0.62 ms, here 7.15.
 hipError_t launch_gemm_tn_bf16(const uint16_t* A, int64_t lda, const uint16_t* B, int64_t ldb, void* C, int64_t ldc,
                                int M, int N, int K, const float* factor, int cus, hipStream_t s) {
   if (M <= 0 || N <= 0) return hipSuccess;
-  if (gemm_tn_short(M, N, K)) {
+  if (gemm_tn_short(C, ldc, K)) {
     const ShortMap map = short_map(M, N);
     hipLaunchKernelGGL(dppo_gemm_tn_short_kernel, dim3(8u * static_cast<unsigned>(map.per_die)), dim3(256), 0, s, A, lda, B, ldb, static_cast<uint16_t*>(C), ldc,
                        M, N, K, map, factor);

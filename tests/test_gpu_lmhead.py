@@ -176,7 +176,9 @@ def test_gemm_tn_exact_inputs_bitwise_and_accumulation(M, N, K, lda, ldb, ldc):
     (256, 256, 64, 256, 256, 256, 0), (8, 8, 1, 8, 8, 8, 0), (300, 520, 100, 304, 520, 520, 0), (1000, 776, 193, 1008, 784, 783, 1),
     (4160, 128, 321, 4160, 128, 128, 0), (777, 261, 129, 784, 264, 264, 0), (151936, 64, 66, 151936, 64, 64, 0), (512, 512, 1000, 512, 512, 520, 3),
     (384, 512, 33, 384, 512, 512, 0), (130, 300, 96, 136, 304, 300, 0), (1100, 2100, 160, 1104, 2104, 2100, 0), (640, 300, 640, 640, 304, 304, 0),
-    (640, 300, 641, 640, 304, 304, 0), (73729, 2048, 70, 73736, 2048, 2048, 0)])
+    (640, 300, 641, 640, 304, 304, 0), (73729, 2048, 70, 73736, 2048, 2048, 0),
+    # results on lines: small tiles up to 896, whole lines in their full tiles; the pitch on lines, the first row not
+    (640, 576, 896, 640, 576, 576, 0), (640, 576, 897, 640, 576, 576, 0), (384, 512, 385, 384, 512, 512, 8), (261, 512, 31, 264, 512, 576, 0)])
 def test_gemm_tn_in_bf16_is_the_fp32_product_scaled_and_rounded_once(M, N, K, lda, ldb, ldc, off):
     """C = bf16(factor * A^T B): bit for bit what scaling and rounding the fp32 product gives, with ragged
     sizes, pitches and a C on any 2-byte address; nothing around C is written."""
