@@ -231,7 +231,7 @@ bool forward_keeps_row(const dppo_args_t* a, int threads, int chunks, bool ragge
   return a->T >= least && a->T <= most && a->ld % 32768 != 0;
 }
 
-// Few long rows, which would leave most compute units idle: divided among workgroups (dppo_split.hip) where the third launch and the
+// Few long rows, which would leave most compute units idle: divided among workgroups (dppo_split.hip) where the second launch and the
 // second read cost less than the idle time, by the same sizes for calls with and without a gradient: where both are divided their per-token
 // outputs agree bit for bit.  Not divided: a gradient that does not share the logits' address modulo 16 (the forward-only call on the same
 // logits still is), DPPO_FLAG_FORCE_STREAMING, the hidden states in several chunks, records and gathered logits beyond 64 KiB.
