@@ -5,6 +5,7 @@ from __future__ import annotations
 
 import glob
 import os
+import re
 import subprocess
 import sys
 from concurrent.futures import ThreadPoolExecutor
@@ -19,6 +20,48 @@ HIPCC_FLAGS = [
     # keep the compiler from forming packed-fp32 instructions
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
 ]
+
+
+# Sources whose kernels name accumulation registers in assembly statements without telling the compiler
+# (dppo_gemm.hip: 256 accumulators per lane).  It must keep nothing of its own there, spilled vector registers
+# included; the generated assembly, which the object is made from, is looked through for that.
+NAMED_ACCUMULATORS = {"dppo_gemm.hip": "dppo_gemm_nt_kernel"}
+NAMED_ACCUMULATORS_FLAGS = [
+    "-mllvm", "-amdgpu-spill-vgpr-to-agpr=0",
+    # keep the assembly; written from there, a warning (a clobbered m0) would quote binary files
+    "--save-temps=obj", "-Wno-inline-asm",
+]
+
+
+def check_named_accumulators(asm: str, kernel: str) -> None:
+    """Raise RuntimeError unless, in the assembly text `asm`, every kernel whose name contains `kernel` has all 256 accumulation
+    registers, mentions them nowhere but in its own assembly statements, and spills no vector register.
+    (Others would not fault: their results would be silently wrong.)"""
+    faults, bodies, entries, name, own = [], set(), set(), None, False
+    for n, line in enumerate(asm.splitlines(), 1):
+        if m := re.match(r"(\w+):", line):
+            name = m[1] if kernel in m[1] else None
+            bodies.add(name)
+        elif line.startswith(".Lfunc_end"):
+            name = None
+        elif "#ASMSTART" in line or "#ASMEND" in line:
+            own = "#ASMSTART" in line
+        elif name and not own:
+            code = line.split(";")[0].strip()
+            if not code.startswith(".") and re.search(r"\ba(\d+|\[\d)", code):
+                faults.append(f"line {n}, {name}: {code}")
+    for entry in asm.partition("amdhsa.kernels:")[2].split("\n  - ")[1:]:
+        f = dict(re.findall(r"^(?: {4})?\.(\w+): +(\S+)$", entry, re.M))
+        if kernel in f.get("name", ""):
+            entries.add(f["name"])
+            if (f["agpr_count"], f["vgpr_spill_count"], f["private_segment_fixed_size"]) != ("256", "0", "0"):
+                faults.append("{name}: {agpr_count} accumulation registers, {vgpr_spill_count} spilled vector registers, "
+                              "{private_segment_fixed_size} bytes of scratch memory".format(**f))
+    bodies.discard(None)
+    if not bodies or bodies != entries:
+        faults.append(f"kernels named {kernel}: {len(bodies)} bodies, {len(entries)} entries")
+    if faults:
+        raise RuntimeError("accumulation registers named in assembly statements are not safe:\n" + "\n".join(faults[:20]))
 
 
 def sources() -> list[str]:
@@ -38,6 +81,18 @@ def _run(cmd: list[str], verbose: bool) -> None:
         print(err)
 
 
+def _compile(hipcc: str, flags: list[str], src: str, obj: str, verbose: bool) -> None:
+    kernel = NAMED_ACCUMULATORS.get(os.path.basename(src))
+    _run([hipcc, *flags, *(NAMED_ACCUMULATORS_FLAGS if kernel else []), "-c", src, "-o", obj], verbose)
+    if kernel:
+        with open(obj[:-2] + "-hip-amdgcn-amd-amdhsa-gfx950.s") as f:
+            asm = f.read()
+        for temp in glob.glob(glob.escape(obj[:-2]) + "[-.]*"):
+            if temp != obj:
+                os.remove(temp)
+        check_named_accumulators(asm, kernel)
+
+
 def build(verbose: bool = True, jobs: int | None = None) -> str:
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     os.makedirs(OBJ_DIR, exist_ok=True)
@@ -46,7 +101,7 @@ def build(verbose: bool = True, jobs: int | None = None) -> str:
     objs = [os.path.join(OBJ_DIR, os.path.basename(s)[:-4] + ".o") for s in srcs]
     jobs = jobs or min(len(srcs), os.cpu_count() or 1, 8)
     with ThreadPoolExecutor(max_workers=jobs) as ex:
-        list(ex.map(lambda so: _run([hipcc, *HIPCC_FLAGS, *inc, "-c", so[0], "-o", so[1]], verbose), zip(srcs, objs)))
+        list(ex.map(lambda so: _compile(hipcc, HIPCC_FLAGS + inc, so[0], so[1], verbose), zip(srcs, objs)))
     _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", LIB_PATH], verbose)
     return LIB_PATH
 

@@ -62,7 +62,8 @@ __device__ __forceinline__ void unrolled(F&& f) {
 // The accumulators of a 256 x 256 tile are the whole accumulation register file, named in the statements that use it: block (i, j) of 16 x 16 is
 // a[4 (8 i + j)] .. + 3.  As values of the compiler's they were moved, some between a tile's products and some in front of its stores, wherever
 // a workgroup forms one tile behind another, and it does not keep the distances that such moves need from products in assembly statements.
-// The compiler itself uses this file for nothing unless it runs out of the other 256 registers.
+// The compiler itself uses this file for nothing unless it runs out of the other 256 registers: the build compiles this source with spills to it switched
+// off and refuses assembly that mentions one of its registers outside the statements below, whatever the compiler's version.
 template <int M, bool FIRST>
 __device__ __forceinline__ void product(bf16x8 x, bf16x8 y) {      // block M += x y, or = x y
   if constexpr (FIRST) asm volatile("v_mfma_f32_16x16x32_bf16 a[%2:%3], %0, %1, 0" ::"v"(x), "v"(y), "n"(4 * M), "n"(4 * M + 3));
