@@ -104,6 +104,10 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));   // one 16-byte vec
 // hardware (a load past `bytes` returns 0, a store past it is dropped), so a 16-byte access is
 // addressed by one per-lane 32-bit offset plus a scalar offset and needs no address arithmetic
 // in vector registers.
+// The check counts the scalar offset: the instruction set manual has an unswizzled access out of range where its offset is at least the size
+// minus the scalar offset (the compiler's description of the builtins, written for older targets too, calls that offset excluded).  A
+// scalar offset beyond the size by itself, which the kernels here rely on, is out of range as well: measured for loads to registers and
+// to shared memory and for stores, sizes 0 .. 40000 and scalar offsets 0 .. 65536, every 4-byte word as if the offsets were added in full width.
 typedef __amdgpu_buffer_rsrc_t row_rsrc_t;
 __device__ __forceinline__ row_rsrc_t make_row_rsrc(const void* base, uint32_t bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, static_cast<int>(bytes), 0x00020000);

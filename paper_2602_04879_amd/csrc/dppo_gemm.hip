@@ -472,7 +472,8 @@ __global__ __launch_bounds__(256) void dppo_gemm_nt_kernel(const uint16_t* __res
   // Loader role: thread t moves LDS vector slot (t % 8) of rows t/8 + 32 i, i = 0..7, of each panel;
   // the slot holds global k-vector slot ^ ((row >> 1) & 7), the same for all eight rows.
   // By rows: load i of a panel (one KiB: two LDS rows) moves k rows 8 i + 2 wave + lane / 32, LDS slot lane % 32: the same global slot for every other i.
-  // What differs from load to load is a scalar offset.
+  // What differs from load to load is a scalar offset, which the range check counts (see row_rsrc_t): rows of a tile or a step that do not exist, and
+  // everything of a view of no bytes, read as zeros without an access.
   auto loader = [&](bool by_rows, uint32_t pitch, int i) -> uint32_t {
     if (!by_rows) return static_cast<uint32_t>(tid >> 3) * pitch + static_cast<uint32_t>(((tid & 7) ^ ((tid >> 4) & 7)) << 4);
     const int k = 8 * i + 2 * wid + (lane >> 5);

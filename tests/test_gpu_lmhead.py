@@ -262,6 +262,28 @@ def test_gemm_tn_poisoned_neighbourhood_and_error_codes():
     torch.cuda.synchronize()
 
 
+@pytest.mark.parametrize("K", [1, 49, 63, 65, 385, 897, 900])
+@pytest.mark.parametrize("lines", [True, False])
+def test_gemm_tn_rows_behind_the_contraction(K, lines):
+    """Rows behind the last one of both operands hold NaN, 256 of them (the allocation holds every address that a step could
+    form): what a step reads there is zero, by 256 x 256 and 128 x 256 tiles alike, for row pieces whose scalar offset lies beyond the
+    buffer's size too (fewer than 49 rows left for a step)."""
+    M, N = 264, 320
+    _say(f"[case] gemm tn rows behind K={K} lines={lines}")
+    g = torch.Generator(device=DEV); g.manual_seed(K)
+    nan_rows = lambda n: torch.full((K + 256, n), float("nan"), dtype=torch.bfloat16, device=DEV)
+    a, b = nan_rows(M), nan_rows(N)
+    a[:K] = (torch.randint(-8, 9, (K, M), generator=g, device=DEV).float() / 8).bfloat16()
+    b[:K] = (torch.randint(-8, 9, (K, N), generator=g, device=DEV).float() / 8).bfloat16()
+    ref = a[:K].double().T @ b[:K].double()                                    # exact in fp32
+    c = torch.empty((M, N), device=DEV)
+    B.gemm_tn_f32(a[:K], b[:K], c)
+    assert torch.equal(c.double(), ref)
+    c16 = torch.empty((M, N + 64), dtype=torch.bfloat16, device=DEV)[:, 0 if lines else 8:][:, :N]
+    B.gemm_tn_bf16(a[:K], b[:K], torch.ones((), device=DEV), c16)
+    assert torch.equal(c16, ref.bfloat16())
+
+
 def test_gemm_ordinary_inputs_within_one_rounding():
     M, N, K = 384, 1000, 1024
     g = torch.Generator(device=DEV); g.manual_seed(3)
