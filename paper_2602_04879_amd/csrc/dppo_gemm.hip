@@ -321,6 +321,7 @@ struct TileMap {
 // most; tiles of 128 steps and more are worth no run: they gain a per cent by it, and workgroups that drift apart lose the panels they
 // share.  Runs of 1 / 2 / 4 / 8 / 32 tiles, us, V = 151936: A B^T 2048 x 2048 975 / 954 / 943 / 938 / 933, 8192 x 4096 6838 / 6770 / 6738 / 6735 / 6712; A^T B
 // 2048 x 2048 983 / 958 / 950 / 945 / 944, 8192 x 4096 (128 steps) 7150 / 7283 / 7377 / 7464 / 7570.
+// A divided contraction (kOutSplit) gets no runs: it has 128 steps and more in all, and tiles of its ranges one behind the other are not built.
 constexpr int kMaxRun = 8;
 TileMap tile_map(int64_t M, int64_t N, int64_t K, int64_t ranges, int cus, int max_run = kMaxRun) {
   TileMap t;
@@ -394,7 +395,7 @@ struct TileAt {
 // into the four consecutive k of one m that a matrix-core operand wants.
 //
 // A workgroup forms a run of tiles (TileMap::run), one behind the other: while it multiplies the last steps of a
-// tile it already loads the first of the next, and its stores travel behind the next tile's products.
+// tile it already loads the first of the next, and its stores travel behind the next tile's products (kOutSplit: one tile, the host asks for runs of one).
 template <int OUT, bool TA, bool TB>
 __global__ __launch_bounds__(256) void dppo_gemm_nt_kernel(const uint16_t* __restrict__ A, int64_t lda,
                                                            const uint16_t* __restrict__ B, int64_t ldb,
@@ -582,7 +583,7 @@ __global__ __launch_bounds__(256) void dppo_gemm_nt_kernel(const uint16_t* __res
     // are loaded there, or, behind the tile's last steps, those of the same place of the next tile.  The fragments of each
     // 32-wide sub-step are read from LDS one sub-step ahead of the matrix-core instructions that consume them.  One barrier per step.
     const int nk = steps_of(tile);
-    const bool has_next = number + map.slots < end;
+    const bool has_next = OUT != kOutSplit && number + map.slots < end;
     TileAt next = tile;
     int nk_next = 0;
     // One step of the contraction out of stage `cur`: two 32-wide sub-steps of 64 matrix-core
@@ -1089,7 +1090,7 @@ hipError_t launch_gemm_nn(const uint16_t* A, int64_t lda, const uint16_t* B, int
     if (N % 4 != 0 || !scratch) return hipErrorInvalidValue;
     const int split_steps = (K / kBK + splits - 1) / splits;
     const int used = (K / kBK + split_steps - 1) / split_steps;       // ranges that hold a step
-    TileMap map = tile_map(M, N, K, used, cus);
+    TileMap map = tile_map(M, N, K, used, cus, 1);
     map.split_steps = split_steps;
     hipLaunchKernelGGL((dppo_gemm_nt_kernel<kOutSplit, false, true>), tile_grid(map), dim3(256), 0, s, A, lda, B, ldb,
                        static_cast<void*>(scratch), static_cast<int64_t>(N), M, N, K, map, GemmStats{});
