@@ -193,8 +193,8 @@ __device__ __forceinline__ float across_rows(float v, F&& f) {
 struct StatRoom {
   float part[2][kBM][3];
 };
-// FULL: every column of the tile exists (rows that do not are zeros and leave nothing).  quarter: room for 64 rows of the tile each.
-template <bool FULL>
+// quarter: room for 64 rows of the tile each.  Columns that do not exist come in whole blocks of 16 (N is a multiple of 64; the host sees to that), rows that do not
+// exist are zeros and leave nothing.
 __device__ __forceinline__ void tile_statistics(const int (&samp)[8], int M, int N, int m0, int n0, const GemmStats& gs, StatRoom& sh,
                                                 unsigned char* const (&quarter)[4], int wid, int lane) {
   const int tid = wid * 64 + lane, wm = wid >> 1, wn = wid & 1, frow = lane & 15, fk = lane >> 4;
@@ -223,16 +223,25 @@ __device__ __forceinline__ void tile_statistics(const int (&samp)[8], int M, int
             u32x2{(__float_as_uint(z[j][0]) >> 16) | __float_as_uint(z[j][1]), (__float_as_uint(z[j][2]) >> 16) | __float_as_uint(z[j][3])};
       }
     }
-    // columns that do not exist, and (rarely: one tile in V / 256 holds a row's) the sampled token's
-    if (!FULL || __any(a_loc >= 0 && a_loc < 128)) {
+    if (N - col0 < 128) {
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+        if (col0 + j * 16 >= N) z[j][0] = z[j][1] = z[j][2] = z[j][3] = -INFINITY;
+    }
+    // The sampled token (rarely: one tile in V / 256 holds a row's), picked by selection and stored once: a store per column, each behind a branch of its own, was 256
+    // branches a tile, 8 us where every column was looked at.
+    if (__any(a_loc >= 0 && a_loc < 128)) {
+      const int e_loc = a_loc - fk * 4;
+      float za = 0.f;
 #pragma unroll
       for (int j = 0; j < 8; ++j)
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const int cl = j * 16 + fk * 4 + e;
-          if (cl == a_loc) gs.gath[static_cast<int64_t>(row) * K1] = z[j][e];
-          if ((!FULL && col0 + cl >= N) || cl == a_loc) z[j][e] = -INFINITY;
+          const bool here = e_loc == j * 16 + e;
+          za = here ? z[j][e] : za;
+          z[j][e] = here ? -INFINITY : z[j][e];
         }
+      if (a_loc >= 0 && a_loc < 128 && ((a_loc >> 2) & 3) == fk) gs.gath[static_cast<int64_t>(row) * K1] = za;
     }
     float mx = -INFINITY;
 #pragma unroll
@@ -689,8 +698,7 @@ __global__ __launch_bounds__(256) void dppo_gemm_nt_kernel(const uint16_t* __res
       static_assert(sizeof(StatRoom) <= kPanelBytes);
       StatRoom& room = *reinterpret_cast<StatRoom*>(panel2);
       unsigned char* const quarter[4] = {panel0, panel1, panel3, panel4};
-      if (N - n0 >= kBN) tile_statistics<true>(samp, M, N, m0, n0, gs, room, quarter, wid, lane_e);
-      else               tile_statistics<false>(samp, M, N, m0, n0, gs, room, quarter, wid, lane_e);
+      tile_statistics(samp, M, N, m0, n0, gs, room, quarter, wid, lane_e);
     } else if constexpr (OUT == kOutBf16) {
       auto store = [&](auto whole) __attribute__((always_inline)) {
         unrolled<8>([&](auto i) __attribute__((always_inline)) {

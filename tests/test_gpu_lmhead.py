@@ -692,6 +692,24 @@ def test_forward_only_ignored_rows_padding_ids_and_ids_in_the_ragged_last_tile()
     _say(f"       {st}")
 
 
+@pytest.mark.parametrize("V", [64, 192, 320, 512])
+@pytest.mark.parametrize("K", [0, 3])
+def test_forward_only_sampled_token_in_every_column(V, K):
+    """The sampled token in each column once, of whole tiles and of tiles a quarter, three quarters and five quarters wide.  (Without
+    diagnostics: the bar of the masses, 2e-7, is for rows of thousands of entries.  Of a few hundred one can be most of the sum, which
+    then has that one's error, the 1.2e-7 of the exponential instruction, three more roundings and the result's own, 6e-8 each: 3.6e-7.)"""
+    w = W.Workload("lm_columns", 1, V, V, W.TOPK_TV if K else W.BINARY_TV, 0.1, K=K, logit_std=3.0, noise_std=1.0, adv="normal", seed=V + K)
+    b = W.make_lmhead_batch(w, 128, DEV, exact=True, shift_sampled=2.0)
+    b["sampled_ids"].copy_(torch.randperm(V, generator=torch.Generator().manual_seed(V)))
+    rows = np.arange(V)
+    ref = _oracle(b, rows, want_grad=False)
+    res = B.run_lmhead(b, backward=False)
+    torch.cuda.synchronize()
+    assert B.last_path() == "lmhead_fused"
+    P.compare_rows(dict(b, logits=None), res, rows, check_grad=False, ref=ref)
+    P.check_loss_scalar(b, res, float(ref["loss_tok"].sum()))
+
+
 def test_forward_only_headline_vocabulary_sampled_rows():
     """V = 151936 (593 tiles and a half), d = 4096, T = 2560 in chunks of 1024: sampled rows against
     the oracle on inputs whose logits are exact in fp32, Top-K TV and Binary KL."""
