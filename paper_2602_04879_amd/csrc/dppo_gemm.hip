@@ -179,8 +179,7 @@ enum : int { kOutBf16 = 0, kOutF32 = 1, kOutF32Add = 2, kOutStats = 3, kOutSplit
 // columns of each of its 8 rows; the four lanes of a row (lane, lane+16, +32, +48) combine by
 // register swaps, the two waves of a row through shared memory.  The logit of the row's sampled token leaves from the registers (one tile in V / 256 holds it).
 // With top-K ids the rounded tile itself goes to shared memory, into the panels of the products (64 rows of 512 bytes each, 32-byte blocks
-// XOR-ed with the row so that a 16-lane write spreads over the banks), from where the logits at the ids that fall into this tile are picked: then
-// no next tile's panels may be on their way, and a workgroup forms one tile.
+// XOR-ed with the row so that a 16-lane write spreads over the banks), from where the logits at the ids that fall into this tile are picked.
 // A value of each of the four rows of 16 lanes, combined over the rows in every lane (register swaps between lane rows: a shuffle through shared memory is 120 cycles
 // that a wave alone on its SIMD waits for).
 template <typename F>
@@ -280,10 +279,11 @@ __device__ __forceinline__ void tile_statistics(const int (&samp)[8], int M, int
     const float t = c0 * fmaf(d0, sh.part[0][tid][1], sh.part[0][tid][2]) + c1 * fmaf(d1, sh.part[1][tid][1], sh.part[1][tid][2]);
     if (row < M) gs.part[static_cast<int64_t>(row) * gs.tiles_n + n0 / kBN] = f32x4{b, s, t, 0.f};
   }
-  // ids fetched sixteen at a time (one memory latency)
+  // ids fetched 22 at a time, one memory latency: 20 ids a row in one go, 64 in three.  Us, 16 at a time / 22: 300 x 4096 x 768 with 20 ids 35.6 / 34.6,
+  // 5000 x 50304 x 768 435 / 424, with 64 497 / 494, with 8 407 / 414.
   const int n_ids = min(kBM, M - m0) * gs.Ktop;
   const int32_t* ids = gs.tk_ids + static_cast<int64_t>(m0) * gs.Ktop;
-  constexpr int kAhead = 16;
+  constexpr int kAhead = 22;
   for (int i0 = tid; i0 < n_ids; i0 += kAhead * kBM) {
     int id[kAhead];
 #pragma unroll
@@ -330,7 +330,10 @@ struct TileMap {
 // most; tiles of 128 steps and more are worth no run: they gain a per cent by it, and workgroups that drift apart lose the panels they
 // share.  Runs of 1 / 2 / 4 / 8 / 32 tiles, us, V = 151936: A B^T 2048 x 2048 975 / 954 / 943 / 938 / 933, 8192 x 4096 6838 / 6770 / 6738 / 6735 / 6712; A^T B
 // 2048 x 2048 983 / 958 / 950 / 945 / 944, 8192 x 4096 (128 steps) 7150 / 7283 / 7377 / 7464 / 7570.
-// A divided contraction (kOutSplit) gets no runs: it has 128 steps and more in all, and tiles of its ranges one behind the other are not built.
+// No runs: a divided contraction (kOutSplit), which has 128 steps and more in all, and the statistics (kOutStats), which store next to nothing, want all of the panels for
+// the tile with top-K ids, and with a next tile on its way keep more addresses than there are scalar registers.  Forward only, us, in runs (but for top-K ids,
+// where the code for them stood unused) / without: 2048 x 50304 x 768 162 / 158, with 20 ids 210 / 189, of one workgroup per tile and two panels each 171 and 201; 64 x 32768 x 768 32.1 / 30.3, 38.5 / 35.0, 32.8 and 37.0;
+// 2048 x 151936 x 2048 973 / 970, 1057 / 1021, 1015 and 1072; 8192 x 151936 x 4096 6925 / 6904, 7287 / 7144, 6990 and 7237.
 constexpr int kMaxRun = 8;
 TileMap tile_map(int64_t M, int64_t N, int64_t K, int64_t ranges, int cus, int max_run = kMaxRun) {
   TileMap t;
@@ -404,7 +407,7 @@ struct TileAt {
 // into the four consecutive k of one m that a matrix-core operand wants.
 //
 // A workgroup forms a run of tiles (TileMap::run), one behind the other: while it multiplies the last steps of a
-// tile it already loads the first of the next, and its stores travel behind the next tile's products (kOutSplit: one tile, the host asks for runs of one).
+// tile it already loads the first of the next, and its stores travel behind the next tile's products (kOutSplit and kOutStats: one tile, the host asks for runs of one).
 template <int OUT, bool TA, bool TB>
 __global__ __launch_bounds__(256) void dppo_gemm_nt_kernel(const uint16_t* __restrict__ A, int64_t lda,
                                                            const uint16_t* __restrict__ B, int64_t ldb,
@@ -419,6 +422,7 @@ __global__ __launch_bounds__(256) void dppo_gemm_nt_kernel(const uint16_t* __res
   auto far_panel = [&](int step) { return step % 3 == 0 ? panel0 : step % 3 == 1 ? panel1 : panel2; };
   auto near_panel = [&](int step) { return step % 2 == 0 ? panel3 : panel4; };
   constexpr bool FAR_A = TA;
+  constexpr bool RUNS = OUT != kOutSplit && OUT != kOutStats;
   const int tid = threadIdx.x, lane = tid & 63, wid = uniform_i(tid >> 6);
   const int wm = wid >> 1, wn = wid & 1;
 
@@ -580,9 +584,11 @@ __global__ __launch_bounds__(256) void dppo_gemm_nt_kernel(const uint16_t* __res
       for (int i = 0; i < 8; ++i) load_far(far_panel(s), rf, i);
     });
   }
-  meet(std::integral_constant<int, 0>{});
+  // Of the forty loads the first sixteen, the first step's, are read at once.  A workgroup of one tile waits for no others here and for the next sixteen in the
+  // middle of that step; where tiles follow, whose first steps begin behind their predecessor's stores, everything is awaited.
+  meet(std::integral_constant<int, RUNS ? 0 : 24>{});
   for (;;) {
-    // The panels hold the tile's first two (three) steps, for everyone.
+    // The panels hold the tile's first step, or its first two (three), for everyone.
     bf16x8 f0[16], f1[16];      // [0..7] B blocks, [8..15] A blocks
 #pragma unroll
     for (int t = 0; t < 16; ++t) f0[kOrder[t]] = read_frag(far_panel(0), near_panel(0), 0, kOrder[t]);
@@ -592,7 +598,7 @@ __global__ __launch_bounds__(256) void dppo_gemm_nt_kernel(const uint16_t* __res
     // are loaded there, or, behind the tile's last steps, those of the same place of the next tile.  The fragments of each
     // 32-wide sub-step are read from LDS one sub-step ahead of the matrix-core instructions that consume them.  One barrier per step.
     const int nk = steps_of(tile);
-    const bool has_next = OUT != kOutSplit && number + map.slots < end;
+    const bool has_next = RUNS && number + map.slots < end;
     TileAt next = tile;
     int nk_next = 0;
     // One step of the contraction out of stage `cur`: two 32-wide sub-steps of 64 matrix-core
@@ -611,12 +617,12 @@ __global__ __launch_bounds__(256) void dppo_gemm_nt_kernel(const uint16_t* __res
         if constexpr (m < 32 && (m & 1) == 0) { f1[kOrder[m >> 1]] = read_frag(far_panel(P), near_panel(P), 1, kOrder[m >> 1]); DPPO_PIN; }
       });
       // The next step's panels are complete (the eight youngest loads are the far panel of the step after it; a tile's second step: complete
-      // since the tile began) and this step's fully read.
-      meet(std::integral_constant<int, (FIRST ? kAnyVm : 8)>{});
+      // since the tile began where there are runs) and this step's fully read.
+      meet(std::integral_constant<int, (FIRST && RUNS ? kAnyVm : 8)>{});
       const bool own_n = STEADY || kt + 2 < nk, own_f = STEADY || kt + 3 < nk;
       const int sn = own_n ? kt + 2 : P % 2, sf = own_f ? kt + 3 : P % 3;
       const row_rsrc_t rn = STEADY ? view_near(tile, sn, true) : view_near(own_n ? tile : next, sn, own_n || sn < nk_next);
-      const row_rsrc_t rf = STEADY ? view_far(tile, sf, true) : view_far(own_f ? tile : next, sf, own_f || (sf < nk_next && !(OUT == kOutStats && P % 3 == 2)));
+      const row_rsrc_t rf = STEADY ? view_far(tile, sf, true) : view_far(own_f ? tile : next, sf, own_f || sf < nk_next);
       unrolled<64>([&](auto mc) __attribute__((always_inline)) {
         constexpr int m = decltype(mc)::value;
         product<m, false>(f1[m & 7], f1[8 + (m >> 3)]); DPPO_PIN;
@@ -693,7 +699,7 @@ __global__ __launch_bounds__(256) void dppo_gemm_nt_kernel(const uint16_t* __res
       DPPO_PIN;
     };
     if constexpr (OUT == kOutStats) {
-      // in the far panel of the next tile's third step, which is loaded behind it (and once every wave's last loads, of nothing, into it have ended)
+      // in the panels, once every wave's last loads into them, of nothing, have ended
       meet(std::integral_constant<int, 0>{});
       static_assert(sizeof(StatRoom) <= kPanelBytes);
       StatRoom& room = *reinterpret_cast<StatRoom*>(panel2);
@@ -763,11 +769,6 @@ __global__ __launch_bounds__(256) void dppo_gemm_nt_kernel(const uint16_t* __res
     }
     if (!has_next) return;
     meet(std::integral_constant<int, kAnyVm>{});
-    if (OUT == kOutStats) {
-      const row_rsrc_t rf = view_far(next, nk_next > 2 ? 2 : 0, nk_next > 2);
-#pragma unroll
-      for (int i = 0; i < 8; ++i) load_far(panel2, rf, i);
-    }
     tile = next;
     number += map.slots;
   }
@@ -976,7 +977,7 @@ hipError_t launch_gemm_nt(const uint16_t* A, int64_t lda, const uint16_t* B, int
 hipError_t launch_gemm_stats(const uint16_t* A, int64_t lda, const uint16_t* B, int64_t ldb, int M, int N, int K,
                              const GemmStats& gs, int cus, hipStream_t s) {
   if (M <= 0 || N <= 0) return hipSuccess;
-  const TileMap map = tile_map(M, N, K, 1, cus, gs.Ktop > 0 ? 1 : kMaxRun);
+  const TileMap map = tile_map(M, N, K, 1, cus, 1);
   if (gs.tiles_n != map.tiles_n) return hipErrorInvalidValue;
   const dim3 grid = tile_grid(map), wg(256);
   hipLaunchKernelGGL((dppo_gemm_nt_kernel<kOutStats, false, false>), grid, wg, 0, s, A, lda, B, ldb, static_cast<void*>(nullptr), int64_t(0), M, N, K,
