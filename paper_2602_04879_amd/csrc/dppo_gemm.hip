@@ -985,10 +985,20 @@ hipError_t launch_gemm_stats(const uint16_t* A, int64_t lda, const uint16_t* B, 
   return hipGetLastError();
 }
 
-// Which contractions are short: us, these tiles / 256 x 256, results on lines, V = 151936: 64 tokens x 2048 110 / 191, 200 179 / 261, 300 222 / 284, 400 264 / 328, 500
-// 307 / 360, 640 364 / 412, 800 442 / 483, 1000 565 / 546; 500 x 768 119 / 133, 500 x 4096 611 / 673, 1000 x 4096 1145 / 1085.  Others leave both kinds of tiles in pieces
-// of 64 bytes: 200 x 2048 237 / 261, 300 284 / 284, 400 324 / 327, 500 369 / 355.
-static bool gemm_tn_short(const void* C, int64_t ldc, int64_t K) { return K <= (result_on_lines(C, ldc) ? 896 : 384); }
+// Which contractions are short.  Ratio of the times, these tiles / 256 x 256 ones, over V = 16000 .. 151936 and 64 .. 4160 columns, results of more than the Infinity Cache in turn:
+//  * a last column of tiles that is cut, which the large tiles store behind a check per vector: up to 640 tokens 0.48-0.95 (results off the lines up to 1.11), 768 .. 1024
+//    0.69-1.04;
+//  * whole columns of tiles, results on lines: up to 640 0.61-1.04, 768 .. 896 0.80-1.05, 930 .. 1024 0.84-1.09, but 0.71-0.98 where the large tiles are at most one per compute unit
+//    (V = 8192 and 16000); V = 151936, 2048 columns: 64 tokens 0.62, 200 0.66, 400 0.74, 640 0.84, 768 0.90, 900 0.96, 1000 1.04 (64 110 / 191 us, 300 222 / 284, 800 442 /
+//    483, 1000 565 / 546);
+//  * whole columns, other results, which both kinds leave in pieces of 64 bytes: up to 300 0.89-1.19, 400 .. 640 0.94-1.15 where the large tiles fill nine tenths of their rounds, 0.92-1.03
+//    where they do not; 768 .. 1024 0.92-1.14.
+static bool gemm_tn_short(const void* C, int64_t ldc, int64_t M, int64_t N, int64_t K, int cus) {
+  const int64_t tiles = ((M + kBM - 1) / kBM) * ((N + kBN - 1) / kBN), rounds = (tiles + cus - 1) / cus;
+  if (N % kBN != 0) return K <= 1024;
+  if (result_on_lines(C, ldc)) return K <= (rounds == 1 ? 1024 : 896);
+  return K <= (tiles * 10 >= rounds * cus * 9 ? 384 : 640);
+}
 
 // C[M, N] bf16 = *factor A^T B, rounded once.
 //
@@ -998,7 +1008,7 @@ static bool gemm_tn_short(const void* C, int64_t ldc, int64_t K) { return K <= (
 hipError_t launch_gemm_tn_bf16(const uint16_t* A, int64_t lda, const uint16_t* B, int64_t ldb, void* C, int64_t ldc,
                                int M, int N, int K, const float* factor, int cus, hipStream_t s) {
   if (M <= 0 || N <= 0) return hipSuccess;
-  if (gemm_tn_short(C, ldc, K)) {
+  if (gemm_tn_short(C, ldc, M, N, K, cus)) {
     const ShortMap map = short_map(M, N);
     hipLaunchKernelGGL(dppo_gemm_tn_short_kernel, dim3(8u * static_cast<unsigned>(map.per_die)), dim3(256), 0, s, A, lda, B, ldb, static_cast<uint16_t*>(C), ldc,
                        M, N, K, map, factor);

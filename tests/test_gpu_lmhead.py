@@ -178,7 +178,10 @@ def test_gemm_tn_exact_inputs_bitwise_and_accumulation(M, N, K, lda, ldb, ldc):
     (384, 512, 33, 384, 512, 512, 0), (130, 300, 96, 136, 304, 300, 0), (1100, 2100, 160, 1104, 2104, 2100, 0), (640, 300, 640, 640, 304, 304, 0),
     (640, 300, 641, 640, 304, 304, 0), (73729, 2048, 70, 73736, 2048, 2048, 0),
     # results on lines: small tiles up to 896, whole lines in their full tiles; the pitch on lines, the first row not
-    (640, 576, 896, 640, 576, 576, 0), (640, 576, 897, 640, 576, 576, 0), (384, 512, 385, 384, 512, 512, 8), (261, 512, 31, 264, 512, 576, 0)])
+    (640, 576, 896, 640, 576, 576, 0), (640, 576, 897, 640, 576, 576, 0), (384, 512, 385, 384, 512, 512, 8), (261, 512, 31, 264, 512, 576, 0),
+    # the lines between small and large tiles: a cut last column of tiles, whole ones with results off the lines, whole ones on them in one round and in more
+    (384, 576, 1024, 384, 576, 576, 0), (384, 576, 1025, 384, 576, 584, 0), (384, 512, 640, 384, 512, 520, 0), (384, 512, 641, 384, 512, 512, 8), (32768, 512, 385, 32768, 512, 520, 0), (384, 512, 1024, 384, 512, 512, 0),
+    (384, 512, 1025, 384, 512, 512, 0), (33280, 512, 896, 33280, 512, 512, 0), (33280, 512, 897, 33280, 512, 512, 0)])
 def test_gemm_tn_in_bf16_is_the_fp32_product_scaled_and_rounded_once(M, N, K, lda, ldb, ldc, off):
     """C = bf16(factor * A^T B): bit for bit what scaling and rounding the fp32 product gives, with ragged
     sizes, pitches and a C on any 2-byte address; nothing around C is written."""
