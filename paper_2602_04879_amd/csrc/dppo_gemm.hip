@@ -575,6 +575,8 @@ __global__ __launch_bounds__(256) void dppo_gemm_nt_kernel(const uint16_t* __res
     const int nk = steps_of(tile);
     unrolled<3>([&](auto sc) __attribute__((always_inline)) {
       constexpr int s = decltype(sc)::value;
+      // (steps that the contraction does not have: sixteen or eight loads of nothing each, half a microsecond of an 8 us product of one step; a workgroup of one tile counts on them)
+      if (RUNS && s > 0 && s >= nk) return;
       const row_rsrc_t rn = view_near(tile, s < nk ? s : 0, s < nk), rf = view_far(tile, s < nk ? s : 0, s < nk);
       if (s < 2) {
 #pragma unroll
