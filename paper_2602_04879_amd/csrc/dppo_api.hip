@@ -235,10 +235,13 @@ bool forward_keeps_row(const dppo_args_t* a, int threads, int chunks, bool ragge
 // second read cost less than the idle time, by the same sizes for calls with and without a gradient: where both are divided their per-token
 // outputs agree bit for bit.  Not divided: a gradient that does not share the logits' address modulo 16 (the forward-only call on the same
 // logits still is), DPPO_FLAG_FORCE_STREAMING, the hidden states in several chunks, records and gathered logits beyond 64 KiB.
-// Ratio of the times, divided / one workgroup per row, with the gradient and without (whole calls, Top-20 TV, 8 / 64 / 96 / 128 tokens of
-// 256 compute units' share): V = 65536 0.94 / 1.02 / 1.02 / 1.09 and 0.95 / 0.98 / 1.04 / 1.04; 81920 0.83 / 0.92 / 0.98 / 0.99 and 0.89 / 0.97 / 1.03 / 1.01; 98304
-// 0.74 / 0.82 / 0.89 / 0.96 and 0.85 / 0.91 / 0.94 / 0.99; 131072 0.60 / 0.73 / 0.81 / 0.88 and 0.73 / 0.85 / 0.89 / 0.94; 151936 0.54 / 0.65 / 0.73 / 0.78
-// and 0.71 / 0.78 / 0.82 / 0.88; 256000 0.31 / 0.44 / 0.58 / 0.69 and 0.54 / 0.68 / 0.77 / 0.86.  160 tokens: 98304 1.06 and 1.05, 131072 1.03 and 1.04, 151936 0.94 and 1.01.
+// Ratio of the times, divided / one workgroup per row, calls in a graph, Top-20 TV, 8 / 64 / 96 / 128 tokens of 256 compute units' share, with the gradient and without, inputs in the
+// caches; the same with inputs from memory: V = 65536 0.73 / 0.83 / 0.87 / 0.96 and 0.77 / 0.85 / 0.87 / 0.94; 0.75 / 0.84 / 0.89 / 0.97 and 0.89 / 0.98 / 1.03 / 1.10.  81920 0.64 / 0.73 / 0.87 /
+// 0.92 and 0.72 / 0.78 / 0.87 / 0.87; 0.64 / 0.76 / 0.91 / 0.97 and 0.82 / 0.95 / 1.06 / 1.09.  98304 0.61 / 0.65 / 0.76 / 0.91 and 0.68 / 0.73 / 0.81 / 0.86; 0.60 / 0.68 / 0.81 / 0.91 and 0.78 / 0.88 / 0.98 / 1.03.
+// 131072 0.48 / 0.61 / 0.74 / 0.83 and 0.61 / 0.71 / 0.78 / 0.86; 0.49 / 0.64 / 0.75 / 0.86 and 0.69 / 0.85 / 0.93 / 0.99.  151936 0.44 / 0.57 / 0.71 / 0.77 and 0.57 / 0.66 / 0.72 / 0.86; 0.45 / 0.60 / 0.74 /
+// 0.84 and 0.65 / 0.80 / 0.88 / 0.95.  256000 0.25 / 0.43 / 0.56 / 0.66 and 0.41 / 0.59 / 0.74 / 0.83; 0.25 / 0.45 / 0.59 / 0.72 and 0.46 / 0.70 / 0.82 / 0.93.  160 tokens: 98304 1.03 and 0.97; 1.03 and 1.12.  131072 0.95
+// and 1.00; 1.01 and 1.02.  151936 0.92 and 1.02; 0.97 and 1.04.  (The lines are those of a form with a third launch.  V = 65536, and more tokens at 81920 and 98304, would gain with
+// the gradient and, from memory, lose without.)
 bool splits_rows(const dppo_args_t* a, bool ragged_ok, const LossScratch& sc, int cus) {
   if (a->V < 81920 || a->V > 64 * 8 * static_cast<int64_t>(dppo::kSplitVecs) - 64 || a->T > (a->V >= 131072 ? cus / 2 : cus / 4)) return false;
   const bool topk = (a->variant == DPPO_TOPK_TV || a->variant == DPPO_TOPK_KL);

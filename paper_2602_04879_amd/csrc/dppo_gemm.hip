@@ -486,8 +486,8 @@ __global__ __launch_bounds__(256) void dppo_gemm_nt_kernel(const uint16_t* __res
   // Loader role: thread t moves LDS vector slot (t % 8) of rows t/8 + 32 i, i = 0..7, of each panel;
   // the slot holds global k-vector slot ^ ((row >> 1) & 7), the same for all eight rows.
   // By rows: load i of a panel (one KiB: two LDS rows) moves k rows 8 i + 2 wave + lane / 32, LDS slot lane % 32: the same global slot for every other i.
-  // What differs from load to load is a scalar offset, which the range check counts (see row_rsrc_t): rows of a tile or a step that do not exist, and
-  // everything of a view of no bytes, read as zeros without an access.
+  // What differs from load to load is a scalar offset, which the range check counts (see row_rsrc_t; offsets stay below 2^31 here): rows of a tile or a step that do not
+  // exist, and everything of a view of no bytes, read as zeros without an access.
   auto loader = [&](bool by_rows, uint32_t pitch, int i) -> uint32_t {
     if (!by_rows) return static_cast<uint32_t>(tid >> 3) * pitch + static_cast<uint32_t>(((tid & 7) ^ ((tid >> 4) & 7)) << 4);
     const int k = 8 * i + 2 * wid + (lane >> 5);
@@ -496,7 +496,7 @@ __global__ __launch_bounds__(256) void dppo_gemm_nt_kernel(const uint16_t* __res
   const uint32_t vo_a[2] = {loader(TA, pitch_a, 0), loader(TA, pitch_a, 1)}, vo_b[2] = {loader(TB, pitch_b, 0), loader(TB, pitch_b, 1)};
   // Global memory -> LDS directly (buffer_load ... lds): lane l of a wave-level load deposits its
   // 16 bytes at (LDS base of the instruction) + 16 l, which is exactly the loader layout above for
-  // the base stage + panel + i * 4096 + wave * 1024.  No staging registers, no LDS store
+  // the base panel + i * 4096 + wave * 1024.  No staging registers, no LDS store
   // instructions; completion is counted with the other vector-memory loads.
   typedef __attribute__((address_space(3))) void* lds_ptr_t;
   auto load_a = [&](unsigned char* panel, row_rsrc_t r, int i) {
@@ -603,12 +603,12 @@ __global__ __launch_bounds__(256) void dppo_gemm_nt_kernel(const uint16_t* __res
     const bool has_next = RUNS && number + map.slots < end;
     TileAt next = tile;
     int nk_next = 0;
-    // One step of the contraction out of stage `cur`: two 32-wide sub-steps of 64 matrix-core
+    // One step of the contraction: two 32-wide sub-steps of 64 matrix-core
     // instructions each (A block i = m / 8 against B block j = m % 8).  Every other instruction sits
     // directly behind a matrix-core instruction, where it issues while that one executes.
     // First sub-step: the 16 fragment reads of the second, behind the first 32 instructions, so they
     // have landed when the barrier is reached.  Second sub-step: the 16 fragment reads of the next
-    // step's first sub-step and the 16 panel loads of the step after next.
+    // step's first sub-step and the panel loads, eight of the near operand two steps on and eight of the far one three steps on.
     // P: kt % 6.
     auto step = [&](int kt, auto phase, auto steady, auto first) __attribute__((always_inline)) {
       constexpr int P = decltype(phase)::value;
@@ -803,7 +803,7 @@ __device__ __forceinline__ void short_tile(unsigned char* lds0, unsigned char* l
 #pragma unroll
       for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.f;
 
-  // Panels by rows as in gemm_tile: LDS row k of the A panel 256 bytes = 16 slots of 16 bytes, of the B panel 512 bytes = 32 slots, slot s
+  // Panels by rows as in the larger tiles: LDS row k of the A panel 256 bytes = 16 slots of 16 bytes, of the B panel 512 bytes = 32 slots, slot s
   // holding the columns of global slot s ^ 2 g(k).
   uint32_t toff_a[4], toff_b[8], vo_a[2], vo_b[4];
   {
@@ -892,7 +892,7 @@ __device__ __forceinline__ void short_tile(unsigned char* lds0, unsigned char* l
     if (kt + 1 < nk) step(lds1, lds0, kt + 1, std::false_type{});
     if (kt + 2 < nk) step(lds2, lds1, kt + 2, std::false_type{});
   }
-  // the products have landed before anything else reads the accumulators (see gemm_tile)
+  // the products have landed before anything else reads the accumulators (as in the larger tiles)
 #define DPPO_THROUGH(CODE, I) asm volatile(CODE : "+a"(acc[I][0]), "+a"(acc[I][1]), "+a"(acc[I][2]), "+a"(acc[I][3]), \
                                                "+a"(acc[I][4]), "+a"(acc[I][5]), "+a"(acc[I][6]), "+a"(acc[I][7]) :: "memory")
   DPPO_THROUGH("s_nop 15\n\ts_nop 15", 0);

@@ -9,11 +9,11 @@
 //                           workgroup writes the per-token outputs.  The second read of a segment comes from the caches: fewer
 //                           rows than 128 are 39 MB at V = 151936, and workgroup ids, so dies, are those of the first kernel.
 //   dppo_split_rows_kernel  forward only: one wave per row
-// The row whose loss term is the last to be left adds them all up, beside the other workgroups' gradients; a kernel of its own for the sum was 2.2 us
-// and a launch.  Whole calls with it / without, V = 151936: 8 tokens 12.2 / 10.7, 64 16.8 / 15.5, 100 20.1 / 20.0; forward only 11.3 / 9.0, 13.8 / 11.9, 15.1 / 13.7.
+// The row whose loss term is the last to be left adds them all up, beside the other workgroups' gradients.
 // Bound by launches and latencies (two kernels, 2 us each when empty) up to some 30 rows, then by the memory traffic of the two passes.
-// V = 151936, calls in a graph, us, one workgroup per row / divided: 8 tokens 23.1 / 12.2, 64 23.4 / 17.1, 128 25.4 / 23.9 (inputs that change from call to call);
-// forward only 14.7 / 10.4, 15.6 / 13.3.
+// V = 151936, Top-20 TV, calls in a graph, us, one workgroup per row / divided, a third kernel for the loss / as it is.  Inputs the same from call to call, in the caches: 8
+// tokens 23.4 / 11.7 / 10.2, 64 23.7 / 14.9 / 13.4, 128 25.8 / 20.7 / 19.8, forward only 15.7 / 9.8 / 8.9, 16.0 / 11.3 / 10.5, 16.5 / 15.4 / 14.3; inputs that
+// change, from memory: 25.6 / 13.3 / 11.5, 26.3 / 17.4 / 15.8, 27.5 / 23.9 / 23.0, forward only 15.7 / 11.5 / 10.2, 16.2 / 14.2 / 12.9, 16.8 / 17.2 / 15.9.
 // Segments of 16 or 64 KiB, and 128 or 512 threads: the same to 30 % slower.  Code that few workgroups need (edges of a row, the
 // sampled token) stands behind branches of the whole workgroup: a kernel this short runs each instruction once and waits
 // for its fetch (100 tokens: 21.6 -> 20.1 us).
