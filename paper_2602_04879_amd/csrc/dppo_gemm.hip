@@ -17,8 +17,9 @@
 // which the Infinity Cache holds), loaded a step and a half ahead, three of the far one (the weight; the logits' gradient for the weight's), loaded
 // two and a half ahead.  And a workgroup forms several tiles one behind the other: the next tile's first panels are loaded during the last steps of a
 // tile, whose stores travel behind the next one's products.  Measured, us, V = 151936, one tile per workgroup and two panels each / as it is:
-// A B^T 300 x 2048 263 / 231, 1000 x 2048 514 / 484, 2048 x 1024 578 / 535, 2048 x 2048 1010 / 928, 8192 x 1024 2170 / 1985, 8192 x 4096 6880 / 6735;
-// bf16 A^T B 500 x 2048 369 / 355, 1000 x 2048 598 / 549, 2048 x 2048 1039 / 934, 4096 x 4096 3720 / 3375, 8192 x 4096 7410 / 7150.
+// A B^T 300 x 2048 267 / 233, 1000 x 2048 519 / 491, 2048 x 1024 591 / 538, 2048 x 2048 1007 / 940, 8192 x 1024 2162 / 2028, 8192 x 4096 6841 / 6717; A B 1000 x 2048 3110 / 2750,
+// 8192 x 4096 6902 / 6677; bf16 A^T B 1000 x 2048 608 / 544, 2048 x 2048 1045 / 947, 4096 x 4096 3790 / 3420, 8192 x 4096 7407 / 7213 (fp32, added to C, 8174 / 7930).  One round of tiles whose
+// operands the L2 holds is up to 2.5 % slower (A B^T 4096 x 4096, K = 8192: 175 / 179).
 // (With operands of zeros, which draw no power, 2048 x 2048 931 / 760, of 520 for the products alone: 130 of the rest are the stores, whose 32 MiB leave at
 // once and fill the dies' way to memory for five microseconds; held back in registers and spread over the next tile's first six steps they cost the
 // same but for 1 %, written in whole lines through shared memory too.)
