@@ -193,7 +193,7 @@ __device__ __forceinline__ float across_rows(float v, F&& f) {
 struct StatRoom {
   float part[2][kBM][3];
 };
-// quarter: room for 64 rows of the tile each.  Columns that do not exist come in whole blocks of 16 (N is a multiple of 64; the host sees to that), rows that do not
+// quarter: room for 64 rows of the tile each.  Columns that do not exist come in whole blocks of 16 (the host sees to that), rows that do not
 // exist are zeros and leave nothing.
 __device__ __forceinline__ void tile_statistics(const int (&samp)[8], int M, int N, int m0, int n0, const GemmStats& gs, StatRoom& sh,
                                                 unsigned char* const (&quarter)[4], int wid, int lane) {
@@ -981,7 +981,7 @@ hipError_t launch_gemm_stats(const uint16_t* A, int64_t lda, const uint16_t* B, 
                              const GemmStats& gs, int cus, hipStream_t s) {
   if (M <= 0 || N <= 0) return hipSuccess;
   const TileMap map = tile_map(M, N, K, 1, cus, 1);
-  if (gs.tiles_n != map.tiles_n) return hipErrorInvalidValue;
+  if (gs.tiles_n != map.tiles_n || N % 16 != 0) return hipErrorInvalidValue;
   const dim3 grid = tile_grid(map), wg(256);
   hipLaunchKernelGGL((dppo_gemm_nt_kernel<kOutStats, false, false>), grid, wg, 0, s, A, lda, B, ldb, static_cast<void*>(nullptr), int64_t(0), M, N, K,
                      map, gs);

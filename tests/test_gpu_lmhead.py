@@ -177,7 +177,7 @@ def test_gemm_tn_exact_inputs_bitwise_and_accumulation(M, N, K, lda, ldb, ldc):
     (4160, 128, 321, 4160, 128, 128, 0), (777, 261, 129, 784, 264, 264, 0), (151936, 64, 66, 151936, 64, 64, 0), (512, 512, 1000, 512, 512, 520, 3),
     (384, 512, 33, 384, 512, 512, 0), (130, 300, 96, 136, 304, 300, 0), (1100, 2100, 160, 1104, 2104, 2100, 0), (640, 300, 640, 640, 304, 304, 0),
     (640, 300, 641, 640, 304, 304, 0), (73729, 2048, 70, 73736, 2048, 2048, 0),
-    # results on lines: small tiles up to 896, whole lines in their full tiles; the pitch on lines, the first row not
+    # results on lines: whole lines in the full ones of the small tiles; the pitch on lines, the first row not
     (640, 576, 896, 640, 576, 576, 0), (640, 576, 897, 640, 576, 576, 0), (384, 512, 385, 384, 512, 512, 8), (261, 512, 31, 264, 512, 576, 0),
     # the lines between small and large tiles: a cut last column of tiles, whole ones with results off the lines, whole ones on them in one round and in more
     (384, 576, 1024, 384, 576, 576, 0), (384, 576, 1025, 384, 576, 584, 0), (384, 512, 640, 384, 512, 520, 0), (384, 512, 641, 384, 512, 512, 8), (32768, 512, 385, 32768, 512, 520, 0), (384, 512, 1024, 384, 512, 512, 0),
@@ -349,8 +349,8 @@ def test_gemm_tiles_one_behind_the_other(steps):
 @pytest.mark.parametrize("d", [64, 128, 192, 256, 384, 576, 704])
 @pytest.mark.parametrize("K", [0, 3])
 def test_forward_tiles_one_behind_the_other(d, K):
-    """The same for the forward-only path, whose statistics use the place of the next tile's third panel (K = 0), and for top-K ids, whose tiles
-    have the shared memory to themselves; rows of every tile height, the last columns half a tile."""
+    """The same number of tiles on the forward-only path, one per workgroup, whose statistics (and, with top-K ids, the rounded tile) take the
+    panels' place; rows of every tile height, the last columns half a tile."""
     w = W.Workload("lm_runs", 7, 100, 64 * 2398, W.TOPK_TV if K else W.BINARY_TV, 0.1, K=K, logit_std=3.0, noise_std=1.0, adv="pm1", seed=d + K)
     _run_and_compare(w, d, shift=2.0, backward=False, rows=np.array([0, 15, 100, 127, 128, 255, 256, 300, 511, 512, 640, 699]))
 
